@@ -240,11 +240,16 @@ __global__ void k_band_tb(BandArgs a) {
 // ---- CIGAR compaction -----------------------------------------------------
 // 16 lanes per pair (most CIGARs have few runs), 16 pairs per block
 __global__ void k_cigar_compact(int64_t npairs, const uint32_t *src, const int64_t *src_off,
-                                const int32_t *len, const int64_t *dst_off, uint32_t *dst) {
+                                const int32_t *len, const int64_t *dst_off, const uint8_t *cls,
+                                const int32_t *qbeg, const int32_t *qend, uint32_t *dst) {
   const int64_t p = (int64_t)blockIdx.x * (blockDim.x / 16) + threadIdx.x / 16;
   if (p >= npairs) return;
   const int32_t n = len[p];
   const int64_t so = src_off[p], d = dst_off[p];
+  if (cls[p] == kTbFlat) {   // one run of M over the rectangle's rows
+    if ((threadIdx.x & 15) == 0) dst[d] = (uint32_t)(qend[p] - qbeg[p] + 1) << 4;
+    return;
+  }
   for (int32_t k = threadIdx.x & 15; k < n; k += 16) dst[d + k] = src[so + k];
 }
 
@@ -672,11 +677,12 @@ hipError_t fill_set(const FillSet &f, hipStream_t st) {
 }
 
 hipError_t launch_cigar_compact(int64_t npairs, const uint32_t *src, const int64_t *src_off,
-                                const int32_t *len, const int64_t *dst_off, uint32_t *dst,
+                                const int32_t *len, const int64_t *dst_off, const uint8_t *cls,
+                                const int32_t *qbeg, const int32_t *qend, uint32_t *dst,
                                 hipStream_t st) {
   if (!npairs) return hipSuccess;
   hipLaunchKernelGGL(k_cigar_compact, dim3(blocks_for(npairs, 16)), dim3(256), 0, st, npairs, src,
-                     src_off, len, dst_off, dst);
+                     src_off, len, dst_off, cls, qbeg, qend, dst);
   return hipGetLastError();
 }
 

@@ -126,18 +126,6 @@ __global__ void k_compact(int64_t n, const uint8_t *flag, const int64_t *pos, in
   if (p < n && flag[p]) out[pos[p]] = p;
 }
 
-__global__ void k_count_classes(int64_t n, const uint8_t *cls, int64_t *counts) {
-  __shared__ int64_t c[8];
-  if (threadIdx.x < 8) c[threadIdx.x] = 0;
-  __syncthreads();
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n; p += stride)
-    atomicAdd((unsigned long long *)&c[cls[p] & 7], 1ull);
-  __syncthreads();
-  if (threadIdx.x < 8 && c[threadIdx.x]) atomicAdd((unsigned long long *)&counts[threadIdx.x],
-                                                   (unsigned long long)c[threadIdx.x]);
-}
-
 // reversed pass setup: drift band per pair and the lane width it runs at.
 // Every alignment of score score1 in the reversed region starts at the
 // reversed corner (T1 leaves no other cell of that value there).  A path
@@ -203,14 +191,6 @@ static hipError_t radix_pairs(bool graph, void *tmp, size_t &bytes, rocprim::dou
                               hipStream_t st) {
   if (graph) return rocprim::radix_sort_pairs<MergeConfig>(tmp, bytes, kb, vb, n, 0u, end_bit, st);
   return rocprim::radix_sort_pairs<OnesweepConfig>(tmp, bytes, kb, vb, n, 0u, end_bit, st);
-}
-
-hipError_t count_classes(int64_t n, const uint8_t *cls, int64_t *counts, hipStream_t st) {
-  if (!n) return hipSuccess;
-  unsigned blocks = nb(n, 256);
-  if (blocks > 1024) blocks = 1024;
-  hipLaunchKernelGGL(k_count_classes, dim3(blocks), dim3(256), 0, st, n, cls, counts);
-  return hipGetLastError();
 }
 
 hipError_t sort_keys(int64_t n, uint64_t *keys, uint64_t *keys_alt, int64_t *vals,

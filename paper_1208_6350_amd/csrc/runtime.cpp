@@ -664,26 +664,24 @@ static int run_traceback(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, 
   uint64_t *k0 = A.get<uint64_t>(np), *k1 = A.get<uint64_t>(np);
   int64_t *v0 = A.get<int64_t>(np), *v1 = A.get<int64_t>(np);
   int64_t *ccap = A.get<int64_t>(np + 1), *coff = A.get<int64_t>(np + 1);
-  int64_t *counts = A.get<int64_t>(8);
+  int64_t *counts = A.get<int64_t>(9);   // pairs per class, then the CIGAR scratch's words
   if (!cls || !k0 || !k1 || !v0 || !v1 || !ccap || !coff || !counts)
     return fail(SWX_ENOMEM, "device pool exhausted (traceback)");
   HIP_TRY(hipMemsetAsync(ccap + np, 0, 8, st));
   HIP_TRY(hipMemsetAsync(counts, 0, 64, st));
-  HIP_TRY(tb_classify(ta, np, cls, k0, v0, ccap, st));
+  HIP_TRY(tb_classify(ta, np, cls, k0, v0, ccap, counts, st));
   if ((rc = scan(ctx, ccap, coff, np + 1))) return rc;
-  HIP_TRY(count_classes(np, cls, counts, st));
   size_t tmp_bytes = 0;
   int64_t *sorted = nullptr;
   HIP_TRY(sort_keys(np, k0, k1, v0, v1, nullptr, &tmp_bytes, &sorted, st, kTbKeyBits));
   void *tmp = A.alloc(tmp_bytes);
   if (!tmp) return fail(SWX_ENOMEM, "device pool exhausted (sort)");
   HIP_TRY(sort_keys(np, k0, k1, v0, v1, tmp, &tmp_bytes, &sorted, st, kTbKeyBits));
-  // the class counts and the CIGAR scratch size in one read (class 7 is
-  // never used)
-  HIP_TRY(hipMemcpyAsync(counts + 7, coff + np, sizeof(int64_t), hipMemcpyDeviceToDevice, st));
-  int64_t hc[8];
-  if ((rc = read_i64(ctx, counts, hc, 8))) return rc;
-  const int64_t capw = hc[7];
+  // the class counts and the CIGAR scratch size in one read
+  HIP_TRY(hipMemcpyAsync(counts + 8, coff + np, sizeof(int64_t), hipMemcpyDeviceToDevice, st));
+  int64_t hc[9];
+  if ((rc = read_i64(ctx, counts, hc, 9))) return rc;
+  const int64_t capw = hc[8];
   uint32_t *cscr = A.get<uint32_t>(capw);
   if (!cscr) return fail(SWX_ENOMEM, "device pool exhausted (CIGAR scratch)");
   ta.cig = cscr;
@@ -850,7 +848,7 @@ static int run_traceback(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, 
     if (!dtmp) return fail(SWX_ENOMEM, "device pool exhausted");
     dst = dtmp;
   }
-  HIP_TRY(launch_cigar_compact(np, cscr, coff, cig_len, cig_off_final, dst, st));
+  HIP_TRY(launch_cigar_compact(np, cscr, coff, cig_len, cig_off_final, cls, qbeg, qend, dst, st));
   if (dtmp && total)
     HIP_TRY(hipMemcpyAsync(out->cigar, dtmp, sizeof(uint32_t) * total, hipMemcpyDeviceToHost, st));
   return SWX_OK;
@@ -1931,9 +1929,8 @@ static int fixed_issue(GraphState &g, hipStream_t st) {
     } else {
     HIP_TRY(fill_i64(1, g.ccap + B, 0, st));
     HIP_TRY(fill_i64(8, g.counts, 0, st));
-    HIP_TRY(tb_classify(ta, B, g.cls, g.tk0, g.tv0, g.ccap, st));
+    HIP_TRY(tb_classify(ta, B, g.cls, g.tk0, g.tv0, g.ccap, g.counts, st));
     if ((rc = fixed_scan(g, g.ccap, g.coff, B + 1, st))) return rc;
-    HIP_TRY(count_classes(B, g.cls, g.counts, st));
     size_t sb = g.tb_sort_bytes;
     HIP_TRY(sort_keys(B, g.tk0, g.tk1, g.tv0, g.tv1, g.tb_sort_tmp, &sb, &g.tb_sorted, st, kTbKeyBits,
                       true));
@@ -1964,13 +1961,14 @@ static int fixed_issue(GraphState &g, hipStream_t st) {
       HIP_TRY(tb_strip(tc, tasks, t.cap_tasks, g.tb_sorted, t.bnd, st));
     }
     }
-    if (B == 1) {
+    if (g.tbw1) {
       HIP_TRY(cigar_one(g.cscr, g.coff, g.cig_len, g.cig_off_final, g.cigar, st));
     } else {
       if (!g.intra) HIP_TRY(fill_i64(1, g.len64 + B, 0, st));
       HIP_TRY(lens_to_i64(B, g.cig_len, g.len64, st));
       if ((rc = fixed_scan(g, g.len64, g.cig_off_final, B + 1, st))) return rc;
-      HIP_TRY(launch_cigar_compact(B, g.cscr, g.coff, g.cig_len, g.cig_off_final, g.cigar, st));
+      HIP_TRY(launch_cigar_compact(B, g.cscr, g.coff, g.cig_len, g.cig_off_final, g.cls, g.qbeg,
+                                   g.qend, g.cigar, st));
     }
   }
   if ((flags & SWX_SCORE2) && g.intra) {

@@ -76,8 +76,9 @@ struct TbTask {
   int64_t dir_off;     // dwords
 };
 
-constexpr int kTbwSlots = 16;
-constexpr int kTbKeyBits = 23;  // traceback sort key: class (3 bits) above 20 bits of rows   // pairs per wide-band traceback task (four lanes each)
+constexpr int kTbwSlots = 16;   // pairs per wide-band traceback task (four lanes each)
+constexpr int kTbKeyBits = 23;  // traceback sort key: class (3 bits) above 20 bits of rows
+constexpr int kTbFlat = 7;      // class of pairs whose alignment is their main diagonal (m M)
 
 struct TbwTask {        // wide-band traceback task (kTbwSlots pairs)
   int32_t nslots, pad_;
@@ -161,8 +162,9 @@ struct TbArgs {
   int64_t wave_cells;    // wide bands with more cells go to the wave-parallel kernel
 };
 
+// counts[c] (cleared by the caller) += pairs of class c
 hipError_t tb_classify(const TbArgs &a, int64_t npairs, uint8_t *cls, uint64_t *key, int64_t *vals,
-                       int64_t *ccap, hipStream_t st);
+                       int64_t *ccap, int64_t *counts, hipStream_t st);
 hipError_t tb_tasks(int64_t n0, int64_t n1, const int64_t *sorted, const TbArgs &a, int32_t bw,
                     TbTask *tasks, int64_t *dir_words, hipStream_t st);
 hipError_t tb_offsets(int64_t ntasks, TbTask *tasks, const int64_t *off, hipStream_t st);
@@ -201,7 +203,6 @@ hipError_t max3_check(unsigned long long *bad, uint64_t *checked, hipStream_t st
 hipError_t lane_probe(int bits, int64_t cols, int64_t blocks, int32_t o, int32_t e, uint32_t *best,
                       hipStream_t st);
 hipError_t class_ranges(const int64_t *counts, int64_t *ranges, hipStream_t st);
-hipError_t count_classes(int64_t n, const uint8_t *cls, int64_t *counts, hipStream_t st);
 // graph: the sort is recorded into a HIP graph (a form that issues no memset)
 hipError_t sort_keys(int64_t n, uint64_t *keys, uint64_t *keys_alt, int64_t *vals,
                      int64_t *vals_alt, void *tmp, size_t *tmp_bytes, int64_t **sorted_out,
@@ -324,8 +325,11 @@ hipError_t fill_set(const FillSet &f, hipStream_t st);
 // pair 0's CIGAR words and final offsets {0, length} (one-pair calls)
 hipError_t cigar_one(const uint32_t *src, const int64_t *src_off, const int32_t *len,
                      int64_t *dst_off, uint32_t *dst, hipStream_t st);
+// cls: the traceback classes (pairs of class kTbFlat hold no scratch words:
+// their one word is made from qbeg and qend)
 hipError_t launch_cigar_compact(int64_t npairs, const uint32_t *src, const int64_t *src_off,
-                                const int32_t *len, const int64_t *dst_off, uint32_t *dst,
+                                const int32_t *len, const int64_t *dst_off, const uint8_t *cls,
+                                const int32_t *qbeg, const int32_t *qend, uint32_t *dst,
                                 hipStream_t st);
 hipError_t launch_score2_inter(const Score2InterArgs &a, hipStream_t st);
 hipError_t launch_score2_plain(int64_t p, const int32_t *maxcol, int64_t lr, const int32_t *score1,

@@ -1,0 +1,55 @@
+"""GPU: the traceback's routes against the oracle, word by word, at the sizes
+where each can go wrong."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import paper_1208_6350_amd as swx
+import workloads as W
+from tests.test_gpu_parity import assert_parity
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = swx.Context(0)
+    yield c
+    c.close()
+
+
+def square_pairs(m, n, alphabet, seed):
+    """Pairs whose alignment is (nearly always) a square rectangle of about m
+    rows: substitutions only in one half, one balanced pair of indels in the
+    other, whose diagonal alone scores less than the alignment with gaps."""
+    g = np.random.Generator(np.random.PCG64(seed))
+    qs, rs = [], []
+    for k in range(n):
+        core = g.integers(0, alphabet, size=m).astype(np.int8)
+        q = core.copy()
+        sub = g.random(m) < 0.03
+        q[sub] = (q[sub] + 1) % alphabet
+        if k % 2 and m >= 24:   # drop a symbol early, add one late
+            a, b = m // 3, 2 * m // 3
+            q = np.concatenate([q[:a], q[a + 1:b], g.integers(0, alphabet, 1).astype(np.int8), q[b:]])
+        left, right = g.integers(0, 20, size=2)
+        r = np.concatenate([g.integers(0, alphabet, left), core, g.integers(0, alphabet, right)])
+        qs.append(q)
+        rs.append(r.astype(np.int8))
+    return qs, rs
+
+
+# the diagonal's sum reads 16-byte words, the last one overlapping
+@pytest.mark.parametrize("m", [1, 2, 15, 16, 17, 31, 32, 33, 150, 257])
+@pytest.mark.parametrize("alphabet", [4, 24])
+def test_main_diagonal_alignments(ctx, m, alphabet):
+    qs, rs = square_pairs(m, 96, alphabet, 4000 + m)
+    if alphabet == 4:
+        b = W.from_lists(f"square-{m}", W.dna_matrix(), 3, 1, qs, rs)
+    else:
+        b = W.from_lists(f"square-{m}-aa", W.protein_matrix_standin(), 11, 1, qs, rs)
+    recs = assert_parity(ctx, b)
+    flat = (recs["cigar_len"] == 1)
+    assert flat.any()
+    assert_parity(ctx, b, flags=swx.SWX_CIGAR)
