@@ -59,6 +59,7 @@ class DevArena {
     fixed_short_ = false;
   }
   void use_pool() { fixed_ = nullptr; }
+  bool fixed() const { return fixed_ != nullptr; }
   bool fixed_exhausted() const { return fixed_short_; }
   void release() {
     for (auto &b : blocks_) (void)hipFree(b.ptr);
@@ -644,7 +645,22 @@ static TbShape tb_wave_shape(int64_t m, int64_t w, int64_t bw, int n, int64_t jo
   return best;
 }
 
+// Traceback a workgroup per pair (k_tb_pairs), by its scratch, which counts
+// the waves' steps (128 bytes each): a whole batch up to kTbPairsBytes, else
+// its wide bands up to kTbWideBytes.  Measured on reads (traceback stage with
+// the per-lane kernels / all by pairs / only wide bands by pairs): 10,000
+// reads (0.2 GB) 1.51 / 0.56 / 1.16 ms, 20,000 (0.4 GB) 1.57 / 0.86 / 1.22,
+// 50,000 (1 GB, 0.15 wide) 1.52 / 1.66 / 1.35, 100,000 (0.3 wide) 1.77 / 2.94
+// / 1.60, 200,000 (0.6 wide) 1.83 / 5.53 / 2.16.  Batches of at most
+// kTbPairsAll pairs skip the sort too.  The call that allocates nothing keeps
+// the per-lane kernels, whose scratch is a few times smaller.
+static constexpr int64_t kTbPairsAll = 4096, kTbPairsMax = int64_t(1) << 18;
+static constexpr int64_t kTbPairsBytes = int64_t(600) << 20, kTbWideBytes = int64_t(384) << 20;
+static constexpr int64_t kTbGraphBytes = int64_t(1) << 30;   // of a graph (fixed, worst case)
+
+// max_rows: most rows of a pair (the shape of the launch, no limit)
 static int run_traceback(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, int64_t np,
+                         int64_t max_rows,
                          const int32_t *score, const int32_t *qbeg, const int32_t *qend,
                          const int64_t *rbeg, const int64_t *rend, const int64_t *qstart,
                          const int64_t *rstart, const int32_t *qlen, const int64_t *rlen,
@@ -664,23 +680,33 @@ static int run_traceback(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, 
   uint64_t *k0 = A.get<uint64_t>(np), *k1 = A.get<uint64_t>(np);
   int64_t *v0 = A.get<int64_t>(np), *v1 = A.get<int64_t>(np);
   int64_t *ccap = A.get<int64_t>(np + 1), *coff = A.get<int64_t>(np + 1);
-  int64_t *counts = A.get<int64_t>(9);   // pairs per class, then the CIGAR scratch's words
+  // pairs per class, the CIGAR scratch's words, then the wave kernel's scratch
+  // bytes per class and its cursor
+  int64_t *counts = A.get<int64_t>(18);
   if (!cls || !k0 || !k1 || !v0 || !v1 || !ccap || !coff || !counts)
     return fail(SWX_ENOMEM, "device pool exhausted (traceback)");
   HIP_TRY(hipMemsetAsync(ccap + np, 0, 8, st));
-  HIP_TRY(hipMemsetAsync(counts, 0, 64, st));
-  HIP_TRY(tb_classify(ta, np, cls, k0, v0, ccap, counts, st));
+  HIP_TRY(hipMemsetAsync(counts, 0, 18 * 8, st));
+  // a small batch is traced pair by pair, in pair order (k_tb_pairs): it
+  // needs no sort unless some of its pairs are long
+  const bool pairs_ok = !A.fixed() && np <= kTbPairsMax;
+  const bool few = pairs_ok && np <= kTbPairsAll;
+  HIP_TRY(tb_classify(ta, np, cls, k0, v0, ccap, counts, pairs_ok ? counts + 9 : nullptr, st));
   if ((rc = scan(ctx, ccap, coff, np + 1))) return rc;
-  size_t tmp_bytes = 0;
   int64_t *sorted = nullptr;
-  HIP_TRY(sort_keys(np, k0, k1, v0, v1, nullptr, &tmp_bytes, &sorted, st, kTbKeyBits));
-  void *tmp = A.alloc(tmp_bytes);
-  if (!tmp) return fail(SWX_ENOMEM, "device pool exhausted (sort)");
-  HIP_TRY(sort_keys(np, k0, k1, v0, v1, tmp, &tmp_bytes, &sorted, st, kTbKeyBits));
-  // the class counts and the CIGAR scratch size in one read
+  auto sort = [&]() -> int {
+    size_t tmp_bytes = 0;
+    HIP_TRY(sort_keys(np, k0, k1, v0, v1, nullptr, &tmp_bytes, &sorted, st, kTbKeyBits));
+    void *tmp = A.alloc(tmp_bytes);
+    if (!tmp) return fail(SWX_ENOMEM, "device pool exhausted (sort)");
+    HIP_TRY(sort_keys(np, k0, k1, v0, v1, tmp, &tmp_bytes, &sorted, st, kTbKeyBits));
+    return SWX_OK;
+  };
+  if (!few && (rc = sort())) return rc;
+  // the class counts and the scratch sizes in one read
   HIP_TRY(hipMemcpyAsync(counts + 8, coff + np, sizeof(int64_t), hipMemcpyDeviceToDevice, st));
-  int64_t hc[9];
-  if ((rc = read_i64(ctx, counts, hc, 9))) return rc;
+  int64_t hc[17];
+  if ((rc = read_i64(ctx, counts, hc, 17))) return rc;
   const int64_t capw = hc[8];
   uint32_t *cscr = A.get<uint32_t>(capw);
   if (!cscr) return fail(SWX_ENOMEM, "device pool exhausted (CIGAR scratch)");
@@ -697,10 +723,39 @@ static int run_traceback(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, 
   int nbands = 0;
   TbwTask *wtasks = nullptr;
   int64_t wnt = 0;
+  // classes traced a workgroup per pair (few: all of them)
+  TbPairs tp{};
+  int64_t pblocks = 0;
+  std::vector<SideLaunch> launches;
+  const bool all = pairs_ok && hc[10] + hc[11] + hc[12] + hc[14] <= kTbPairsBytes;
+  const bool direct = few && all;
+  auto by_pairs = [&](int c) { return all || (pairs_ok && c == 5 && hc[9 + c] <= kTbWideBytes); };
+  if (few && (!direct || hc[6] > 0) && (rc = sort())) return rc;
   int64_t pos = hc[0];
+  for (int c : {1, 2, 3, 5}) {
+    if (hc[c] > 0 && by_pairs(c)) {
+      tp.lo[tp.ranges] = pos;
+      tp.cnt[tp.ranges++] = hc[c];
+      pblocks += hc[c];
+      tp.cap += hc[9 + c];
+      hc[c] = -hc[c];   // done here
+    }
+    pos += hc[c] < 0 ? -hc[c] : hc[c];
+  }
+  if (pblocks > 0) {
+    tp.sorted = direct ? nullptr : sorted;
+    tp.cls = cls;
+    tp.used = (unsigned long long *)(counts + 17);
+    tp.scratch = A.get<uint8_t>(tp.cap);
+    if (!tp.scratch) return fail(SWX_ENOMEM, "device pool exhausted (pair traceback)");
+    const int64_t blocks = direct ? np : pblocks;
+    launches.push_back({(double)tp.cap * 2, [=](hipStream_t s_) { return tb_pairs(ta, tp, blocks, max_rows, s_); }});
+  }
+  pos = hc[0];
   for (int c = 1; c <= 3; ++c) {
     const int64_t nc = hc[c];
-    if (nc == 0) continue;
+    if (nc < 0) pos -= nc;
+    if (nc <= 0) continue;
     const int32_t bw = 8 << (c - 1);
     const int64_t nt = (nc + 63) / 64;
     TbTask *tasks = A.get<TbTask>(nt);
@@ -714,6 +769,7 @@ static int run_traceback(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, 
     bands[nbands++] = BandPlan{tasks, nt, bw};
     pos += nc;
   }
+  if (hc[5] < 0) pos -= hc[5];
   if (hc[5] > 0) {   // bands wider than 64 diagonals: row strips, columns swept
     const int64_t nc = hc[5];
     const int64_t nt = (nc + kTbwSlots - 1) / kTbwSlots;
@@ -734,7 +790,6 @@ static int run_traceback(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, 
     wnt = nt;
     pos += nc;
   }
-  std::vector<SideLaunch> launches;
   if (nbands > 0 || wnt > 0) {
     int64_t ht[5];
     if ((rc = read_i64(ctx, totals, ht, 5))) return rc;
@@ -1490,7 +1545,7 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
   HIP_TRY(hipMemsetAsync(cig_off_final, 0, sizeof(int64_t) * (np + 1), st));
   int rc_range = SWX_OK;
   if (flags & SWX_CIGAR) {
-    if ((rc = run_traceback(ctx, sc, b, np, score, qbeg, qend, rbeg, rend, qstart, rstart, qlen,
+    if ((rc = run_traceback(ctx, sc, b, np, hstats[0], score, qbeg, qend, rbeg, rend, qstart, rstart, qlen,
                             rlen, cig_len, cig_off_final, err, out, &flags, &rc_range)))
       return rc;
   } else {
@@ -1586,7 +1641,7 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
     so.cigar_cap = out->cigar_cap > base ? out->cigar_cap - base : 0;
     uint32_t sflags = SWX_BEGIN | SWX_CIGAR;
     int rc_sub = SWX_OK;
-    if ((rc = run_traceback(ctx, sc, b, np, s_score, s_qbeg, s_qend, s_rbeg, s_rend, qstart,
+    if ((rc = run_traceback(ctx, sc, b, np, hstats[0], s_score, s_qbeg, s_qend, s_rbeg, s_rend, qstart,
                             rstart, qlen, rlen, s_cig_len, s_cig_off, err, &so, &sflags, &rc_sub)))
       return rc;
     out->cigar_used = base + so.cigar_used;
@@ -1698,6 +1753,10 @@ struct GraphState {
   void *tb_sort_tmp = nullptr;
   size_t tb_sort_bytes = 0;
   FixedTb tb[6];
+  // graphs of 2 to kTbPairsAll pairs: a workgroup per pair instead
+  bool tb_by_pairs = false;
+  int64_t tbp_stride = 0;
+  uint8_t *tbp_scratch = nullptr;
   // one-pair graphs: the pair's traceback on the wave kernel, its job planned
   // on the device (instead of the class, sort and task kernels of a batch)
   bool tbw1 = false;
@@ -1929,8 +1988,15 @@ static int fixed_issue(GraphState &g, hipStream_t st) {
     } else {
     HIP_TRY(fill_i64(1, g.ccap + B, 0, st));
     HIP_TRY(fill_i64(8, g.counts, 0, st));
-    HIP_TRY(tb_classify(ta, B, g.cls, g.tk0, g.tv0, g.ccap, g.counts, st));
+    HIP_TRY(tb_classify(ta, B, g.cls, g.tk0, g.tv0, g.ccap, g.counts, nullptr, st));
     if ((rc = fixed_scan(g, g.ccap, g.coff, B + 1, st))) return rc;
+    if (g.tb_by_pairs) {
+      TbPairs tp{};
+      tp.cls = g.cls;
+      tp.stride = g.tbp_stride;
+      tp.scratch = g.tbp_scratch;
+      HIP_TRY(tb_pairs(ta, tp, B, std::min<int64_t>(g.QM, g.RM), st));
+    } else {
     size_t sb = g.tb_sort_bytes;
     HIP_TRY(sort_keys(B, g.tk0, g.tk1, g.tv0, g.tv1, g.tb_sort_tmp, &sb, &g.tb_sorted, st, kTbKeyBits,
                       true));
@@ -1959,6 +2025,7 @@ static int fixed_issue(GraphState &g, hipStream_t st) {
       TbArgs tc = ta;
       tc.dir = t.dir;
       HIP_TRY(tb_strip(tc, tasks, t.cap_tasks, g.tb_sorted, t.bnd, st));
+    }
     }
     }
     if (g.tbw1) {
@@ -2088,9 +2155,19 @@ static int graph_alloc(GraphState &g) {
     if ((rc = fixed_plan_alloc(g, g.p32, 32, R))) return rc;
     if ((rc = fixed_plan_alloc(g, g.r32, 32, R))) return rc;
   }
-  // traceback classes: up to every pair in one class
+  // traceback: a workgroup per pair where its fixed scratch stays small, else
+  // the band classes, up to every pair in one class
+  const int64_t tbp_stride = round_up(tb_wave_dir_bytes(g.QM, g.RM, kTbPairRows), 256) +
+                             tb_pair_bnd_bytes(g.QM, g.RM);
+  g.tb_by_pairs = B > 1 && B <= kTbPairsAll && B * tbp_stride <= kTbGraphBytes &&
+                  (g.QM + 64 * kTbPairRows - 1) / (64 * kTbPairRows) <= tb_wave_max_strips();
+  if (g.tb_by_pairs) {
+    g.tbp_stride = tbp_stride;
+    g.tbp_scratch = A.get<uint8_t>(B * tbp_stride);
+    if (!g.tbp_scratch) return fail(SWX_ENOMEM, "device pool exhausted (graph traceback)");
+  }
   const int64_t capT = (B + 63) / 64;
-  for (int c = 1; c <= 3; ++c) {
+  for (int c = 1; c <= 3 && !g.tb_by_pairs; ++c) {
     FixedTb &t = g.tb[c];
     t.cap_tasks = capT;
     t.tasks = A.get<TbTask>(capT);
@@ -2099,7 +2176,7 @@ static int graph_alloc(GraphState &g) {
     t.dir = A.get<uint32_t>(capT * (g.QM + 2) * ((8 << (c - 1)) / 8) * 64);
     if (!t.tasks || !t.dsz || !t.doff || !t.dir) return fail(SWX_ENOMEM, "device pool exhausted (graph traceback)");
   }
-  {
+  if (!g.tb_by_pairs) {
     FixedTb &t = g.tb[5];
     const int64_t capW = (B + kTbwSlots - 1) / kTbwSlots;
     t.cap_tasks = capW;

@@ -144,6 +144,23 @@ __host__ __device__ inline void tbw_window(int64_t s, int64_t SH, int64_t dlo, i
   *chi = hi > lo ? hi : lo;
 }
 
+// Scratch of a pair on k_tb_pairs: hand-over rows, then choice codes.
+constexpr int kTbPairRows = 4;   // rows per lane
+__host__ __device__ inline int64_t tb_pair_bnd_bytes(int64_t m, int64_t w) {
+  const int64_t nstrips = (m + 64 * kTbPairRows - 1) / (64 * kTbPairRows);
+  return (8 * (w + 1) * (nstrips + 1) + 255) / 256 * 256;
+}
+__host__ __device__ inline int64_t tb_pair_bytes(int64_t m, int64_t w, int64_t dlo, int64_t bw) {
+  constexpr int64_t SH = 64 * kTbPairRows;
+  int64_t steps = 0;
+  for (int64_t s = 0; s * SH < m; ++s) {
+    int64_t lo, hi;
+    tbw_window(s, SH, dlo, bw, w, &lo, &hi);
+    steps += hi - lo + 63;
+  }
+  return tb_pair_bnd_bytes(m, w) + (steps * 64 * tb_code_bytes(kTbPairRows) + 255) / 256 * 256;
+}
+
 struct TbArgs {
   const int32_t *score;
   const int32_t *qbeg, *qend;
@@ -162,9 +179,25 @@ struct TbArgs {
   int64_t wave_cells;    // wide bands with more cells go to the wave-parallel kernel
 };
 
-// counts[c] (cleared by the caller) += pairs of class c
+// counts[c] (cleared by the caller) += pairs of class c, and with bytes (may be
+// null) bytes[c] += their scratch on the wave kernel (k_tb_pairs)
 hipError_t tb_classify(const TbArgs &a, int64_t npairs, uint8_t *cls, uint64_t *key, int64_t *vals,
-                       int64_t *ccap, int64_t *counts, hipStream_t st);
+                       int64_t *ccap, int64_t *counts, int64_t *bytes, hipStream_t st);
+// Wave traceback planned on the device, a workgroup per pair: pairs
+// sorted[lo[x] .. lo[x] + cnt[x]) of each range, or (sorted null) every pair
+// by its class.  Scratch: stride bytes per block, or taken from cap bytes
+// through *used.
+struct TbPairs {
+  const int64_t *sorted;
+  const uint8_t *cls;
+  int64_t lo[4], cnt[4];
+  int32_t ranges, pad_;
+  int64_t stride, cap;
+  unsigned long long *used;
+  uint8_t *scratch;
+};
+hipError_t tb_pairs(const TbArgs &a, const TbPairs &t, int64_t blocks, int64_t max_rows,
+                    hipStream_t st);
 hipError_t tb_tasks(int64_t n0, int64_t n1, const int64_t *sorted, const TbArgs &a, int32_t bw,
                     TbTask *tasks, int64_t *dir_words, hipStream_t st);
 hipError_t tb_offsets(int64_t ntasks, TbTask *tasks, const int64_t *off, hipStream_t st);

@@ -122,14 +122,14 @@ __device__ __forceinline__ int32_t diagonal_sum(const int8_t *q, const int8_t *r
 
 __global__ __launch_bounds__(256) void k_tb_classify(TbArgs a, int64_t npairs, uint8_t *cls,
                                                      uint64_t *key, int64_t *vals, int64_t *ccap,
-                                                     int64_t *counts) {
+                                                     int64_t *counts, int64_t *bytes) {
   __shared__ int8_t s_mat[32 * 32];
-  __shared__ unsigned long long s_cnt[8];
+  __shared__ unsigned long long s_cnt[8], s_bytes[8];
   for (int k = threadIdx.x; k < 32 * 32; k += blockDim.x) {
     const int qc = k / 32, rc = k % 32;
     s_mat[k] = qc < a.n && rc < a.n ? a.matrix[qc * a.n + rc] : (int8_t)0;
   }
-  if (threadIdx.x < 8) s_cnt[threadIdx.x] = 0;
+  if (threadIdx.x < 8) s_cnt[threadIdx.x] = s_bytes[threadIdx.x] = 0;
   __syncthreads();
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < npairs; p += stride) {
@@ -175,6 +175,10 @@ __global__ __launch_bounds__(256) void k_tb_classify(TbArgs a, int64_t npairs, u
     vals[p] = p;
     ccap[p] = (c != 0 && c != kTbFlat) ? (m + w + 2) : 0;
     if (c == kTbFlat) a.cig_len[p] = 1;
+    if (bytes && c >= 1 && c <= 5) {   // too tall for the wave kernel's strips: more than any scratch
+      const bool fits = (m + 64 * kTbPairRows - 1) / (64 * kTbPairRows) <= kTbMaxStripsDecl;
+      atomicAdd(&s_bytes[c], (unsigned long long)(fits ? tb_pair_bytes(m, w, dlo, bw) : int64_t(1) << 40));
+    }
     // class counts: one LDS atomic per class present in the wave
     for (int k = 0; k < 8; ++k) {
       const unsigned long long in = __ballot(c == k);
@@ -184,6 +188,8 @@ __global__ __launch_bounds__(256) void k_tb_classify(TbArgs a, int64_t npairs, u
   __syncthreads();
   if (threadIdx.x < 8 && s_cnt[threadIdx.x])
     atomicAdd((unsigned long long *)&counts[threadIdx.x], s_cnt[threadIdx.x]);
+  if (threadIdx.x < 8 && s_bytes[threadIdx.x])
+    atomicAdd((unsigned long long *)&bytes[threadIdx.x], s_bytes[threadIdx.x]);
 }
 
 __device__ __forceinline__ int64_t wave_max_i64(int64_t v) {
@@ -553,11 +559,11 @@ __global__ __launch_bounds__(256) void k_tb_band(TbArgs a, const TbTask *tasks, 
 static inline unsigned nblk(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 
 hipError_t tb_classify(const TbArgs &a, int64_t npairs, uint8_t *cls, uint64_t *key, int64_t *vals,
-                       int64_t *ccap, int64_t *counts, hipStream_t st) {
+                       int64_t *ccap, int64_t *counts, int64_t *bytes, hipStream_t st) {
   if (!npairs) return hipSuccess;
   // at most 8 blocks per compute unit: each adds its class counts once
   hipLaunchKernelGGL(k_tb_classify, dim3(std::min(nblk(npairs, 256), 2048u)), dim3(256), 0, st, a, npairs, cls, key,
-                     vals, ccap, counts);
+                     vals, ccap, counts, bytes);
   return hipGetLastError();
 }
 
@@ -1067,49 +1073,30 @@ __device__ __forceinline__ void tb_prof_load(const int8_t *src, uint32_t (&w)[RL
 }
 
 // The walk back along the path (rule T3) over one pair's stored codes, by
-// one wave (uniform state); defined below.
-template <int RL>
+// one wave (uniform state), TILE bytes of codes at a time; defined below.
+template <int RL, int TILE>
 __device__ void tb_wave_walk(const TbArgs &a, const TbWaveJob &jb, const uint8_t *dir,
                              uint4 *s_tile, int lane);
 
-// SPREAD: the pair's strips on the waves of `segs` workgroups (progress
-// records in global memory, agent scope, as in the intra-sequence fill; the
-// grid fits on the device at once), and the walk left to k_tb_walk.
+// The choice codes of one pair: its strips on the waves of G workgroups (this
+// one is number seg; SPREAD: progress records in global memory, agent scope).
+// s_prof: this workgroup's profiles, [(n+1)][64][RL] score bytes per wave;
+// s_mat: room for the matrix; s_prog, s_done: progress per strip.
 template <int RL, bool SPREAD>
-__global__ __launch_bounds__(64 * kTbMaxWaves) void k_tb_wave(TbArgs a, const TbWaveJob *jobs,
-                                                              int64_t njobs, int segs,
-                                                              IntraSync *sync, uint8_t *dirw,
-                                                              int32_t *bndbuf) {
+__device__ __forceinline__ void tb_wave_fill(const TbArgs &a, const TbWaveJob &jb, int64_t seg,
+                                             int G, int32_t *s_prog, int32_t *s_done,
+                                             int8_t *s_mat, int8_t *s_profs, uint8_t *dir,
+                                             int32_t *bnd0) {
   constexpr int64_t SH = 64 * RL;
   constexpr int WB = RL / 2;                      // code bytes per lane and step
-  extern __shared__ uint4 s_dyn[];                // per wave: profile [(n+1)][64][RL] score bytes
-  __shared__ uint4 s_tile[SPREAD ? 1 : kTbTileBytes / 16];
-  __shared__ int8_t s_mat[32 * 32];
-  __shared__ int32_t l_prog[SPREAD ? 1 : kTbMaxStrips];   // columns of strip s's last row published
-  __shared__ int32_t l_done[SPREAD ? 1 : kTbMaxStrips];
   constexpr int SCOPE = SPREAD ? __HIP_MEMORY_SCOPE_AGENT : __HIP_MEMORY_SCOPE_WORKGROUP;
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int NW = blockDim.x >> 6;
-  // spread grids: block 8 * slot + x (slot = (j / 8) * G + segment) puts the
-  // segments of job j on XCD j % 8; blocks past the last job leave at once
-  const int G = SPREAD ? segs : 1;
-  int64_t jix = blockIdx.x, seg = 0;
-  if constexpr (SPREAD) {
-    const int64_t slot = blockIdx.x / 8;
-    jix = (slot / G) * 8 + blockIdx.x % 8;
-    seg = slot % G;
-    if (jix >= njobs) return;
-  }
-  int32_t *s_prog = SPREAD ? sync[jix].prog : l_prog;
-  int32_t *s_done = SPREAD ? sync[jix].done : l_done;
-  const TbWaveJob jb = jobs[jix];
-  if (jb.m <= 0) return;   // a job without an alignment (one-pair graphs plan it on the device)
   const int64_t p = jb.pair, m = jb.m, w = jb.w;
   const int n = a.n;
   const int32_t o = a.o, e = a.e;
   const int64_t nstrips = (m + SH - 1) / SH;
-  uint8_t *dir = dirw + jb.dir_off;
   for (int k = threadIdx.x; k < n * n; k += blockDim.x) s_mat[k] = a.matrix[k];
   if constexpr (!SPREAD) {   // spread jobs: set by intra_sync_init before the launch
     for (int k = threadIdx.x; k < nstrips && k < kTbMaxStrips; k += blockDim.x) {
@@ -1121,7 +1108,6 @@ __global__ __launch_bounds__(64 * kTbMaxWaves) void k_tb_wave(TbArgs a, const Tb
   const int8_t *r = a.rcat + a.rstart[p] + a.rbeg[p];
   // hand-over rows: row 0 is the virtual top row H(0,0) = 0,
   // H(0,j) = -(o + (j-1)e), F(0,j) = -inf; row s + 1 is strip s's last row
-  int32_t *bnd0 = bndbuf + jb.bnd_off;
   if (seg == 0) {   // strip 0 (segment 0, wave 0) reads it after the barrier below
     for (int64_t j = threadIdx.x; j <= w; j += blockDim.x) {
       bnd0[j] = (j == 0) ? 0 : -(o + (int32_t)(j - 1) * e);
@@ -1130,7 +1116,7 @@ __global__ __launch_bounds__(64 * kTbMaxWaves) void k_tb_wave(TbArgs a, const Tb
   }
   __threadfence_block();
   __syncthreads();
-  int8_t *s_prof = reinterpret_cast<int8_t *>(s_dyn) + (size_t)wave * (n + 1) * 64 * RL;
+  int8_t *s_prof = s_profs + (size_t)wave * (n + 1) * 64 * RL;
   bool spin_fail = false;
 
   // choice codes of strip s start this many bytes after those of strip 0
@@ -1214,7 +1200,9 @@ __global__ __launch_bounds__(64 * kTbMaxWaves) void k_tb_wave(TbArgs a, const Tb
     int32_t hout = kNeg, fout = kNeg;
     int32_t hbuf = kNeg, fbuf = kNeg;
     int32_t obH = 0, obF = 0;
-    const int64_t nsteps = (chi - clo) + 63;
+    // the last strip ends once the lane that holds the last row has swept
+    // the window (nothing leaves lane 63)
+    const int64_t nsteps = (chi - clo) + (hand_over ? 63 : (m - s * SH + RL - 1) / RL - 1);
     // reference symbols of columns [c0, c0 + 64) at lane c - c0; the profile
     // row of a step is read one step ahead (its symbol is the one the lane
     // above holds now)
@@ -1317,12 +1305,112 @@ __global__ __launch_bounds__(64 * kTbMaxWaves) void k_tb_wave(TbArgs a, const Tb
     publish((int32_t)(chi - clo), true);
   }
   if (spin_fail && lane == 0) a.err[p] = 1;   // reported as an internal failure
+}
+
+// SPREAD: the pair's strips on the waves of `segs` workgroups (progress
+// records in global memory, agent scope, as in the intra-sequence fill; the
+// grid fits on the device at once), and the walk left to k_tb_walk.
+template <int RL, bool SPREAD>
+__global__ __launch_bounds__(64 * kTbMaxWaves) void k_tb_wave(TbArgs a, const TbWaveJob *jobs,
+                                                              int64_t njobs, int segs,
+                                                              IntraSync *sync, uint8_t *dirw,
+                                                              int32_t *bndbuf) {
+  extern __shared__ uint4 s_dyn[];                // per wave: profile [(n+1)][64][RL] score bytes
+  __shared__ uint4 s_tile[SPREAD ? 1 : kTbTileBytes / 16];
+  __shared__ int8_t s_mat[32 * 32];
+  __shared__ int32_t l_prog[SPREAD ? 1 : kTbMaxStrips];   // columns of strip s's last row published
+  __shared__ int32_t l_done[SPREAD ? 1 : kTbMaxStrips];
+  // spread grids: block 8 * slot + x (slot = (j / 8) * G + segment) puts the
+  // segments of job j on XCD j % 8; blocks past the last job leave at once
+  const int G = SPREAD ? segs : 1;
+  int64_t jix = blockIdx.x, seg = 0;
+  if constexpr (SPREAD) {
+    const int64_t slot = blockIdx.x / 8;
+    jix = (slot / G) * 8 + blockIdx.x % 8;
+    seg = slot % G;
+    if (jix >= njobs) return;
+  }
+  const TbWaveJob jb = jobs[jix];
+  if (jb.m <= 0) return;   // a job without an alignment (one-pair graphs plan it on the device)
+  uint8_t *dir = dirw + jb.dir_off;
+  tb_wave_fill<RL, SPREAD>(a, jb, seg, G, SPREAD ? sync[jix].prog : l_prog,
+                           SPREAD ? sync[jix].done : l_done, s_mat,
+                           reinterpret_cast<int8_t *>(s_dyn), dir, bndbuf + jb.bnd_off);
   if constexpr (!SPREAD) {
     // the walk reads every wave's codes: the barrier makes the workgroup's
     // stores visible to it (they pass through this compute unit's caches)
     __syncthreads();
-    if (wave == 0) tb_wave_walk<RL>(a, jb, dir, s_tile, lane);
+    if (threadIdx.x < 64) tb_wave_walk<RL, kTbTileBytes>(a, jb, dir, s_tile, (int)threadIdx.x);
   }
+}
+
+// One pair per workgroup, planned by the workgroup itself: the traceback of
+// batches (or classes of a batch) too small for the per-lane kernels.  Those
+// put 64 or 16 pairs on a wave and take as long as one lane needs for its
+// pair, 0.16 (8-wide bands) to 1.0 ms (wide bands) for a read of 150-250 nt
+// however few pairs there are, one class after the other in a graph; a
+// wavefront over the pair's rows takes about 50 us, and the device runs a few
+// thousand such waves at once.  Bound by the wavefront's step chain (few
+// pairs), then by VALU issue over all 64 lanes, of which a short read fills
+// half: per cell the per-lane kernels are 3-4 times cheaper.  Measured on
+// reads (whole traceback stage): 101 pairs 1.14 -> 0.19 ms, 4,000 1.8 ->
+// 0.32, 20,000 1.92 -> 0.86; 512 in a graph 1.85 -> 0.1.
+constexpr int kTbPairTile = 8192;
+constexpr int kTbPairMaxWaves = 4;
+
+__global__ __launch_bounds__(64 * kTbPairMaxWaves) void k_tb_pairs(TbArgs a, TbPairs t) {
+  constexpr int RL = kTbPairRows;
+  extern __shared__ uint4 s_dyn[];
+  __shared__ uint4 s_tile[kTbPairTile / 16];
+  __shared__ int8_t s_mat[32 * 32];
+  __shared__ int32_t s_prog[kTbMaxStrips], s_done[kTbMaxStrips];
+  __shared__ int64_t s_off;
+  int64_t p = blockIdx.x;
+  if (t.sorted) {
+    int64_t k = p;
+    int x = 0;
+    while (x + 1 < t.ranges && k >= t.cnt[x]) k -= t.cnt[x++];
+    p = t.sorted[t.lo[x] + k];
+  } else {
+    const uint8_t c = t.cls[p];
+    if (c == 0 || c == 6 || c == kTbFlat) return;   // nothing to trace, or another kernel's pair
+  }
+  TbWaveJob jb{};
+  jb.pair = p;
+  jb.m = a.qend[p] - a.qbeg[p] + 1;
+  jb.w = a.rend[p] - a.rbeg[p] + 1;
+  safe_band(jb.m, jb.w, a.score[p], a.smax, a.o, a.e, &jb.dlo, &jb.bw);
+  const int64_t bytes = tb_pair_bytes(jb.m, jb.w, jb.dlo, jb.bw);
+  int64_t off = t.stride * (int64_t)blockIdx.x, room = t.stride;
+  if (t.used) {
+    if (threadIdx.x == 0) s_off = (int64_t)atomicAdd(t.used, (unsigned long long)bytes);
+    __syncthreads();
+    off = s_off;
+    room = t.cap - off;
+  }
+  if (bytes > room || (jb.m + 64 * RL - 1) / (64 * RL) > kTbMaxStrips) {
+    if (threadIdx.x == 0) a.err[p] = 1;   // never expected: the caller sized the scratch
+    return;
+  }
+  int32_t *bnd = reinterpret_cast<int32_t *>(t.scratch + off);
+  uint8_t *dir = t.scratch + off + tb_pair_bnd_bytes(jb.m, jb.w);
+  tb_wave_fill<RL, false>(a, jb, 0, 1, s_prog, s_done, s_mat, reinterpret_cast<int8_t *>(s_dyn),
+                          dir, bnd);
+  __syncthreads();
+  if (threadIdx.x < 64) tb_wave_walk<RL, kTbPairTile>(a, jb, dir, s_tile, (int)threadIdx.x);
+}
+
+hipError_t tb_pairs(const TbArgs &a, const TbPairs &t, int64_t blocks, int64_t max_rows,
+                    hipStream_t st) {
+  if (blocks == 0) return hipSuccess;
+  if (!t.sorted && !t.cls) return hipErrorInvalidValue;
+  const int64_t per = (int64_t)(a.n + 1) * 64 * kTbPairRows;
+  int64_t waves = (max_rows + 64 * kTbPairRows - 1) / (64 * kTbPairRows);
+  waves = std::min<int64_t>({waves, (int64_t)kTbPairMaxWaves, (65536 - 16384) / per});
+  if (waves < 1) waves = 1;
+  hipLaunchKernelGGL(k_tb_pairs, dim3((unsigned)blocks), dim3((unsigned)(64 * waves)),
+                     (size_t)(per * waves), st, a, t);
+  return hipGetLastError();
 }
 
 // The walk of spread pairs, one wave per pair, after their fill kernel.
@@ -1331,15 +1419,15 @@ __global__ __launch_bounds__(64) void k_tb_walk(TbArgs a, const TbWaveJob *jobs,
   __shared__ uint4 s_tile[kTbTileBytes / 16];
   const TbWaveJob jb = jobs[blockIdx.x];
   if (jb.m <= 0) return;
-  tb_wave_walk<RL>(a, jb, dirw + jb.dir_off, s_tile, (int)(threadIdx.x & 63));
+  tb_wave_walk<RL, kTbTileBytes>(a, jb, dirw + jb.dir_off, s_tile, (int)(threadIdx.x & 63));
 }
 
-template <int RL>
+template <int RL, int TILE>
 __device__ void tb_wave_walk(const TbArgs &a, const TbWaveJob &jb, const uint8_t *dir,
                              uint4 *s_tile, int lane) {
   constexpr int64_t SH = 64 * RL;
   constexpr int WB = RL / 2;
-  constexpr int TS = kTbTileBytes / (64 * WB);
+  constexpr int TS = TILE / (64 * WB);
   const int64_t p = jb.pair, m = jb.m, w = jb.w;
   const int32_t o = a.o, e = a.e;
   const int64_t nstrips = (m + SH - 1) / SH;

@@ -53,3 +53,31 @@ def test_main_diagonal_alignments(ctx, m, alphabet):
     flat = (recs["cigar_len"] == 1)
     assert flat.any()
     assert_parity(ctx, b, flags=swx.SWX_CIGAR)
+
+
+# a workgroup per pair: strips of 256 rows, one wave each up to four, then in
+# turn; the last strip ends with the last row's lane
+@pytest.mark.parametrize("m", [1, 3, 4, 5, 255, 256, 257, 512, 700, 1300])
+@pytest.mark.parametrize("alphabet", [4, 24])
+def test_pair_per_workgroup(ctx, m, alphabet):
+    g = np.random.Generator(np.random.PCG64(5000 + m))
+    qs, rs = [], []
+    for k in range(24):
+        core = g.integers(0, alphabet, size=m).astype(np.int8)
+        q, _ = W.mutate_many(g, core, np.array([0, m]), 0.05, 0.03, 0.03, 6, alphabet)
+        if len(q) == 0 or k % 4 == 3:   # unrelated: weak alignments, wide bands
+            q = g.integers(0, alphabet, size=m).astype(np.int8)
+        left, right = g.integers(0, 90, size=2)
+        r = np.concatenate([g.integers(0, alphabet, left), core, g.integers(0, alphabet, right)])
+        qs.append(q)
+        rs.append(r.astype(np.int8))
+    mat, o, e = (W.dna_matrix(), 3, 1) if alphabet == 4 else (W.protein_matrix_standin(), 11, 1)
+    assert_parity(ctx, W.from_lists(f"pairs-{m}-{alphabet}", mat, o, e, qs, rs))
+
+
+# the routes by scratch size: a few pairs in pair order, a batch by classes,
+# and one large enough that only its wide bands go pair by pair
+@pytest.mark.parametrize("npairs", [65, 5000, 45000])
+def test_traceback_routes_by_batch_size(ctx, npairs):
+    b = W.config4(npairs=npairs)
+    assert_parity(ctx, b)
