@@ -683,80 +683,73 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_intra_fill16(IntraArgs a) {
 }
 
 // ---- end of the best alignment and score2 from the max array --------------
-// Two phases: blocks (slice, pair) reduce a slice of one pair's max array to
-// its best (value, column) -- the largest value, then the smallest column --
-// and one block per pair reduces the slices.  T1 takes every column; T4
-// skips the masked columns around the primary alignment.
+// The best (value, column) of a pair's max array: the largest value, then the
+// smallest column.  T1 takes every column; T4 skips the masked columns around
+// the primary alignment.  References of up to kOneBlockCols columns take one
+// block per pair (a wave up to kOneWaveCols); longer ones are cut into
+// kSlices slices, reduced by a block each, and one wave per pair reduces the
+// slices.  Bound by launches and latency: with every reference cut into 64
+// slices, the 14,000 long pairs of a 20,000-read batch took 900,000 blocks and
+// 2.5 ms for both reductions (0.1 now), and the serial reduction of the slices
+// 7 us of a one-pair call.
 constexpr int kSlices = 64;
+constexpr int64_t kOneWaveCols = 1024, kOneBlockCols = 8192;
 
 __device__ __forceinline__ void better(int32_t &bv, int64_t &bj, int32_t v, int64_t j) {
   if (v > bv || (v == bv && j < bj)) { bv = v; bj = j; }
 }
 
-__device__ void block_best(int32_t &bv, int64_t &bj) {
-  __shared__ int32_t sv[256];
-  __shared__ int64_t sj[256];
-  sv[threadIdx.x] = bv;
-  sj[threadIdx.x] = bj;
-  __syncthreads();
-  for (int w = blockDim.x / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) {
-      int32_t v = sv[threadIdx.x];
-      int64_t j = sj[threadIdx.x];
-      better(v, j, sv[threadIdx.x + w], sj[threadIdx.x + w]);
-      sv[threadIdx.x] = v;
-      sj[threadIdx.x] = j;
-    }
-    __syncthreads();
+__device__ __forceinline__ void wave_best(int32_t &bv, int64_t &bj) {
+  for (int off = 32; off >= 1; off >>= 1) {
+    const int32_t v = __shfl_xor(bv, off, 64);
+    const int64_t j = __shfl_xor(bj, off, 64);
+    better(bv, bj, v, j);
   }
-  bv = sv[0];
-  bj = sj[0];
-  __syncthreads();
 }
 
-// mode 0: T1 over all columns; mode 1: T4 outside the mask
-__global__ __launch_bounds__(256) void k_intra_slices(IntraPairArgs a, int mode) {
-  const IntraPair ip = a.pairs[blockIdx.y];
+// every thread's best to the block's (up to four waves), on all threads
+template <int WAVES>
+__device__ __forceinline__ void block_best(int32_t &bv, int64_t &bj) {
+  wave_best(bv, bj);
+  if constexpr (WAVES > 1) {
+    __shared__ int32_t sv[WAVES];
+    __shared__ int64_t sj[WAVES];
+    if ((threadIdx.x & 63) == 0) {
+      sv[threadIdx.x >> 6] = bv;
+      sj[threadIdx.x >> 6] = bj;
+    }
+    __syncthreads();
+    for (int w = 0; w < WAVES; ++w) better(bv, bj, sv[w], sj[w]);
+  }
+}
+
+// best of columns [j0, j1) of one pair, this thread taking every `step`-th
+// from j0 + threadIdx.x.  mode 0: T1 over all columns; mode 1: T4 outside the mask
+__device__ __forceinline__ void scan_columns(const IntraPairArgs &a, const IntraPair &ip, int mode,
+                                             int64_t j0, int64_t j1, int32_t &bv, int64_t &bj) {
   const int64_t p = ip.pair;
-  const int64_t Lr = a.rlen[p];
   const uint32_t *mc = a.maxcol + ip.mc_off;
   int64_t lo = 1, hi = 0;   // masked columns [lo, hi]
-  bool skip = false;
+  bv = 0;
+  bj = INT64_MAX;
   if (mode == 1) {
-    skip = a.score[p] <= 0;
+    if (a.score[p] <= 0) return;
     int64_t m = a.mask_len;
     if (m < 0) { m = a.qlen[p] / 2; if (m < 15) m = 15; }
     lo = a.rbeg[p] - m;
     hi = a.rend[p] + m;
   }
-  const int64_t per = (Lr + kSlices - 1) / kSlices;
-  const int64_t j0 = (int64_t)blockIdx.x * per;
-  const int64_t j1 = (j0 + per < Lr) ? j0 + per : Lr;
-  int32_t bv = 0;
-  int64_t bj = INT64_MAX;
-  if (!skip) {
-    for (int64_t j = j0 + threadIdx.x; j < j1; j += blockDim.x) {
-      if (j >= lo && j <= hi) continue;
-      const int32_t v = (int32_t)(mc[j] >> ip.kbits);
-      if (v > bv) { bv = v; bj = j; }
-    }
-  }
-  block_best(bv, bj);
-  if (threadIdx.x == 0) {
-    a.part_v[(int64_t)blockIdx.y * kSlices + blockIdx.x] = bv;
-    a.part_j[(int64_t)blockIdx.y * kSlices + blockIdx.x] = bj;
+#pragma unroll 4
+  for (int64_t j = j0 + threadIdx.x; j < j1; j += blockDim.x) {
+    const int32_t v = (int32_t)(mc[j] >> ip.kbits);
+    if ((j < lo || j > hi) && v > bv) { bv = v; bj = j; }
   }
 }
 
-__global__ __launch_bounds__(64) void k_intra_finish(IntraPairArgs a, int mode) {
-  const IntraPair ip = a.pairs[blockIdx.x];
+// one thread: a pair's result from its best
+__device__ __forceinline__ void put_best(const IntraPairArgs &a, const IntraPair &ip, int mode,
+                                         int32_t bv, int64_t bj) {
   const int64_t p = ip.pair;
-  if (threadIdx.x != 0) return;
-  int32_t bv = 0;
-  int64_t bj = INT64_MAX;
-  for (int k = 0; k < kSlices; ++k)
-    better(bv, bj, a.part_v[(int64_t)blockIdx.x * kSlices + k],
-           a.part_j[(int64_t)blockIdx.x * kSlices + k]);
   if (mode == 0) {
     const uint32_t M = (1u << ip.kbits) - 1u;
     if (bv > 0) {
@@ -775,6 +768,40 @@ __global__ __launch_bounds__(64) void k_intra_finish(IntraPairArgs a, int mode) 
     a.score2[p] = bv;
     a.rend2[p] = bv > 0 ? bj : -1;
   }
+}
+
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void k_intra_best(IntraPairArgs a, int mode) {
+  const IntraPair ip = a.pairs[blockIdx.x];
+  int32_t bv;
+  int64_t bj;
+  scan_columns(a, ip, mode, 0, a.rlen[ip.pair], bv, bj);
+  block_best<WAVES>(bv, bj);
+  if (threadIdx.x == 0) put_best(a, ip, mode, bv, bj);
+}
+
+__global__ __launch_bounds__(256) void k_intra_slices(IntraPairArgs a, int mode) {
+  const IntraPair ip = a.pairs[blockIdx.y];
+  const int64_t Lr = a.rlen[ip.pair];
+  const int64_t per = (Lr + kSlices - 1) / kSlices;
+  const int64_t j0 = (int64_t)blockIdx.x * per;
+  int32_t bv;
+  int64_t bj;
+  scan_columns(a, ip, mode, j0, (j0 + per < Lr) ? j0 + per : Lr, bv, bj);
+  block_best<4>(bv, bj);
+  if (threadIdx.x == 0) {
+    a.part_v[(int64_t)blockIdx.y * kSlices + blockIdx.x] = bv;
+    a.part_j[(int64_t)blockIdx.y * kSlices + blockIdx.x] = bj;
+  }
+}
+
+__global__ __launch_bounds__(64) void k_intra_finish(IntraPairArgs a, int mode) {
+  static_assert(kSlices == 64, "one lane per slice");
+  const int64_t k = (int64_t)blockIdx.x * kSlices + threadIdx.x;
+  int32_t bv = a.part_v[k];
+  int64_t bj = a.part_j[k];
+  wave_best(bv, bj);
+  if (threadIdx.x == 0) put_best(a, a.pairs[blockIdx.x], mode, bv, bj);
 }
 
 // ---- fixed-capacity (graph) jobs: fixed counts and strides -----------------
@@ -949,6 +976,14 @@ size_t intra_static_lds() { return 32 * 32 + kMaxStrips * (4 + 4 + 8 + 4) + 8 + 
 int intra_slices() { return kSlices; }
 
 static hipError_t reduce(const IntraPairArgs &a, int64_t npairs, int mode, hipStream_t st) {
+  if (a.max_rlen <= kOneBlockCols) {
+    if (npairs > INT32_MAX) return hipErrorInvalidValue;
+    if (a.max_rlen <= kOneWaveCols)
+      hipLaunchKernelGGL(k_intra_best<1>, dim3((unsigned)npairs), dim3(64), 0, st, a, mode);
+    else
+      hipLaunchKernelGGL(k_intra_best<4>, dim3((unsigned)npairs), dim3(256), 0, st, a, mode);
+    return hipGetLastError();
+  }
   for (int64_t b0 = 0; b0 < npairs; b0 += 65535) {
     const int64_t nb = (npairs - b0 < 65535) ? npairs - b0 : 65535;
     IntraPairArgs s = a;

@@ -919,6 +919,7 @@ struct LongPath {
   std::vector<int64_t> ids;     // long pair ids (host)
   std::vector<int64_t> info;    // gather_pairs fields per long pair
   std::vector<IntraPair> pairs;
+  int64_t max_rlen = 0;
   IntraPair *d_pairs = nullptr;
   uint32_t *d_maxcol = nullptr;
   int32_t *d_part_v = nullptr;  // partial bests of the max-array reductions
@@ -1172,7 +1173,10 @@ static int run_intra_forward(swx_ctx *ctx, const Scoring &sc, LongPath &lp, cons
                              const FillOut &out, uint8_t *err, uint8_t *lanebits) {
   DevArena &A = ctx->arena;
   int64_t total_r = 0;
-  for (int64_t k = 0; k < lp.nlong; ++k) total_r += std::max<int64_t>(lp.info[6 * k + 1], 1);
+  for (int64_t k = 0; k < lp.nlong; ++k) {
+    total_r += std::max<int64_t>(lp.info[6 * k + 1], 1);
+    lp.max_rlen = std::max(lp.max_rlen, lp.info[6 * k + 1]);
+  }
   Jobs16 jobs16;
   std::vector<int64_t> ids16, ids32;
   lp.pairs.clear();
@@ -1282,7 +1286,7 @@ static int run_intra_forward(swx_ctx *ctx, const Scoring &sc, LongPath &lp, cons
   IntraPairArgs e{};
   e.pairs = lp.d_pairs; e.maxcol = lp.d_maxcol; e.qlen = view.qlen; e.rlen = view.rlen;
   e.score = out.score; e.qend = out.qend; e.rend = out.rend; e.overflow = out.overflow;
-  e.part_v = lp.d_part_v; e.part_j = lp.d_part_j;
+  e.part_v = lp.d_part_v; e.part_j = lp.d_part_j; e.max_rlen = lp.max_rlen;
   HIP_TRY(intra_end(e, lp.nlong, ctx->stream));
   return SWX_OK;
 }
@@ -1571,7 +1575,7 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
       e.pairs = lp.d_pairs; e.maxcol = lp.d_maxcol; e.qlen = qlen; e.rlen = rlen;
       e.score = score; e.qend = qend; e.rend = rend; e.rbeg = rbeg;
       e.mask_len = mask_len; e.score2 = score2; e.rend2 = rend2;
-      e.part_v = lp.d_part_v; e.part_j = lp.d_part_j;
+      e.part_v = lp.d_part_v; e.part_j = lp.d_part_j; e.max_rlen = lp.max_rlen;
       HIP_TRY(intra_score2(e, lp.nlong, st));
     }
   }
@@ -1921,7 +1925,7 @@ static int fixed_issue(GraphState &g, hipStream_t st) {
     IntraPairArgs e{};
     e.pairs = g.ipairs; e.maxcol = g.maxcol; e.qlen = g.qlen; e.rlen = g.rlen;
     e.score = g.score; e.qend = g.qend; e.rend = g.rend; e.overflow = g.ovf;
-    e.part_v = g.part_v; e.part_j = g.part_j;
+    e.part_v = g.part_v; e.part_j = g.part_j; e.max_rlen = g.RM;
     HIP_TRY(intra_end(e, B, st));
   } else if ((rc = fixed_fill(g, g.p16, nullptr, nullptr, g.qlen, g.rlen, nullptr, nullptr, fview, false,
                               nullptr, fout, st))) {
@@ -2043,7 +2047,7 @@ static int fixed_issue(GraphState &g, hipStream_t st) {
     e.pairs = g.ipairs; e.maxcol = g.maxcol; e.qlen = g.qlen; e.rlen = g.rlen;
     e.score = g.score; e.qend = g.qend; e.rend = g.rend; e.rbeg = g.rbeg;
     e.mask_len = g.cfg.mask_len; e.score2 = g.score2; e.rend2 = g.rend2;
-    e.part_v = g.part_v; e.part_j = g.part_j;
+    e.part_v = g.part_v; e.part_j = g.part_j; e.max_rlen = g.RM;
     HIP_TRY(intra_score2(e, B, st));
   } else if (flags & SWX_SCORE2) {
     Score2InterArgs s2{};

@@ -274,6 +274,7 @@ struct IntraPairArgs {
   int64_t *rend2;
   int32_t *part_v;         // per (pair, slice) partial bests: intra_slices() per pair
   int64_t *part_j;
+  int64_t max_rlen;        // longest reference of the launch (its shape)
 };
 size_t intra_lds_bytes(int n, int RL);
 int intra_slices();
