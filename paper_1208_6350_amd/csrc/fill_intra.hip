@@ -460,8 +460,12 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_intra_fill16(IntraArgs a) {
   const int wave = threadIdx.x >> 6;
   const int NW = blockDim.x >> 6;
   const int n = a.n;
-  const IntraJob jA = a.jobs[2 * (int64_t)blockIdx.x];
-  const IntraJob jB = a.jobs[2 * (int64_t)blockIdx.x + 1];
+  // one pair of jobs per workgroup, its strips on the waves; or (a.segs > 1,
+  // jobs of one strip) a pair of jobs per wave
+  const int64_t jx = a.segs > 1 ? (int64_t)blockIdx.x * NW + wave : (int64_t)blockIdx.x;
+  const bool present = 2 * jx < a.njobs;   // the last workgroup may have waves without jobs
+  const IntraJob jA = a.jobs[present ? 2 * jx : 0];
+  const IntraJob jB = a.jobs[present ? 2 * jx + 1 : 1];
   const bool hasB = jB.pair >= 0;
   const int64_t pA = jA.pair, pB = hasB ? jB.pair : jA.pair;
   const int32_t LqA = a.view.qlen[pA], LqB = a.view.qlen[pB];
@@ -487,8 +491,9 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_intra_fill16(IntraArgs a) {
   uint8_t *s_profB = s_profA + tbl;
   // v_perm selectors: the low (A) or high (B) 16-bit half of H above a 16-bit code
   const uint32_t selA = 0x05040100u, selB = 0x07060100u;
+  if (!present) return;
 
-  for (int s = wave; s < nstrips; s += NW) {
+  for (int s = a.segs > 1 ? 0 : wave; s < nstrips; s += a.segs > 1 ? 1 : NW) {
     uint32_t *bHA = a.bnd + jA.bnd_off + 2 * widthA * (int64_t)s;
     uint32_t *bFA = bHA + widthA;
     uint32_t *bHB = a.bnd + (hasB ? jB.bnd_off : jA.bnd_off) + 2 * widthB * (int64_t)s;
@@ -929,7 +934,8 @@ hipError_t intra_sync_init(IntraSync *sync, int64_t njobs, hipStream_t st) {
 
 template <int RL>
 static void launch_rl16(const IntraArgs &a, int waves, bool m3, hipStream_t st) {
-  const dim3 g((unsigned)(a.njobs / 2)), b(64 * waves);
+  const int64_t pairs = a.njobs / 2;
+  const dim3 g((unsigned)(a.segs > 1 ? (pairs + waves - 1) / waves : pairs)), b(64 * waves);
   const size_t lds = intra_lds_bytes16(a.n, RL) * waves;
   if (a.bias == a.o) {   // H and H - o are one value
     if (m3) hipLaunchKernelGGL((k_intra_fill16<RL, true, true>), g, b, lds, st, a);

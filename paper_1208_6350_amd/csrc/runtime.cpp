@@ -1095,14 +1095,89 @@ static IntraShape intra_shape(int64_t rows, int64_t width, int32_t band, int n, 
   return best;
 }
 
+// How the forward pass of long pairs cuts up: rows per lane and, for one pair,
+// columns per chunk, planned so that the waves of all jobs number one per SIMD
+// (`lanes` jobs share a wave: two on 16-bit lanes).  A second wave on a SIMD
+// halves both (the pass is bound by VALU issue), and only shortens the chunks,
+// not their warm-up; short lanes cut a query into strips that run beside each
+// other, so that fewer, longer chunks fill the device and repeat less warm-up.
+// Only shapes whose workgroups put one wave on each SIMD of a compute unit:
+// four strips or more, or (16-bit lanes) one strip, four pairs of jobs to a
+// workgroup; workgroups of one or two waves pile up on some SIMDs (1,000 x
+// 5,000,000 in two strips: 3.79 ms).  Measured, 16-bit lanes, 1,000 x
+// 5,000,000: 1.6 waves per SIMD 3.85 ms, one 2.65; 300 x 5,000,000: 1.69,
+// 1.02; 32-bit lanes, 1,000 x 1,000,000: one strip 1.58 ms, four 1.13.
+struct FwdPlan {
+  int rl = 0;
+  int64_t jobs = 0;
+  double est = 0;   // instructions of the longest path
+};
+
+constexpr int64_t kFwdPlanPairs = 64;
+
+static int64_t fwd_chunk(const Scoring &sc, int64_t Lq, int64_t Lr, int RL, int64_t waves,
+                         int64_t max_jobs, int64_t total_r) {
+  if (intra_warmup(sc, Lq, Lr) >= Lr) return std::max<int64_t>(Lr, 1);
+  const int64_t S = (Lq + 64 * RL - 1) / (64 * RL);
+  const double share = (double)Lr / (double)std::max<int64_t>(total_r, 1);
+  const int64_t want = std::max<int64_t>(
+      1, (int64_t)std::min((double)waves * share / (double)S, (double)max_jobs * share));
+  return std::max<int64_t>((Lr + want - 1) / want, 64);
+}
+
+// The cheapest plan over the pairs `ids` of info (gather_pairs fields): the
+// longer of the longest job's chain of strips (each about 150 columns after
+// the one above) and all the work over the SIMDs.
+static FwdPlan plan_forward(const Scoring &sc, const std::vector<int64_t> &info,
+                            const std::vector<int64_t> &ids, int lanes, int64_t max_jobs,
+                            int32_t cus) {
+  FwdPlan best;
+  int64_t total_r = 0;
+  for (int64_t k : ids) total_r += std::max<int64_t>(info[6 * k + 1], 1);
+  const int64_t simds = 4 * (int64_t)std::max(cus, 1);
+  for (int RL : {4, 8, 16, 32}) {
+    const int64_t lds = lanes == 2 ? (int64_t)intra_lds_bytes16(sc.n, RL) + 4096
+                                   : (int64_t)(intra_lds_bytes(sc.n, RL) + intra_static_lds());
+    if (lds > 65536) continue;
+    FwdPlan pl;
+    pl.rl = RL;
+    double work = 0, chain = 0;
+    bool fits = true;
+    const double cost = (12 * RL + (lanes == 2 ? 40 : 25));
+    for (int64_t k : ids) {
+      const int64_t Lq = info[6 * k], Lr = info[6 * k + 1];
+      if (Lr == 0) continue;
+      const int64_t S = (Lq + 64 * RL - 1) / (64 * RL);
+      if (S > intra_max_strips() || (S < 4 && (lanes == 1 || S > 1)) ||
+          (lanes == 2 && !intra_fits16(sc, Lq, Lr, RL))) {
+        fits = false;
+        break;
+      }
+      const int64_t wv = lanes == 2 ? intra_waves16(S, sc.n, RL) : intra_waves(S, sc.n, RL);
+      const int64_t C = fwd_chunk(sc, Lq, Lr, RL, simds * lanes, max_jobs, total_r);
+      const int64_t n = (Lr + C - 1) / C, width = std::min(Lr, C + intra_warmup(sc, Lq, Lr));
+      pl.jobs += n;
+      work += (double)n * (double)S * (double)(width + 63) * cost / lanes;
+      const double turns = (double)((S + wv - 1) / wv) * (double)(width + 63);
+      chain = std::max(chain, std::max((double)((S - 1) * 150 + width + 63), turns) * cost);
+    }
+    if (!fits) continue;
+    pl.est = std::max(chain, work / (double)simds);
+    if (best.rl == 0 || pl.est < best.est) best = pl;
+  }
+  return best;
+}
+
 // 16-bit forward jobs keyed by (rows per lane, strips): jobs of one key share
 // their padded height, so any two of them can share a wave.
 typedef std::map<std::pair<int, int64_t>, std::vector<IntraJob>> Jobs16;
 
 // Upload the 16-bit jobs (each key's list padded to an even count with an
 // empty job) and launch them, a pair of jobs per workgroup.
+// packed: jobs of one strip go four waves to a workgroup, a pair of jobs each
+// (planned chunks of equal width: a workgroup ends with its longest wave).
 static int launch_intra16_jobs(swx_ctx *ctx, const Jobs16 &jobs, IntraArgs a, const Scoring &sc,
-                               bool m3) {
+                               bool m3, bool packed) {
   if (jobs.empty()) return SWX_OK;
   std::vector<IntraJob> all;
   std::vector<std::pair<int64_t, int64_t>> span;   // per key: first job, count
@@ -1125,7 +1200,10 @@ static int launch_intra16_jobs(swx_ctx *ctx, const Jobs16 &jobs, IntraArgs a, co
     const int RL = kv.first.first;
     a.jobs = dj + span[k].first;
     a.njobs = span[k].second;
-    HIP_TRY(intra_fill16(a, RL, intra_waves16(kv.first.second, sc.n, RL), m3, ctx->stream));
+    int waves = intra_waves16(kv.first.second, sc.n, RL);
+    a.segs = 1;
+    if (packed && kv.first.second == 1) a.segs = waves = intra_waves16(4, sc.n, RL);
+    HIP_TRY(intra_fill16(a, RL, waves, m3, ctx->stream));
     ++k;
   }
   HIP_TRY(hipStreamSynchronize(ctx->stream));   // the host job table must outlive the copy
@@ -1201,15 +1279,28 @@ static int run_intra_forward(swx_ctx *ctx, const Scoring &sc, LongPath &lp, cons
   }
   // lanes of each pair, and the 32-bit jobs that will share the device
   std::vector<uint8_t> is16(lp.nlong);
-  int64_t jobs32 = 0;
+  std::vector<int64_t> k16, k32;
+  int64_t jobs32 = 0, r16 = 0, r32 = 0;
   for (int64_t k = 0; k < lp.nlong; ++k) {
     const int64_t Lq = lp.info[6 * k], Lr = lp.info[6 * k + 1];
     is16[k] = (ctx->intra_bits == 16 || auto16) && intra_fits16(sc, Lq, Lr, pick_rl(Lq, sc.n));
+    (is16[k] ? k16 : k32).push_back(k);
+    (is16[k] ? r16 : r32) += std::max<int64_t>(Lr, 1);
     if (!is16[k] && Lr > 0) {
       const int64_t C = intra_chunk(sc, Lq, Lr, ctx->intra_jobs, total_r);
       jobs32 += (Lr + C - 1) / C;
     }
   }
+  // a few pairs are planned together (many fill the device by their number);
+  // 32-bit jobs that leave compute units idle spread over several workgroups
+  // each (intra_shape) instead
+  FwdPlan f16, f32;
+  if (lp.nlong <= kFwdPlanPairs) {
+    f16 = plan_forward(sc, lp.info, k16, 2, 2 * ctx->intra_jobs, ctx->cus);
+    f32 = plan_forward(sc, lp.info, k32, 1, ctx->intra_jobs, ctx->cus);
+  }
+  const bool plan16 = f16.rl != 0, plan32 = f32.rl != 0 && f32.jobs >= ctx->cus;
+  const int64_t simds = 4 * (int64_t)std::max(ctx->cus, 1);
   IntraGroups groups;
   int64_t mc_words = 0, bnd_words = 0;
   bool m3 = true;   // every 16-bit pair's lane values below 0x7C00
@@ -1217,9 +1308,18 @@ static int run_intra_forward(swx_ctx *ctx, const Scoring &sc, LongPath &lp, cons
     const int64_t p = lp.ids[k], Lq = lp.info[6 * k], Lr = lp.info[6 * k + 1];
     const bool w16 = is16[k];
     const int64_t W = intra_warmup(sc, Lq, Lr);
-    const int64_t C = intra_chunk(sc, Lq, Lr, (w16 ? 2 : 1) * ctx->intra_jobs, total_r);
-    const IntraShape shape = w16 ? IntraShape{pick_rl(Lq, sc.n), 0, 1}
-                                 : intra_shape(Lq, std::min(Lr, C + W), -1, sc.n, jobs32, ctx->cus);
+    int64_t C = intra_chunk(sc, Lq, Lr, (w16 ? 2 : 1) * ctx->intra_jobs, total_r);
+    IntraShape shape{};
+    if (w16 && plan16) {
+      C = fwd_chunk(sc, Lq, Lr, f16.rl, 2 * simds, 2 * ctx->intra_jobs, r16);
+      shape = IntraShape{f16.rl, 0, 1};
+    } else if (!w16 && plan32) {
+      C = fwd_chunk(sc, Lq, Lr, f32.rl, simds, ctx->intra_jobs, r32);
+      shape = IntraShape{f32.rl, intra_waves((Lq + 64 * f32.rl - 1) / (64 * f32.rl), sc.n, f32.rl), 1};
+    } else {
+      shape = w16 ? IntraShape{pick_rl(Lq, sc.n), 0, 1}
+                  : intra_shape(Lq, std::min(Lr, C + W), -1, sc.n, jobs32, ctx->cus);
+    }
     const int RL = shape.rl;
     const int64_t SH = 64 * RL;
     const int64_t qp = (Lq + SH - 1) / SH * SH;
@@ -1272,7 +1372,7 @@ static int run_intra_forward(swx_ctx *ctx, const Scoring &sc, LongPath &lp, cons
   if (!a.bnd) return fail(SWX_ENOMEM, "device pool exhausted (hand-over rows)");
   int rc;
   if ((rc = launch_intra_jobs(ctx, groups, a, bnd_words, false))) return rc;
-  if ((rc = launch_intra16_jobs(ctx, jobs16, a, sc, m3))) return rc;
+  if ((rc = launch_intra16_jobs(ctx, jobs16, a, sc, m3, plan16))) return rc;
   // lane widths of the long pairs (diagnostic)
   for (int w = 0; w < 2; ++w) {
     const std::vector<int64_t> &ids = w ? ids32 : ids16;

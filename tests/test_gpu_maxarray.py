@@ -39,3 +39,29 @@ def test_end_and_score2_with_ties(ctx, rlen):
     b = W.from_lists(f"ties-{rlen}", W.dna_matrix(), 3, 1, qs, rs)
     assert_parity(ctx, b)
     assert_parity(ctx, b, mask_len=3)
+
+
+# the forward pass of a few long pairs, cut so that the waves number one per
+# SIMD: one strip, four pairs of jobs to a workgroup (the last one partly
+# filled), or four strips and more; with a reference shorter than the warm-up
+# and one that is empty beside them
+@pytest.mark.parametrize("bits", [16, 32])
+@pytest.mark.parametrize("qlen,rlens", [(30, [9000]), (150, [30001, 700, 5000]), (256, [70000]),
+                                        (257, [20000, 20001]), (900, [40000, 0, 1500]),
+                                        (1030, [30000])])
+def test_planned_chunks(qlen, rlens, bits):
+    c = swx.Context(0)
+    c.set_tuning(long_cells=0, long_rlen=0, intra_bits=bits)
+    g = np.random.Generator(np.random.PCG64(6100 + qlen))
+    qs, rs = [], []
+    for n in rlens:
+        q = g.integers(0, 4, size=qlen).astype(np.int8)
+        r = g.integers(0, 4, size=n).astype(np.int8)
+        for at in (0, n // 2, n - qlen):   # copies with gaps, their tails reaching the next chunks
+            if 0 <= at and at + qlen <= n:
+                cp, _ = W.mutate_many(g, q, np.array([0, qlen]), 0.02, 0.01, 0.01, 5)
+                r[at:at + min(qlen, len(cp))] = cp[:qlen]
+        qs.append(q)
+        rs.append(r)
+    assert_parity(c, W.from_lists(f"planned-{qlen}", W.dna_matrix(), 3, 1, qs, rs))
+    c.close()
