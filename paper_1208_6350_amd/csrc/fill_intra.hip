@@ -93,16 +93,8 @@ __device__ __forceinline__ void lds_store_words(uint8_t *dst, const uint32_t (&w
 // strip depends only on the one above, the waves of a workgroup are resident
 // together, and no strip ever waits on a later one, so the waits always end;
 // a spin limit still bounds them (exceeding it flags the pair as failed).
-//
-// Spread jobs (SPREAD): the strips of one job run on the waves of `segs`
-// workgroups (global wave g = segment * NW + wave takes strips g, g + segs*NW,
-// ...), with the progress counters, the reversed pass's hits and a completion
-// count in global memory (IntraSync, agent-scope release and acquire).  The
-// host launches a spread grid only when every workgroup of it fits on the
-// device at once (at most one per compute unit), so a strip's producer is
-// always running; the same spin limit bounds the waits.
 constexpr int kMaxStrips = kIntraMaxStrips;
-constexpr int kMaxWaves = 8;
+constexpr int kMaxWaves = 8, kSpreadMaxWaves = 4;
 constexpr int64_t kSpinLimit = int64_t(1) << 26;
 
 __device__ __forceinline__ void lds_wave_sync() {
@@ -110,39 +102,21 @@ __device__ __forceinline__ void lds_wave_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
-template <int RL, bool REV, bool SPREAD, bool HO>
+template <int RL, bool REV, bool HO>
 __global__ __launch_bounds__(64 * kMaxWaves) void k_intra_fill(IntraArgs a) {
   extern __shared__ uint4 s_dyn[];            // per wave: [(n + 1) symbols][64 lanes][RL bytes]
   __shared__ int8_t s_mat[32 * 32];
-  __shared__ int32_t l_prog[SPREAD ? 1 : kMaxStrips];      // columns published by strip s (from its window start)
-  __shared__ int32_t l_done[SPREAD ? 1 : kMaxStrips];      // strip s finished (its progress is final)
-  __shared__ int64_t l_rcol[SPREAD ? 1 : kMaxStrips];      // reversed pass: first column of strip s reaching the target
-  __shared__ int32_t l_rrow[SPREAD ? 1 : kMaxStrips];
-  __shared__ unsigned long long l_best;       // reversed pass: smallest such column so far (~0: none)
+  __shared__ int32_t s_prog[kMaxStrips];      // columns published by strip s (from its window start)
+  __shared__ int32_t s_done[kMaxStrips];      // strip s finished (its progress is final)
+  __shared__ int64_t s_rcol[kMaxStrips];      // reversed pass: first column of strip s reaching the target
+  __shared__ int32_t s_rrow[kMaxStrips];
+  __shared__ unsigned long long s_best;       // reversed pass: smallest such column so far (~0: none)
   constexpr int SH = 64 * RL;
-  constexpr int SCOPE = SPREAD ? __HIP_MEMORY_SCOPE_AGENT : __HIP_MEMORY_SCOPE_WORKGROUP;
+  constexpr int SCOPE = __HIP_MEMORY_SCOPE_WORKGROUP;
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int NW = blockDim.x >> 6;
-  // spread grids: workgroups go to the 8 XCDs round robin by block id, so
-  // block 8 * slot + x (slot = (j / 8) * G + segment) puts every segment of
-  // job j on XCD j % 8, where the hand-over rows stay in one L2; the grid is
-  // 8 * G * ceil(njobs / 8) blocks and those past the last job leave at once
-  const int G = SPREAD ? a.segs : 1;
-  int64_t jix = blockIdx.x, seg = 0;
-  if constexpr (SPREAD) {
-    const int64_t slot = blockIdx.x / 8;
-    jix = (slot / G) * 8 + blockIdx.x % 8;
-    seg = slot % G;
-    if (jix >= a.njobs) return;
-  }
-  IntraSync *gs = SPREAD ? a.sync + jix : nullptr;
-  int32_t *s_prog = SPREAD ? gs->prog : l_prog;
-  int32_t *s_done = SPREAD ? gs->done : l_done;
-  int64_t *s_rcol = SPREAD ? gs->rcol : l_rcol;
-  int32_t *s_rrow = SPREAD ? gs->rrow : l_rrow;
-  unsigned long long *s_best = SPREAD ? &gs->best : &l_best;
-  const IntraJob jb = a.jobs[jix];
+  const IntraJob jb = a.jobs[blockIdx.x];
   if (!REV && jb.c1 <= jb.cw) return;   // an empty column chunk
   const int64_t p = jb.pair;
   const int32_t Lq = a.view.qlen[p];
@@ -154,15 +128,13 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_intra_fill(IntraArgs a) {
   const int64_t qp = ((int64_t)Lq + SH - 1) / SH * SH;
   const int nstrips = (int)(qp / SH);
   for (int i = threadIdx.x; i < n * n; i += blockDim.x) s_mat[i] = a.matrix[i];
-  if constexpr (!SPREAD) {   // spread jobs: set by intra_sync_init before the launch
-    for (int i = threadIdx.x; i < nstrips && i < kMaxStrips; i += blockDim.x) {
-      s_prog[i] = 0;
-      s_done[i] = 0;
-      s_rcol[i] = -1;
-      s_rrow[i] = -1;
-    }
-    if (threadIdx.x == 0) *s_best = ~0ull;
+  for (int i = threadIdx.x; i < nstrips && i < kMaxStrips; i += blockDim.x) {
+    s_prog[i] = 0;
+    s_done[i] = 0;
+    s_rcol[i] = -1;
+    s_rrow[i] = -1;
   }
+  if (threadIdx.x == 0) s_best = ~0ull;
   __syncthreads();
 
   const int64_t qpad = REV ? 0 : qp - Lq;   // forward: padding rows on top
@@ -188,16 +160,10 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_intra_fill(IntraArgs a) {
     if (chi < clo) chi = clo;
   };
 
-  auto fence_rel = [] {
-    if constexpr (SPREAD) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    else __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  };
-  auto fence_acq = [] {
-    if constexpr (SPREAD) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    else __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-  };
+  auto fence_rel = [] { __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup"); };
+  auto fence_acq = [] { __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup"); };
 
-  for (int s = (int)seg * NW + wave; s < nstrips; s += G * NW) {
+  for (int s = wave; s < nstrips; s += NW) {
     int64_t clo, chi, plo = 0, phi = 0;
     window(s, clo, chi);
     if (s > 0) window(s - 1, plo, phi);
@@ -215,7 +181,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_intra_fill(IntraArgs a) {
       }
     };
     // the reversed pass skips a strip that cannot hold an earlier column
-    if (REV && __hip_atomic_load(s_best, __ATOMIC_RELAXED, SCOPE) <= (unsigned long long)clo) {
+    if (REV && __hip_atomic_load(&s_best, __ATOMIC_RELAXED, SCOPE) <= (unsigned long long)clo) {
       publish(0, true);
       continue;
     }
@@ -310,8 +276,11 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_intra_fill(IntraArgs a) {
 #pragma unroll 1
     for (int64_t t0 = 0; t0 < nsteps; t0 += 64) {
       if (REV && t0 >= 63 &&
-          (unsigned long long)(clo + t0 - 63) >= __hip_atomic_load(s_best, __ATOMIC_RELAXED, SCOPE)) {
-        cdone = clo + t0 - 63;   // an earlier strip already reached the target at or before here
+          (unsigned long long)(clo + t0 - 63) >= __hip_atomic_load(&s_best, __ATOMIC_RELAXED, SCOPE)) {
+        // an earlier strip already reached the target at or before here; the
+        // last step's column is still queued
+        flush(clo + t0 - 64, 0);
+        cdone = clo + t0 - 63;
         break;
       }
       if (t0 > 0) {
@@ -379,7 +348,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_intra_fill(IntraArgs a) {
               if (lane == 0) {
                 s_rcol[s] = col;
                 s_rrow[s] = (int32_t)(M - (oc & M));
-                atomicMin(s_best, (unsigned long long)col);
+                atomicMin(&s_best, (unsigned long long)col);
               }
               return true;
             }
@@ -407,19 +376,7 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_intra_fill(IntraArgs a) {
     publish((int32_t)(cdone - clo), true);
     if (spin_fail && lane == 0) a.err[p] = 1;   // reported as an internal failure
   }
-  if constexpr (SPREAD) {
-    if constexpr (!REV) return;
-    // the last segment of the job to finish reduces the strips' hits
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    __syncthreads();
-    __shared__ int32_t s_last;
-    if (threadIdx.x == 0) s_last = atomicAdd(&gs->fin, 1) == G - 1;
-    __syncthreads();
-    if (!s_last) return;
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-  } else {
-    __syncthreads();
-  }
+  __syncthreads();
 
   if (REV && threadIdx.x == 0) {
     // first column reaching the target; on a tie the earlier strip (smaller row)
@@ -433,6 +390,298 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_intra_fill(IntraArgs a) {
     a.out.qend[p] = hit ? br : -1;
     a.out.rend[p] = hit ? bc : -1;
     a.out.overflow[p] = 0;
+  }
+}
+
+// ---- spread jobs: one pair's strips over several workgroups -------------------
+// The 32-bit pass with the strips of one job on the waves of `segs` workgroups
+// (global wave g = segment * NW + wave takes strips g, g + segs * NW, ...).
+// The host launches it only when every workgroup of the grid fits on the
+// device at once (at most one per compute unit), so a strip's producer is
+// always running; a spin limit bounds the waits all the same.
+//
+// Bound by the chain of strips: strip s + 1 follows strip s by the wavefront's
+// 63 steps plus what the hand-over takes, once per strip.  The hand-over is one
+// 64-bit word per column, valid << 63 | F << 32 | H, stored and loaded with
+// relaxed agent-scope atomics: the word is its own flag, so no fence (a write
+// back of the L2 per publish) and no progress counter stand between the store
+// and the load, and 16 columns go at a time.  The words are cleared before the
+// launch.  A block of 16 steps reads its words one block ahead and looks at
+// them again only when some were not there yet.  With counters, fences and 64
+// columns at a time a strip started 270 steps after the one above, now TBD.
+// Measured, 10,000 x 20,000: forward 4.3 -> TBD ms, reversed 3.5 -> TBD.
+constexpr int kSpreadBlock = 16;
+constexpr uint64_t kWordValid = 1ull << 63;
+
+// RL profile bytes of one lane and symbol as words (RL = 2: the low half)
+template <int RL>
+__device__ __forceinline__ void prof_load(const uint8_t *src, uint32_t (&w)[RL >= 4 ? RL / 4 : 1]) {
+  if constexpr (RL >= 4) lds_load_words<RL>(src, w);
+  else w[0] = *reinterpret_cast<const uint16_t *>(src);
+}
+
+template <int RL, bool REV, bool HO>
+__global__ __launch_bounds__(64 * kSpreadMaxWaves) void k_intra_spread(IntraArgs a) {
+  extern __shared__ uint4 s_dyn[];            // per wave: [(n + 1) symbols][64 lanes][RL bytes]
+  __shared__ int8_t s_mat[32 * 32];
+  __shared__ int32_t s_last;
+  constexpr int SH = 64 * RL;
+  constexpr int XW = RL >= 4 ? RL / 4 : 1;
+  constexpr int kUnroll = RL <= 4 ? kSpreadBlock : (RL == 8 ? 4 : 1);
+  constexpr int AGENT = __HIP_MEMORY_SCOPE_AGENT;
+  using T = VT<uint32_t>;
+  const int lane = threadIdx.x & 63;
+  const int wave = threadIdx.x >> 6;
+  const int NW = blockDim.x >> 6;
+  // workgroups go to the 8 XCDs round robin by block id, so block 8 * slot + x
+  // (slot = (j / 8) * G + segment) puts every segment of job j on XCD j % 8,
+  // where the hand-over words stay in one L2; the grid is 8 * G * ceil(njobs /
+  // 8) blocks and those past the last job leave at once
+  const int G = a.segs;
+  const int64_t slot = blockIdx.x / 8;
+  const int64_t jix = (slot / G) * 8 + blockIdx.x % 8;
+  const int seg = (int)(slot % G);
+  if (jix >= a.njobs) return;
+  IntraSync *gs = a.sync + jix;
+  const IntraJob jb = a.jobs[jix];
+  const int64_t p = jb.pair;
+  const int32_t Lq = a.view.qlen[p];
+  const int64_t Lr = a.view.rlen[p];
+  const int8_t *qs = a.view.qcat + a.view.qstart[p];
+  const int8_t *rs = a.view.rcat + a.view.rstart[p];
+  const bool rv = a.view.reversed != 0;
+  const int n = a.n;
+  const int64_t qp = ((int64_t)Lq + SH - 1) / SH * SH;
+  const int nstrips = (int)(qp / SH);
+  for (int i = threadIdx.x; i < n * n; i += blockDim.x) s_mat[i] = a.matrix[i];
+  __syncthreads();
+
+  const int64_t qpad = REV ? 0 : qp - Lq;   // forward: padding rows on top
+  const int kb = jb.kbits;
+  const uint32_t M = (1u << kb) - 1u;
+  const int32_t tgt = REV ? a.target[p] : 0;
+  const int64_t width = jb.c1 - jb.cw;
+  uint32_t *mc = a.maxcol + jb.mc_off;
+  uint64_t *rows = reinterpret_cast<uint64_t *>(a.bnd + jb.bnd_off);   // [strip][width]
+  const uint32_t vbias = (uint32_t)a.bias, vo = (uint32_t)a.o, ve = (uint32_t)a.e;
+  uint8_t *s_prof = reinterpret_cast<uint8_t *>(s_dyn) + (size_t)wave * (n + 1) * 64 * RL;
+
+  // column window of strip s (the reversed pass bands it)
+  auto window = [&](int s, int64_t &clo, int64_t &chi) {
+    clo = jb.cw;
+    chi = jb.c1;
+    if (REV && jb.band >= 0) {
+      const int64_t l = (int64_t)s * SH - jb.band;
+      if (l > clo) clo = l;
+      const int64_t h = (int64_t)s * SH + SH + jb.band;
+      if (h < chi) chi = h;
+    }
+    if (chi < clo) chi = clo;
+  };
+
+  for (int s = seg * NW + wave; s < nstrips; s += G * NW) {
+    int64_t clo, chi, plo = 0, phi = 0;
+    window(s, clo, chi);
+    if (s > 0) window(s - 1, plo, phi);
+    uint64_t *out = rows + width * (int64_t)s;   // this strip's words
+    const uint64_t *in = out - width;            // those of strip s - 1
+    const bool hand_over = (s + 1 < nstrips);
+    bool spin_fail = false;
+    auto finish = [&]() {   // every word of the strip is stored
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      if (lane == 0) __hip_atomic_store(&gs->done[s], 1, __ATOMIC_RELAXED, AGENT);
+    };
+    // the reversed pass skips a strip that cannot hold an earlier column
+    if (chi <= clo ||
+        (REV && __hip_atomic_load(&gs->best, __ATOMIC_RELAXED, AGENT) <= (unsigned long long)clo)) {
+      finish();
+      continue;
+    }
+
+    // strip profile: biased scores of this lane's RL rows against every symbol
+    {
+      int32_t qv[RL];
+#pragma unroll
+      for (int r = 0; r < RL; ++r) {
+        const int64_t i = (int64_t)s * SH + lane * RL + r - qpad;
+        qv[r] = (i >= 0 && i < Lq) ? (int32_t)qs[rv ? Lq - 1 - i : i] : -1;
+      }
+      for (int sy = 0; sy <= n; ++sy) {
+        uint32_t w[XW];
+#pragma unroll
+        for (int k = 0; k < XW; ++k) w[k] = 0u;
+#pragma unroll
+        for (int r = 0; r < RL; ++r) {
+          const uint32_t b = (qv[r] >= 0 && sy < n) ? (uint32_t)(uint8_t)(s_mat[qv[r] * n + sy] + a.bias) : 0u;
+          w[r >> 2] |= b << (8 * (r & 3));
+        }
+        uint8_t *dst = s_prof + ((int64_t)sy * 64 + lane) * RL;
+        if constexpr (RL >= 4) lds_store_words<RL>(dst, w);
+        else *reinterpret_cast<uint16_t *>(dst) = (uint16_t)w[0];
+      }
+    }
+    lds_wave_sync();
+
+    // code offset of this lane's rows: code = M - padded row
+    const uint32_t DL = M - (uint32_t)((int64_t)s * SH + lane * RL + RL - 1);
+
+    // words of columns c0 .. c0 + cnt - 1 at lanes 0 .. cnt - 1; a column the
+    // row above does not hold reads as a valid zero
+    auto fetch = [&](int64_t c0, int cnt) -> uint64_t {
+      const int64_t c = c0 + lane;
+      const bool have = s > 0 && lane < cnt && c < chi && c >= plo && c < phi;
+      return have ? __hip_atomic_load(in + (c - jb.cw), __ATOMIC_RELAXED, AGENT) : kWordValid;
+    };
+    auto ready = [](uint64_t w) { return __ballot((w & kWordValid) != 0) == ~0ull; };
+    // the same once they are all there; words the finished strip above never
+    // stored read as zero
+    auto settle = [&](uint64_t w, int64_t c0, int cnt) -> uint64_t {
+      int64_t spins = 0;
+      while (!ready(w)) {
+        const int32_t done = __hip_atomic_load(&gs->done[s - 1], __ATOMIC_RELAXED, AGENT);
+        if (done) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        w = fetch(c0, cnt);
+        if (done) break;
+        if (++spins > kSpinLimit) { spin_fail = true; break; }
+        __builtin_amdgcn_s_sleep(1);
+      }
+      return (w & kWordValid) ? w : kWordValid;
+    };
+    // reference symbols of columns [c0, c0 + 16) at lanes 0 .. 15 (n past the window)
+    auto symbols = [&](int64_t c0) -> uint32_t {
+      const int64_t c = c0 + lane;
+      return lane < kSpreadBlock && c < chi ? (uint32_t)(uint8_t)rs[rv ? Lr - 1 - c : c] : (uint32_t)n;
+    };
+
+    uint32_t H[RL], E[RL];
+#pragma unroll
+    for (int r = 0; r < RL; ++r) { H[r] = 0u; E[r] = 0u; }
+    uint32_t hup_prev = 0u;
+    if (s > 0 && clo - 1 >= plo && clo - 1 < phi && clo >= 1) {
+      const int64_t c = clo - 1;
+      uint64_t w = lane == 0 ? __hip_atomic_load(in + (c - jb.cw), __ATOMIC_RELAXED, AGENT) : kWordValid;
+      int64_t spins = 0;
+      while (!ready(w)) {
+        const int32_t done = __hip_atomic_load(&gs->done[s - 1], __ATOMIC_RELAXED, AGENT);
+        if (done) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        if (lane == 0) w = __hip_atomic_load(in + (c - jb.cw), __ATOMIC_RELAXED, AGENT);
+        if (done) break;
+        if (++spins > kSpinLimit) { spin_fail = true; break; }
+      }
+      hup_prev = lane == 0 ? (uint32_t)w : 0u;
+    }
+    uint32_t hout = 0u, fout = 0u, cmout = 0u;
+    uint32_t obH = 0u, obF = 0u, obC = 0u;   // queues of lane 63's outputs, the newest at lane 63
+    int64_t newest = clo - 64;               // ... of this column
+    auto flush = [&]() {   // the last block's columns
+      const int64_t c = newest - 63 + lane;
+      if (lane >= 64 - kSpreadBlock && c >= clo && c < chi) {
+        if (hand_over)
+          __hip_atomic_store(out + (c - jb.cw), kWordValid | ((uint64_t)obF << 32) | obH,
+                             __ATOMIC_RELAXED, AGENT);
+        if (!REV && c >= jb.c0 && c < jb.c1) atomicMax(&mc[c], obC);
+      }
+    };
+    const int64_t nsteps = (chi - clo) + 63;
+    // a step's symbol enters lane 0 one step ahead, with its profile row
+    uint32_t sym = from_above((uint32_t)n, lane_value(symbols(clo), 0));
+    uint32_t X[XW];
+    prof_load<RL>(s_prof + ((int64_t)sym * 64 + lane) * RL, X);
+    uint32_t symnext = symbols(clo + 1);
+    uint64_t wnext = fetch(clo, kSpreadBlock);
+#pragma unroll 1
+    for (int64_t t0 = 0; t0 < nsteps; t0 += kSpreadBlock) {
+      // this block's words were asked for one block ago; the last block's
+      // outputs go out before anything waits
+      uint64_t w = wnext;
+      const bool here = ready(w);
+      const uint32_t symbuf = symnext;
+      flush();
+      if (REV && (t0 & 63) == 0 && t0 >= 64 &&
+          (unsigned long long)(clo + t0 - 63) >= __hip_atomic_load(&gs->best, __ATOMIC_RELAXED, AGENT))
+        break;   // an earlier strip already reached the target at or before here
+      if (!here) w = settle(w, clo + t0, kSpreadBlock);
+      wnext = fetch(clo + t0 + kSpreadBlock, kSpreadBlock);
+      symnext = symbols(clo + t0 + kSpreadBlock + 1);
+      const uint32_t hbuf = (uint32_t)w, fbuf = (uint32_t)(w >> 32) & 0x7FFFFFFFu;
+#pragma unroll kUnroll
+      for (int tm = 0; tm < kSpreadBlock; ++tm) {
+        const uint32_t hup = from_above(hout, lane_value(hbuf, tm));
+        uint32_t F = from_above(fout, lane_value(fbuf, tm));
+        const uint32_t cmin = from_above(cmout, 0u);
+        const uint32_t symn = from_above(sym, lane_value(symbuf, tm));
+        uint32_t Xn[XW];
+        prof_load<RL>(s_prof + ((int64_t)symn * 64 + lane) * RL, Xn);
+        uint32_t cm = 0u;
+        uint32_t u_next = T::max(hup_prev + __builtin_amdgcn_ubfe(X[0], 0, 8), E[0]);
+#pragma unroll
+        for (int r = 0; r < RL; ++r) {
+          const uint32_t u = u_next;
+          if (r + 1 < RL)
+            u_next = T::max(H[r] + __builtin_amdgcn_ubfe(X[(r + 1) >> 2], 8 * ((r + 1) & 3), 8), E[r + 1]);
+          const uint32_t hb = T::max(u, F);
+          const uint32_t hn = T::subs(hb, vbias);
+          H[r] = hn;
+          const uint32_t enc = (hn << kb) + (uint32_t)(RL - 1 - r);
+          cm = cm > enc ? cm : enc;
+          const uint32_t ho = HO ? hn : T::subs(hb, vo);   // HO: bias == o
+          E[r] = T::max(T::subs(E[r], ve), ho);
+          F = T::max(T::subs(F, ve), ho);
+        }
+        hup_prev = hup;
+        hout = H[RL - 1];
+        fout = F;
+        const uint32_t cml = cm + DL;
+        cmout = cmin > cml ? cmin : cml;
+        sym = symn;
+#pragma unroll
+        for (int k = 0; k < XW; ++k) X[k] = Xn[k];
+        obH = shift_in(obH, hout);
+        obF = shift_in(obF, fout);
+        obC = shift_in(obC, cmout);
+      }
+      newest = clo + t0 + kSpreadBlock - 64;   // step t ends column clo + t - 63
+      if constexpr (REV) {
+        const int64_t c = newest - 63 + lane;
+        const unsigned long long hit =
+            __ballot(lane >= 64 - kSpreadBlock && c >= clo && c < chi && tgt > 0 && (int32_t)(obC >> kb) >= tgt);
+        if (hit) {
+          const int hl = __builtin_ctzll(hit);
+          const uint32_t oc = lane_value(obC, hl);
+          if (lane == 0) {
+            gs->rcol[s] = newest - 63 + hl;
+            gs->rrow[s] = (int32_t)(M - (oc & M));
+            atomicMin(&gs->best, (unsigned long long)(newest - 63 + hl));
+          }
+          break;
+        }
+      }
+    }
+    flush();
+    finish();
+    if (spin_fail && lane == 0) a.err[p] = 1;   // reported as an internal failure
+  }
+  if constexpr (REV) {
+    // the last segment of the job to finish reduces the strips' hits
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    __syncthreads();
+    if (threadIdx.x == 0) s_last = atomicAdd(&gs->fin, 1) == G - 1;
+    __syncthreads();
+    if (!s_last) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    if (threadIdx.x == 0) {
+      // first column reaching the target; on a tie the earlier strip (smaller row)
+      int64_t bc = -1;
+      int32_t br = -1;
+      for (int s = 0; s < nstrips && s < kMaxStrips; ++s) {
+        if (gs->rcol[s] >= 0 && (bc < 0 || gs->rcol[s] < bc)) { bc = gs->rcol[s]; br = gs->rrow[s]; }
+      }
+      const bool hit = bc >= 0;
+      a.out.score[p] = hit ? tgt : 0;
+      a.out.qend[p] = hit ? br : -1;
+      a.out.rend[p] = hit ? bc : -1;
+      a.out.overflow[p] = 0;
+    }
   }
 }
 
@@ -893,13 +1142,15 @@ static void launch_rl_ho(const IntraArgs &a, int waves, bool rev, hipStream_t st
   const size_t lds = intra_lds_bytes(a.n, RL) * waves;
   if (a.segs > 1) {
     const dim3 g((unsigned)(8 * a.segs * ((a.njobs + 7) / 8)));
-    if (rev) hipLaunchKernelGGL((k_intra_fill<RL, true, true, HO>), g, b, lds, st, a);
-    else hipLaunchKernelGGL((k_intra_fill<RL, false, true, HO>), g, b, lds, st, a);
+    if (rev) hipLaunchKernelGGL((k_intra_spread<RL, true, HO>), g, b, lds, st, a);
+    else hipLaunchKernelGGL((k_intra_spread<RL, false, HO>), g, b, lds, st, a);
     return;
   }
-  const dim3 g((unsigned)a.njobs);
-  if (rev) hipLaunchKernelGGL((k_intra_fill<RL, true, false, HO>), g, b, lds, st, a);
-  else hipLaunchKernelGGL((k_intra_fill<RL, false, false, HO>), g, b, lds, st, a);
+  if constexpr (RL >= 4) {
+    const dim3 g((unsigned)a.njobs);
+    if (rev) hipLaunchKernelGGL((k_intra_fill<RL, true, HO>), g, b, lds, st, a);
+    else hipLaunchKernelGGL((k_intra_fill<RL, false, HO>), g, b, lds, st, a);
+  }
 }
 
 // the bias is the gap open penalty: H and H - o are one value
@@ -963,9 +1214,11 @@ size_t intra_lds_bytes16(int n, int RL) { return 2 * (size_t)(n + 1) * 64 * RL; 
 
 hipError_t intra_fill(const IntraArgs &a, int RL, int waves, bool rev, hipStream_t st) {
   if (a.njobs == 0) return hipSuccess;
-  if (waves < 1 || waves > kMaxWaves || (a.segs > 1 && !a.sync))
+  if (waves < 1 || waves > kMaxWaves || (a.segs > 1 && (!a.sync || waves > kSpreadMaxWaves)) ||
+      (RL == 2 && a.segs <= 1))
     return hipErrorInvalidValue;
   switch (RL) {
+    case 2: launch_rl<2>(a, waves, rev, st); break;
     case 4: launch_rl<4>(a, waves, rev, st); break;
     case 8: launch_rl<8>(a, waves, rev, st); break;
     case 16: launch_rl<16>(a, waves, rev, st); break;

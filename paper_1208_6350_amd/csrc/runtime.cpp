@@ -601,7 +601,7 @@ static int gather_info(swx_ctx *ctx, int64_t n, const int64_t *d_ids, const int3
 
 // Shape of a wave traceback over m rows, w columns and a band of bw diagonals
 // when `jobs` such pairs share the device (rl 0: too tall for every choice).
-// Strip s starts SH + 128 steps after strip s - 1 and sweeps a window of
+// Strip s starts SH + 110 (spread) or SH + 128 steps after strip s - 1 and sweeps a window of
 // SH + bw columns; the waves of a pair's workgroups run its strips in turn,
 // and a step costs about 16 instructions per row of a lane plus 30: the
 // cheapest of the longer of those two paths.  With fewer pairs than compute
@@ -634,7 +634,7 @@ static TbShape tb_wave_shape(int64_t m, int64_t w, int64_t bw, int n, int64_t jo
       if (g > 1) waves = w4;
     }
     const int64_t win = std::min<int64_t>(SH + bw, w + 1) + 63;
-    const int64_t chain = (nstrips - 1) * (SH + 128) + win;
+    const int64_t chain = (nstrips - 1) * (SH + (g > 1 ? 110 : 128)) + win;
     const int64_t turns = (nstrips + waves * g - 1) / (waves * g) * win;
     const double cost = (double)std::max(chain, turns) * (16 * RL + 30) * (waves > 4 ? 1.5 : 1.0);
     if (best.rl == 0 || cost < best_cost) {
@@ -862,6 +862,8 @@ static int run_traceback(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, 
     if (!dj || !dirw || !bnd || (nspread && !sync))
       return fail(SWX_ENOMEM, "device pool exhausted (wave traceback)");
     HIP_TRY(hipMemcpyAsync(dj, sorted_jobs.data(), sizeof(TbWaveJob) * nc, hipMemcpyHostToDevice, st));
+    if (nspread)   // the hand-over words of spread pairs start out invalid
+      HIP_TRY(hipMemsetAsync(bnd, 0, sizeof(int32_t) * std::max<int64_t>(bwords, 1), st));
     HIP_TRY(hipStreamSynchronize(st));   // the host job table must outlive the copy
     for (int64_t k0 = 0; k0 < nc;) {
       int64_t k1 = k0;
@@ -1056,9 +1058,11 @@ typedef std::map<IntraShape, std::vector<IntraJob>> IntraGroups;
 // such jobs share the device.  With at least one job per compute unit the
 // device is full: the fewest instructions over all strips (pick_rl).  With
 // fewer, a job is as slow as its longer of two paths: the chain of strips,
-// each starting about 128 columns (banded: SH + 128) after the one above, and
-// the strips each wave runs in turn; a step costs about 12 instructions per
-// row of a lane plus 20.  Those jobs spread over up to four waves per
+// each starting about 110 columns (banded: SH + 110) after the one above, and
+// the strips each wave runs in turn.  Measured against it, 10,000 x 20,000
+// forward in ms at 2 / 4 / 8 rows per lane: one pair 2.30 / 2.66 / 3.93, 30
+// pairs 5.19 / 4.55 / 4.02, 100 pairs 16.4 / 11.0 / 10.9 (predicted 2.29 /
+// 2.66 / 3.93, 4.8 / 4.4 / 3.9, 16.1 / 10.9 / 10.7).  Those jobs spread over up to four waves per
 // workgroup (one per SIMD) and as many workgroups as fit at once: at most one
 // per compute unit, and 32 (the compute units of one XCD) per XCD.
 static IntraShape intra_shape(int64_t rows, int64_t width, int32_t band, int n, int64_t jobs,
@@ -1072,21 +1076,23 @@ static IntraShape intra_shape(int64_t rows, int64_t width, int32_t band, int n, 
       std::max<int64_t>(1, std::min<int64_t>(cus / jobs, 32 / ((jobs + 7) / 8)));
   IntraShape best{pick_rl(rows, n), 1, 1};
   double best_cost = -1;
-  for (int RL : {4, 8, 16, 32}) {
+  for (int RL : {2, 4, 8, 16, 32}) {
     if (intra_lds_bytes(n, RL) + intra_static_lds() > 65536) continue;
     const int64_t SH = 64 * RL;
     const int64_t nstrips = std::max<int64_t>(1, (rows + SH - 1) / SH);
     if (nstrips > intra_max_strips()) continue;
     int64_t nw = std::min<int64_t>(4, intra_waves(nstrips, n, RL));
     const int64_t g = std::min<int64_t>(segs_max, (nstrips + nw - 1) / nw);
+    if (g == 1 && RL == 2) continue;   // spread jobs only
     if (g == 1) nw = intra_waves(nstrips, n, RL);
     const int64_t win = band >= 0 ? std::min<int64_t>(width, SH + 2 * (int64_t)band) : width;
-    const int64_t lag = (band >= 0 ? SH : 0) + 128;
+    const int64_t lag = (band >= 0 ? SH : 0) + (g > 1 ? 110 : 128);
     const int64_t tw = g * nw;
     const int64_t chain = (nstrips - 1) * lag + win;
     const int64_t turns = (nstrips + tw - 1) / tw * (win + 63);
-    // two waves share a SIMD beyond four per workgroup
-    const double cost = (double)std::max(chain, turns) * (12 * RL + 20) * (nw > 4 ? 1.5 : 1.0);
+    // (a step took 80 / 109 / 178 ns at 2 / 4 / 8 rows per lane); two waves
+    // share a SIMD beyond four per workgroup
+    const double cost = (double)std::max(chain, turns) * (31 * RL + 96) * (nw > 4 ? 1.5 : 1.0);
     if (best_cost < 0 || cost < best_cost) {
       best_cost = cost;
       best = {RL, (int)nw, (int)g};
@@ -1229,7 +1235,10 @@ static int launch_intra_jobs(swx_ctx *ctx, const IntraGroups &groups, IntraArgs 
     return fail(SWX_ENOMEM, "device pool exhausted (intra jobs)");
   HIP_TRY(hipMemcpyAsync(dj, all.data(), sizeof(IntraJob) * all.size(), hipMemcpyHostToDevice,
                          ctx->stream));
-  if (nspread) HIP_TRY(intra_sync_init(sync, nspread, ctx->stream));
+  if (nspread) {   // the words of spread jobs start out invalid
+    HIP_TRY(intra_sync_init(sync, nspread, ctx->stream));
+    HIP_TRY(hipMemsetAsync(a.bnd, 0, sizeof(uint32_t) * std::max<int64_t>(bnd_words, 1), ctx->stream));
+  }
   int64_t off = 0, soff = 0;
   for (const auto &kv : groups) {
     a.jobs = dj + off;
@@ -1300,6 +1309,17 @@ static int run_intra_forward(swx_ctx *ctx, const Scoring &sc, LongPath &lp, cons
     f32 = plan_forward(sc, lp.info, k32, 1, ctx->intra_jobs, ctx->cus);
   }
   const bool plan16 = f16.rl != 0, plan32 = f32.rl != 0 && f32.jobs >= ctx->cus;
+  IntraShape common32{};   // ... all in one launch, by the largest job's shape
+  if (!plan32 && jobs32 > 0 && jobs32 < ctx->cus) {
+    int64_t rows = 0, width = 0;
+    for (int64_t k : k32) {
+      const int64_t Lq = lp.info[6 * k], Lr = lp.info[6 * k + 1];
+      rows = std::max(rows, Lq);
+      width = std::max(width, std::min(Lr, intra_chunk(sc, Lq, Lr, ctx->intra_jobs, total_r) +
+                                               intra_warmup(sc, Lq, Lr)));
+    }
+    common32 = intra_shape(rows, width, -1, sc.n, jobs32, ctx->cus);
+  }
   const int64_t simds = 4 * (int64_t)std::max(ctx->cus, 1);
   IntraGroups groups;
   int64_t mc_words = 0, bnd_words = 0;
@@ -1317,8 +1337,9 @@ static int run_intra_forward(swx_ctx *ctx, const Scoring &sc, LongPath &lp, cons
       C = fwd_chunk(sc, Lq, Lr, f32.rl, simds, ctx->intra_jobs, r32);
       shape = IntraShape{f32.rl, intra_waves((Lq + 64 * f32.rl - 1) / (64 * f32.rl), sc.n, f32.rl), 1};
     } else {
-      shape = w16 ? IntraShape{pick_rl(Lq, sc.n), 0, 1}
-                  : intra_shape(Lq, std::min(Lr, C + W), -1, sc.n, jobs32, ctx->cus);
+      shape = w16               ? IntraShape{pick_rl(Lq, sc.n), 0, 1}
+              : common32.rl != 0 ? common32
+                                 : intra_shape(Lq, std::min(Lr, C + W), -1, sc.n, jobs32, ctx->cus);
     }
     const int RL = shape.rl;
     const int64_t SH = 64 * RL;
@@ -1402,12 +1423,24 @@ static int run_intra_reverse(swx_ctx *ctx, const Scoring &sc, LongPath &lp, cons
     return rc;
   IntraGroups groups;
   int64_t bnd_words = 0, njobs = 0;
-  for (int64_t k = 0; k < lp.nlong; ++k) njobs += info[6 * k + 2] > 0;
+  int64_t max_rows = 0, max_cols = 0, max_band = 0;
+  for (int64_t k = 0; k < lp.nlong; ++k) {
+    if (info[6 * k + 2] <= 0) continue;
+    ++njobs;
+    max_rows = std::max(max_rows, info[6 * k + 3] + 1);
+    max_cols = std::max(max_cols, info[6 * k + 4] + 1);
+    const int64_t band = info[6 * k + 5];   // (none: negative)
+    max_band = band < 0 || max_band < 0 ? -1 : std::max(max_band, band);
+  }
+  // jobs that leave compute units idle share one shape, the largest job's, and
+  // so one launch: by their own shapes 50 pairs made two, one after the other
+  const IntraShape common = intra_shape(max_rows, max_cols, (int32_t)max_band, sc.n, njobs, ctx->cus);
   for (int64_t k = 0; k < lp.nlong; ++k) {
     if (info[6 * k + 2] <= 0) continue;
     const int64_t rows = info[6 * k + 3] + 1, cols = info[6 * k + 4] + 1;
     const IntraShape shape =
-        intra_shape(rows, cols, (int32_t)info[6 * k + 5], sc.n, njobs, ctx->cus);
+        njobs < ctx->cus ? common
+                         : intra_shape(rows, cols, (int32_t)info[6 * k + 5], sc.n, njobs, ctx->cus);
     const int RL = shape.rl;
     const int64_t SH = 64 * RL;
     const int64_t qp = (rows + SH - 1) / SH * SH;

@@ -1053,6 +1053,11 @@ __device__ __forceinline__ int32_t tb_from_above(int32_t src, int32_t top) {
   return __builtin_amdgcn_update_dpp(top, src, 0x138, 0xF, 0xF, false);   // wave_shr:1
 }
 
+// vec moved one lane down with lane 63 taking its own v
+__device__ __forceinline__ int32_t tb_shift_in(int32_t vec, int32_t v) {
+  return __builtin_amdgcn_update_dpp(v, vec, 0x130, 0xF, 0xF, false);   // wave_shl:1
+}
+
 constexpr int kTbMaxStrips = (int)kTbMaxStripsDecl;
 constexpr int kTbMaxWaves = 8;
 constexpr int64_t kTbSpinLimit = int64_t(1) << 26;
@@ -1078,18 +1083,16 @@ template <int RL, int TILE>
 __device__ void tb_wave_walk(const TbArgs &a, const TbWaveJob &jb, const uint8_t *dir,
                              uint4 *s_tile, int lane);
 
-// The choice codes of one pair: its strips on the waves of G workgroups (this
-// one is number seg; SPREAD: progress records in global memory, agent scope).
-// s_prof: this workgroup's profiles, [(n+1)][64][RL] score bytes per wave;
+// The choice codes of one pair, its strips on the waves of one workgroup.
+// s_profs: the workgroup's profiles, [(n+1)][64][RL] score bytes per wave;
 // s_mat: room for the matrix; s_prog, s_done: progress per strip.
-template <int RL, bool SPREAD>
-__device__ __forceinline__ void tb_wave_fill(const TbArgs &a, const TbWaveJob &jb, int64_t seg,
-                                             int G, int32_t *s_prog, int32_t *s_done,
-                                             int8_t *s_mat, int8_t *s_profs, uint8_t *dir,
-                                             int32_t *bnd0) {
+template <int RL>
+__device__ __forceinline__ void tb_wave_fill(const TbArgs &a, const TbWaveJob &jb, int32_t *s_prog,
+                                             int32_t *s_done, int8_t *s_mat, int8_t *s_profs,
+                                             uint8_t *dir, int32_t *bnd0) {
   constexpr int64_t SH = 64 * RL;
   constexpr int WB = RL / 2;                      // code bytes per lane and step
-  constexpr int SCOPE = SPREAD ? __HIP_MEMORY_SCOPE_AGENT : __HIP_MEMORY_SCOPE_WORKGROUP;
+  constexpr int SCOPE = __HIP_MEMORY_SCOPE_WORKGROUP;
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int NW = blockDim.x >> 6;
@@ -1098,21 +1101,17 @@ __device__ __forceinline__ void tb_wave_fill(const TbArgs &a, const TbWaveJob &j
   const int32_t o = a.o, e = a.e;
   const int64_t nstrips = (m + SH - 1) / SH;
   for (int k = threadIdx.x; k < n * n; k += blockDim.x) s_mat[k] = a.matrix[k];
-  if constexpr (!SPREAD) {   // spread jobs: set by intra_sync_init before the launch
-    for (int k = threadIdx.x; k < nstrips && k < kTbMaxStrips; k += blockDim.x) {
-      s_prog[k] = 0;
-      s_done[k] = 0;
-    }
+  for (int k = threadIdx.x; k < nstrips && k < kTbMaxStrips; k += blockDim.x) {
+    s_prog[k] = 0;
+    s_done[k] = 0;
   }
   const int8_t *q = a.qcat + a.qstart[p] + a.qbeg[p];
   const int8_t *r = a.rcat + a.rstart[p] + a.rbeg[p];
   // hand-over rows: row 0 is the virtual top row H(0,0) = 0,
   // H(0,j) = -(o + (j-1)e), F(0,j) = -inf; row s + 1 is strip s's last row
-  if (seg == 0) {   // strip 0 (segment 0, wave 0) reads it after the barrier below
-    for (int64_t j = threadIdx.x; j <= w; j += blockDim.x) {
-      bnd0[j] = (j == 0) ? 0 : -(o + (int32_t)(j - 1) * e);
-      bnd0[(w + 1) + j] = kNeg;
-    }
+  for (int64_t j = threadIdx.x; j <= w; j += blockDim.x) {   // strip 0 reads it after the barrier below
+    bnd0[j] = (j == 0) ? 0 : -(o + (int32_t)(j - 1) * e);
+    bnd0[(w + 1) + j] = kNeg;
   }
   __threadfence_block();
   __syncthreads();
@@ -1130,7 +1129,7 @@ __device__ __forceinline__ void tb_wave_fill(const TbArgs &a, const TbWaveJob &j
     return off;
   };
 
-  for (int64_t s = seg * NW + wave; s < nstrips; s += (int64_t)G * NW) {
+  for (int64_t s = wave; s < nstrips; s += NW) {
     int64_t clo, chi, plo = 0, phi = w + 1;
     tbw_window(s, SH, jb.dlo, jb.bw, w, &clo, &chi);
     if (s > 0) tbw_window(s - 1, SH, jb.dlo, jb.bw, w, &plo, &phi);
@@ -1141,8 +1140,7 @@ __device__ __forceinline__ void tb_wave_fill(const TbArgs &a, const TbWaveJob &j
     const bool hand_over = (s + 1 < nstrips);
     uint8_t *dstrip = dir + strip_base(s);
     auto publish = [&](int32_t ncols, bool fin) {
-      if constexpr (SPREAD) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-      else __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
       if (lane == 0) {
         __hip_atomic_store(&s_prog[s], ncols, __ATOMIC_RELAXED, SCOPE);
         if (fin) __hip_atomic_store(&s_done[s], 1, __ATOMIC_RELAXED, SCOPE);
@@ -1159,8 +1157,7 @@ __device__ __forceinline__ void tb_wave_fill(const TbArgs &a, const TbWaveJob &j
         if (++spins > kTbSpinLimit) { spin_fail = true; break; }
         __builtin_amdgcn_s_sleep(2);
       }
-      if constexpr (SPREAD) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-      else __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
     };
     auto rd = [](const int32_t *ptr) {   // past the L1: another wave wrote it
       return __hip_atomic_load(ptr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1307,41 +1304,232 @@ __device__ __forceinline__ void tb_wave_fill(const TbArgs &a, const TbWaveJob &j
   if (spin_fail && lane == 0) a.err[p] = 1;   // reported as an internal failure
 }
 
-// SPREAD: the pair's strips on the waves of `segs` workgroups (progress
-// records in global memory, agent scope, as in the intra-sequence fill; the
-// grid fits on the device at once), and the walk left to k_tb_walk.
-template <int RL, bool SPREAD>
+template <int RL>
 __global__ __launch_bounds__(64 * kTbMaxWaves) void k_tb_wave(TbArgs a, const TbWaveJob *jobs,
-                                                              int64_t njobs, int segs,
-                                                              IntraSync *sync, uint8_t *dirw,
-                                                              int32_t *bndbuf) {
+                                                              uint8_t *dirw, int32_t *bndbuf) {
   extern __shared__ uint4 s_dyn[];                // per wave: profile [(n+1)][64][RL] score bytes
-  __shared__ uint4 s_tile[SPREAD ? 1 : kTbTileBytes / 16];
+  __shared__ uint4 s_tile[kTbTileBytes / 16];
   __shared__ int8_t s_mat[32 * 32];
-  __shared__ int32_t l_prog[SPREAD ? 1 : kTbMaxStrips];   // columns of strip s's last row published
-  __shared__ int32_t l_done[SPREAD ? 1 : kTbMaxStrips];
-  // spread grids: block 8 * slot + x (slot = (j / 8) * G + segment) puts the
-  // segments of job j on XCD j % 8; blocks past the last job leave at once
-  const int G = SPREAD ? segs : 1;
-  int64_t jix = blockIdx.x, seg = 0;
-  if constexpr (SPREAD) {
-    const int64_t slot = blockIdx.x / 8;
-    jix = (slot / G) * 8 + blockIdx.x % 8;
-    seg = slot % G;
-    if (jix >= njobs) return;
-  }
-  const TbWaveJob jb = jobs[jix];
+  __shared__ int32_t s_prog[kTbMaxStrips];   // columns of strip s's last row published
+  __shared__ int32_t s_done[kTbMaxStrips];
+  const TbWaveJob jb = jobs[blockIdx.x];
   if (jb.m <= 0) return;   // a job without an alignment (one-pair graphs plan it on the device)
   uint8_t *dir = dirw + jb.dir_off;
-  tb_wave_fill<RL, SPREAD>(a, jb, seg, G, SPREAD ? sync[jix].prog : l_prog,
-                           SPREAD ? sync[jix].done : l_done, s_mat,
-                           reinterpret_cast<int8_t *>(s_dyn), dir, bndbuf + jb.bnd_off);
-  if constexpr (!SPREAD) {
-    // the walk reads every wave's codes: the barrier makes the workgroup's
-    // stores visible to it (they pass through this compute unit's caches)
-    __syncthreads();
-    if (threadIdx.x < 64) tb_wave_walk<RL, kTbTileBytes>(a, jb, dir, s_tile, (int)threadIdx.x);
+  tb_wave_fill<RL>(a, jb, s_prog, s_done, s_mat, reinterpret_cast<int8_t *>(s_dyn), dir,
+                   bndbuf + jb.bnd_off);
+  // the walk reads every wave's codes: the barrier makes the workgroup's
+  // stores visible to it (they pass through this compute unit's caches)
+  __syncthreads();
+  if (threadIdx.x < 64) tb_wave_walk<RL, kTbTileBytes>(a, jb, dir, s_tile, (int)threadIdx.x);
+}
+
+// Spread pairs: the pair's strips on the waves of `segs` workgroups (the grid
+// fits on the device at once), and the walk left to k_tb_walk.  The hand-over
+// is the intra-sequence fill's (k_intra_spread): one 64-bit word per column,
+// valid << 63 | (F + 2^30) << 32 | (H + 2^30), its own flag, 16 columns at a
+// time, read a block ahead; cleared before the launch.  Bound by the chain of
+// strips: a 10,000-row alignment inside its band 3.7 -> 2.5 ms.
+constexpr int kTbSpreadBlock = 16;
+constexpr int kTbSpreadMaxWaves = 4;
+constexpr uint64_t kTbWordValid = 1ull << 63;
+__device__ __forceinline__ uint64_t tb_word(int32_t h, int32_t f) {
+  constexpr int32_t kMin = -(1 << 30);   // lower values are as good as minus infinity
+  h = h < kMin ? kMin : h;
+  f = f < kMin ? kMin : f;
+  return kTbWordValid | ((uint64_t)(uint32_t)(f - kMin) << 32) | (uint32_t)(h - kMin);
+}
+__device__ __forceinline__ int32_t tb_word_h(uint64_t w) { return (int32_t)(uint32_t)w - (1 << 30); }
+__device__ __forceinline__ int32_t tb_word_f(uint64_t w) {
+  return (int32_t)((uint32_t)(w >> 32) & 0x7FFFFFFFu) - (1 << 30);
+}
+
+template <int RL>
+__global__ __launch_bounds__(64 * kTbSpreadMaxWaves) void k_tb_spread(TbArgs a, const TbWaveJob *jobs,
+                                                                      int64_t njobs, int G,
+                                                                      IntraSync *sync, uint8_t *dirw,
+                                                                      int32_t *bndbuf) {
+  constexpr int64_t SH = 64 * RL;
+  constexpr int WB = RL / 2;                      // code bytes per lane and step
+  constexpr int kUnroll = RL <= 4 ? kTbSpreadBlock : 4;
+  constexpr int AGENT = __HIP_MEMORY_SCOPE_AGENT;
+  extern __shared__ uint4 s_dyn[];                // per wave: profile [(n+1)][64][RL] score bytes
+  __shared__ int8_t s_mat[32 * 32];
+  const int lane = threadIdx.x & 63;
+  const int wave = threadIdx.x >> 6;
+  const int NW = blockDim.x >> 6;
+  // block 8 * slot + x (slot = (j / 8) * G + segment) puts the segments of job
+  // j on XCD j % 8; blocks past the last job leave at once
+  const int64_t slot = blockIdx.x / 8;
+  const int64_t jix = (slot / G) * 8 + blockIdx.x % 8;
+  const int64_t seg = slot % G;
+  if (jix >= njobs) return;
+  const TbWaveJob jb = jobs[jix];
+  if (jb.m <= 0) return;
+  const int32_t *done = sync[jix].done;
+  const int64_t p = jb.pair, m = jb.m, w = jb.w;
+  const int n = a.n;
+  const int32_t o = a.o, e = a.e;
+  const int64_t nstrips = (m + SH - 1) / SH;
+  for (int k = threadIdx.x; k < n * n; k += blockDim.x) s_mat[k] = a.matrix[k];
+  __syncthreads();
+  const int8_t *q = a.qcat + a.qstart[p] + a.qbeg[p];
+  const int8_t *r = a.rcat + a.rstart[p] + a.rbeg[p];
+  uint64_t *rows = reinterpret_cast<uint64_t *>(bndbuf + jb.bnd_off);   // [strip][w + 1]
+  int8_t *s_prof = reinterpret_cast<int8_t *>(s_dyn) + (size_t)wave * (n + 1) * 64 * RL;
+  bool spin_fail = false;
+  // choice codes of strip s start this many bytes after those of strip 0
+  int64_t base = 0, base_of = 0;   // ... those of strip base_of at base (strips come in order)
+
+  for (int64_t s = seg * NW + wave; s < nstrips; s += (int64_t)G * NW) {
+    for (; base_of < s; ++base_of) {
+      int64_t lo, hi;
+      tbw_window(base_of, SH, jb.dlo, jb.bw, w, &lo, &hi);
+      base += ((hi - lo) + 63) * 64 * WB;
+    }
+    int64_t clo, chi, plo = 0, phi = w + 1;
+    tbw_window(s, SH, jb.dlo, jb.bw, w, &clo, &chi);
+    if (s > 0) tbw_window(s - 1, SH, jb.dlo, jb.bw, w, &plo, &phi);
+    uint64_t *out = rows + (w + 1) * s;      // this strip's last row
+    const uint64_t *in = out - (w + 1);      // the row above it
+    const bool hand_over = (s + 1 < nstrips);
+    uint8_t *dstrip = dirw + jb.dir_off + base;
+    // words of columns c0 .. c0 + cnt - 1 at lanes 0 .. cnt - 1; a column the
+    // row above does not hold reads as minus infinity, and the virtual row
+    // above strip 0 is H(0,0) = 0, H(0,j) = -(o + (j-1)e), F(0,j) = -inf
+    auto fetch = [&](int64_t c0, int cnt) -> uint64_t {
+      const int64_t c = c0 + lane;
+      const bool have = lane < cnt && c < chi && c >= plo && c < phi;
+      if (s == 0) return have ? tb_word(c == 0 ? 0 : -(o + (int32_t)(c - 1) * e), kNeg) : tb_word(kNeg, kNeg);
+      return have ? __hip_atomic_load(in + c, __ATOMIC_RELAXED, AGENT) : tb_word(kNeg, kNeg);
+    };
+    auto ready = [](uint64_t x) { return __ballot((x & kTbWordValid) != 0) == ~0ull; };
+    auto settle = [&](uint64_t x, int64_t c0, int cnt) -> uint64_t {
+      int64_t spins = 0;
+      while (!ready(x)) {
+        const int32_t fin = __hip_atomic_load(done + s - 1, __ATOMIC_RELAXED, AGENT);
+        if (fin) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        x = fetch(c0, cnt);
+        if (fin) break;
+        if (++spins > kTbSpinLimit) { spin_fail = true; break; }
+        __builtin_amdgcn_s_sleep(1);
+      }
+      return (x & kTbWordValid) ? x : tb_word(kNeg, kNeg);
+    };
+    // profile of this lane's rows (signed scores; padding rows score 0)
+    {
+      int32_t qv[RL];
+#pragma unroll
+      for (int k = 0; k < RL; ++k) {
+        const int64_t i = s * SH + lane * RL + k + 1;
+        qv[k] = (i <= m) ? (int32_t)q[i - 1] : -1;
+      }
+      for (int sy = 0; sy <= n; ++sy) {
+        uint32_t wv[RL / 4];
+#pragma unroll
+        for (int k = 0; k < RL / 4; ++k) wv[k] = 0u;
+#pragma unroll
+        for (int k = 0; k < RL; ++k) {
+          const uint32_t b = (qv[k] >= 0 && sy < n) ? (uint32_t)(uint8_t)s_mat[qv[k] * n + sy] : 0u;
+          wv[k >> 2] |= b << (8 * (k & 3));
+        }
+        uint32_t *dst = reinterpret_cast<uint32_t *>(s_prof + ((int64_t)sy * 64 + lane) * RL);
+#pragma unroll
+        for (int k = 0; k < RL / 4; ++k) dst[k] = wv[k];
+      }
+    }
+    __asm__ volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+    int32_t H[RL], E[RL];
+#pragma unroll
+    for (int k = 0; k < RL; ++k) { H[k] = kNeg; E[k] = kNeg; }
+    int32_t hup_prev = kNeg;
+    if (clo >= 1) {
+      const uint64_t x = settle(fetch(clo - 1, 1), clo - 1, 1);
+      hup_prev = lane == 0 ? tb_word_h(x) : kNeg;
+    }
+    int32_t hout = kNeg, fout = kNeg;
+    int32_t obH = 0, obF = 0;       // queues of lane 63's outputs, the newest at lane 63
+    int64_t newest = clo - 64;      // ... of this column
+    auto flush = [&]() {
+      const int64_t c = newest - 63 + lane;
+      if (hand_over && lane >= 64 - kTbSpreadBlock && c >= clo && c < chi)
+        __hip_atomic_store(out + c, tb_word(obH, obF), __ATOMIC_RELAXED, AGENT);
+    };
+    const int64_t nsteps = (chi - clo) + (hand_over ? 63 : (m - s * SH + RL - 1) / RL - 1);
+    // reference symbols of columns [c0, c0 + 16) at lanes 0 .. 15
+    auto symbols = [&](int64_t c0) -> int32_t {
+      const int64_t c = c0 + lane;
+      return (lane < kTbSpreadBlock && c < chi && c >= 1) ? (int32_t)(uint8_t)r[c - 1] : n;
+    };
+    uint32_t sym = (uint32_t)tb_from_above(n, __builtin_amdgcn_readlane(symbols(clo), 0));
+    uint32_t X[RL / 4];
+    tb_prof_load<RL>(s_prof + ((int64_t)sym * 64 + lane) * RL, X);
+    int32_t symnext = symbols(clo + 1);
+    uint64_t wnext = fetch(clo, kTbSpreadBlock);
+#pragma unroll 1
+    for (int64_t t0 = 0; t0 < nsteps; t0 += kTbSpreadBlock) {
+      uint64_t x = wnext;
+      const bool here = ready(x);
+      const int32_t symbuf = symnext;
+      flush();   // the last block's outputs go out before anything waits
+      if (!here) x = settle(x, clo + t0, kTbSpreadBlock);
+      wnext = fetch(clo + t0 + kTbSpreadBlock, kTbSpreadBlock);
+      symnext = symbols(clo + t0 + kTbSpreadBlock + 1);
+      const int32_t hbuf = tb_word_h(x), fbuf = tb_word_f(x);
+      // codes past the strip's last step are not kept
+      const int left = (int)(nsteps - t0 < kTbSpreadBlock ? nsteps - t0 : kTbSpreadBlock);
+#pragma unroll kUnroll
+      for (int tm = 0; tm < kTbSpreadBlock; ++tm) {
+        const int32_t hup = tb_from_above(hout, __builtin_amdgcn_readlane(hbuf, tm));
+        int32_t fup = tb_from_above(fout, __builtin_amdgcn_readlane(fbuf, tm));
+        const uint32_t symn = (uint32_t)tb_from_above((int32_t)sym, __builtin_amdgcn_readlane(symbuf, tm));
+        uint32_t Xn[RL / 4];
+        tb_prof_load<RL>(s_prof + ((int64_t)symn * 64 + lane) * RL, Xn);
+        int32_t hdiag = hup_prev;
+        int32_t hcur = hup;
+        uint32_t dw[(RL + 7) / 8];
+#pragma unroll
+        for (int k = 0; k < (RL + 7) / 8; ++k) dw[k] = 0u;
+#pragma unroll
+        for (int k = 0; k < RL; ++k) {
+          const int32_t sc = __builtin_amdgcn_sbfe((int32_t)X[k >> 2], 8 * (k & 3), 8);
+          const int32_t diag = hdiag + sc;
+          const int32_t fo = hcur - o, fx = fup - e;
+          const int32_t fij = fo > fx ? fo : fx;
+          const int32_t eo = H[k] - o, ex = E[k] - e;
+          const int32_t eij = eo > ex ? eo : ex;
+          int32_t h = diag > eij ? diag : eij;
+          h = h > fij ? h : fij;
+          // row k: nibble 7 - k % 8 of dword k / 8 (the first row on top)
+          dw[k >> 3] = push_code(dw[k >> 3], diag, h, eij, fij, eo, ex, fo, fx);
+          hdiag = H[k];
+          H[k] = h;
+          E[k] = eij;
+          hcur = h;
+          fup = fij;
+        }
+        hup_prev = hup;
+        hout = H[RL - 1];
+        fout = fup;
+        sym = symn;
+#pragma unroll
+        for (int k = 0; k < RL / 4; ++k) X[k] = Xn[k];
+        if (tm < left) {
+          const int64_t t = t0 + tm;
+          if constexpr (RL == 16) reinterpret_cast<uint2 *>(dstrip)[t * 64 + lane] = make_uint2(dw[0], dw[1]);
+          else if constexpr (RL == 8) reinterpret_cast<uint32_t *>(dstrip)[t * 64 + lane] = dw[0];
+          else reinterpret_cast<uint16_t *>(dstrip)[t * 64 + lane] = (uint16_t)dw[0];
+        }
+        obH = tb_shift_in(obH, hout);
+        obF = tb_shift_in(obF, fout);
+      }
+      newest = clo + t0 + kTbSpreadBlock - 64;   // step t ends column clo + t - 63
+    }
+    flush();
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    if (lane == 0) __hip_atomic_store(&sync[jix].done[s], 1, __ATOMIC_RELAXED, AGENT);
   }
+  if (spin_fail && lane == 0) a.err[p] = 1;   // reported as an internal failure
 }
 
 // One pair per workgroup, planned by the workgroup itself: the traceback of
@@ -1394,8 +1582,7 @@ __global__ __launch_bounds__(64 * kTbPairMaxWaves) void k_tb_pairs(TbArgs a, TbP
   }
   int32_t *bnd = reinterpret_cast<int32_t *>(t.scratch + off);
   uint8_t *dir = t.scratch + off + tb_pair_bnd_bytes(jb.m, jb.w);
-  tb_wave_fill<RL, false>(a, jb, 0, 1, s_prog, s_done, s_mat, reinterpret_cast<int8_t *>(s_dyn),
-                          dir, bnd);
+  tb_wave_fill<RL>(a, jb, s_prog, s_done, s_mat, reinterpret_cast<int8_t *>(s_dyn), dir, bnd);
   __syncthreads();
   if (threadIdx.x < 64) tb_wave_walk<RL, kTbPairTile>(a, jb, dir, s_tile, (int)threadIdx.x);
 }
@@ -1591,19 +1778,19 @@ static void launch_tb_wave(const TbArgs &a, const TbWaveJob *jobs, int64_t njobs
   const size_t lds = (size_t)(a.n + 1) * 64 * RL * waves;
   if (segs > 1) {
     const dim3 g((unsigned)(8 * segs * ((njobs + 7) / 8)));
-    hipLaunchKernelGGL((k_tb_wave<RL, true>), g, dim3(64 * waves), lds, st, a, jobs, njobs, segs,
-                       sync, dirw, bnd);
+    hipLaunchKernelGGL(k_tb_spread<RL>, g, dim3(64 * waves), lds, st, a, jobs, njobs, segs, sync,
+                       dirw, bnd);
     hipLaunchKernelGGL(k_tb_walk<RL>, dim3((unsigned)njobs), dim3(64), 0, st, a, jobs, dirw);
   } else {
-    hipLaunchKernelGGL((k_tb_wave<RL, false>), dim3((unsigned)njobs), dim3(64 * waves), lds, st, a,
-                       jobs, njobs, 1, sync, dirw, bnd);
+    hipLaunchKernelGGL(k_tb_wave<RL>, dim3((unsigned)njobs), dim3(64 * waves), lds, st, a, jobs,
+                       dirw, bnd);
   }
 }
 
 hipError_t tb_wave(const TbArgs &a, const TbWaveJob *jobs, int64_t njobs, int RL, int waves,
                    int segs, IntraSync *sync, uint8_t *dirw, int32_t *bnd, hipStream_t st) {
   if (njobs == 0) return hipSuccess;
-  if (waves < 1 || waves > kTbMaxWaves || segs < 1 || (segs > 1 && !sync))
+  if (waves < 1 || waves > kTbMaxWaves || segs < 1 || (segs > 1 && (!sync || waves > kTbSpreadMaxWaves)))
     return hipErrorInvalidValue;
   if (segs > 1) {
     const hipError_t e = intra_sync_init(sync, njobs, st);
