@@ -141,12 +141,11 @@ int swx_profile_destroy(swx_profile *p);
  * returns when out is filled (it waits for that stream, never for the whole
  * device).  out->cigar is malloc'd by the library (NULL when the CIGAR was
  * not requested or is empty; release with swx_result_free).  A pair of
- * qlen <= 4096 and rlen <= 65536 replays a graph of capacity one pair (the
- * chain of swx_graph_*, one pair spread over a wave) captured on first use
- * for its scoring scheme, flags, mask width and power-of-two size class and
- * kept on the context (at most 8, least recently used replaced); larger pairs,
- * and calls with SWX_SUBOPT, take the batch path.  Either way the result
- * equals swx_align_batch's.
+ * qlen <= 2048 and rlen <= 65536 runs in three kernels of its own (inputs
+ * staged and checked; the forward pass, a workgroup per column chunk;
+ * everything after it on one workgroup); larger pairs, and calls with
+ * SWX_SUBOPT, take the batch path.  Either way the result equals
+ * swx_align_batch's.
  * Errors: SWX_EINVAL (null p or out, rlen < 0, unknown flag bits, a symbol
  * >= n: out untouched beyond being zeroed), SWX_EDEVICE, SWX_ENOMEM. */
 #define SWX_REF_DEVICE (1u << 8)

@@ -630,25 +630,6 @@ hipError_t launch_band_tb(const BandArgs &a, hipStream_t st) {
   return hipGetLastError();
 }
 
-// the CIGAR of pair 0 of a one-pair call: its final offsets (0 and its
-// length) and its words, in one launch
-__global__ void k_cigar_one(const uint32_t *src, const int64_t *src_off, const int32_t *len,
-                            int64_t *dst_off, uint32_t *dst) {
-  const int32_t n = len[0];
-  if (threadIdx.x == 0) {
-    dst_off[0] = 0;
-    dst_off[1] = n;
-  }
-  const int64_t so = src_off[0];
-  for (int32_t k = threadIdx.x; k < n; k += blockDim.x) dst[k] = src[so + k];
-}
-
-hipError_t cigar_one(const uint32_t *src, const int64_t *src_off, const int32_t *len,
-                     int64_t *dst_off, uint32_t *dst, hipStream_t st) {
-  hipLaunchKernelGGL(k_cigar_one, dim3(1), dim3(256), 0, st, src, src_off, len, dst_off, dst);
-  return hipGetLastError();
-}
-
 // Clears of many buffers in one launch (graph capture records no memset):
 // entry k sets f.n[k] elements of f.size[k] bytes at f.p[k] to f.v[k].
 __global__ void k_fill_set(FillSet f) {

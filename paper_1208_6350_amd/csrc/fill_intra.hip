@@ -24,6 +24,9 @@
 // the bias is the gap open penalty, also the H - o that opens a gap).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
+#include "intra_strips.h"
 #include "lanes.h"
 #include "swx_internal.h"
 #include "swx_kernels.h"
@@ -31,60 +34,6 @@
 namespace swx {
 
 typedef u16x2 V16;
-
-constexpr int kDppWaveShr1 = 0x138;   // DPP control: lane k reads lane k - 1
-
-// value of src from the lane above; lane 0 takes `top`
-__device__ __forceinline__ uint32_t from_above(uint32_t src, uint32_t top) {
-  return (uint32_t)__builtin_amdgcn_update_dpp((int)top, (int)src, kDppWaveShr1, 0xF, 0xF, false);
-}
-
-__device__ __forceinline__ uint32_t lane_value(uint32_t v, int lane) {
-  return (uint32_t)__builtin_amdgcn_readlane((int)v, lane);
-}
-
-// vec with lane `at` of the wave replaced by the (uniform) v
-__device__ __forceinline__ uint32_t set_lane(uint32_t vec, int at, uint32_t v) {
-  return ((int)(threadIdx.x & 63) == at) ? v : vec;
-}
-
-constexpr int kDppWaveShl1 = 0x130;   // DPP control: lane k reads lane k + 1
-
-// vec moved one lane down (lane k takes lane k + 1) with lane 63 taking its
-// own v: a queue of lane 63's values, the newest at lane 63
-__device__ __forceinline__ uint32_t shift_in(uint32_t vec, uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)vec, kDppWaveShl1, 0xF, 0xF, false);
-}
-
-// RL bytes (RL a multiple of 4) of the LDS profile as RL/4 words
-template <int RL>
-__device__ __forceinline__ void lds_load_words(const uint8_t *src, uint32_t (&w)[RL / 4]) {
-  if constexpr (RL % 16 == 0) {
-#pragma unroll
-    for (int k = 0; k < RL / 16; ++k) {
-      const uint4 v = reinterpret_cast<const uint4 *>(src)[k];
-      w[4 * k] = v.x; w[4 * k + 1] = v.y; w[4 * k + 2] = v.z; w[4 * k + 3] = v.w;
-    }
-  } else if constexpr (RL == 8) {
-    const uint2 v = *reinterpret_cast<const uint2 *>(src);
-    w[0] = v.x; w[1] = v.y;
-  } else {
-    w[0] = *reinterpret_cast<const uint32_t *>(src);
-  }
-}
-
-template <int RL>
-__device__ __forceinline__ void lds_store_words(uint8_t *dst, const uint32_t (&w)[RL / 4]) {
-  if constexpr (RL % 16 == 0) {
-#pragma unroll
-    for (int k = 0; k < RL / 16; ++k)
-      reinterpret_cast<uint4 *>(dst)[k] = make_uint4(w[4 * k], w[4 * k + 1], w[4 * k + 2], w[4 * k + 3]);
-  } else if constexpr (RL == 8) {
-    *reinterpret_cast<uint2 *>(dst) = make_uint2(w[0], w[1]);
-  } else {
-    *reinterpret_cast<uint32_t *>(dst) = w[0];
-  }
-}
 
 // Strips of one job run on the waves of one workgroup: wave w takes strips
 // w, w + NW, w + 2*NW, ...  Strip s reads the hand-over row of strip s - 1
@@ -95,13 +44,6 @@ __device__ __forceinline__ void lds_store_words(uint8_t *dst, const uint32_t (&w
 // a spin limit still bounds them (exceeding it flags the pair as failed).
 constexpr int kMaxStrips = kIntraMaxStrips;
 constexpr int kMaxWaves = 8, kSpreadMaxWaves = 4;
-constexpr int64_t kSpinLimit = int64_t(1) << 26;
-
-__device__ __forceinline__ void lds_wave_sync() {
-  __asm__ volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-  __builtin_amdgcn_wave_barrier();
-}
-
 template <int RL, bool REV, bool HO>
 __global__ __launch_bounds__(64 * kMaxWaves) void k_intra_fill(IntraArgs a) {
   extern __shared__ uint4 s_dyn[];            // per wave: [(n + 1) symbols][64 lanes][RL bytes]
@@ -398,38 +340,13 @@ __global__ __launch_bounds__(64 * kMaxWaves) void k_intra_fill(IntraArgs a) {
 // (global wave g = segment * NW + wave takes strips g, g + segs * NW, ...).
 // The host launches it only when every workgroup of the grid fits on the
 // device at once (at most one per compute unit), so a strip's producer is
-// always running; a spin limit bounds the waits all the same.
-//
-// Bound by the chain of strips: strip s + 1 follows strip s by the wavefront's
-// 63 steps plus what the hand-over takes, once per strip.  The hand-over is one
-// 64-bit word per column, valid << 63 | F << 32 | H, stored and loaded with
-// relaxed agent-scope atomics: the word is its own flag, so no fence (a write
-// back of the L2 per publish) and no progress counter stand between the store
-// and the load, and 16 columns go at a time.  The words are cleared before the
-// launch.  A block of 16 steps reads its words one block ahead and looks at
-// them again only when some were not there yet.  With counters, fences and 64
-// columns at a time a strip started 270 steps after the one above, now TBD.
-// Measured, 10,000 x 20,000: forward 4.3 -> TBD ms, reversed 3.5 -> TBD.
-constexpr int kSpreadBlock = 16;
-constexpr uint64_t kWordValid = 1ull << 63;
-
-// RL profile bytes of one lane and symbol as words (RL = 2: the low half)
-template <int RL>
-__device__ __forceinline__ void prof_load(const uint8_t *src, uint32_t (&w)[RL >= 4 ? RL / 4 : 1]) {
-  if constexpr (RL >= 4) lds_load_words<RL>(src, w);
-  else w[0] = *reinterpret_cast<const uint16_t *>(src);
-}
-
+// always running.
 template <int RL, bool REV, bool HO>
 __global__ __launch_bounds__(64 * kSpreadMaxWaves) void k_intra_spread(IntraArgs a) {
   extern __shared__ uint4 s_dyn[];            // per wave: [(n + 1) symbols][64 lanes][RL bytes]
   __shared__ int8_t s_mat[32 * 32];
   __shared__ int32_t s_last;
   constexpr int SH = 64 * RL;
-  constexpr int XW = RL >= 4 ? RL / 4 : 1;
-  constexpr int kUnroll = RL <= 4 ? kSpreadBlock : (RL == 8 ? 4 : 1);
-  constexpr int AGENT = __HIP_MEMORY_SCOPE_AGENT;
-  using T = VT<uint32_t>;
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int NW = blockDim.x >> 6;
@@ -445,223 +362,32 @@ __global__ __launch_bounds__(64 * kSpreadMaxWaves) void k_intra_spread(IntraArgs
   IntraSync *gs = a.sync + jix;
   const IntraJob jb = a.jobs[jix];
   const int64_t p = jb.pair;
-  const int32_t Lq = a.view.qlen[p];
-  const int64_t Lr = a.view.rlen[p];
-  const int8_t *qs = a.view.qcat + a.view.qstart[p];
-  const int8_t *rs = a.view.rcat + a.view.rstart[p];
-  const bool rv = a.view.reversed != 0;
-  const int n = a.n;
-  const int64_t qp = ((int64_t)Lq + SH - 1) / SH * SH;
-  const int nstrips = (int)(qp / SH);
-  for (int i = threadIdx.x; i < n * n; i += blockDim.x) s_mat[i] = a.matrix[i];
+  for (int i = threadIdx.x; i < a.n * a.n; i += blockDim.x) s_mat[i] = a.matrix[i];
   __syncthreads();
-
-  const int64_t qpad = REV ? 0 : qp - Lq;   // forward: padding rows on top
-  const int kb = jb.kbits;
-  const uint32_t M = (1u << kb) - 1u;
-  const int32_t tgt = REV ? a.target[p] : 0;
-  const int64_t width = jb.c1 - jb.cw;
-  uint32_t *mc = a.maxcol + jb.mc_off;
-  uint64_t *rows = reinterpret_cast<uint64_t *>(a.bnd + jb.bnd_off);   // [strip][width]
-  const uint32_t vbias = (uint32_t)a.bias, vo = (uint32_t)a.o, ve = (uint32_t)a.e;
-  uint8_t *s_prof = reinterpret_cast<uint8_t *>(s_dyn) + (size_t)wave * (n + 1) * 64 * RL;
-
-  // column window of strip s (the reversed pass bands it)
-  auto window = [&](int s, int64_t &clo, int64_t &chi) {
-    clo = jb.cw;
-    chi = jb.c1;
-    if (REV && jb.band >= 0) {
-      const int64_t l = (int64_t)s * SH - jb.band;
-      if (l > clo) clo = l;
-      const int64_t h = (int64_t)s * SH + SH + jb.band;
-      if (h < chi) chi = h;
-    }
-    if (chi < clo) chi = clo;
-  };
-
-  for (int s = seg * NW + wave; s < nstrips; s += G * NW) {
-    int64_t clo, chi, plo = 0, phi = 0;
-    window(s, clo, chi);
-    if (s > 0) window(s - 1, plo, phi);
-    uint64_t *out = rows + width * (int64_t)s;   // this strip's words
-    const uint64_t *in = out - width;            // those of strip s - 1
-    const bool hand_over = (s + 1 < nstrips);
-    bool spin_fail = false;
-    auto finish = [&]() {   // every word of the strip is stored
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-      if (lane == 0) __hip_atomic_store(&gs->done[s], 1, __ATOMIC_RELAXED, AGENT);
-    };
-    // the reversed pass skips a strip that cannot hold an earlier column
-    if (chi <= clo ||
-        (REV && __hip_atomic_load(&gs->best, __ATOMIC_RELAXED, AGENT) <= (unsigned long long)clo)) {
-      finish();
-      continue;
-    }
-
-    // strip profile: biased scores of this lane's RL rows against every symbol
-    {
-      int32_t qv[RL];
-#pragma unroll
-      for (int r = 0; r < RL; ++r) {
-        const int64_t i = (int64_t)s * SH + lane * RL + r - qpad;
-        qv[r] = (i >= 0 && i < Lq) ? (int32_t)qs[rv ? Lq - 1 - i : i] : -1;
-      }
-      for (int sy = 0; sy <= n; ++sy) {
-        uint32_t w[XW];
-#pragma unroll
-        for (int k = 0; k < XW; ++k) w[k] = 0u;
-#pragma unroll
-        for (int r = 0; r < RL; ++r) {
-          const uint32_t b = (qv[r] >= 0 && sy < n) ? (uint32_t)(uint8_t)(s_mat[qv[r] * n + sy] + a.bias) : 0u;
-          w[r >> 2] |= b << (8 * (r & 3));
-        }
-        uint8_t *dst = s_prof + ((int64_t)sy * 64 + lane) * RL;
-        if constexpr (RL >= 4) lds_store_words<RL>(dst, w);
-        else *reinterpret_cast<uint16_t *>(dst) = (uint16_t)w[0];
-      }
-    }
-    lds_wave_sync();
-
-    // code offset of this lane's rows: code = M - padded row
-    const uint32_t DL = M - (uint32_t)((int64_t)s * SH + lane * RL + RL - 1);
-
-    // words of columns c0 .. c0 + cnt - 1 at lanes 0 .. cnt - 1; a column the
-    // row above does not hold reads as a valid zero
-    auto fetch = [&](int64_t c0, int cnt) -> uint64_t {
-      const int64_t c = c0 + lane;
-      const bool have = s > 0 && lane < cnt && c < chi && c >= plo && c < phi;
-      return have ? __hip_atomic_load(in + (c - jb.cw), __ATOMIC_RELAXED, AGENT) : kWordValid;
-    };
-    auto ready = [](uint64_t w) { return __ballot((w & kWordValid) != 0) == ~0ull; };
-    // the same once they are all there; words the finished strip above never
-    // stored read as zero
-    auto settle = [&](uint64_t w, int64_t c0, int cnt) -> uint64_t {
-      int64_t spins = 0;
-      while (!ready(w)) {
-        const int32_t done = __hip_atomic_load(&gs->done[s - 1], __ATOMIC_RELAXED, AGENT);
-        if (done) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        w = fetch(c0, cnt);
-        if (done) break;
-        if (++spins > kSpinLimit) { spin_fail = true; break; }
-        __builtin_amdgcn_s_sleep(1);
-      }
-      return (w & kWordValid) ? w : kWordValid;
-    };
-    // reference symbols of columns [c0, c0 + 16) at lanes 0 .. 15 (n past the window)
-    auto symbols = [&](int64_t c0) -> uint32_t {
-      const int64_t c = c0 + lane;
-      return lane < kSpreadBlock && c < chi ? (uint32_t)(uint8_t)rs[rv ? Lr - 1 - c : c] : (uint32_t)n;
-    };
-
-    uint32_t H[RL], E[RL];
-#pragma unroll
-    for (int r = 0; r < RL; ++r) { H[r] = 0u; E[r] = 0u; }
-    uint32_t hup_prev = 0u;
-    if (s > 0 && clo - 1 >= plo && clo - 1 < phi && clo >= 1) {
-      const int64_t c = clo - 1;
-      uint64_t w = lane == 0 ? __hip_atomic_load(in + (c - jb.cw), __ATOMIC_RELAXED, AGENT) : kWordValid;
-      int64_t spins = 0;
-      while (!ready(w)) {
-        const int32_t done = __hip_atomic_load(&gs->done[s - 1], __ATOMIC_RELAXED, AGENT);
-        if (done) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        if (lane == 0) w = __hip_atomic_load(in + (c - jb.cw), __ATOMIC_RELAXED, AGENT);
-        if (done) break;
-        if (++spins > kSpinLimit) { spin_fail = true; break; }
-      }
-      hup_prev = lane == 0 ? (uint32_t)w : 0u;
-    }
-    uint32_t hout = 0u, fout = 0u, cmout = 0u;
-    uint32_t obH = 0u, obF = 0u, obC = 0u;   // queues of lane 63's outputs, the newest at lane 63
-    int64_t newest = clo - 64;               // ... of this column
-    auto flush = [&]() {   // the last block's columns
-      const int64_t c = newest - 63 + lane;
-      if (lane >= 64 - kSpreadBlock && c >= clo && c < chi) {
-        if (hand_over)
-          __hip_atomic_store(out + (c - jb.cw), kWordValid | ((uint64_t)obF << 32) | obH,
-                             __ATOMIC_RELAXED, AGENT);
-        if (!REV && c >= jb.c0 && c < jb.c1) atomicMax(&mc[c], obC);
-      }
-    };
-    const int64_t nsteps = (chi - clo) + 63;
-    // a step's symbol enters lane 0 one step ahead, with its profile row
-    uint32_t sym = from_above((uint32_t)n, lane_value(symbols(clo), 0));
-    uint32_t X[XW];
-    prof_load<RL>(s_prof + ((int64_t)sym * 64 + lane) * RL, X);
-    uint32_t symnext = symbols(clo + 1);
-    uint64_t wnext = fetch(clo, kSpreadBlock);
-#pragma unroll 1
-    for (int64_t t0 = 0; t0 < nsteps; t0 += kSpreadBlock) {
-      // this block's words were asked for one block ago; the last block's
-      // outputs go out before anything waits
-      uint64_t w = wnext;
-      const bool here = ready(w);
-      const uint32_t symbuf = symnext;
-      flush();
-      if (REV && (t0 & 63) == 0 && t0 >= 64 &&
-          (unsigned long long)(clo + t0 - 63) >= __hip_atomic_load(&gs->best, __ATOMIC_RELAXED, AGENT))
-        break;   // an earlier strip already reached the target at or before here
-      if (!here) w = settle(w, clo + t0, kSpreadBlock);
-      wnext = fetch(clo + t0 + kSpreadBlock, kSpreadBlock);
-      symnext = symbols(clo + t0 + kSpreadBlock + 1);
-      const uint32_t hbuf = (uint32_t)w, fbuf = (uint32_t)(w >> 32) & 0x7FFFFFFFu;
-#pragma unroll kUnroll
-      for (int tm = 0; tm < kSpreadBlock; ++tm) {
-        const uint32_t hup = from_above(hout, lane_value(hbuf, tm));
-        uint32_t F = from_above(fout, lane_value(fbuf, tm));
-        const uint32_t cmin = from_above(cmout, 0u);
-        const uint32_t symn = from_above(sym, lane_value(symbuf, tm));
-        uint32_t Xn[XW];
-        prof_load<RL>(s_prof + ((int64_t)symn * 64 + lane) * RL, Xn);
-        uint32_t cm = 0u;
-        uint32_t u_next = T::max(hup_prev + __builtin_amdgcn_ubfe(X[0], 0, 8), E[0]);
-#pragma unroll
-        for (int r = 0; r < RL; ++r) {
-          const uint32_t u = u_next;
-          if (r + 1 < RL)
-            u_next = T::max(H[r] + __builtin_amdgcn_ubfe(X[(r + 1) >> 2], 8 * ((r + 1) & 3), 8), E[r + 1]);
-          const uint32_t hb = T::max(u, F);
-          const uint32_t hn = T::subs(hb, vbias);
-          H[r] = hn;
-          const uint32_t enc = (hn << kb) + (uint32_t)(RL - 1 - r);
-          cm = cm > enc ? cm : enc;
-          const uint32_t ho = HO ? hn : T::subs(hb, vo);   // HO: bias == o
-          E[r] = T::max(T::subs(E[r], ve), ho);
-          F = T::max(T::subs(F, ve), ho);
-        }
-        hup_prev = hup;
-        hout = H[RL - 1];
-        fout = F;
-        const uint32_t cml = cm + DL;
-        cmout = cmin > cml ? cmin : cml;
-        sym = symn;
-#pragma unroll
-        for (int k = 0; k < XW; ++k) X[k] = Xn[k];
-        obH = shift_in(obH, hout);
-        obF = shift_in(obF, fout);
-        obC = shift_in(obC, cmout);
-      }
-      newest = clo + t0 + kSpreadBlock - 64;   // step t ends column clo + t - 63
-      if constexpr (REV) {
-        const int64_t c = newest - 63 + lane;
-        const unsigned long long hit =
-            __ballot(lane >= 64 - kSpreadBlock && c >= clo && c < chi && tgt > 0 && (int32_t)(obC >> kb) >= tgt);
-        if (hit) {
-          const int hl = __builtin_ctzll(hit);
-          const uint32_t oc = lane_value(obC, hl);
-          if (lane == 0) {
-            gs->rcol[s] = newest - 63 + hl;
-            gs->rrow[s] = (int32_t)(M - (oc & M));
-            atomicMin(&gs->best, (unsigned long long)(newest - 63 + hl));
-          }
-          break;
-        }
-      }
-    }
-    flush();
-    finish();
-    if (spin_fail && lane == 0) a.err[p] = 1;   // reported as an internal failure
-  }
+  StripJob x{};
+  x.qs = a.view.qcat + a.view.qstart[p];
+  x.rs = a.view.rcat + a.view.rstart[p];
+  x.Lq = a.view.qlen[p];
+  x.rv = a.view.reversed != 0;
+  x.Lr = a.view.rlen[p];
+  x.cw = jb.cw;
+  x.c0 = jb.c0;
+  x.c1 = jb.c1;
+  x.band = jb.band;
+  x.kb = jb.kbits;
+  x.tgt = REV ? a.target[p] : 0;
+  x.mc = a.maxcol + jb.mc_off;
+  x.rows = reinterpret_cast<uint64_t *>(a.bnd + jb.bnd_off);
+  x.done = gs->done;
+  x.rcol = gs->rcol;
+  x.rrow = gs->rrow;
+  x.best = &gs->best;
+  const StripScoring sc{a.n, (uint32_t)a.bias, (uint32_t)a.o, (uint32_t)a.e};
+  uint8_t *s_prof = reinterpret_cast<uint8_t *>(s_dyn) + (size_t)wave * (a.n + 1) * 64 * RL;
+  if (strips_of_wave<RL, REV, HO>(x, sc, s_mat, s_prof, seg * NW + wave, G * NW) && lane == 0)
+    a.err[p] = 1;   // reported as an internal failure
   if constexpr (REV) {
+    const int nstrips = (int)(((int64_t)x.Lq + SH - 1) / SH);
     // the last segment of the job to finish reduces the strips' hits
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     __syncthreads();
@@ -677,7 +403,7 @@ __global__ __launch_bounds__(64 * kSpreadMaxWaves) void k_intra_spread(IntraArgs
         if (gs->rcol[s] >= 0 && (bc < 0 || gs->rcol[s] < bc)) { bc = gs->rcol[s]; br = gs->rrow[s]; }
       }
       const bool hit = bc >= 0;
-      a.out.score[p] = hit ? tgt : 0;
+      a.out.score[p] = hit ? x.tgt : 0;
       a.out.qend[p] = hit ? br : -1;
       a.out.rend[p] = hit ? bc : -1;
       a.out.overflow[p] = 0;
@@ -1130,6 +856,96 @@ hipError_t intra_rev_jobs_fixed(int64_t B, const int32_t *score, const int64_t *
   if (B <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_intra_rev_jobs_fixed, dim3((unsigned)((B + 255) / 256)), dim3(256), 0, st, B,
                      score, rend, band, kbits, bnd_stride, jobs);
+  return hipGetLastError();
+}
+
+// ---- the one-pair call: inputs and forward pass -------------------------------
+// Codes into device memory, one outside [0, n) reported and replaced (so that
+// it indexes no table), and the words of several strips cleared.
+__global__ __launch_bounds__(256) void k_pair_stage(PairArgs a) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t nt = (int64_t)gridDim.x * blockDim.x;
+  bool bad = false;
+  auto copy = [&](const int8_t *src, int8_t *dst, int64_t len) {
+    for (int64_t k = t; k < len; k += nt) {
+      const int8_t v = src[k];
+      const bool ok = v >= 0 && v < a.n;
+      dst[k] = ok ? v : (int8_t)0;
+      bad |= !ok;
+    }
+  };
+  copy(a.src_q, a.q, a.Lq);
+  copy(a.src_r, a.r, a.Lr);
+  for (int64_t k = t; k < (int64_t)a.n * a.n; k += nt) a.m[k] = a.src_m[k];
+  if (bad) a.out->bad = 1;
+  if (a.strips > 1) {   // (one strip stores every max array word itself)
+    for (int64_t k = t; k < a.fstride * a.nchunks; k += nt) a.fwords[k] = 0;
+    for (int64_t k = t; k < a.rcount; k += nt) a.rwords[k] = 0;
+    for (int64_t k = t; k < a.Lr; k += nt) a.maxcol[k] = 0u;
+  }
+}
+
+template <bool HO, bool ALONE>
+__global__ __launch_bounds__(64 * kPairWaves) void k_pair_forward(PairArgs a) {
+  extern __shared__ uint4 s_dyn[];            // per wave: [(n + 1) symbols][64 lanes][rows] bytes
+  __shared__ int8_t s_mat[32 * 32];
+  __shared__ int32_t s_done[kPairWaves];
+  const int wave = threadIdx.x >> 6;
+  for (int i = threadIdx.x; i < a.n * a.n; i += blockDim.x) s_mat[i] = a.m[i];
+  if (threadIdx.x < kPairWaves) s_done[threadIdx.x] = 0;
+  __syncthreads();
+  StripJob x{};
+  x.qs = a.q;
+  x.rs = a.r;
+  x.Lq = a.Lq;
+  x.Lr = a.Lr;
+  x.c0 = a.chunk * blockIdx.x;
+  x.c1 = x.c0 + a.chunk < a.Lr ? x.c0 + a.chunk : a.Lr;
+  x.cw = x.c0 > a.warm ? x.c0 - a.warm : 0;
+  x.band = -1;
+  x.kb = a.kb;
+  x.mc = a.maxcol;
+  x.rows = a.fwords + a.fstride * blockIdx.x;
+  x.done = s_done;
+  const StripScoring sc{a.n, (uint32_t)a.bias, (uint32_t)a.o, (uint32_t)a.e};
+  uint8_t *s_prof = reinterpret_cast<uint8_t *>(s_dyn) + (size_t)wave * (a.n + 1) * 64 * kPairRows;
+  if constexpr (ALONE) {
+    strip_alone<kPairRows, false, HO>(x, sc, s_mat, s_prof);
+  } else {
+    if (strips_of_wave<kPairRows, false, HO>(x, sc, s_mat, s_prof, wave, (int)(blockDim.x >> 6)) &&
+        (threadIdx.x & 63) == 0)
+      a.out->err = 1;
+  }
+}
+
+hipError_t pair_stage(const PairArgs &a, hipStream_t st) {
+  int64_t work = a.Lq + a.Lr;
+  if (a.strips > 1) work = std::max(work, a.fstride * a.nchunks + a.rcount);
+  const unsigned blocks = (unsigned)std::min<int64_t>((work + 255) / 256, 512);
+  hipLaunchKernelGGL(k_pair_stage, dim3(blocks), dim3(256), 0, st, a);
+  return hipGetLastError();
+}
+
+// one wave per strip, as far as the profiles fit in LDS beside the last
+// kernel's 12 KiB
+int pair_waves(int strips, int n) {
+  const int room = (int)((65536 - 12288) / intra_lds_bytes(n, kPairRows));
+  return std::min(std::min(strips, kPairWaves), room);
+}
+
+hipError_t pair_forward(const PairArgs &a, hipStream_t st) {
+  if (a.strips < 1 || a.strips > kPairWaves || a.nchunks < 1) return hipErrorInvalidValue;
+  const int waves = pair_waves(a.strips, a.n);
+  const dim3 g((unsigned)a.nchunks), b(64 * waves);
+  const size_t lds = intra_lds_bytes(a.n, kPairRows) * waves;
+  const bool ho = a.bias == a.o;   // H and H - o are one value
+  if (a.strips == 1) {
+    if (ho) hipLaunchKernelGGL((k_pair_forward<true, true>), g, b, lds, st, a);
+    else hipLaunchKernelGGL((k_pair_forward<false, true>), g, b, lds, st, a);
+  } else {
+    if (ho) hipLaunchKernelGGL((k_pair_forward<true, false>), g, b, lds, st, a);
+    else hipLaunchKernelGGL((k_pair_forward<false, false>), g, b, lds, st, a);
+  }
   return hipGetLastError();
 }
 

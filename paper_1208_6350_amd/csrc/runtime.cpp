@@ -10,6 +10,7 @@
 #include <cstring>
 #include <functional>
 #include <map>
+#include <memory>
 #include <tuple>
 #include <mutex>
 #include <numeric>
@@ -167,21 +168,10 @@ struct swx_ctx {
   hipStream_t aux[kAux] = {};
   hipEvent_t fork_ev = nullptr;
   hipEvent_t join_ev[kAux] = {};
-  // one-pair calls (swx_align): captured graphs of capacity one pair, one per
-  // scoring scheme, flags and power-of-two size class, least recently used
-  // evicted; pair_mu serialises their use (taken before mu, never inside it)
-  struct PairGraph {
-    std::vector<int8_t> matrix;
-    int32_t n = 0, o = 0, e = 0, mask_len = 0;
-    uint32_t flags = 0;
-    int32_t qcap = 0;
-    int64_t rcap = 0;
-    swx_graph *g = nullptr;
-    uint64_t last_use = 0;
-  };
-  std::mutex pair_mu;
-  std::vector<PairGraph> pair_graphs;
-  uint64_t pair_clock = 0;
+  // one-pair calls (swx_align): pinned host memory the kernels read the inputs
+  // from and write the result to, made on first use
+  int8_t *pair_in = nullptr;
+  swx::PairOut *pair_out = nullptr;
   // pinned landing area of the small device-to-host reads between stages
   static constexpr int64_t kPinned = 512;   // int64 values
   int64_t *pinned = nullptr;
@@ -1890,17 +1880,10 @@ struct GraphState {
   void *tb_sort_tmp = nullptr;
   size_t tb_sort_bytes = 0;
   FixedTb tb[6];
-  // graphs of 2 to kTbPairsAll pairs: a workgroup per pair instead
+  // graphs of up to kTbPairsAll pairs: a workgroup per pair instead
   bool tb_by_pairs = false;
   int64_t tbp_stride = 0;
   uint8_t *tbp_scratch = nullptr;
-  // one-pair graphs: the pair's traceback on the wave kernel, its job planned
-  // on the device (instead of the class, sort and task kernels of a batch)
-  bool tbw1 = false;
-  int tbw_rl = 4, tbw_waves = 1;
-  TbWaveJob *tbw_job = nullptr;
-  uint8_t *tbw_dir = nullptr;
-  int32_t *tbw_bnd = nullptr;
   uint32_t *cscr = nullptr;
   // intra route: every pair spread over a wave (one job per pair)
   bool intra = false;
@@ -2119,10 +2102,6 @@ static int fixed_issue(GraphState &g, hipStream_t st) {
     ta.wave_cells = INT64_MAX;   // no host-planned wave traceback in a graph
     ta.cig = g.cscr;
     ta.cig_off = g.coff;
-    if (g.tbw1) {
-      HIP_TRY(tb_wave_job1(ta, g.tbw_job, g.coff, st));
-      HIP_TRY(tb_wave(ta, g.tbw_job, 1, g.tbw_rl, g.tbw_waves, 1, nullptr, g.tbw_dir, g.tbw_bnd, st));
-    } else {
     HIP_TRY(fill_i64(1, g.ccap + B, 0, st));
     HIP_TRY(fill_i64(8, g.counts, 0, st));
     HIP_TRY(tb_classify(ta, B, g.cls, g.tk0, g.tv0, g.ccap, g.counts, nullptr, st));
@@ -2164,16 +2143,11 @@ static int fixed_issue(GraphState &g, hipStream_t st) {
       HIP_TRY(tb_strip(tc, tasks, t.cap_tasks, g.tb_sorted, t.bnd, st));
     }
     }
-    }
-    if (g.tbw1) {
-      HIP_TRY(cigar_one(g.cscr, g.coff, g.cig_len, g.cig_off_final, g.cigar, st));
-    } else {
       if (!g.intra) HIP_TRY(fill_i64(1, g.len64 + B, 0, st));
       HIP_TRY(lens_to_i64(B, g.cig_len, g.len64, st));
       if ((rc = fixed_scan(g, g.len64, g.cig_off_final, B + 1, st))) return rc;
       HIP_TRY(launch_cigar_compact(B, g.cscr, g.coff, g.cig_len, g.cig_off_final, g.cls, g.qbeg,
                                    g.qend, g.cigar, st));
-    }
   }
   if ((flags & SWX_SCORE2) && g.intra) {
     IntraPairArgs e{};
@@ -2200,9 +2174,6 @@ static int fixed_issue(GraphState &g, hipStream_t st) {
   HIP_TRY(launch_any_flag(B, g.err, g.status, st));
   return SWX_OK;
 }
-
-// Code bytes up to which a one-pair graph traces its pair on the wave kernel.
-static constexpr int64_t kGraphWaveTbBytes = int64_t(64) << 20;
 
 static int graph_alloc(GraphState &g) {
   DevArena &A = g.A;
@@ -2296,7 +2267,7 @@ static int graph_alloc(GraphState &g) {
   // the band classes, up to every pair in one class
   const int64_t tbp_stride = round_up(tb_wave_dir_bytes(g.QM, g.RM, kTbPairRows), 256) +
                              tb_pair_bnd_bytes(g.QM, g.RM);
-  g.tb_by_pairs = B > 1 && B <= kTbPairsAll && B * tbp_stride <= kTbGraphBytes &&
+  g.tb_by_pairs = B <= kTbPairsAll && B * tbp_stride <= kTbGraphBytes &&
                   (g.QM + 64 * kTbPairRows - 1) / (64 * kTbPairRows) <= tb_wave_max_strips();
   if (g.tb_by_pairs) {
     g.tbp_stride = tbp_stride;
@@ -2329,22 +2300,6 @@ static int graph_alloc(GraphState &g) {
     t.bnd = A.get<int32_t>(capW * 2 * (g.RM + 1) * kTbwSlots);
     if (!t.tasks || !t.dsz || !t.doff || !t.bsz || !t.boff || !t.dir || !t.bnd)
       return fail(SWX_ENOMEM, "device pool exhausted (graph traceback)");
-  }
-  if (B == 1) {
-    // codes of at most QM rows over at most RM + 1 columns per strip
-    const int RL = 4;
-    const int64_t dbytes = tb_wave_dir_bytes(g.QM, g.RM, RL);
-    const int64_t nstrips = (g.QM + 64 * RL - 1) / (64 * RL);
-    if (dbytes <= kGraphWaveTbBytes && nstrips <= tb_wave_max_strips()) {
-      g.tbw_rl = RL;
-      g.tbw_waves = tb_wave_waves(g.QM, g.sc.n, RL);
-      g.tbw_job = A.get<TbWaveJob>(1);
-      g.tbw_dir = A.get<uint8_t>(dbytes);
-      g.tbw_bnd = A.get<int32_t>(2 * (g.RM + 1) * (nstrips + 1));
-      if (!g.tbw_job || !g.tbw_dir || !g.tbw_bnd)
-        return fail(SWX_ENOMEM, "device pool exhausted (graph wave traceback)");
-      g.tbw1 = true;
-    }
   }
   size_t sb = 0;
   HIP_TRY(sort_keys(B, g.tk0, g.tk1, g.tv0, g.tv1, nullptr, &sb, &g.tb_sorted, nullptr, kTbKeyBits,
@@ -2434,6 +2389,8 @@ static void release_ctx(swx_ctx *ctx) {
   ctx->arena.release();
   if (ctx->queue) (void)hipFree(ctx->queue);
   if (ctx->pinned) (void)hipHostFree(ctx->pinned);
+  if (ctx->pair_in) (void)hipHostFree(ctx->pair_in);
+  if (ctx->pair_out) (void)hipHostFree(ctx->pair_out);
   for (auto &e : ctx->ev)
     if (e) (void)hipEventDestroy(e);
   for (int k = 0; k < swx_ctx::kAux; ++k) {
@@ -2490,11 +2447,6 @@ int swx_ctx_create(int device, swx_ctx **out) {
 
 int swx_ctx_destroy(swx_ctx *ctx) {
   if (!ctx) return fail(SWX_EINVAL, "ctx is null");
-  {
-    std::lock_guard<std::mutex> lk(ctx->pair_mu);
-    for (auto &pg : ctx->pair_graphs) swx_graph_destroy(pg.g);
-    ctx->pair_graphs.clear();
-  }
   {
     std::lock_guard<std::mutex> g(ctx->mu);
     (void)hipSetDevice(ctx->device);
@@ -2642,8 +2594,10 @@ int64_t swx_cigar_bound(const swx_batch *b) {
   return (b->flags & SWX_SUBOPT) ? 2 * s : s;
 }
 
+// dev_ref: the reference codes in device memory of a host-memory batch (whose
+// rcat then only has to be non-null)
 static int align_batch_locked(swx_ctx *ctx, const swx_batch *b, swx_batch_out *out,
-                              const swx_profile *prof = nullptr) {
+                              const swx_profile *prof = nullptr, const int8_t *dev_ref = nullptr) {
   Scoring sc;
   int rc = make_scoring(b->matrix, b->n, b->gap_open, b->gap_extend, &sc);
   if (rc) return rc;
@@ -2673,19 +2627,20 @@ static int align_batch_locked(swx_ctx *ctx, const swx_batch *b, swx_batch_out *o
     db.qcat = b->qcat; db.rcat = b->rcat; db.qoff = b->qoff; db.roff = b->roff;
     db.pair_q = b->pair_q; db.pair_r = b->pair_r;
   } else {
-    int8_t *qc = A.get<int8_t>(b->qcat_len), *rc8 = A.get<int8_t>(b->rcat_len);
+    int8_t *qc = A.get<int8_t>(b->qcat_len), *rc8 = dev_ref ? nullptr : A.get<int8_t>(b->rcat_len);
     int64_t *qo = A.get<int64_t>(b->nq + 1), *ro = A.get<int64_t>(b->nr + 1);
     int64_t *pq = A.get<int64_t>(b->npairs), *pr = A.get<int64_t>(b->npairs);
-    if (!qc || !rc8 || !qo || !ro || !pq || !pr) return fail(SWX_ENOMEM, "device pool exhausted");
+    if (!qc || (!rc8 && !dev_ref) || !qo || !ro || !pq || !pr) return fail(SWX_ENOMEM, "device pool exhausted");
     if (b->qcat_len) HIP_TRY(hipMemcpyAsync(qc, b->qcat, b->qcat_len, hipMemcpyHostToDevice, st));
-    if (b->rcat_len) HIP_TRY(hipMemcpyAsync(rc8, b->rcat, b->rcat_len, hipMemcpyHostToDevice, st));
+    if (b->rcat_len && !dev_ref)
+      HIP_TRY(hipMemcpyAsync(rc8, b->rcat, b->rcat_len, hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(qo, b->qoff, 8 * (b->nq + 1), hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(ro, b->roff, 8 * (b->nr + 1), hipMemcpyHostToDevice, st));
     if (b->npairs) {
       HIP_TRY(hipMemcpyAsync(pq, b->pair_q, 8 * b->npairs, hipMemcpyHostToDevice, st));
       HIP_TRY(hipMemcpyAsync(pr, b->pair_r, 8 * b->npairs, hipMemcpyHostToDevice, st));
     }
-    db.qcat = qc; db.rcat = rc8; db.qoff = qo; db.roff = ro; db.pair_q = pq; db.pair_r = pr;
+    db.qcat = qc; db.rcat = dev_ref ? dev_ref : rc8; db.qoff = qo; db.roff = ro; db.pair_q = pq; db.pair_r = pr;
   }
   if (b->npairs == 0) {
     out->cigar_used = 0;
@@ -2738,62 +2693,106 @@ int swx_align_batch_noalloc(swx_ctx *ctx, const swx_batch *b, swx_batch_out *out
   return rc;
 }
 
-// The one-pair call through a cached graph (intra route: the pair spread over
-// a wave).  Returns 1 when no graph serves the pair (too large, or one could
-// not be made): the caller then takes the batch path.
-static constexpr int32_t kPairGraphMaxQ = 4096;
-static constexpr int64_t kPairGraphMaxR = int64_t(1) << 16;
-static constexpr size_t kPairGraphs = 8;
-
-static int graph_run_on(swx_graph *gr, void *hip_stream);
-
-static int align_pair_graph(const swx_profile *p, int64_t rlen, uint32_t flags,
-                            int32_t mask_len, const swx_batch &b, void *hip_stream, swx_rec &rec,
-                            std::vector<uint32_t> &cig) {
+// The one-pair call of short queries (kPairMaxQ x kPairMaxR) in three kernels.
+// ref: host memory, or device memory with ref_dev.  Callers hold ctx->mu and a
+// StreamScope.
+static int align_pair_short(const swx_profile *p, const int8_t *ref, bool ref_dev, int64_t rlen,
+                            uint32_t flags, int32_t mask_len, swx_result *out) {
   swx_ctx *ctx = p->ctx;
-  const int64_t ql = (int64_t)p->query.size();
-  if (ql > kPairGraphMaxQ || rlen > kPairGraphMaxR) return 1;
-  int32_t qcap = 64;
-  while (qcap < ql) qcap *= 2;
-  int64_t rcap = 256;
-  while (rcap < rlen) rcap *= 2;
-  std::lock_guard<std::mutex> lk(ctx->pair_mu);
-  swx_ctx::PairGraph *hit = nullptr;
-  for (auto &pg : ctx->pair_graphs)
-    if (pg.n == p->n && pg.o == p->o && pg.e == p->e && pg.flags == flags &&
-        pg.mask_len == mask_len && pg.qcap == qcap && pg.rcap == rcap && pg.matrix == p->matrix) {
-      hit = &pg;
-      break;
-    }
-  if (!hit) {
-    if (ctx->pair_graphs.size() >= kPairGraphs) {   // evict the least recently used
-      size_t old = 0;
-      for (size_t k = 1; k < ctx->pair_graphs.size(); ++k)
-        if (ctx->pair_graphs[k].last_use < ctx->pair_graphs[old].last_use) old = k;
-      swx_graph_destroy(ctx->pair_graphs[old].g);
-      ctx->pair_graphs.erase(ctx->pair_graphs.begin() + (std::ptrdiff_t)old);
-    }
-    swx_graph_cfg cfg{};
-    cfg.matrix = p->matrix.data(); cfg.n = p->n; cfg.gap_open = p->o; cfg.gap_extend = p->e;
-    cfg.max_pairs = 1; cfg.max_qlen = qcap; cfg.max_rlen = rcap;
-    cfg.qcat_cap = qcap; cfg.rcat_cap = rcap; cfg.nq_cap = 1; cfg.nr_cap = 2;
-    cfg.flags = flags; cfg.mask_len = mask_len; cfg.route = SWX_ROUTE_INTRA;
-    swx_graph *gr = nullptr;
-    swx_graph_io io{};
-    if (swx_graph_create(ctx, &cfg, &gr, &io) != SWX_OK) return 1;
-    swx_ctx::PairGraph pg;
-    pg.matrix = p->matrix; pg.n = p->n; pg.o = p->o; pg.e = p->e;
-    pg.flags = flags; pg.mask_len = mask_len; pg.qcap = qcap; pg.rcap = rcap; pg.g = gr;
-    ctx->pair_graphs.push_back(std::move(pg));
-    hit = &ctx->pair_graphs.back();
+  if (hipSetDevice(ctx->device) != hipSuccess) return fail(SWX_EDEVICE, "hipSetDevice failed");
+  const int64_t Lq = (int64_t)p->query.size();
+  Scoring sc;
+  int rc = make_scoring(p->matrix.data(), p->n, p->o, p->e, &sc);
+  if (rc) return rc;
+  constexpr int64_t kInR = kPairMaxQ, kInM = kInR + kPairMaxR;   // offsets of the staged inputs
+  if (!ctx->pair_in &&
+      hipHostMalloc(&ctx->pair_in, kInM + 32 * 32, hipHostMallocDefault) != hipSuccess) {
+    ctx->pair_in = nullptr;
+    return fail(SWX_ENOMEM, "pinned host allocation failed");
   }
-  hit->last_use = ++ctx->pair_clock;
-  int rc = swx_graph_load(hit->g, &b);
-  if (rc == SWX_OK) rc = graph_run_on(hit->g, hip_stream);
-  if (rc != SWX_OK) return rc;
-  swx_batch_out bo{&rec, cig.data(), (int64_t)cig.size(), 0, SWX_MEM_HOST};
-  return swx_graph_read(hit->g, 1, &bo);
+  if (!ctx->pair_out &&
+      hipHostMalloc(&ctx->pair_out, sizeof(PairOut) + 4 * (kPairMaxQ + kPairMaxR + 2),
+                    hipHostMallocDefault) != hipSuccess) {
+    ctx->pair_out = nullptr;
+    return fail(SWX_ENOMEM, "pinned host allocation failed");
+  }
+  if (flags & (SWX_CIGAR | SWX_SCORE2)) flags |= SWX_BEGIN;
+  PairArgs a{};
+  a.Lq = (int32_t)Lq;
+  a.Lr = rlen;
+  a.n = sc.n; a.o = sc.o; a.e = sc.e; a.bias = sc.bias; a.smax = sc.smax;
+  a.strips = (int32_t)((Lq + 64 * kPairRows - 1) / (64 * kPairRows));
+  a.kb = code_bits((int64_t)a.strips * 64 * kPairRows);
+  a.flags = flags;
+  a.mask_len = mask_len;
+  // column chunks, each on a workgroup of its own: as many as shorten the
+  // longest (its warm-up is the widest positive-scoring span), and several
+  // strips' words within a few megabytes
+  a.warm = intra_warmup(sc, Lq, rlen);
+  a.chunk = std::max<int64_t>(rlen, 1);
+  if (a.warm < rlen)
+    a.chunk = std::max<int64_t>(64, (rlen + (a.strips == 1 ? 255 : 127)) / (a.strips == 1 ? 256 : 128));
+  a.nchunks = (int32_t)((rlen + a.chunk - 1) / a.chunk);
+  a.fstride = (a.strips - 1) * std::min(rlen, a.chunk + a.warm);
+  a.rcount = (a.strips - 1) * rlen;
+  ctx->arena.reset();
+  DevArena &A = ctx->arena;
+  a.q = A.get<int8_t>(Lq);
+  a.r = A.get<int8_t>(rlen);
+  a.m = A.get<int8_t>((int64_t)sc.n * sc.n);
+  a.maxcol = A.get<uint32_t>(rlen);
+  a.fwords = A.get<uint64_t>(a.fstride * a.nchunks);
+  a.rwords = A.get<uint64_t>(a.rcount);
+  a.state = A.get<PairState>(1);
+  uint32_t *cig = A.get<uint32_t>(Lq + rlen + 2);
+  if (!a.q || !a.r || !a.m || !a.maxcol || !a.fwords || !a.rwords || !a.state || !cig)
+    return fail(SWX_ENOMEM, "device pool exhausted (pair)");
+  if (flags & SWX_CIGAR) {
+    // an alignment of positive score spans at most the warm-up's columns
+    const int64_t w = std::min(rlen, a.warm);
+    a.dir = A.get<uint8_t>(tb_wave_dir_bytes(Lq, w, kPairRows));
+    a.bnd = A.get<int32_t>(2 * (w + 1) * (a.strips + 1));
+    if (!a.dir || !a.bnd) return fail(SWX_ENOMEM, "device pool exhausted (pair traceback)");
+  }
+  PairState *y = a.state;
+  TbArgs &t = a.tb;
+  t.score = &y->score; t.qbeg = &y->qbeg; t.qend = &y->qend; t.rbeg = &y->rbeg; t.rend = &y->rend;
+  t.qstart = &y->qstart; t.rstart = &y->rstart; t.qlen = &y->qlen; t.rlen = &y->rlen;
+  t.qcat = a.q; t.rcat = a.r; t.matrix = a.m;
+  t.n = sc.n; t.o = sc.o; t.e = sc.e; t.smax = sc.smax;
+  t.cig = cig; t.cig_off = &y->cig_off; t.cig_len = &y->cig_len; t.err = &y->err;
+  memcpy(ctx->pair_in, p->query.data(), (size_t)Lq);
+  if (!ref_dev) memcpy(ctx->pair_in + kInR, ref, (size_t)rlen);
+  memcpy(ctx->pair_in + kInM, p->matrix.data(), (size_t)sc.n * sc.n);
+  a.src_q = ctx->pair_in;
+  a.src_r = ref_dev ? ref : ctx->pair_in + kInR;
+  a.src_m = ctx->pair_in + kInM;
+  a.out = ctx->pair_out;
+  a.out->bad = a.out->err = 0;
+  hipError_t he = pair_stage(a, ctx->stream);
+  if (he == hipSuccess) he = pair_forward(a, ctx->stream);
+  if (he == hipSuccess) he = pair_rest(a, ctx->stream);
+  const hipError_t hw = wait_stream(ctx->stream);   // the pinned buffers are the next call's too
+  if (he == hipSuccess) he = hw;
+  if (he != hipSuccess) return fail(SWX_EDEVICE, std::string("one-pair call: ") + hipGetErrorString(he));
+  if (a.out->bad) return fail(SWX_EINVAL, "symbol code outside [0, n)");
+  if (a.out->err) return fail(SWX_EINTERNAL, "internal consistency check failed");
+  memcpy(&out->rec, &a.out->rec, sizeof(swx_rec));
+  if (out->rec.cigar_len > 0) {
+    const size_t bytes = sizeof(uint32_t) * (size_t)out->rec.cigar_len;
+    out->cigar = (uint32_t *)malloc(bytes);
+    if (!out->cigar) {
+      memset(out, 0, sizeof(*out));
+      return fail(SWX_ENOMEM, "host allocation failed");
+    }
+    memcpy(out->cigar, a.out + 1, bytes);
+  }
+  return SWX_OK;
 }
+
+// Pairs of at most this size are always aligned on 32-bit long-pair lanes
+// (the record's lane_bits), whatever the context's routing.
+static constexpr int64_t kPair32MaxQ = 4096;
 
 int swx_align(const swx_profile *p, const int8_t *ref, int64_t rlen, uint32_t flags,
               int32_t mask_len, void *hip_stream, swx_result *out) {
@@ -2804,73 +2803,90 @@ int swx_align(const swx_profile *p, const int8_t *ref, int64_t rlen, uint32_t fl
   memset(out, 0, sizeof(*out));
   const bool subopt = (flags & SWX_SUBOPT) != 0;
   if (subopt) flags |= SWX_ALL;
-  std::vector<int8_t> href;
-  const int8_t *rptr = ref;
-  if (flags & SWX_REF_DEVICE) {
-    href.resize((size_t)rlen);
-    // ordered after the caller's work on its stream (which may write ref)
-    if (rlen) {
-      if (hip_stream) {
-        if (hipMemcpyAsync(href.data(), ref, (size_t)rlen, hipMemcpyDeviceToHost,
-                           (hipStream_t)hip_stream) != hipSuccess ||
-            wait_stream((hipStream_t)hip_stream) != hipSuccess)
-          return fail(SWX_EDEVICE, "could not read the device reference");
-      } else if (hipMemcpy(href.data(), ref, (size_t)rlen, hipMemcpyDeviceToHost) != hipSuccess) {
-        return fail(SWX_EDEVICE, "could not read the device reference");
-      }
-    }
-    rptr = href.data();
-  }
-  if (!subopt) {
-    const int64_t qoff[2] = {0, (int64_t)p->query.size()};
-    const int64_t roff[2] = {0, rlen};
-    const int64_t pq = 0, pr = 0;
-    swx_batch b{};
-    b.matrix = p->matrix.data(); b.n = p->n; b.gap_open = p->o; b.gap_extend = p->e;
-    b.qcat = p->query.data(); b.qcat_len = (int64_t)p->query.size(); b.qoff = qoff; b.nq = 1;
-    b.rcat = rptr; b.rcat_len = rlen; b.roff = roff; b.nr = 1;
-    b.pair_q = &pq; b.pair_r = &pr; b.npairs = 1;
-    b.flags = flags & SWX_ALL; b.mask_len = mask_len; b.in_mem = SWX_MEM_HOST;
-    swx_rec rec{};
-    std::vector<uint32_t> cig((size_t)(p->query.size() + rlen + 2));
-    const int rc = align_pair_graph(p, rlen, flags & SWX_ALL, mask_len, b, hip_stream, rec, cig);
-    if (rc < 0) return rc;
-    if (rc == SWX_OK) {
-      out->rec = rec;
-      out->cigar = nullptr;
-      if (rec.cigar_len > 0) {
-        out->cigar = (uint32_t *)malloc(sizeof(uint32_t) * rec.cigar_len);
-        if (!out->cigar) return fail(SWX_ENOMEM, "host allocation failed");
-        memcpy(out->cigar, cig.data() + rec.cigar_off, sizeof(uint32_t) * rec.cigar_len);
-      }
-      out->rec.cigar_off = 0;
-      return SWX_OK;
-    }
-  }
+  bool ref_dev = (flags & SWX_REF_DEVICE) != 0 && rlen > 0;
+  const int64_t Lq = (int64_t)p->query.size();
   std::lock_guard<std::mutex> g(ctx->mu);
+  std::vector<int8_t> href;
+  if (ref_dev) {
+    if (hipSetDevice(ctx->device) != hipSuccess) return fail(SWX_EDEVICE, "hipSetDevice failed");
+    // device memory of this GPU is read in place (a 5,000,000-column reference
+    // took 1 ms to the host and back); anything else goes through a copy,
+    // which also reports what cannot be read
+    hipPointerAttribute_t at{};
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    const bool here = hipPointerGetAttributes(&at, ref) == hipSuccess &&
+                      at.type == hipMemoryTypeDevice && at.device == ctx->device && !at.isManaged &&
+                      hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)ref) == hipSuccess &&
+                      (const int8_t *)base + size >= ref + rlen;
+    if (!here) (void)hipGetLastError();
+    // ordered after the caller's work: on its stream, or (none given) on the
+    // default stream, where a copy of one byte waits as one of all would
+    const size_t bytes = here ? 1 : (size_t)rlen;
+    href.resize(bytes);
+    if (!hip_stream) {
+      if (hipMemcpy(href.data(), ref, bytes, hipMemcpyDeviceToHost) != hipSuccess)
+        return fail(SWX_EDEVICE, "could not read the device reference");
+    } else if (!here) {
+      if (hipMemcpyAsync(href.data(), ref, bytes, hipMemcpyDeviceToHost, (hipStream_t)hip_stream) !=
+              hipSuccess ||
+          wait_stream((hipStream_t)hip_stream) != hipSuccess)
+        return fail(SWX_EDEVICE, "could not read the device reference");
+    }
+    if (!here) {
+      ref = href.data();
+      ref_dev = false;
+    }
+  }
   StreamScope ss(ctx, hip_stream);
-  const int64_t qoff[2] = {0, (int64_t)p->query.size()};
+  const bool plain = !subopt && Lq <= kPair32MaxQ && rlen <= kPairMaxR;
+  if (plain && Lq <= kPairMaxQ && rlen > 0)
+    return align_pair_short(p, ref, ref_dev, rlen, flags & SWX_ALL, mask_len, out);
+  struct Routing {   // plain pairs: the 32-bit long-pair lanes
+    swx_ctx *c;
+    int64_t cells, len;
+    int32_t bits;
+    Routing(swx_ctx *c_, bool on) : c(c_), cells(c_->long_cells), len(c_->long_rlen), bits(c_->intra_bits) {
+      if (on) {
+        c->long_cells = 0;
+        c->intra_bits = 32;
+      }
+    }
+    ~Routing() {
+      c->long_cells = cells;
+      c->long_rlen = len;
+      c->intra_bits = bits;
+    }
+  } routing(ctx, plain);
+  const int64_t qoff[2] = {0, Lq};
   const int64_t roff[2] = {0, rlen};
   const int64_t pq = 0, pr = 0;
   swx_batch b{};
   b.matrix = p->matrix.data(); b.n = p->n; b.gap_open = p->o; b.gap_extend = p->e;
-  b.qcat = p->query.data(); b.qcat_len = (int64_t)p->query.size(); b.qoff = qoff; b.nq = 1;
-  b.rcat = rptr; b.rcat_len = rlen; b.roff = roff; b.nr = 1;
+  b.qcat = p->query.data(); b.qcat_len = Lq; b.qoff = qoff; b.nq = 1;
+  b.rcat = ref; b.rcat_len = rlen; b.roff = roff; b.nr = 1;
   b.pair_q = &pq; b.pair_r = &pr; b.npairs = 1;
   b.flags = flags & (SWX_ALL | SWX_SUBOPT); b.mask_len = mask_len; b.in_mem = SWX_MEM_HOST;
   swx_rec rec{}, sub{};
-  // the suboptimal alignment's CIGAR goes to the same arena
-  std::vector<uint32_t> cig((size_t)((subopt ? 2 : 1) * (p->query.size() + rlen + 2)));
-  swx_batch_out bo{&rec, cig.data(), (int64_t)cig.size(), 0, SWX_MEM_HOST, 0, subopt ? &sub : nullptr};
-  int rc = align_batch_locked(ctx, &b, &bo, p);
+  Scoring sc;
+  int rc = make_scoring(p->matrix.data(), p->n, p->o, p->e, &sc);
   if (rc) return rc;
+  // an alignment spans at most the widest positive-scoring path's columns; the
+  // suboptimal alignment's CIGAR goes to the same arena
+  const int64_t cap = (subopt ? 2 : 1) * (Lq + std::min(rlen, intra_warmup(sc, Lq, rlen)) + 2);
+  std::unique_ptr<uint32_t[]> cig(new (std::nothrow) uint32_t[(size_t)cap]);
+  if (!cig) return fail(SWX_ENOMEM, "host allocation failed");
+  swx_batch_out bo{&rec, cig.get(), cap, 0, SWX_MEM_HOST, 0, subopt ? &sub : nullptr};
+  rc = align_batch_locked(ctx, &b, &bo, p, ref_dev ? ref : nullptr);
+  if (rc) return rc;
+  if (plain && rlen == 0) rec.lane_bits = 32;
   auto copy_out = [&](const swx_rec &r, swx_rec &dst, uint32_t *&dcig) {
     dst = r;
     dcig = nullptr;
     if (r.cigar_len > 0) {
       dcig = (uint32_t *)malloc(sizeof(uint32_t) * r.cigar_len);
       if (!dcig) return false;
-      memcpy(dcig, cig.data() + r.cigar_off, sizeof(uint32_t) * r.cigar_len);
+      memcpy(dcig, cig.get() + r.cigar_off, sizeof(uint32_t) * r.cigar_len);
     }
     dst.cigar_off = 0;
     return true;

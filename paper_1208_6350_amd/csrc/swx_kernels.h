@@ -215,10 +215,7 @@ hipError_t tbw_offsets(int64_t ntasks, TbwTask *tasks, const int64_t *doff, cons
                        hipStream_t st);
 hipError_t tb_strip(const TbArgs &a, const TbwTask *tasks, int64_t ntasks, const int64_t *sorted,
                     int32_t *bndbuf, hipStream_t st);
-// One-pair graphs: pair 0's wave job planned on the device (m = 0 when it has
-// no alignment; its CIGAR scratch offset cig_off[0] = 0), and an upper bound
-// of the code bytes of a pair of at most m rows and w columns
-hipError_t tb_wave_job1(const TbArgs &a, TbWaveJob *job, int64_t *cig_off, hipStream_t st);
+// upper bound of the code bytes of a pair of at most m rows and w columns
 int64_t tb_wave_dir_bytes(int64_t m, int64_t w, int RL);
 // segs > 1: each pair's strips spread over that many workgroups (sync: one
 // record per pair), then a walk kernel; else the fill and the walk in one
@@ -276,6 +273,48 @@ struct IntraPairArgs {
   int64_t *part_j;
   int64_t max_rlen;        // longest reference of the launch (its shape)
 };
+
+// The one-pair call (swx_align) of short queries, in three kernels: the inputs
+// staged and checked, the forward pass on a workgroup per column chunk, and
+// everything after it on one workgroup.
+constexpr int kPairRows = 4;          // rows per lane
+constexpr int kPairWaves = 8;         // most waves of a workgroup, and most strips of a query
+constexpr int32_t kPairMaxQ = 64 * kPairRows * kPairWaves;
+constexpr int64_t kPairMaxR = int64_t(1) << 16;
+struct PairOut {         // in pinned host memory, the CIGAR's words after it
+  swx_rec_dev rec;
+  int32_t bad;           // a symbol code outside [0, n)
+  int32_t err;           // an internal check failed
+};
+struct PairState {       // the pair's arrays of one element each (TbArgs)
+  int64_t qstart, rstart, rbeg, rend, rlen, cig_off;
+  int32_t score, qbeg, qend, qlen, cig_len;
+  uint8_t err;
+};
+struct PairArgs {
+  const int8_t *src_q, *src_r, *src_m;   // pinned host memory, or the caller's device reference
+  int8_t *q, *r, *m;                     // device copies, every code inside [0, n)
+  int32_t Lq, kb;
+  int64_t Lr;
+  int32_t n, o, e, bias, smax;
+  int64_t chunk, warm;                   // columns per chunk, warm-up before it
+  int32_t nchunks, strips;
+  uint32_t *maxcol;                      // [Lr]
+  uint64_t *fwords, *rwords;             // hand-over words of several strips, cleared by the staging
+  int64_t fstride, rcount;               // words per chunk; words of the reversed pass
+  uint32_t flags;
+  int32_t mask_len;
+  TbArgs tb;
+  PairState *state;
+  uint8_t *dir;
+  int32_t *bnd;
+  PairOut *out;
+};
+int pair_waves(int strips, int n);
+hipError_t pair_stage(const PairArgs &a, hipStream_t st);
+hipError_t pair_forward(const PairArgs &a, hipStream_t st);
+hipError_t pair_rest(const PairArgs &a, hipStream_t st);
+
 size_t intra_lds_bytes(int n, int RL);
 int intra_slices();
 hipError_t intra_fill(const IntraArgs &a, int RL, int waves, bool rev, hipStream_t st);
@@ -357,8 +396,6 @@ struct FillSet {
 };
 hipError_t fill_set(const FillSet &f, hipStream_t st);
 // pair 0's CIGAR words and final offsets {0, length} (one-pair calls)
-hipError_t cigar_one(const uint32_t *src, const int64_t *src_off, const int32_t *len,
-                     int64_t *dst_off, uint32_t *dst, hipStream_t st);
 // cls: the traceback classes (pairs of class kTbFlat hold no scratch words:
 // their one word is made from qbeg and qend)
 hipError_t launch_cigar_compact(int64_t npairs, const uint32_t *src, const int64_t *src_off,

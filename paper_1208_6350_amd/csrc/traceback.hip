@@ -20,6 +20,7 @@
 
 #include <algorithm>
 
+#include "intra_strips.h"
 #include "swx_internal.h"
 #include "swx_kernels.h"
 
@@ -1805,29 +1806,195 @@ hipError_t tb_wave(const TbArgs &a, const TbWaveJob *jobs, int64_t njobs, int RL
   return hipGetLastError();
 }
 
-// The wave job of pair 0 of a one-pair graph, planned on the device: the
-// rectangle and safe band of its alignment, codes and hand-over rows at the
-// start of their buffers (m = 0: no alignment, nothing to trace), and its
-// CIGAR scratch at offset 0.
-__global__ void k_tb_wave_job1(TbArgs a, TbWaveJob *job, int64_t *cig_off) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  TbWaveJob jb{};
-  jb.pair = 0;
-  if (a.score[0] > 0) {
-    if (tb_coords_ok(a, 0)) {
-      jb.m = a.qend[0] - a.qbeg[0] + 1;
-      jb.w = a.rend[0] - a.rbeg[0] + 1;
-      safe_band(jb.m, jb.w, a.score[0], a.smax, a.o, a.e, &jb.dlo, &jb.bw);
-    } else {
-      a.err[0] = 1;
+// ---- the one-pair call: everything after the forward pass -----------------------
+// One workgroup: the end from the max array, the reversed pass, score2, the
+// banded pass and its walk, and the record and CIGAR into pinned host memory.
+// Bound by the two strip chains and the walk; as separate kernels in a graph
+// these steps took fifteen launches of 4.6 us each beside them, and four
+// copies to the host.  Measured, the whole call: 150 x 2,000 318 -> 153 us,
+// 300 x 350 amino acids 426 -> 208, 1,000 x 2,000 1,553 -> 802.
+template <bool HO>
+__global__ __launch_bounds__(64 * kPairWaves) void k_pair_rest(PairArgs a) {
+  constexpr int RL = kPairRows;
+  constexpr int SH = 64 * RL;
+  const int NW = (int)(blockDim.x >> 6);
+  extern __shared__ uint4 s_dyn[];
+  __shared__ uint4 s_tile[kTbPairTile / 16];
+  __shared__ int8_t s_mat[32 * 32];
+  __shared__ int32_t s_prog[kPairWaves], s_done[kPairWaves], s_rrow[kPairWaves], s_v[kPairWaves];
+  __shared__ int64_t s_rcol[kPairWaves], s_j[kPairWaves];
+  __shared__ unsigned long long s_best;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  for (int k = threadIdx.x; k < a.n * a.n; k += blockDim.x) s_mat[k] = a.m[k];
+  if (threadIdx.x < kPairWaves) {
+    s_done[threadIdx.x] = 0;
+    s_rcol[threadIdx.x] = -1;
+    s_rrow[threadIdx.x] = -1;
+  }
+  if (threadIdx.x == 0) s_best = ~0ull;
+
+  // largest value, then smallest column, outside columns [lo, hi]
+  auto best_column = [&](int64_t lo, int64_t hi, int32_t &bv, int64_t &bj) {
+    bv = 0;
+    bj = INT64_MAX;
+#pragma unroll 4
+    for (int64_t j = threadIdx.x; j < a.Lr; j += blockDim.x) {
+      const int32_t v = (int32_t)(a.maxcol[j] >> a.kb);
+      if ((j < lo || j > hi) && v > bv) { bv = v; bj = j; }
+    }
+    auto better = [&](int32_t v, int64_t j) {
+      if (v > bv || (v == bv && j < bj)) { bv = v; bj = j; }
+    };
+    for (int off = 32; off >= 1; off >>= 1) {
+      const int32_t v = __shfl_xor(bv, off, 64);
+      const int64_t j = __shfl_xor(bj, off, 64);
+      better(v, j);
+    }
+    __syncthreads();   // (the slots may still be read from the last time)
+    if (lane == 0) {
+      s_v[wave] = bv;
+      s_j[wave] = bj;
+    }
+    __syncthreads();
+    for (int w = 0; w < NW; ++w) better(s_v[w], s_j[w]);
+  };
+
+  swx_rec_dev rec;
+  rec.score1 = rec.score2 = 0;
+  rec.read_begin1 = rec.read_end1 = -1;
+  rec.ref_begin1 = rec.ref_end1 = rec.ref_end2 = -1;
+  rec.cigar_off = 0;
+  rec.cigar_len = 0;
+  rec.lane_bits = 32;
+  int32_t s1;
+  int64_t je;
+  best_column(1, 0, s1, je);
+  bool err = false;
+  if (s1 > 0) {
+    const uint32_t M = (1u << a.kb) - 1u;
+    const int32_t ie = (int32_t)(M - (a.maxcol[je] & M)) - (a.strips * SH - a.Lq);
+    rec.score1 = s1;
+    rec.read_end1 = ie;
+    rec.ref_end1 = je;
+    err = ie < 0 || ie >= a.Lq;
+    if ((a.flags & 1u) && !err) {
+      // the drift band of the reversed pass (see k_rev_prepare)
+      int32_t band = -1;
+      if (a.e > 0) {
+        const int64_t rows = (int64_t)ie + 1, cols = je + 1;
+        const int64_t base = -(int64_t)a.o + a.e - s1;
+        auto drift = [](int64_t num, int64_t den) {
+          const int64_t g = num / den;
+          return g < 0 ? (int64_t)0 : (g > (1 << 30) ? int64_t(1) << 30 : g);
+        };
+        const int64_t g = drift((int64_t)a.smax * (rows < cols ? rows : cols) + base, a.e);
+        int64_t gq = drift((int64_t)a.smax * rows + base, (int64_t)a.smax + a.e);
+        int64_t gr = drift((int64_t)a.smax * cols + base, (int64_t)a.smax + a.e);
+        gq = gq < g ? gq : g;
+        gr = gr < g ? gr : g;
+        band = (int32_t)(gq > gr ? gq : gr);
+      }
+      StripJob x{};
+      x.qs = a.q;
+      x.rs = a.r;
+      x.Lq = ie + 1;
+      x.rv = true;
+      x.Lr = je + 1;
+      x.c1 = je + 1;
+      x.band = band;
+      x.kb = a.kb;
+      x.tgt = s1;
+      x.rows = a.rwords;
+      x.done = s_done;
+      x.rcol = s_rcol;
+      x.rrow = s_rrow;
+      x.best = &s_best;
+      const StripScoring sc{a.n, (uint32_t)a.bias, (uint32_t)a.o, (uint32_t)a.e};
+      uint8_t *s_prof = reinterpret_cast<uint8_t *>(s_dyn) + (size_t)wave * (a.n + 1) * 64 * RL;
+      if (x.Lq <= SH) {
+        if (wave == 0) strip_alone<RL, true, HO>(x, sc, s_mat, s_prof);
+      } else if (strips_of_wave<RL, true, HO>(x, sc, s_mat, s_prof, wave, NW) && lane == 0) {
+        a.out->err = 1;
+      }
+      __syncthreads();
+      int64_t bc = -1;   // first column reaching score1; on a tie the earlier strip
+      int32_t br = -1;
+      for (int s = 0; s < kPairWaves; ++s)
+        if (s_rcol[s] >= 0 && (bc < 0 || s_rcol[s] < bc)) { bc = s_rcol[s]; br = s_rrow[s]; }
+      rec.read_begin1 = ie - br;
+      rec.ref_begin1 = je - bc;
+      err = bc < 0 || br < 0 || br > ie;
+    }
+    if ((a.flags & 4u) && !err) {
+      int64_t mask = a.mask_len;
+      if (mask < 0) { mask = a.Lq / 2; if (mask < 15) mask = 15; }
+      int64_t j2;
+      best_column(rec.ref_begin1 - mask, je + mask, rec.score2, j2);
+      rec.ref_end2 = rec.score2 > 0 ? j2 : -1;
+    }
+    if ((a.flags & 2u) && !err) {
+      TbWaveJob jb{};
+      jb.m = rec.read_end1 - rec.read_begin1 + 1;
+      jb.w = rec.ref_end1 - rec.ref_begin1 + 1;
+      uint32_t *cigar = reinterpret_cast<uint32_t *>(a.out + 1);
+      bool flat = false;
+      if (jb.m == jb.w) {   // kTbFlat: the main diagonal alone scores score1
+        int32_t sum = 0;
+        for (int64_t k = threadIdx.x; k < jb.m; k += blockDim.x)
+          sum += s_mat[a.q[rec.read_begin1 + k] * a.n + a.r[rec.ref_begin1 + k]];
+        for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, 64);
+        __syncthreads();
+        if (lane == 0) s_v[wave] = sum;
+        __syncthreads();
+        sum = 0;
+        for (int w = 0; w < NW; ++w) sum += s_v[w];
+        flat = sum == s1;
+      }
+      if (flat) {
+        rec.cigar_len = 1;
+        if (threadIdx.x == 0) cigar[0] = (uint32_t)jb.m << 4;
+      } else {
+        safe_band(jb.m, jb.w, s1, a.smax, a.o, a.e, &jb.dlo, &jb.bw);
+        if (threadIdx.x == 0) {
+          PairState &y = *a.state;
+          y.qstart = y.rstart = y.cig_off = 0;
+          y.rbeg = rec.ref_begin1;
+          y.rend = rec.ref_end1;
+          y.rlen = a.Lr;
+          y.score = s1;
+          y.qbeg = rec.read_begin1;
+          y.qend = rec.read_end1;
+          y.qlen = a.Lq;
+          y.cig_len = 0;
+          y.err = 0;
+        }
+        __threadfence_block();
+        __syncthreads();
+        tb_wave_fill<RL>(a.tb, jb, s_prog, s_done, s_mat, reinterpret_cast<int8_t *>(s_dyn), a.dir,
+                         a.bnd);
+        __syncthreads();
+        if (wave == 0) tb_wave_walk<RL, kTbPairTile>(a.tb, jb, a.dir, s_tile, lane);
+        __threadfence_block();
+        __syncthreads();
+        rec.cigar_len = a.state->cig_len;
+        err = a.state->err != 0;
+        for (int32_t k = threadIdx.x; k < rec.cigar_len; k += blockDim.x) cigar[k] = a.tb.cig[k];
+      }
     }
   }
-  *job = jb;
-  cig_off[0] = 0;
+  if (threadIdx.x == 0) {
+    a.out->rec = rec;
+    if (err) a.out->err = 1;
+  }
 }
 
-hipError_t tb_wave_job1(const TbArgs &a, TbWaveJob *job, int64_t *cig_off, hipStream_t st) {
-  hipLaunchKernelGGL(k_tb_wave_job1, dim3(1), dim3(64), 0, st, a, job, cig_off);
+hipError_t pair_rest(const PairArgs &a, hipStream_t st) {
+  // (four waves at least: they scan the max array together)
+  const int waves = std::max(pair_waves(a.strips, a.n), 4);
+  const dim3 b(64 * waves);
+  const size_t lds = (size_t)(a.n + 1) * 64 * kPairRows * waves;
+  if (a.bias == a.o) hipLaunchKernelGGL(k_pair_rest<true>, dim3(1), b, lds, st, a);
+  else hipLaunchKernelGGL(k_pair_rest<false>, dim3(1), b, lds, st, a);
   return hipGetLastError();
 }
 
