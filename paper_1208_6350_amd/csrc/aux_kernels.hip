@@ -436,32 +436,46 @@ __global__ void k_validate(ValidateArgs a) {
 }
 
 // ---- small helpers ------------------------------------------------------------
-// stats[0] = max over pairs of min(qlen, rlen); stats[1] = sum of qlen * rlen
+// stats[0] = max over pairs of min(qlen, rlen); [1] = sum of qlen * rlen;
+// [2], [3] = longest query, reference; [4] = sum of rlen
 __global__ void k_pair_stats(int64_t n, const int32_t *qlen, const int64_t *rlen, int64_t *stats) {
-  int64_t best = 0, cells = 0;
+  int64_t v[5] = {0, 0, 0, 0, 0};
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n; p += stride) {
-    const int64_t m = qlen[p] < rlen[p] ? qlen[p] : rlen[p];
-    best = m > best ? m : best;
-    cells += (int64_t)qlen[p] * rlen[p];
+    const int64_t q = qlen[p], r = rlen[p];
+    const int64_t m = q < r ? q : r;
+    v[0] = m > v[0] ? m : v[0];
+    v[1] += q * r;
+    v[2] = q > v[2] ? q : v[2];
+    v[3] = r > v[3] ? r : v[3];
+    v[4] += r;
   }
+  auto merge = [&](const int64_t *o) {
+    v[0] = o[0] > v[0] ? o[0] : v[0];
+    v[1] += o[1];
+    v[2] = o[2] > v[2] ? o[2] : v[2];
+    v[3] = o[3] > v[3] ? o[3] : v[3];
+    v[4] += o[4];
+  };
   for (int off = 32; off >= 1; off >>= 1) {
-    const int64_t o = __shfl_xor(best, off, 64);
-    best = o > best ? o : best;
-    cells += __shfl_xor(cells, off, 64);
+    int64_t o[5];
+    for (int k = 0; k < 5; ++k) o[k] = __shfl_xor(v[k], off, 64);
+    merge(o);
   }
-  // one pair of atomics per block, not per wave: they all meet at two words
-  __shared__ int64_t s_best[4], s_cells[4];
+  // one set of atomics per block, not per wave: they all meet at five words
+  __shared__ int64_t s_v[4][5];
   const int wv = (int)(threadIdx.x >> 6);
-  if ((threadIdx.x & 63) == 0) { s_best[wv] = best; s_cells[wv] = cells; }
+  if ((threadIdx.x & 63) == 0)
+    for (int k = 0; k < 5; ++k) s_v[wv][k] = v[k];
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int k = 1; k < (int)(blockDim.x >> 6); ++k) {
-      best = s_best[k] > best ? s_best[k] : best;
-      cells += s_cells[k];
+    for (int k = 1; k < (int)(blockDim.x >> 6); ++k) merge(s_v[k]);
+    for (int k = 0; k < 5; ++k) {
+      unsigned long long *at = (unsigned long long *)&stats[k];
+      if (v[k] <= 0) continue;
+      if (k == 1 || k == 4) atomicAdd(at, (unsigned long long)v[k]);
+      else atomicMax(at, (unsigned long long)v[k]);
     }
-    if (best > 0) atomicMax((unsigned long long *)&stats[0], (unsigned long long)best);
-    if (cells > 0) atomicAdd((unsigned long long *)&stats[1], (unsigned long long)cells);
   }
 }
 

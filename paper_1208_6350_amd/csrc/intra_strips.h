@@ -96,6 +96,7 @@ struct StripJob {
   int64_t *rcol;               // reversed pass: first column of strip s reaching the target (-1)
   int32_t *rrow;               // ... and its padded row
   unsigned long long *best;    // ... smallest such column so far (~0: none)
+  int32_t row0;                // one strip: padded row of the strip's first row in the row code
 };
 struct StripScoring {
   int n;
@@ -352,8 +353,10 @@ __device__ __forceinline__ bool strips_of_wave(const StripJob &x, const StripSco
 // Nothing is handed over, so no row enters lane 0 and only the column maxima
 // leave lane 63; padding rows stand on top in both directions, and the lanes
 // that hold nothing else are skipped: the reference symbols enter at the first
-// lane with a row.  Every owned column is this wave's alone: its max array
-// words are stored, not merged.  Bound by instruction issue of one wave (about
+// lane with a row.  The row code counts padded rows from x.row0 on, so that
+// strips of different heights can share one coding (64 * RL + x.row0 rows).
+// Every owned column is this wave's alone: its max array words are stored, not
+// merged.  Bound by instruction issue of one wave (about
 // 48 per step and four rows; the sweep for several strips 73).  Reversed:
 // *rcol, *rrow (query row) of the first column reaching the target, or -1.
 template <int RL, bool REV, bool HO>
@@ -365,9 +368,9 @@ __device__ __forceinline__ void strip_alone(const StripJob &x, const StripScorin
   using T = VT<uint32_t>;
   const int lane = threadIdx.x & 63;
   const int qpad = SH - x.Lq;
-  const int f = qpad / RL;   // the first lane with a row of the query
+  const int f = qpad < SH ? qpad / RL : 63;   // the first lane with a row of the query
   const uint32_t M = (1u << x.kb) - 1u;
-  const uint32_t DL = M - (uint32_t)(lane * RL + RL - 1);
+  const uint32_t DL = M - (uint32_t)(x.row0 + lane * RL + RL - 1);
   const int64_t clo = x.cw;
   int64_t chi = x.c1;
   if (REV && x.band >= 0 && (int64_t)x.Lq + x.band < chi) chi = (int64_t)x.Lq + x.band;
@@ -441,12 +444,117 @@ __device__ __forceinline__ void strip_alone(const StripJob &x, const StripScorin
         const int hl = __builtin_ctzll(hit);
         if (lane == hl) {
           *x.rcol = c;
-          *x.rrow = (int32_t)(M - (obC & M)) - qpad;
+          *x.rrow = (int32_t)(M - (obC & M)) - qpad - x.row0;
         }
         break;
       }
     } else {
       if (mine && c >= x.c0) x.mc[c] = obC;
+    }
+  }
+}
+
+// ---- one strip of two pairs on packed 16-bit lanes -------------------------------
+// The forward sweep of strip_alone for two pairs (A in the low halves, B in
+// the high ones; B may be absent: width 0) whose scores stay below 2^15: one
+// packed instruction updates a cell of each.  Row-code bits 16.  M3: every
+// lane value stays below 0x7C00, so H is one packed three-way maximum; HO: the
+// bias is the gap open penalty.  s_profA, s_profB: a profile each.
+template <int RL, bool M3, bool HO>
+__device__ __forceinline__ void strip_alone16(const StripJob &x, const StripJob &y,
+                                              const StripScoring &sc, const int8_t *s_mat,
+                                              uint8_t *s_profA, uint8_t *s_profB) {
+  constexpr int SH = 64 * RL;
+  constexpr int kUnroll = RL <= 4 ? kSpreadBlock : 4;
+  using T = VT<u16x2>;
+  const int lane = threadIdx.x & 63;
+  const int qpadA = SH - x.Lq, qpadB = SH - y.Lq;
+  const int qpad = qpadA < qpadB ? qpadA : qpadB;
+  const int f = qpad < SH ? qpad / RL : 63;   // the first lane with a row of either
+  const uint32_t DL = 65535u - (uint32_t)(x.row0 + lane * RL + RL - 1);
+  const int64_t wA = x.c1 - x.cw, wB = y.c1 - y.cw;
+  const int64_t width = wA > wB ? wA : wB;
+  strip_profile<RL>(x, sc, s_mat, s_profA, lane * RL - qpadA);
+  strip_profile<RL>(y, sc, s_mat, s_profB, lane * RL - qpadB);
+  lds_wave_sync();
+  // both pairs' symbols of step offsets [o0, o0 + 16), A in the low byte
+  const int8_t *ra = x.rs + x.cw, *rb = y.rs + y.cw;
+  auto symbols = [&](int64_t o0) -> uint32_t {
+    const int64_t off = o0 + lane;
+    const uint32_t a = lane < kSpreadBlock && off < wA ? (uint32_t)(uint8_t)ra[off] : (uint32_t)sc.n;
+    const uint32_t b = lane < kSpreadBlock && off < wB ? (uint32_t)(uint8_t)rb[off] : (uint32_t)sc.n;
+    return a | (b << 8);
+  };
+  const bool enter = lane == f;
+  const u16x2 vbias = T::splat(sc.bias), vo = T::splat(sc.o), ve = T::splat(sc.e);
+  const uint32_t selA = 0x05040100u, selB = 0x07060100u;   // a half of H above a 16-bit code
+  const uint32_t none = (uint32_t)sc.n * 0x101u;
+  u16x2 H[RL], E[RL];
+#pragma unroll
+  for (int r = 0; r < RL; ++r) { H[r] = T::zero(); E[r] = T::zero(); }
+  u16x2 hup_prev = T::zero(), hout = T::zero(), fout = T::zero();
+  uint32_t cmoutA = 0u, cmoutB = 0u, obA = 0u, obB = 0u;
+  const uint32_t first = lane_value(symbols(0), 0);
+  uint32_t sym = enter ? first : none;
+  uint32_t XA[RL / 4], XB[RL / 4];
+  lds_load_words<RL>(s_profA + ((int64_t)(sym & 0xFFu) * 64 + lane) * RL, XA);
+  lds_load_words<RL>(s_profB + ((int64_t)((sym >> 8) & 0xFFu) * 64 + lane) * RL, XB);
+  uint32_t symnext = symbols(1);
+  const int64_t nsteps = width + 63 - f;
+#pragma unroll 1
+  for (int64_t t0 = 0; t0 < nsteps; t0 += kSpreadBlock) {
+    const uint32_t symbuf = symnext;
+    symnext = symbols(t0 + kSpreadBlock + 1);
+#pragma unroll kUnroll
+    for (int tm = 0; tm < kSpreadBlock; ++tm) {
+      const u16x2 hup = T::from(from_above(T::bits(hout), 0u));
+      u16x2 F = T::from(from_above(T::bits(fout), 0u));
+      const uint32_t cminA = from_above(cmoutA, 0u), cminB = from_above(cmoutB, 0u);
+      const uint32_t snew = lane_value(symbuf, tm);
+      const uint32_t sdown = from_above(sym, none);
+      const uint32_t symn = enter ? snew : sdown;
+      uint32_t XnA[RL / 4], XnB[RL / 4];
+      lds_load_words<RL>(s_profA + ((int64_t)(symn & 0xFFu) * 64 + lane) * RL, XnA);
+      lds_load_words<RL>(s_profB + ((int64_t)((symn >> 8) & 0xFFu) * 64 + lane) * RL, XnB);
+      uint32_t cmA = 0u, cmB = 0u;
+      auto score_of = [&](int r) -> u16x2 { return T::from(perm(XB[r >> 2], XA[r >> 2], T::sel_const(r & 3))); };
+      u16x2 u_next = M3 ? T::add(hup_prev, score_of(0)) : T::max(T::add(hup_prev, score_of(0)), E[0]);
+#pragma unroll
+      for (int r = 0; r < RL; ++r) {
+        const u16x2 u = u_next;
+        if (r + 1 < RL) {
+          u_next = T::add(H[r], score_of(r + 1));
+          if constexpr (!M3) u_next = T::max(u_next, E[r + 1]);
+        }
+        u16x2 hb;
+        if constexpr (M3) hb = T::max3(u, E[r], F);
+        else hb = T::max(u, F);
+        const u16x2 hn = T::subs(hb, vbias);
+        H[r] = hn;
+        const uint32_t kc = (uint32_t)(RL - 1 - r);
+        const uint32_t wa = perm(T::bits(hn), kc, selA), wb = perm(T::bits(hn), kc, selB);
+        cmA = cmA > wa ? cmA : wa;
+        cmB = cmB > wb ? cmB : wb;
+        const u16x2 ho = HO ? hn : T::subs(hb, vo);
+        E[r] = T::max(T::subs(E[r], ve), ho);
+        F = T::max(T::subs(F, ve), ho);
+      }
+      hup_prev = hup;
+      hout = H[RL - 1];
+      fout = F;
+      const uint32_t cmlA = cmA + DL, cmlB = cmB + DL;
+      cmoutA = cminA > cmlA ? cminA : cmlA;
+      cmoutB = cminB > cmlB ? cminB : cmlB;
+      sym = symn;
+#pragma unroll
+      for (int k = 0; k < RL / 4; ++k) { XA[k] = XnA[k]; XB[k] = XnB[k]; }
+      obA = shift_in(obA, cmoutA);
+      obB = shift_in(obB, cmoutB);
+    }
+    const int64_t off = t0 + kSpreadBlock - 1 - (63 - f) - 63 + lane;
+    if (lane >= 64 - kSpreadBlock && off >= 0) {
+      if (off < wA && x.cw + off >= x.c0) x.mc[x.cw + off] = obA;
+      if (off < wB && y.cw + off >= y.c0) y.mc[y.cw + off] = obB;
     }
   }
 }

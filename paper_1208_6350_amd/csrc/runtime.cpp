@@ -642,11 +642,12 @@ static TbShape tb_wave_shape(int64_t m, int64_t w, int64_t bw, int n, int64_t jo
 // reads (0.2 GB) 1.51 / 0.56 / 1.16 ms, 20,000 (0.4 GB) 1.57 / 0.86 / 1.22,
 // 50,000 (1 GB, 0.15 wide) 1.52 / 1.66 / 1.35, 100,000 (0.3 wide) 1.77 / 2.94
 // / 1.60, 200,000 (0.6 wide) 1.83 / 5.53 / 2.16.  Batches of at most
-// kTbPairsAll pairs skip the sort too.  The call that allocates nothing keeps
+// kTbPairsAll pairs are not sorted either, unless the sizes turn out larger
+// than kTbPairsBytes (then after the read that tells).  The call that allocates nothing keeps
 // the per-lane kernels, whose scratch is a few times smaller.
-static constexpr int64_t kTbPairsAll = 4096, kTbPairsMax = int64_t(1) << 18;
+static constexpr int64_t kTbPairsAll = 32768, kTbPairsMax = int64_t(1) << 18;
 static constexpr int64_t kTbPairsBytes = int64_t(600) << 20, kTbWideBytes = int64_t(384) << 20;
-static constexpr int64_t kTbGraphBytes = int64_t(1) << 30;   // of a graph (fixed, worst case)
+static constexpr int64_t kTbGraphPairs = 4096, kTbGraphBytes = int64_t(1) << 30;   // of a graph (fixed, worst case)
 
 // max_rows: most rows of a pair (the shape of the launch, no limit)
 static int run_traceback(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, int64_t np,
@@ -972,7 +973,14 @@ static int split_pairs(swx_ctx *ctx, int64_t np, const int32_t *qlen, const int6
   if ((rc = select_flagged(ctx, fl, np, &lp.d_long, &lp.nlong))) return rc;
   lp.nshort = np - lp.nlong;
   if (lp.nlong == 0) return SWX_OK;
-  if ((rc = select_flagged(ctx, fs, np, &lp.d_short, &lp.nshort))) return rc;
+  const int64_t *nshort = nullptr;
+  return lp.nshort > 0 ? select_flagged_dev(ctx, fs, np, &lp.d_short, &nshort) : SWX_OK;
+}
+
+// the long pairs' ids and lengths on the host
+static int read_long(swx_ctx *ctx, const int32_t *qlen, const int64_t *rlen, LongPath &lp) {
+  if (!lp.ids.empty()) return SWX_OK;
+  int rc;
   lp.ids.resize(lp.nlong);
   if ((rc = read_i64(ctx, lp.d_long, lp.ids.data(), lp.nlong))) return rc;
   return gather_info(ctx, lp.nlong, lp.d_long, qlen, rlen, nullptr, nullptr, nullptr, nullptr,
@@ -1246,43 +1254,173 @@ static int launch_intra_jobs(swx_ctx *ctx, const IntraGroups &groups, IntraArgs 
 
 // Forward pass of the long pairs: column chunks with a warm-up overlap, the
 // encoded max array per pair, then the end (T1) of each pair.
+static int64_t long_rlen(const LongPath &lp) {
+  int64_t total = 0;
+  for (int64_t k = 0; k < lp.nlong; ++k) total += std::max<int64_t>(lp.info[6 * k + 1], 1);
+  return total;
+}
+
+// Packed 16-bit lanes run two chunks per wave, with half the waves per
+// workgroup (two profiles each in LDS), on twice the chunk target. Chosen
+// automatically only when those waves still cover every SIMD of the device:
+// a few long pairs in few chunks finish sooner on 32-bit lanes.
+static bool choose16(const swx_ctx *ctx, const Scoring &sc, const LongPath &lp) {
+  if (ctx->intra_bits != 0) return ctx->intra_bits == 16;
+  const int64_t total_r = long_rlen(lp);
+  std::map<std::pair<int, int64_t>, int64_t> count;
+  for (int64_t k = 0; k < lp.nlong; ++k) {
+    const int64_t Lq = lp.info[6 * k], Lr = lp.info[6 * k + 1];
+    const int RL = pick_rl(Lq, sc.n);
+    if (Lr == 0 || !intra_fits16(sc, Lq, Lr, RL)) continue;
+    const int64_t C = intra_chunk(sc, Lq, Lr, 2 * ctx->intra_jobs, total_r);
+    count[{RL, round_up(Lq, 64 * RL) / (64 * RL)}] += (Lr + C - 1) / C;
+  }
+  int64_t waves = 0;
+  for (const auto &kv : count)
+    waves += (kv.second + 1) / 2 * intra_waves16(kv.first.second, sc.n, kv.first.first);
+  return waves >= kIntra16MinWavesPerCu * (int64_t)ctx->cus;
+}
+
+// ---- short queries of the long-pair path (AloneArgs) -------------------------
+// The long pairs of a batch whose queries have at most kAloneMaxQ rows and
+// whose references at most kAloneMaxR columns, each on a wave (or half a
+// wave's 16-bit lanes) over its whole reference.
+struct AlonePath {
+  bool on = false, all = false;   // all: the batched passes are empty
+  int64_t *ids = nullptr;         // (null: every pair in turn)
+  int64_t count = 0, n32 = 0;     // the first n32 on 32-bit lanes
+  uint32_t *maxcol = nullptr;
+  int64_t stride = 0;
+  int32_t max_q = 0;
+};
+// References above kAloneSweep columns keep the chunks of the general path
+// until there is a job per pair anyway.
+static constexpr int64_t kAloneMaxR = 8192, kAloneSweep = 1024;
+// Where no score of a batch can saturate the batched pass's 16-bit lanes, its
+// short pairs go the same way, on 16-bit lanes too, up to this many pairs in
+// all (score only, with the reversed pass): nothing is batched then, so there
+// is no plan to build and read back, no pack, and no fill with a few tasks.
+// Measured, whole call, long ones alone / all alone / all batched: 20,000
+// reads 3.04 / 2.06 / 3.57 ms, 30,000 3.74 / 2.79 / 3.87, 50,000 4.31 / 4.07 /
+// 4.29, 60,000 4.52 / 4.54 / 4.53 (forward pass alone 1.41 / 1.81 / 1.42,
+// even at 33,000; reversed 1.15 / 1.07 / 1.16); the 4,950 overlaps of 100
+// reads of 70 (none long) 0.98 / 0.50 / 0.98, 19,900 of 200 1.17 / 0.81 / 1.17.
+static constexpr int64_t kAlonePairs = 32768, kAlonePairsRev = 49152;
+
+static int plan_alone(swx_ctx *ctx, const Scoring &sc, int64_t np, uint32_t flags, const int64_t *stats,
+                      const int32_t *qlen, const int64_t *rlen, LongPath &lp, AlonePath &al) {
+  DevArena &A = ctx->arena;
+  const int64_t max_q = stats[2], max_r = stats[3], sum_r = stats[4];
+  const int64_t bound = (int64_t)std::max(sc.smax, 0) * stats[0];
+  if (A.fixed() || max_q > kAloneMaxQ || max_r > kAloneMaxR) return SWX_OK;
+  if (max_r > kAloneSweep && lp.nlong < 2 * ctx->intra_jobs) return SWX_OK;
+  // (a threshold set by the caller says itself which pairs are batched)
+  const bool all = lp.nshort == 0 || (ctx->long_cells < 0 && bound < kInter16Limit &&
+                                      np <= ((flags & SWX_BEGIN) ? kAlonePairsRev : kAlonePairs));
+  if (lp.nlong == 0 && !all) return SWX_OK;
+  if (bound + sc.bias > 32766) return SWX_OK;          // (16-bit lanes, 16 code bits)
+  if (np * max_r > 4 * sum_r + (int64_t(1) << 20)) return SWX_OK;   // fixed strides: few skewed pairs
+  // the lanes that the general path takes: by the number of its chunks, of
+  // which a pair has at least one and at most one per 256 columns
+  int rc;
+  bool w16 = ctx->intra_bits == 16;
+  if (ctx->intra_bits == 0) {
+    const int64_t need = 2 * kIntra16MinWavesPerCu * (int64_t)ctx->cus;
+    w16 = lp.nlong >= need;
+    if (!w16 && lp.nlong * ((max_r + 255) / 256) + 2 >= need) {
+      if ((rc = read_long(ctx, qlen, rlen, lp))) return rc;
+      w16 = choose16(ctx, sc, lp);
+    }
+  }
+  al.on = true;
+  al.all = all;
+  al.count = al.all ? np : lp.nlong;
+  al.n32 = w16 ? 0 : lp.nlong;
+  al.stride = max_r;
+  al.max_q = (int32_t)max_q;
+  al.maxcol = A.get<uint32_t>(al.count * max_r);
+  if (!al.maxcol) return fail(SWX_ENOMEM, "device pool exhausted (max array)");
+  if (!al.all) {
+    al.ids = lp.d_long;
+  } else if (lp.nlong > 0 && lp.nshort > 0 && !w16) {   // the long pairs first
+    al.ids = A.get<int64_t>(np);
+    if (!al.ids) return fail(SWX_ENOMEM, "device pool exhausted (pair list)");
+    HIP_TRY(hipMemcpyAsync(al.ids, lp.d_long, 8 * lp.nlong, hipMemcpyDeviceToDevice, ctx->stream));
+    HIP_TRY(hipMemcpyAsync(al.ids + lp.nlong, lp.d_short, 8 * lp.nshort, hipMemcpyDeviceToDevice,
+                           ctx->stream));
+  }
+  if (al.all) {   // none is left to batch
+    lp.nshort = 0;
+    lp.nlong = np;
+  }
+  return SWX_OK;
+}
+
+static AloneArgs alone_args(const Scoring &sc, const AlonePath &al, const PairView &view,
+                            const FillOut &out) {
+  AloneArgs a{};
+  a.ids = al.ids;
+  a.count = al.count;
+  a.view = view;
+  a.matrix = sc.dmat;
+  a.n = sc.n; a.o = sc.o; a.e = sc.e; a.bias = sc.bias;
+  a.max_q = al.max_q;
+  a.maxcol = al.maxcol;
+  a.stride = al.stride;
+  a.out = out;
+  return a;
+}
+
+static IntraPairArgs alone_pairs(const AlonePath &al, const int32_t *qlen, const int64_t *rlen) {
+  IntraPairArgs e{};
+  e.ids = al.ids;
+  e.stride = al.stride;
+  e.maxcol = al.maxcol;
+  e.qlen = qlen;
+  e.rlen = rlen;
+  e.max_rlen = al.stride;
+  return e;
+}
+
+static int run_alone_forward(swx_ctx *ctx, const Scoring &sc, const AlonePath &al, int64_t bound,
+                             const PairView &view, const FillOut &out, uint8_t *lanebits) {
+  AloneArgs a = alone_args(sc, al, view, out);
+  if (al.n32 > 0) {
+    AloneArgs w = a;
+    w.count = al.n32;
+    w.lanebits = lanebits;
+    HIP_TRY(alone_forward(w, ctx->stream));
+  }
+  if (al.count > al.n32) {
+    if (al.n32 > 0) a.ids += al.n32;   // (a list, then)
+    a.maxcol += al.n32 * al.stride;
+    a.count -= al.n32;
+    HIP_TRY(alone_forward16(a, bound + sc.bias <= kMax3Lane, ctx->stream));
+  }
+  IntraPairArgs e = alone_pairs(al, view.qlen, view.rlen);
+  e.score = out.score; e.qend = out.qend; e.rend = out.rend; e.overflow = out.overflow;
+  HIP_TRY(intra_end(e, al.count, ctx->stream));
+  return SWX_OK;
+}
+
 static int run_intra_forward(swx_ctx *ctx, const Scoring &sc, LongPath &lp, const PairView &view,
                              const FillOut &out, uint8_t *err, uint8_t *lanebits) {
   DevArena &A = ctx->arena;
-  int64_t total_r = 0;
-  for (int64_t k = 0; k < lp.nlong; ++k) {
-    total_r += std::max<int64_t>(lp.info[6 * k + 1], 1);
-    lp.max_rlen = std::max(lp.max_rlen, lp.info[6 * k + 1]);
-  }
+  int rc;
+  if ((rc = read_long(ctx, view.qlen, view.rlen, lp))) return rc;
+  const int64_t total_r = long_rlen(lp);
+  for (int64_t k = 0; k < lp.nlong; ++k) lp.max_rlen = std::max(lp.max_rlen, lp.info[6 * k + 1]);
   Jobs16 jobs16;
   std::vector<int64_t> ids16, ids32;
   lp.pairs.clear();
-  // Packed 16-bit lanes run two chunks per wave, with half the waves per
-  // workgroup (two profiles each in LDS), on twice the chunk target. Chosen
-  // automatically only when those waves still cover every SIMD of the device:
-  // a few long pairs in few chunks finish sooner on 32-bit lanes.
-  bool auto16 = false;
-  if (ctx->intra_bits == 0) {
-    std::map<std::pair<int, int64_t>, int64_t> count;
-    for (int64_t k = 0; k < lp.nlong; ++k) {
-      const int64_t Lq = lp.info[6 * k], Lr = lp.info[6 * k + 1];
-      const int RL = pick_rl(Lq, sc.n);
-      if (Lr == 0 || !intra_fits16(sc, Lq, Lr, RL)) continue;
-      const int64_t C = intra_chunk(sc, Lq, Lr, 2 * ctx->intra_jobs, total_r);
-      count[{RL, round_up(Lq, 64 * RL) / (64 * RL)}] += (Lr + C - 1) / C;
-    }
-    int64_t waves = 0;
-    for (const auto &kv : count)
-      waves += (kv.second + 1) / 2 * intra_waves16(kv.first.second, sc.n, kv.first.first);
-    auto16 = waves >= kIntra16MinWavesPerCu * (int64_t)ctx->cus;
-  }
+  const bool auto16 = choose16(ctx, sc, lp);
   // lanes of each pair, and the 32-bit jobs that will share the device
   std::vector<uint8_t> is16(lp.nlong);
   std::vector<int64_t> k16, k32;
   int64_t jobs32 = 0, r16 = 0, r32 = 0;
   for (int64_t k = 0; k < lp.nlong; ++k) {
     const int64_t Lq = lp.info[6 * k], Lr = lp.info[6 * k + 1];
-    is16[k] = (ctx->intra_bits == 16 || auto16) && intra_fits16(sc, Lq, Lr, pick_rl(Lq, sc.n));
+    is16[k] = auto16 && intra_fits16(sc, Lq, Lr, pick_rl(Lq, sc.n));
     (is16[k] ? k16 : k32).push_back(k);
     (is16[k] ? r16 : r32) += std::max<int64_t>(Lr, 1);
     if (!is16[k] && Lr > 0) {
@@ -1381,7 +1519,6 @@ static int run_intra_forward(swx_ctx *ctx, const Scoring &sc, LongPath &lp, cons
   a.err = err;
   a.bnd = A.get<uint32_t>(bnd_words > 0 ? bnd_words : 1);
   if (!a.bnd) return fail(SWX_ENOMEM, "device pool exhausted (hand-over rows)");
-  int rc;
   if ((rc = launch_intra_jobs(ctx, groups, a, bnd_words, false))) return rc;
   if ((rc = launch_intra16_jobs(ctx, jobs16, a, sc, m3, plan16))) return rc;
   // lane widths of the long pairs (diagnostic)
@@ -1494,7 +1631,7 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
   uint8_t *ovf = A.get<uint8_t>(np), *lanebits = A.get<uint8_t>(np), *err = A.get<uint8_t>(np);
   int32_t *qbeg = A.get<int32_t>(np), *score2 = A.get<int32_t>(np);
   int64_t *rbeg = A.get<int64_t>(np), *rend2 = A.get<int64_t>(np);
-  int64_t *stats = A.get<int64_t>(4);
+  int64_t *stats = A.get<int64_t>(5);
   if (!qstart || !rstart || !rlen || !qlen || !score || !qend || !rend || !ovf || !lanebits ||
       !err || !qbeg || !score2 || !rbeg || !rend2 || !stats)
     return fail(SWX_ENOMEM, "device pool exhausted (pair arrays)");
@@ -1506,10 +1643,10 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
                          st));
   }
   // a score can reach smax * min(qlen, rlen); the 32-bit lanes hold < 2^26
-  HIP_TRY(hipMemsetAsync(stats, 0, 8 * 4, st));
+  HIP_TRY(hipMemsetAsync(stats, 0, 8 * 5, st));
   HIP_TRY(launch_pair_stats(np, qlen, rlen, stats, st));
-  int64_t hstats[4];
-  if ((rc = read_i64(ctx, stats, hstats, 4))) return rc;
+  int64_t hstats[5];
+  if ((rc = read_i64(ctx, stats, hstats, 5))) return rc;
   const int64_t score_bound = (int64_t)std::max(sc.smax, 0) * hstats[0];
   if (score_bound >= (1 << 26) - 1)
     return fail(SWX_EOVERFLOW, "a score could exceed the 32-bit lane range");
@@ -1555,6 +1692,12 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
   // long pairs take the intra-sequence path, the rest the batched one
   LongPath lp;
   if ((rc = split_pairs(ctx, np, qlen, rlen, hstats[1], lp))) return rc;
+  AlonePath al;
+  if ((rc = plan_alone(ctx, sc, np, flags, hstats, qlen, rlen, lp, al))) return rc;
+  auto long_forward = [&]() -> int {
+    return al.on ? run_alone_forward(ctx, sc, al, score_bound, fview, fout, lanebits)
+                 : run_intra_forward(ctx, sc, lp, fview, fout, err, lanebits);
+  };
 
   // forward fill, 16-bit lanes (events 1 and 2 bracket the fill kernels)
   Plan p16, p32;
@@ -1573,7 +1716,7 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
     if (beside) {
       {
         StreamScope on_side(ctx, ctx->aux[0]);   // the pass's launches and waits go there
-        rc = run_intra_forward(ctx, sc, lp, fview, fout, err, lanebits);
+        rc = long_forward();
       }
       if (rc) {   // nothing of the call may still run when it returns
         (void)hipStreamSynchronize(ctx->aux[0]);
@@ -1581,15 +1724,18 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
       }
       HIP_TRY(hipEventRecord(ctx->join_ev[0], ctx->aux[0]));
       HIP_TRY(hipStreamWaitEvent(st, ctx->join_ev[0], 0));
-    } else if ((rc = run_intra_forward(ctx, sc, lp, fview, fout, err, lanebits))) {
+    } else if ((rc = long_forward())) {
       return rc;
     }
     HIP_TRY(hipEventRecord(ctx->ev[2], st));
   }
 
-  // saturated pairs: exact re-run on 32-bit lanes
+  // saturated pairs: exact re-run on 32-bit lanes (none where no score of the
+  // batch can reach the 16-bit limit, and none of the long pairs)
   int64_t *wide = nullptr, nwide = 0;
-  if ((rc = select_flagged(ctx, ovf, np, &wide, &nwide))) return rc;
+  if (lp.nshort > 0 && score_bound >= kInter16Limit &&
+      (rc = select_flagged(ctx, ovf, np, &wide, &nwide)))
+    return rc;
   if (nwide > 0) {
     if ((rc = plan_pass(ctx, sc, wide, nwide, qlen, rlen, nullptr, nullptr, 32, R, p32, sp))) return rc;
     if ((rc = run_fill(ctx, p32, sc, fview, false, nullptr, fout, score_bound, -1, 0, 0, sp))) return rc;
@@ -1611,7 +1757,7 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
                              rrl, tgt, err, st));
     HIP_TRY(rev_prepare(np, score, qend, rend, lanebits, sc.smax, sc.o, sc.e, band, band_q, f16,
                         f32, st));
-    if (lp.nlong > 0) HIP_TRY(clear_flags(lp.nlong, lp.d_long, f16, f32, st));
+    if (lp.nlong > 0 && lp.nshort > 0) HIP_TRY(clear_flags(lp.nlong, lp.d_long, f16, f32, st));
     HIP_TRY(hipMemsetAsync(rsc, 0, sizeof(int32_t) * np, st));
     PairView rview{rqs, rrs, rql, rrl, b.qcat, b.rcat, 1};
     FillOut rout{rsc, rqe, rre, rov, err};
@@ -1621,15 +1767,25 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
     const int64_t *rcd[2] = {nullptr, nullptr};
     int64_t *rc2 = A.get<int64_t>(2);
     if (!rc2) return fail(SWX_ENOMEM, "device pool exhausted (reverse counts)");
-    for (int k = 0; k < 2; ++k) {
+    // (without a pair above the 16-bit limit, the second list is empty)
+    const int widths = lp.nshort == 0 ? 0 : score_bound >= kInter16Limit ? 2 : 1;
+    for (int k = 0; k < widths; ++k) {
       if ((rc = select_flagged_dev(ctx, k == 0 ? f16 : f32, np, &rids[k], &rcd[k]))) return rc;
       HIP_TRY(hipMemcpyAsync(rc2 + k, rcd[k], sizeof(int64_t), hipMemcpyDeviceToDevice, st));
     }
-    if ((rc = read_i64(ctx, rc2, rcnt, 2))) return rc;
+    if (widths > 0 && (rc = read_i64(ctx, rc2, rcnt, widths))) return rc;
     // as in the forward pass, the long pairs' reversed pass runs on a side
     // stream beside the batched one (16-bit lanes)
     const bool beside = lp.nlong > 0 && rcnt[0] > 0 && have_side_streams(ctx);
     bool long_done = false;
+    auto long_reverse = [&]() -> int {
+      if (!al.on) return run_intra_reverse(ctx, sc, lp, rview, score, qend, rend, band, tgt, rout, err);
+      AloneArgs a = alone_args(sc, al, rview, rout);
+      a.target = tgt;
+      a.band = band;
+      HIP_TRY(alone_reverse(a, ctx->stream));
+      return SWX_OK;
+    };
     for (int k = 0; k < 2; ++k) {
       if (rcnt[k] == 0) continue;
       Plan pr;
@@ -1644,7 +1800,7 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
       if (k == 0 && beside) {
         {
           StreamScope on_side(ctx, ctx->aux[0]);
-          rc = run_intra_reverse(ctx, sc, lp, rview, score, qend, rend, band, tgt, rout, err);
+          rc = long_reverse();
         }
         if (rc) {   // nothing of the call may still run when it returns
           (void)hipStreamSynchronize(ctx->aux[0]);
@@ -1656,8 +1812,7 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
     }
     if (long_done) {
       HIP_TRY(hipStreamWaitEvent(st, ctx->join_ev[0], 0));
-    } else if (lp.nlong > 0 &&
-               (rc = run_intra_reverse(ctx, sc, lp, rview, score, qend, rend, band, tgt, rout, err))) {
+    } else if (lp.nlong > 0 && (rc = long_reverse())) {
       return rc;
     }
     HIP_TRY(launch_begins(np, score, qend, rend, rsc, rqe, rre, qbeg, rbeg, err, st));
@@ -1694,12 +1849,14 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
       HIP_TRY(launch_score2_inter(s2, st));
     }
     if (lp.nlong > 0) {
-      IntraPairArgs e{};
-      e.pairs = lp.d_pairs; e.maxcol = lp.d_maxcol; e.qlen = qlen; e.rlen = rlen;
+      IntraPairArgs e = alone_pairs(al, qlen, rlen);
+      if (!al.on) {
+        e.pairs = lp.d_pairs; e.maxcol = lp.d_maxcol;
+        e.part_v = lp.d_part_v; e.part_j = lp.d_part_j; e.max_rlen = lp.max_rlen;
+      }
       e.score = score; e.qend = qend; e.rend = rend; e.rbeg = rbeg;
       e.mask_len = mask_len; e.score2 = score2; e.rend2 = rend2;
-      e.part_v = lp.d_part_v; e.part_j = lp.d_part_j; e.max_rlen = lp.max_rlen;
-      HIP_TRY(intra_score2(e, lp.nlong, st));
+      HIP_TRY(intra_score2(e, al.on ? al.count : lp.nlong, st));
     }
   }
   HIP_TRY(hipEventRecord(ctx->ev[6], st));
@@ -1880,7 +2037,7 @@ struct GraphState {
   void *tb_sort_tmp = nullptr;
   size_t tb_sort_bytes = 0;
   FixedTb tb[6];
-  // graphs of up to kTbPairsAll pairs: a workgroup per pair instead
+  // graphs of up to kTbGraphPairs pairs: a workgroup per pair instead
   bool tb_by_pairs = false;
   int64_t tbp_stride = 0;
   uint8_t *tbp_scratch = nullptr;
@@ -1889,6 +2046,7 @@ struct GraphState {
   bool intra = false;
   int RL = 16, waves = 1;
   int32_t kbits = 1, sh = 1024;
+  AlonePath alone;             // ... of short queries: no jobs
   int64_t bnd_stride = 0;      // reversed pass: hand-over rows per pair
   int32_t nc = 1;              // forward pass: column chunks per pair ...
   int64_t chunk = 0;           // ... of this many columns ...
@@ -2007,7 +2165,7 @@ static int fixed_issue(GraphState &g, hipStream_t st) {
     fs.add(g.status, 1, 8, 0);
     fs.add(g.err, B, 1, 0);
     fs.add(g.lanebits, B, 1, 32);
-    fs.add(g.maxcol, B * g.RM, 4, 0);
+    if (!g.alone.on) fs.add(g.maxcol, B * g.RM, 4, 0);
     fs.add(g.rsc, B, 4, 0);
     fs.add(g.cig_len, B, 4, 0);
     fs.add(g.cig_off_final, B + 1, 8, 0);
@@ -2031,7 +2189,12 @@ static int fixed_issue(GraphState &g, hipStream_t st) {
   PairView fview{g.qstart, g.rstart, g.qlen, g.rlen, g.qcat, g.rcat, 0};
   FillOut fout{g.score, g.qend, g.rend, g.ovf, g.err};
   IntraArgs ia{};
-  if (g.intra) {
+  if (g.alone.on) {
+    HIP_TRY(alone_forward(alone_args(g.sc, g.alone, fview, fout), st));
+    IntraPairArgs e = alone_pairs(g.alone, g.qlen, g.rlen);
+    e.score = g.score; e.qend = g.qend; e.rend = g.rend; e.overflow = g.ovf;
+    HIP_TRY(intra_end(e, B, st));
+  } else if (g.intra) {
     HIP_TRY(intra_jobs_chunked(B, g.nc, g.chunk, g.qlen, g.rlen, g.sc.smax, g.sc.o, g.sc.e,
                                g.kbits, g.sh, g.RM, g.fbnd_stride, g.jobs, g.ipairs, st));
     ia.jobs = g.jobs; ia.njobs = B * g.nc; ia.view = fview; ia.matrix = g.sc.dmat;
@@ -2063,7 +2226,12 @@ static int fixed_issue(GraphState &g, hipStream_t st) {
     if (!g.intra) HIP_TRY(fill_u8(4 * B, (uint8_t *)g.rsc, 0, st));
     PairView rview{g.rqs, g.rrs, g.rql, g.rrl, g.qcat, g.rcat, 1};
     FillOut rout{g.rsc, g.rqe, g.rre, g.rov, g.err};
-    if (g.intra) {
+    if (g.alone.on) {
+      AloneArgs a = alone_args(g.sc, g.alone, rview, rout);
+      a.target = g.tgt;
+      a.band = g.band;
+      HIP_TRY(alone_reverse(a, st));
+    } else if (g.intra) {
       HIP_TRY(intra_rev_jobs_fixed(B, g.score, g.rend, g.band, g.kbits, g.bnd_stride, g.rjobs, st));
       IntraArgs ra = ia;
       ra.jobs = g.rjobs;
@@ -2150,11 +2318,13 @@ static int fixed_issue(GraphState &g, hipStream_t st) {
                                    g.qend, g.cigar, st));
   }
   if ((flags & SWX_SCORE2) && g.intra) {
-    IntraPairArgs e{};
-    e.pairs = g.ipairs; e.maxcol = g.maxcol; e.qlen = g.qlen; e.rlen = g.rlen;
+    IntraPairArgs e = alone_pairs(g.alone, g.qlen, g.rlen);
+    if (!g.alone.on) {
+      e.pairs = g.ipairs; e.maxcol = g.maxcol;
+      e.part_v = g.part_v; e.part_j = g.part_j; e.max_rlen = g.RM;
+    }
     e.score = g.score; e.qend = g.qend; e.rend = g.rend; e.rbeg = g.rbeg;
     e.mask_len = g.cfg.mask_len; e.score2 = g.score2; e.rend2 = g.rend2;
-    e.part_v = g.part_v; e.part_j = g.part_j; e.max_rlen = g.RM;
     HIP_TRY(intra_score2(e, B, st));
   } else if (flags & SWX_SCORE2) {
     Score2InterArgs s2{};
@@ -2244,6 +2414,9 @@ static int graph_alloc(GraphState &g) {
         g.chunk = (g.RM + nc - 1) / nc;
       }
     }
+    // short queries: a wave per pair (as in plan_alone, for the capacities)
+    g.alone.on = g.QM <= kAloneMaxQ && g.RM <= kAloneMaxR && g.RM >= 1 && bound + g.sc.bias <= 32766 &&
+                 (g.RM <= kAloneSweep || B >= 16 * (int64_t)g.cus);
     g.fbnd_stride = 2 * (nstrips - 1) * std::min<int64_t>(g.RM, g.chunk + wcap);
     g.jobs = A.get<IntraJob>(B * g.nc);
     g.rjobs = A.get<IntraJob>(B);
@@ -2253,6 +2426,10 @@ static int graph_alloc(GraphState &g) {
         {B * g.bnd_stride, B * g.nc * g.fbnd_stride, int64_t(1)}));
     g.part_v = A.get<int32_t>(B * intra_slices());
     g.part_j = A.get<int64_t>(B * intra_slices());
+    g.alone.count = g.alone.n32 = B;
+    g.alone.maxcol = g.maxcol;
+    g.alone.stride = g.RM;
+    g.alone.max_q = (int32_t)g.QM;
     if (!g.jobs || !g.rjobs || !g.ipairs || !g.maxcol || !g.ibnd || !g.part_v || !g.part_j)
       return fail(SWX_ENOMEM, "device pool exhausted (graph intra route)");
   } else {
@@ -2267,7 +2444,7 @@ static int graph_alloc(GraphState &g) {
   // the band classes, up to every pair in one class
   const int64_t tbp_stride = round_up(tb_wave_dir_bytes(g.QM, g.RM, kTbPairRows), 256) +
                              tb_pair_bnd_bytes(g.QM, g.RM);
-  g.tb_by_pairs = B <= kTbPairsAll && B * tbp_stride <= kTbGraphBytes &&
+  g.tb_by_pairs = B <= kTbGraphPairs && B * tbp_stride <= kTbGraphBytes &&
                   (g.QM + 64 * kTbPairRows - 1) / (64 * kTbPairRows) <= tb_wave_max_strips();
   if (g.tb_by_pairs) {
     g.tbp_stride = tbp_stride;

@@ -257,7 +257,9 @@ struct IntraPair {         // one long pair's forward max array
   int32_t sh;              // strip height of its forward jobs (padding rows = roundup(qlen, sh) - qlen)
 };
 struct IntraPairArgs {
-  const IntraPair *pairs;
+  const IntraPair *pairs;  // null: pair ids[k] (ids null: k) as AloneArgs lays it out
+  const int64_t *ids;
+  int64_t stride;
   const uint32_t *maxcol;
   const int32_t *qlen;
   const int64_t *rlen;
@@ -272,7 +274,31 @@ struct IntraPairArgs {
   int32_t *part_v;         // per (pair, slice) partial bests: intra_slices() per pair
   int64_t *part_j;
   int64_t max_rlen;        // longest reference of the launch (its shape)
+  int64_t first;           // (launches of part of the list) its first pair
 };
+
+// Long-path pairs of short queries, a wave per pair (or two pairs on 16-bit
+// lanes), whole references: no job tables.  ids (null: every pair in turn) and
+// the max array words of the k-th at maxcol + k * stride, row-code bits
+// kAloneBits, rows coded in kAloneMaxQ padded rows.
+constexpr int32_t kAloneMaxQ = 512;
+constexpr int32_t kAloneBits = 16;
+struct AloneArgs {
+  const int64_t *ids;
+  int64_t count;
+  PairView view;
+  const int8_t *matrix;
+  int32_t n, o, e, bias;
+  int32_t max_q;             // longest query of the launch (its shape)
+  uint32_t *maxcol;
+  int64_t stride;
+  uint8_t *lanebits;         // forward: 32 is written (32-bit lanes; may be null)
+  const int32_t *target, *band;   // reversed pass
+  FillOut out;
+};
+hipError_t alone_forward(const AloneArgs &a, hipStream_t st);
+hipError_t alone_forward16(const AloneArgs &a, bool m3, hipStream_t st);
+hipError_t alone_reverse(const AloneArgs &a, hipStream_t st);
 
 // The one-pair call (swx_align) of short queries, in three kernels: the inputs
 // staged and checked, the forward pass on a workgroup per column chunk, and
