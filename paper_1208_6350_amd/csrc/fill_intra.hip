@@ -883,14 +883,16 @@ __device__ __forceinline__ StripJob alone_job(const AloneArgs &a, int64_t k, boo
   x.Lr = a.view.rlen[p];
   x.rv = a.view.reversed != 0;
   x.c1 = x.Lr;
-  x.band = rev ? a.band[p] : -1;
+  x.band = rev && a.band ? a.band[p] : -1;
+  x.anchor = a.anchor;
   x.kb = kAloneBits;
   x.tgt = rev ? a.target[p] : 0;
   x.mc = a.maxcol + k * a.stride;
   return x;
 }
 
-template <bool REV, bool HO>
+// LAST: the suboptimal alignment's end, over a window that ends at its column
+template <bool REV, bool HO, bool LAST>
 __global__ __launch_bounds__(64) void k_alone_fill(AloneArgs a) {
   extern __shared__ uint4 s_dyn[];   // [(n + 1) symbols][64 lanes][rows] bytes
   __shared__ int8_t s_mat[32 * 32];
@@ -902,16 +904,16 @@ __global__ __launch_bounds__(64) void k_alone_fill(AloneArgs a) {
   lds_wave_sync();
   StripJob x = alone_job(a, k, REV);
   if (!REV && a.lanebits && threadIdx.x == 0) a.lanebits[p] = 32;
-  if (x.Lr < 1 || (REV && x.Lq < 1)) return;   // (reversed: nothing to find, preset)
+  if (x.Lr < 1 || ((REV || LAST) && x.Lq < 1)) return;   // (nothing to find: preset)
   x.rcol = &s_rcol;
   x.rrow = &s_rrow;
   const StripScoring sc{a.n, (uint32_t)a.bias, (uint32_t)a.o, (uint32_t)a.e};
   uint8_t *s_prof = reinterpret_cast<uint8_t *>(s_dyn);
-  if (x.Lq <= 256) {
+  if (x.Lq + (REV && a.anchor ? 1 : 0) <= 256) {
     x.row0 = kAloneMaxQ - 256;
-    strip_alone<4, REV, HO>(x, sc, s_mat, s_prof);
+    strip_alone<4, REV, HO, LAST>(x, sc, s_mat, s_prof);
   } else {
-    strip_alone<8, REV, HO>(x, sc, s_mat, s_prof);
+    strip_alone<8, REV, HO, LAST>(x, sc, s_mat, s_prof);
   }
   if constexpr (REV) {
     lds_wave_sync();
@@ -920,6 +922,17 @@ __global__ __launch_bounds__(64) void k_alone_fill(AloneArgs a) {
       a.out.score[p] = hit ? x.tgt : 0;
       a.out.qend[p] = hit ? s_rrow : -1;
       a.out.rend[p] = hit ? s_rcol : -1;
+      a.out.overflow[p] = 0;
+    }
+  } else if constexpr (LAST) {
+    lds_wave_sync();
+    if (threadIdx.x == 0) {
+      const uint32_t w = (uint32_t)s_rrow;
+      const int32_t v = (int32_t)(w >> kAloneBits);
+      const uint32_t M = (1u << kAloneBits) - 1u;
+      a.out.score[p] = v;
+      a.out.qend[p] = v > 0 ? (int32_t)(M - (w & M)) - (kAloneMaxQ - x.Lq) : -1;
+      a.out.rend[p] = v > 0 ? x.Lr - 1 : -1;
       a.out.overflow[p] = 0;
     }
   }
@@ -948,21 +961,19 @@ __global__ __launch_bounds__(64) void k_alone_fill16(AloneArgs a) {
 
 static size_t alone_lds(const AloneArgs &a) { return (size_t)(a.n + 1) * 64 * (a.max_q <= 256 ? 4 : 8); }
 
-hipError_t alone_forward(const AloneArgs &a, hipStream_t st) {
+template <bool REV, bool LAST>
+static hipError_t alone_fill(const AloneArgs &a, hipStream_t st) {
   if (a.count == 0) return hipSuccess;
   if (a.max_q > kAloneMaxQ) return hipErrorInvalidValue;
-  if (a.bias == a.o) hipLaunchKernelGGL((k_alone_fill<false, true>), dim3((unsigned)a.count), dim3(64), alone_lds(a), st, a);
-  else hipLaunchKernelGGL((k_alone_fill<false, false>), dim3((unsigned)a.count), dim3(64), alone_lds(a), st, a);
+  const dim3 g((unsigned)a.count), b(64);
+  if (a.bias == a.o) hipLaunchKernelGGL((k_alone_fill<REV, true, LAST>), g, b, alone_lds(a), st, a);
+  else hipLaunchKernelGGL((k_alone_fill<REV, false, LAST>), g, b, alone_lds(a), st, a);
   return hipGetLastError();
 }
 
-hipError_t alone_reverse(const AloneArgs &a, hipStream_t st) {
-  if (a.count == 0) return hipSuccess;
-  if (a.max_q > kAloneMaxQ) return hipErrorInvalidValue;
-  if (a.bias == a.o) hipLaunchKernelGGL((k_alone_fill<true, true>), dim3((unsigned)a.count), dim3(64), alone_lds(a), st, a);
-  else hipLaunchKernelGGL((k_alone_fill<true, false>), dim3((unsigned)a.count), dim3(64), alone_lds(a), st, a);
-  return hipGetLastError();
-}
+hipError_t alone_forward(const AloneArgs &a, hipStream_t st) { return alone_fill<false, false>(a, st); }
+hipError_t alone_last(const AloneArgs &a, hipStream_t st) { return alone_fill<false, true>(a, st); }
+hipError_t alone_reverse(const AloneArgs &a, hipStream_t st) { return alone_fill<true, false>(a, st); }
 
 hipError_t alone_forward16(const AloneArgs &a, bool m3, hipStream_t st) {
   if (a.count == 0) return hipSuccess;

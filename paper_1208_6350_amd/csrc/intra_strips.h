@@ -97,6 +97,7 @@ struct StripJob {
   int32_t *rrow;               // ... and its padded row
   unsigned long long *best;    // ... smallest such column so far (~0: none)
   int32_t row0;                // one strip: padded row of the strip's first row in the row code
+  uint32_t anchor;             // one strip, reversed: the score that a path from the first cell starts with
 };
 struct StripScoring {
   int n;
@@ -358,8 +359,12 @@ __device__ __forceinline__ bool strips_of_wave(const StripJob &x, const StripSco
 // Every owned column is this wave's alone: its max array words are stored, not
 // merged.  Bound by instruction issue of one wave (about
 // 48 per step and four rows; the sweep for several strips 73).  Reversed:
-// *rcol, *rrow (query row) of the first column reaching the target, or -1.
-template <int RL, bool REV, bool HO>
+// *rcol, *rrow (query row) of the first column reaching the target, or -1;
+// with an anchor above every score (Lq < 64 * RL then), the padding row above
+// the first one starts from the anchor and holds the gap run that leaves it
+// (a forward alignment may end in a deletion run), so that only paths from
+// that corner can reach a target above the anchor.  LAST: only the last column's word is wanted, in *rrow.
+template <int RL, bool REV, bool HO, bool LAST = false>
 __device__ __forceinline__ void strip_alone(const StripJob &x, const StripScoring &sc,
                                             const int8_t *s_mat, uint8_t *s_prof) {
   constexpr int SH = 64 * RL;
@@ -368,7 +373,9 @@ __device__ __forceinline__ void strip_alone(const StripJob &x, const StripScorin
   using T = VT<uint32_t>;
   const int lane = threadIdx.x & 63;
   const int qpad = SH - x.Lq;
-  const int f = qpad < SH ? qpad / RL : 63;   // the first lane with a row of the query
+  // the first lane with a row of the query, or with the anchored row above it
+  const int top = REV && x.anchor ? qpad - 1 : qpad;
+  const int f = top < SH ? top / RL : 63;
   const uint32_t M = (1u << x.kb) - 1u;
   const uint32_t DL = M - (uint32_t)(x.row0 + lane * RL + RL - 1);
   const int64_t clo = x.cw;
@@ -389,6 +396,17 @@ __device__ __forceinline__ void strip_alone(const StripJob &x, const StripScorin
 #pragma unroll
   for (int r = 0; r < RL; ++r) { H[r] = 0u; E[r] = 0u; }
   uint32_t hup_prev = 0u, hout = 0u, fout = 0u, cmout = 0u, obC = 0u;
+  if constexpr (REV) {
+    if (x.anchor) {
+#pragma unroll
+      for (int r = 0; r < RL; ++r)
+        if (enter && r == top - f * RL) {
+          H[r] = x.anchor;
+          E[r] = x.anchor - sc.o + sc.bias;
+        }
+      hout = H[RL - 1];   // (the row below may be the next lane's)
+    }
+  }
   const uint32_t first = lane_value(symbols(clo), 0);   // (by every lane, not inside the choice)
   uint32_t sym = enter ? first : (uint32_t)sc.n;
   uint32_t X[XW];
@@ -448,6 +466,8 @@ __device__ __forceinline__ void strip_alone(const StripJob &x, const StripScorin
         }
         break;
       }
+    } else if constexpr (LAST) {
+      if (mine && c == chi - 1) *x.rrow = (int32_t)obC;
     } else {
       if (mine && c >= x.c0) x.mc[c] = obC;
     }

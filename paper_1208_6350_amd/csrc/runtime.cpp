@@ -1868,7 +1868,12 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
   // anchor cell can reach the target), its CIGAR (the banded traceback),
   // placed in the arena after every primary CIGAR.
   if (flags & SWX_SUBOPT) {
-    constexpr uint32_t kAnchor = 1u << 25;
+    // Where nothing was batched these passes take a wave per pair too, 32-bit
+    // lanes as here, over every pair (those without a score2 have no columns):
+    // no selection, plan, pack or read.  20,000 reads, 14,000 with a score2:
+    // 2.07 + 1.60 ms for the two passes with their planning -> 0.46 + 0.36.
+    const bool sub_alone = al.all && al.max_q < kAloneMaxQ;
+    const uint32_t kAnchor = sub_alone ? kAloneAnchor : 1u << 25;
     if (score_bound >= (int64_t(1) << 24))
       return fail(SWX_EOVERFLOW, "scores too large for the suboptimal alignment's anchored pass");
     int64_t *wrs = A.get<int64_t>(np), *wrl = A.get<int64_t>(np), *wre = A.get<int64_t>(np);
@@ -1892,7 +1897,12 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
     HIP_TRY(hipMemsetAsync(wsc, 0, sizeof(int32_t) * np, st));
     HIP_TRY(hipMemsetAsync(wqe, 0xFF, sizeof(int32_t) * np, st));
     int64_t *ids = nullptr, cnt = 0;
-    if ((rc = select_flagged(ctx, sfl, np, &ids, &cnt))) return rc;
+    if (sub_alone) {
+      const PairView wview{qstart, wrs, qlen, wrl, b.qcat, b.rcat, 0};
+      HIP_TRY(alone_last(alone_args(sc, al, wview, FillOut{wsc, wqe, wre, wov, err}), st));
+    } else if ((rc = select_flagged(ctx, sfl, np, &ids, &cnt))) {
+      return rc;
+    }
     if (cnt > 0) {
       Plan pw;
       if ((rc = plan_pass(ctx, sc, ids, cnt, qlen, wrl, nullptr, nullptr, 32, R, pw, sp))) return rc;
@@ -1904,7 +1914,17 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
     HIP_TRY(launch_sub_rev_views(np, qstart, rstart, qlen, score2, rend2, wsc, wqe, kAnchor, rqs,
                                  rql, rrs, rrl, tgt, sfl, err, st));
     HIP_TRY(hipMemsetAsync(rsc, 0, sizeof(int32_t) * np, st));
-    if ((rc = select_flagged(ctx, sfl, np, &ids, &cnt))) return rc;
+    cnt = 0;
+    if (sub_alone) {
+      const PairView rview{rqs, rrs, rql, rrl, b.qcat, b.rcat, 1};
+      AloneArgs a = alone_args(sc, al, rview, FillOut{rsc, rqe, rre, rov, err});
+      a.target = tgt;
+      a.anchor = kAnchor;
+      a.max_q += 1;
+      HIP_TRY(alone_reverse(a, st));
+    } else if ((rc = select_flagged(ctx, sfl, np, &ids, &cnt))) {
+      return rc;
+    }
     if (cnt > 0) {
       Plan pr;
       if ((rc = plan_pass(ctx, sc, ids, cnt, rql, rrl, nullptr, nullptr, 32, R, pr, sp))) return rc;

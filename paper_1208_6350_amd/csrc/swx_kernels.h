@@ -293,10 +293,14 @@ struct AloneArgs {
   uint32_t *maxcol;
   int64_t stride;
   uint8_t *lanebits;         // forward: 32 is written (32-bit lanes; may be null)
-  const int32_t *target, *band;   // reversed pass
+  const int32_t *target, *band;   // reversed pass (band may be null)
+  uint32_t anchor;           // ... of paths from the corner alone (queries shorter than max_q then), else 0
   FillOut out;
 };
+// above every score of a pair whose words have room for the anchor and a score
+constexpr uint32_t kAloneAnchor = 1u << 15;
 hipError_t alone_forward(const AloneArgs &a, hipStream_t st);
+hipError_t alone_last(const AloneArgs &a, hipStream_t st);   // best of the last column only; empty references skipped
 hipError_t alone_forward16(const AloneArgs &a, bool m3, hipStream_t st);
 hipError_t alone_reverse(const AloneArgs &a, hipStream_t st);
 

@@ -6,6 +6,7 @@ from __future__ import annotations
 import numpy as np
 import pytest
 
+import oracle
 import paper_1208_6350_amd as swx
 import workloads as W
 from tests.test_gpu_parity import assert_parity, run_both
@@ -93,3 +94,36 @@ def test_with_short_pairs(nlong, nshort, match):
     wide = np.full(n, nlong < 1024)
     wide[small] = False
     np.testing.assert_array_equal(recs["lane_bits"], np.where(wide, 32, 16))
+
+
+# the suboptimal alignment's passes: first rows at each place in a lane and lane
+# of a strip, scores above and below a byte's, a long window and a short one
+# (a second alignment just outside a short mask may end in a gap); 512 rows
+# leave no room for the anchored row
+@pytest.mark.parametrize("mask_len", [0, 2, -1])
+@pytest.mark.parametrize("match", [2, 60])
+@pytest.mark.parametrize("top", [256, 511, 512])
+def test_suboptimal(mask_len, match, top):
+    ql = [1, 2, 100, 101, 102, 103, 0, 253, 254, 255, 256, 257, 258, 505, 508, 510, 511, 512]
+    ql = [m for m in ql if m <= top]
+    qs, rs = pairs(ql, [40 + 3 * m for m in ql], 8800)
+    for k in range(0, len(ql), 2):   # a second copy, changed a little, behind the first
+        rs[k] = np.concatenate([rs[k], qs[k][ql[k] // 5:]])
+    m = W.dna_matrix() * 0 - (2 if match == 2 else 55)
+    np.fill_diagonal(m, match)
+    b = W.from_lists("alone-sub", m.astype(np.int8), *((3, 1) if match == 2 else (58, 20)), qs, rs)
+    c = swx.Context(0)
+    recs, cig, sub = c.align_batch(b.matrix, b.gap_open, b.gap_extend, b.qcat, b.qoff, b.rcat, b.roff,
+                                   b.pair_q, b.pair_r, swx.SWX_ALL | swx.SWX_SUBOPT, mask_len)
+    c.close()
+    ref, _, _ = oracle.align_many(b.qcat, b.qoff, b.rcat, b.roff, b.pair_q, b.pair_r, b.matrix,
+                                  b.gap_open, b.gap_extend, swx.SWX_ALL, mask_len)
+    sref, scig, scoff = oracle.suboptimal_many(b.qcat, b.qoff, b.rcat, b.roff, b.pair_q, b.pair_r,
+                                               b.matrix, b.gap_open, b.gap_extend, ref[:, 1], ref[:, 6])
+    assert (ref[:, 1] > 0).sum() > len(ql) // 3
+    np.testing.assert_array_equal(sub["score1"], ref[:, 1])
+    for f, col in (("read_begin1", 0), ("read_end1", 1), ("ref_begin1", 2)):
+        np.testing.assert_array_equal(sub[f], sref[:, col], err_msg=f)
+    for p in range(b.npairs):
+        g = cig[sub["cigar_off"][p]:sub["cigar_off"][p] + sub["cigar_len"][p]]
+        np.testing.assert_array_equal(g, scig[scoff[p]:scoff[p] + sref[p, 3]])
