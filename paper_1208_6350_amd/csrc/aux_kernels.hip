@@ -20,41 +20,62 @@ namespace swx {
 // length to the caps): input that the validation kernel flags still drives
 // every later kernel inside its buffers, where a caller's device buffers
 // (the graph's) are checked only by that kernel, in the same launch order.
-__global__ void k_views(int64_t npairs, const int64_t *qoff, const int64_t *roff,
-                        const int64_t *pair_q, const int64_t *pair_r, ViewCaps caps,
-                        int64_t *qstart, int32_t *qlen, int64_t *rstart, int64_t *rlen) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= npairs) return;
+// stats (may be null): [0] = max over pairs of min(qlen, rlen); [1] = sum of
+// qlen * rlen; [2], [3] = longest query, reference; [4] = sum of rlen.
+__global__ __launch_bounds__(256) void k_views(int64_t npairs, const int64_t *qoff, const int64_t *roff,
+                                               const int64_t *pair_q, const int64_t *pair_r,
+                                               ViewCaps caps, int64_t *qstart, int32_t *qlen,
+                                               int64_t *rstart, int64_t *rlen, int64_t *stats) {
   auto clamp = [](int64_t v, int64_t lo, int64_t hi) { return v < lo ? lo : (v > hi ? hi : v); };
-  const int64_t qi = clamp(pair_q[p], 0, caps.nq - 1), ri = clamp(pair_r[p], 0, caps.nr - 1);
-  const int64_t q0 = clamp(qoff[qi], 0, caps.qcat_len);
-  const int64_t q1 = clamp(qoff[qi + 1], q0, caps.qcat_len);
-  const int64_t r0 = clamp(roff[ri], 0, caps.rcat_len);
-  const int64_t r1 = clamp(roff[ri + 1], r0, caps.rcat_len);
-  qstart[p] = q0;
-  qlen[p] = (int32_t)(q1 - q0 < caps.max_qlen ? q1 - q0 : caps.max_qlen);
-  rstart[p] = r0;
-  rlen[p] = r1 - r0 < caps.max_rlen ? r1 - r0 : caps.max_rlen;
-}
-
-// Reversed prefixes q[0..qend] and r[0..rend] (read backwards by the fill).
-__global__ void k_rev_views(int64_t npairs, const int64_t *qstart, const int64_t *rstart,
-                            const int32_t *qlen, const int64_t *rlen,
-                            const int32_t *score, const int32_t *qend, const int64_t *rend,
-                            int64_t *rqstart, int32_t *rqlen, int64_t *rrstart, int64_t *rrlen,
-                            int32_t *target, uint8_t *err) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= npairs) return;
-  bool ok = score[p] > 0;
-  if (ok && (qend[p] < 0 || qend[p] >= qlen[p] || rend[p] < 0 || rend[p] >= rlen[p])) {
-    err[p] = 1;   // an end outside the pair: never read past the sequences
-    ok = false;
+  int64_t v[5] = {0, 0, 0, 0, 0};
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < npairs; p += stride) {
+    const int64_t qi = clamp(pair_q[p], 0, caps.nq - 1), ri = clamp(pair_r[p], 0, caps.nr - 1);
+    const int64_t q0 = clamp(qoff[qi], 0, caps.qcat_len);
+    const int64_t q1 = clamp(qoff[qi + 1], q0, caps.qcat_len);
+    const int64_t r0 = clamp(roff[ri], 0, caps.rcat_len);
+    const int64_t r1 = clamp(roff[ri + 1], r0, caps.rcat_len);
+    const int64_t q = q1 - q0 < caps.max_qlen ? q1 - q0 : caps.max_qlen;
+    const int64_t r = r1 - r0 < caps.max_rlen ? r1 - r0 : caps.max_rlen;
+    qstart[p] = q0;
+    qlen[p] = (int32_t)q;
+    rstart[p] = r0;
+    rlen[p] = r;
+    const int64_t m = q < r ? q : r;
+    v[0] = m > v[0] ? m : v[0];
+    v[1] += q * r;
+    v[2] = q > v[2] ? q : v[2];
+    v[3] = r > v[3] ? r : v[3];
+    v[4] += r;
   }
-  rqstart[p] = qstart[p];
-  rrstart[p] = rstart[p];
-  rqlen[p] = ok ? qend[p] + 1 : 0;
-  rrlen[p] = ok ? rend[p] + 1 : 0;
-  target[p] = ok ? score[p] : 0;
+  if (!stats) return;
+  auto merge = [&](const int64_t *o) {
+    v[0] = o[0] > v[0] ? o[0] : v[0];
+    v[1] += o[1];
+    v[2] = o[2] > v[2] ? o[2] : v[2];
+    v[3] = o[3] > v[3] ? o[3] : v[3];
+    v[4] += o[4];
+  };
+  for (int off = 32; off >= 1; off >>= 1) {
+    int64_t o[5];
+    for (int k = 0; k < 5; ++k) o[k] = __shfl_xor(v[k], off, 64);
+    merge(o);
+  }
+  // one set of atomics per block, not per wave: they all meet at five words
+  __shared__ int64_t s_v[4][5];
+  const int wv = (int)(threadIdx.x >> 6);
+  if ((threadIdx.x & 63) == 0)
+    for (int k = 0; k < 5; ++k) s_v[wv][k] = v[k];
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int k = 1; k < 4; ++k) merge(s_v[k]);
+    for (int k = 0; k < 5; ++k) {
+      unsigned long long *at = (unsigned long long *)&stats[k];
+      if (v[k] <= 0) continue;
+      if (k == 1 || k == 4) atomicAdd(at, (unsigned long long)v[k]);
+      else atomicMax(at, (unsigned long long)v[k]);
+    }
+  }
 }
 
 // ---- banded global DP and traceback (one thread per pair) ------------------
@@ -360,9 +381,10 @@ __global__ void k_records(int64_t npairs, const int32_t *score1, const int32_t *
                           const int32_t *qbeg, const int32_t *qend, const int64_t *rbeg,
                           const int64_t *rend, const int64_t *rend2, const int64_t *cig_off,
                           const int32_t *cig_len, const uint8_t *lane_bits, uint32_t flags,
-                          swx_rec_dev *recs) {
+                          swx_rec_dev *recs, const uint8_t *err, int64_t *nerr) {
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= npairs) return;
+  if (err && err[p]) atomicAdd((unsigned long long *)nerr, 1ull);
   swx_rec_dev r;
   const bool ok = score1[p] > 0;
   const bool beg = (flags & 1u) && ok;
@@ -436,52 +458,55 @@ __global__ void k_validate(ValidateArgs a) {
 }
 
 // ---- small helpers ------------------------------------------------------------
-// stats[0] = max over pairs of min(qlen, rlen); [1] = sum of qlen * rlen;
-// [2], [3] = longest query, reference; [4] = sum of rlen
-__global__ void k_pair_stats(int64_t n, const int32_t *qlen, const int64_t *rlen, int64_t *stats) {
-  int64_t v[5] = {0, 0, 0, 0, 0};
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n; p += stride) {
-    const int64_t q = qlen[p], r = rlen[p];
-    const int64_t m = q < r ? q : r;
-    v[0] = m > v[0] ? m : v[0];
-    v[1] += q * r;
-    v[2] = q > v[2] ? q : v[2];
-    v[3] = r > v[3] ? r : v[3];
-    v[4] += r;
-  }
-  auto merge = [&](const int64_t *o) {
-    v[0] = o[0] > v[0] ? o[0] : v[0];
-    v[1] += o[1];
-    v[2] = o[2] > v[2] ? o[2] : v[2];
-    v[3] = o[3] > v[3] ? o[3] : v[3];
-    v[4] += o[4];
-  };
-  for (int off = 32; off >= 1; off >>= 1) {
-    int64_t o[5];
-    for (int k = 0; k < 5; ++k) o[k] = __shfl_xor(v[k], off, 64);
-    merge(o);
-  }
-  // one set of atomics per block, not per wave: they all meet at five words
-  __shared__ int64_t s_v[4][5];
-  const int wv = (int)(threadIdx.x >> 6);
-  if ((threadIdx.x & 63) == 0)
-    for (int k = 0; k < 5; ++k) s_v[wv][k] = v[k];
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int k = 1; k < (int)(blockDim.x >> 6); ++k) merge(s_v[k]);
-    for (int k = 0; k < 5; ++k) {
-      unsigned long long *at = (unsigned long long *)&stats[k];
-      if (v[k] <= 0) continue;
-      if (k == 1 || k == 4) atomicAdd(at, (unsigned long long)v[k]);
-      else atomicMax(at, (unsigned long long)v[k]);
-    }
-  }
-}
-
 __global__ void k_lens_to_i64(int64_t n, const int32_t *len, int64_t *out) {
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (p < n) out[p] = len[p];
+}
+
+// One block over the whole array, 4,096 lengths per round: a round is one
+// dependent load and a scan, about 2 us, so it pays while launches cost more
+// than the rounds (k_lens_to_i64 and the device-wide scan: three launches).
+__global__ __launch_bounds__(1024) void k_scan_lens(int64_t n, const int32_t *len, int64_t *off) {
+  __shared__ int64_t s_sum[17];
+  const int lane = (int)(threadIdx.x & 63), wv = (int)(threadIdx.x >> 6);
+  int64_t base = 0;
+  for (int64_t t0 = 0; t0 < n; t0 += 4096) {
+    const int64_t k0 = t0 + 4 * (int64_t)threadIdx.x;
+    int64_t v[4], own = 0;
+    for (int k = 0; k < 4; ++k) {
+      v[k] = own;
+      own += k0 + k < n ? len[k0 + k] : 0;
+    }
+    int64_t s = own;
+    for (int d = 1; d < 64; d <<= 1) {
+      const int64_t u = __shfl_up(s, d, 64);
+      if (lane >= d) s += u;
+    }
+    if (lane == 63) s_sum[wv] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      int64_t t = 0;
+      for (int k = 0; k < 16; ++k) {
+        const int64_t u = s_sum[k];
+        s_sum[k] = t;
+        t += u;
+      }
+      s_sum[16] = t;
+    }
+    __syncthreads();
+    const int64_t at = base + s_sum[wv] + s - own;
+    for (int k = 0; k < 4; ++k)
+      if (k0 + k < n) off[k0 + k] = at + v[k];
+    base += s_sum[16];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) off[n] = base;
+}
+
+hipError_t scan_lens(int64_t n, const int32_t *len, int64_t *off, hipStream_t st) {
+  if (n > kScanLensMax) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_scan_lens, dim3(1), dim3(1024), 0, st, n, len, off);
+  return hipGetLastError();
 }
 
 __global__ void k_mark_lanes(int64_t n, const int64_t *n_dev, const int64_t *ids, uint8_t *lanebits,
@@ -491,26 +516,8 @@ __global__ void k_mark_lanes(int64_t n, const int64_t *n_dev, const int64_t *ids
   if (k < n) lanebits[ids[k]] = v;
 }
 
-__global__ void k_any_flag(int64_t n, const uint8_t *flag, int64_t *count) {
-  int64_t c = 0;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n; p += stride)
-    c += flag[p] ? 1 : 0;
-  for (int off = 32; off >= 1; off >>= 1) c += __shfl_xor(c, off, 64);
-  if ((threadIdx.x & 63) == 0 && c) atomicAdd((unsigned long long *)count, (unsigned long long)c);
-}
-
 // ---- launchers --------------------------------------------------------------
 static inline unsigned blocks_for(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
-
-hipError_t launch_pair_stats(int64_t n, const int32_t *qlen, const int64_t *rlen, int64_t *stats,
-                             hipStream_t st) {
-  if (!n) return hipSuccess;
-  unsigned b = blocks_for(n, 256);
-  if (b > 256) b = 256;
-  hipLaunchKernelGGL(k_pair_stats, dim3(b), dim3(256), 0, st, n, qlen, rlen, stats);
-  return hipGetLastError();
-}
 
 hipError_t lens_to_i64(int64_t n, const int32_t *len, int64_t *out, hipStream_t st) {
   if (!n) return hipSuccess;
@@ -530,14 +537,6 @@ hipError_t mark_lanes_dev(int64_t cap, const int64_t *n_dev, const int64_t *ids,
   if (!cap) return hipSuccess;
   hipLaunchKernelGGL(k_mark_lanes, dim3(blocks_for(cap, 256)), dim3(256), 0, st, cap, n_dev, ids,
                      lanebits, (uint8_t)v);
-  return hipGetLastError();
-}
-
-hipError_t launch_any_flag(int64_t n, const uint8_t *flag, int64_t *count, hipStream_t st) {
-  if (!n) return hipSuccess;
-  unsigned b = blocks_for(n, 256);
-  if (b > 1024) b = 1024;
-  hipLaunchKernelGGL(k_any_flag, dim3(b), dim3(256), 0, st, n, flag, count);
   return hipGetLastError();
 }
 
@@ -606,23 +605,12 @@ hipError_t launch_exclusive_scan(const int64_t *in, int64_t *out, int64_t n, voi
 hipError_t launch_views(int64_t npairs, const int64_t *qoff, const int64_t *roff,
                         const int64_t *pair_q, const int64_t *pair_r, const ViewCaps &caps,
                         int64_t *qstart, int32_t *qlen, int64_t *rstart, int64_t *rlen,
-                        hipStream_t st) {
+                        int64_t *stats, hipStream_t st) {
   if (!npairs) return hipSuccess;
   if (caps.nq < 1 || caps.nr < 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_views, dim3(blocks_for(npairs, 256)), dim3(256), 0, st, npairs, qoff, roff,
-                     pair_q, pair_r, caps, qstart, qlen, rstart, rlen);
-  return hipGetLastError();
-}
-
-hipError_t launch_rev_views(int64_t npairs, const int64_t *qstart, const int64_t *rstart,
-                            const int32_t *qlen, const int64_t *rlen,
-                            const int32_t *score, const int32_t *qend, const int64_t *rend,
-                            int64_t *rqstart, int32_t *rqlen, int64_t *rrstart, int64_t *rrlen,
-                            int32_t *target, uint8_t *err, hipStream_t st) {
-  if (!npairs) return hipSuccess;
-  hipLaunchKernelGGL(k_rev_views, dim3(blocks_for(npairs, 256)), dim3(256), 0, st, npairs, qstart,
-                     rstart, qlen, rlen, score, qend, rend, rqstart, rqlen, rrstart, rrlen, target,
-                     err);
+  const unsigned blocks = std::min(blocks_for(npairs, 256), stats ? 512u : UINT_MAX);
+  hipLaunchKernelGGL(k_views, dim3(blocks), dim3(256), 0, st, npairs, qoff, roff, pair_q, pair_r,
+                     caps, qstart, qlen, rstart, rlen, stats);
   return hipGetLastError();
 }
 
@@ -667,7 +655,10 @@ __global__ void k_fill_set(FillSet f) {
 hipError_t fill_set(const FillSet &f, hipStream_t st) {
   if (f.count < 0 || f.count > kFillSetMax) return hipErrorInvalidValue;
   if (f.count == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_fill_set, dim3(64), dim3(256), 0, st, f);
+  int64_t most = 0;
+  for (int k = 0; k < f.count; ++k) most = std::max(most, f.n[k]);
+  const unsigned blocks = (unsigned)std::min<int64_t>(1024, std::max<int64_t>(64, most / 1024));
+  hipLaunchKernelGGL(k_fill_set, dim3(blocks), dim3(256), 0, st, f);
   return hipGetLastError();
 }
 
@@ -700,11 +691,11 @@ hipError_t launch_records(int64_t npairs, const int32_t *score1, const int32_t *
                           const int32_t *qbeg, const int32_t *qend, const int64_t *rbeg,
                           const int64_t *rend, const int64_t *rend2, const int64_t *cig_off,
                           const int32_t *cig_len, const uint8_t *lane_bits, uint32_t flags,
-                          swx_rec_dev *recs, hipStream_t st) {
+                          swx_rec_dev *recs, const uint8_t *err, int64_t *nerr, hipStream_t st) {
   if (!npairs) return hipSuccess;
   hipLaunchKernelGGL(k_records, dim3(blocks_for(npairs, 256)), dim3(256), 0, st, npairs, score1,
                      score2, qbeg, qend, rbeg, rend, rend2, cig_off, cig_len, lane_bits, flags,
-                     recs);
+                     recs, err, nerr);
   return hipGetLastError();
 }
 
@@ -830,13 +821,31 @@ hipError_t launch_begins(int64_t npairs, const int32_t *score1, const int32_t *q
 }
 
 // ---- long/short split and small gathers for the intra-sequence path -------
-__global__ void k_split_long(int64_t n, const int32_t *qlen, const int64_t *rlen, int64_t cells_thr,
-                             int64_t rlen_thr, uint8_t *is_long, uint8_t *is_short) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= n) return;
-  const bool lg = (int64_t)qlen[p] * rlen[p] > cells_thr || rlen[p] > rlen_thr;
-  is_long[p] = lg ? 1 : 0;
-  is_short[p] = lg ? 0 : 1;
+// Long pairs: above cells_thr cells (negative: twice the batch's average per
+// lane half of a full device, from stats[1], times mult), or a reference above
+// rlen_thr.  *count: how many.
+__global__ __launch_bounds__(256) void k_split_long(int64_t n, const int32_t *qlen, const int64_t *rlen,
+                                                    int64_t cells_thr, int64_t mult, int64_t rlen_thr,
+                                                    const int64_t *stats, uint8_t *is_long,
+                                                    uint8_t *is_short, int64_t *count) {
+  __shared__ unsigned s_cnt;
+  if (threadIdx.x == 0) s_cnt = 0;
+  __syncthreads();
+  if (cells_thr < 0) {
+    const int64_t base = 2 * stats[1] / (2048 * 128);
+    cells_thr = mult * (base > 2048 ? base : 2048);
+  }
+  unsigned mine = 0;
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n; p += stride) {
+    const bool lg = (int64_t)qlen[p] * rlen[p] > cells_thr || rlen[p] > rlen_thr;
+    is_long[p] = lg ? 1 : 0;
+    is_short[p] = lg ? 0 : 1;
+    mine += lg ? 1u : 0u;
+  }
+  if (mine) atomicAdd(&s_cnt, mine);
+  __syncthreads();
+  if (threadIdx.x == 0 && s_cnt) atomicAdd((unsigned long long *)count, (unsigned long long)s_cnt);
 }
 
 // out[6k + f]: qlen, rlen, score, qend, rend, band of pair ids[k] (0 for null arrays)
@@ -862,10 +871,11 @@ __global__ void k_clear_flags(int64_t n, const int64_t *ids, uint8_t *f1, uint8_
 }
 
 hipError_t split_long(int64_t n, const int32_t *qlen, const int64_t *rlen, int64_t cells_thr,
-                      int64_t rlen_thr, uint8_t *is_long, uint8_t *is_short, hipStream_t st) {
+                      int64_t mult, int64_t rlen_thr, const int64_t *stats, uint8_t *is_long,
+                      uint8_t *is_short, int64_t *count, hipStream_t st) {
   if (!n) return hipSuccess;
-  hipLaunchKernelGGL(k_split_long, dim3(blocks_for(n, 256)), dim3(256), 0, st, n, qlen, rlen,
-                     cells_thr, rlen_thr, is_long, is_short);
+  hipLaunchKernelGGL(k_split_long, dim3(std::min(blocks_for(n, 256), 1024u)), dim3(256), 0, st, n, qlen,
+                     rlen, cells_thr, mult, rlen_thr, stats, is_long, is_short, count);
   return hipGetLastError();
 }
 

@@ -143,17 +143,19 @@ __device__ __forceinline__ int64_t rev_drift(int64_t num, int64_t den) {
   return g < 0 ? 0 : (g > (1 << 30) ? (1 << 30) : g);
 }
 
-__global__ void k_rev_prepare(int64_t n, const int32_t *score, const int32_t *qend,
-                              const int64_t *rend, const uint8_t *lanebits, int32_t smax,
-                              int32_t o, int32_t e, int32_t *band, int32_t *band_q, uint8_t *f16,
-                              uint8_t *f32) {
+// The same launch makes the pass's views (prefixes q[0..qend] and r[0..rend],
+// read backwards by the fill), its target, presets its score to none and flags
+// the pairs by lane width (f16, f32: may be null).
+__global__ void k_rev_setup(int64_t n, PairView v, const int32_t *score, const int32_t *qend,
+                            const int64_t *rend, const uint8_t *lanebits, int32_t smax, int32_t o,
+                            int32_t e, RevSetup s, uint8_t *err) {
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= n) return;
-  const bool ok = score[p] > 0;
+  bool ok = score[p] > 0;
+  const int64_t rows = (int64_t)qend[p] + 1, cols = rend[p] + 1;
   int32_t b = 0, bq = 0;
   if (ok) {
     if (e > 0) {
-      const int64_t rows = (int64_t)qend[p] + 1, cols = rend[p] + 1;
       const int64_t base = -(int64_t)o + e - score[p];
       const int64_t g = rev_drift((int64_t)smax * (rows < cols ? rows : cols) + base, e);
       int64_t gq = rev_drift((int64_t)smax * rows + base, (int64_t)smax + e);
@@ -166,10 +168,22 @@ __global__ void k_rev_prepare(int64_t n, const int32_t *score, const int32_t *qe
       b = bq = -1;
     }
   }
-  band[p] = b;
-  band_q[p] = bq;
-  f16[p] = (ok && lanebits[p] == 16) ? 1 : 0;
-  f32[p] = (ok && lanebits[p] == 32) ? 1 : 0;
+  s.band[p] = b;
+  s.band_q[p] = bq;
+  if (s.f16) {
+    s.f16[p] = (ok && lanebits[p] == 16) ? 1 : 0;
+    s.f32[p] = (ok && lanebits[p] == 32) ? 1 : 0;
+  }
+  if (ok && (rows < 1 || rows > v.qlen[p] || cols < 1 || cols > v.rlen[p])) {
+    err[p] = 1;   // an end outside the pair: never read past the sequences
+    ok = false;
+  }
+  s.qstart[p] = v.qstart[p];
+  s.rstart[p] = v.rstart[p];
+  s.qlen[p] = ok ? (int32_t)rows : 0;
+  s.rlen[p] = ok ? cols : 0;
+  s.target[p] = ok ? score[p] : 0;
+  s.score[p] = 0;
 }
 
 static inline unsigned nb(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
@@ -203,13 +217,12 @@ hipError_t sort_keys(int64_t n, uint64_t *keys, uint64_t *keys_alt, int64_t *val
   return e;
 }
 
-hipError_t rev_prepare(int64_t npairs, const int32_t *score, const int32_t *qend,
-                       const int64_t *rend, const uint8_t *lanebits, int32_t smax, int32_t o,
-                       int32_t e, int32_t *band, int32_t *band_q, uint8_t *f16, uint8_t *f32,
-                       hipStream_t st) {
+hipError_t rev_setup(int64_t npairs, const PairView &v, const int32_t *score, const int32_t *qend,
+                     const int64_t *rend, const uint8_t *lanebits, int32_t smax, int32_t o, int32_t e,
+                     const RevSetup &s, uint8_t *err, hipStream_t st) {
   if (!npairs) return hipSuccess;
-  hipLaunchKernelGGL(k_rev_prepare, dim3(nb(npairs, 256)), dim3(256), 0, st, npairs, score, qend,
-                     rend, lanebits, smax, o, e, band, band_q, f16, f32);
+  hipLaunchKernelGGL(k_rev_setup, dim3(nb(npairs, 256)), dim3(256), 0, st, npairs, v, score, qend, rend,
+                     lanebits, smax, o, e, s, err);
   return hipGetLastError();
 }
 

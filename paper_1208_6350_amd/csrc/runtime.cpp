@@ -670,20 +670,18 @@ static int run_traceback(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, 
   uint8_t *cls = A.get<uint8_t>(np);
   uint64_t *k0 = A.get<uint64_t>(np), *k1 = A.get<uint64_t>(np);
   int64_t *v0 = A.get<int64_t>(np), *v1 = A.get<int64_t>(np);
-  int64_t *ccap = A.get<int64_t>(np + 1), *coff = A.get<int64_t>(np + 1);
+  int64_t *coff = A.get<int64_t>(np);
   // pairs per class, the CIGAR scratch's words, then the wave kernel's scratch
   // bytes per class and its cursor
   int64_t *counts = A.get<int64_t>(18);
-  if (!cls || !k0 || !k1 || !v0 || !v1 || !ccap || !coff || !counts)
+  if (!cls || !k0 || !k1 || !v0 || !v1 || !coff || !counts)
     return fail(SWX_ENOMEM, "device pool exhausted (traceback)");
-  HIP_TRY(hipMemsetAsync(ccap + np, 0, 8, st));
   HIP_TRY(hipMemsetAsync(counts, 0, 18 * 8, st));
   // a small batch is traced pair by pair, in pair order (k_tb_pairs): it
   // needs no sort unless some of its pairs are long
   const bool pairs_ok = !A.fixed() && np <= kTbPairsMax;
   const bool few = pairs_ok && np <= kTbPairsAll;
-  HIP_TRY(tb_classify(ta, np, cls, k0, v0, ccap, counts, pairs_ok ? counts + 9 : nullptr, st));
-  if ((rc = scan(ctx, ccap, coff, np + 1))) return rc;
+  HIP_TRY(tb_classify(ta, np, cls, k0, v0, coff, counts, counts + 8, pairs_ok ? counts + 9 : nullptr, st));
   int64_t *sorted = nullptr;
   auto sort = [&]() -> int {
     size_t tmp_bytes = 0;
@@ -695,7 +693,6 @@ static int run_traceback(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, 
   };
   if (!few && (rc = sort())) return rc;
   // the class counts and the scratch sizes in one read
-  HIP_TRY(hipMemcpyAsync(counts + 8, coff + np, sizeof(int64_t), hipMemcpyDeviceToDevice, st));
   int64_t hc[17];
   if ((rc = read_i64(ctx, counts, hc, 17))) return rc;
   const int64_t capw = hc[8];
@@ -876,11 +873,15 @@ static int run_traceback(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, 
   }
   if ((rc = run_side_by_side(ctx, launches))) return rc;
   // final CIGAR offsets and compaction into the caller's arena
-  int64_t *len64 = A.get<int64_t>(np + 1);
-  if (!len64) return fail(SWX_ENOMEM, "device pool exhausted");
-  HIP_TRY(hipMemsetAsync(len64 + np, 0, 8, st));
-  HIP_TRY(lens_to_i64(np, cig_len, len64, st));
-  if ((rc = scan(ctx, len64, cig_off_final, np + 1))) return rc;
+  if (np <= kScanLensMax) {
+    HIP_TRY(scan_lens(np, cig_len, cig_off_final, st));
+  } else {
+    int64_t *len64 = A.get<int64_t>(np + 1);
+    if (!len64) return fail(SWX_ENOMEM, "device pool exhausted");
+    HIP_TRY(hipMemsetAsync(len64 + np, 0, 8, st));
+    HIP_TRY(lens_to_i64(np, cig_len, len64, st));
+    if ((rc = scan(ctx, len64, cig_off_final, np + 1))) return rc;
+  }
   int64_t total = 0;
   if ((rc = read_i64(ctx, cig_off_final + np, &total))) return rc;
   out->cigar_used = total;
@@ -909,6 +910,7 @@ struct LongPath {
   int64_t nlong = 0, nshort = 0;
   int64_t *d_long = nullptr;    // long pair ids (device)
   int64_t *d_short = nullptr;   // short pair ids (device; null: every pair is short)
+  uint8_t *is_long = nullptr, *is_short = nullptr;   // per pair (device)
   std::vector<int64_t> ids;     // long pair ids (host)
   std::vector<int64_t> info;    // gather_pairs fields per long pair
   std::vector<IntraPair> pairs;
@@ -939,11 +941,10 @@ static int pick_rl(int64_t rows, int n) {
 // average work per half would finish last -- it is faster spread over a wave.
 // A batch of few tasks runs each on four waves (cooperative strips), which
 // shortens a task's time about four times.
-static int64_t long_threshold(const swx_ctx *ctx, int64_t total_cells, int64_t npairs) {
-  if (ctx->long_cells >= 0) return ctx->long_cells;
-  const int64_t base = std::max<int64_t>(2048, 2 * total_cells / (2048 * 128));
+// (k_split_long computes it from the batch's cells; this is its factor.)
+static int64_t long_factor(const swx_ctx *ctx, int64_t npairs) {
   const int64_t tasks = (npairs + kSlots16 - 1) / kSlots16;
-  return coop_waves(ctx->fill_coop, tasks, ctx->cus) > 1 ? base * kCoopWaves : base;
+  return coop_waves(ctx->fill_coop, tasks, ctx->cus) > 1 ? kCoopWaves : 1;
 }
 
 static int code_bits(int64_t rows_padded) {
@@ -962,19 +963,13 @@ static int gather_info(swx_ctx *ctx, int64_t n, const int64_t *d_ids, const int3
   return read_i64(ctx, d, info.data(), 6 * n);
 }
 
-static int split_pairs(swx_ctx *ctx, int64_t np, const int32_t *qlen, const int64_t *rlen,
-                       int64_t total_cells, LongPath &lp) {
-  DevArena &A = ctx->arena;
-  uint8_t *fl = A.get<uint8_t>(np), *fs = A.get<uint8_t>(np);
-  if (!fl || !fs) return fail(SWX_ENOMEM, "device pool exhausted (split)");
-  HIP_TRY(split_long(np, qlen, rlen, long_threshold(ctx, total_cells, np), ctx->long_rlen, fl, fs,
-                     ctx->stream));
+// the long and the short pairs' lists, once their counts are known
+static int list_pairs(swx_ctx *ctx, int64_t np, LongPath &lp) {
+  if (lp.nlong == 0 || lp.d_long) return SWX_OK;
   int rc;
-  if ((rc = select_flagged(ctx, fl, np, &lp.d_long, &lp.nlong))) return rc;
-  lp.nshort = np - lp.nlong;
-  if (lp.nlong == 0) return SWX_OK;
-  const int64_t *nshort = nullptr;
-  return lp.nshort > 0 ? select_flagged_dev(ctx, fs, np, &lp.d_short, &nshort) : SWX_OK;
+  const int64_t *count = nullptr;
+  if ((rc = select_flagged_dev(ctx, lp.is_long, np, &lp.d_long, &count))) return rc;
+  return lp.nshort > 0 ? select_flagged_dev(ctx, lp.is_short, np, &lp.d_short, &count) : SWX_OK;
 }
 
 // the long pairs' ids and lengths on the host
@@ -1328,6 +1323,7 @@ static int plan_alone(swx_ctx *ctx, const Scoring &sc, int64_t np, uint32_t flag
     const int64_t need = 2 * kIntra16MinWavesPerCu * (int64_t)ctx->cus;
     w16 = lp.nlong >= need;
     if (!w16 && lp.nlong * ((max_r + 255) / 256) + 2 >= need) {
+      if ((rc = list_pairs(ctx, np, lp))) return rc;
       if ((rc = read_long(ctx, qlen, rlen, lp))) return rc;
       w16 = choose16(ctx, sc, lp);
     }
@@ -1340,6 +1336,7 @@ static int plan_alone(swx_ctx *ctx, const Scoring &sc, int64_t np, uint32_t flag
   al.max_q = (int32_t)max_q;
   al.maxcol = A.get<uint32_t>(al.count * max_r);
   if (!al.maxcol) return fail(SWX_ENOMEM, "device pool exhausted (max array)");
+  if ((!al.all || (lp.nlong > 0 && lp.nshort > 0 && !w16)) && (rc = list_pairs(ctx, np, lp))) return rc;
   if (!al.all) {
     al.ids = lp.d_long;
   } else if (lp.nlong > 0 && lp.nshort > 0 && !w16) {   // the long pairs first
@@ -1608,21 +1605,6 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
   int rc;
   HIP_TRY(hipEventRecord(ctx->ev[0], st));
 
-  // validation (before any alignment work)
-  uint32_t *d_bad = A.get<uint32_t>(1);
-  if (!d_bad) return fail(SWX_ENOMEM, "device pool exhausted");
-  HIP_TRY(hipMemsetAsync(d_bad, 0, sizeof(uint32_t), st));
-  ValidateArgs va{b.qcat, b.qcat_len, b.qoff, b.nq, b.rcat, b.rcat_len, b.roff, b.nr,
-                  b.pair_q, b.pair_r, np, sc.n, d_bad};
-  HIP_TRY(launch_validate(va, st));
-  uint32_t bad = 0;
-  HIP_TRY(hipMemcpyAsync(ctx->pinned, d_bad, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
-  HIP_TRY(wait_stream(st));
-  memcpy(&bad, ctx->pinned, sizeof(uint32_t));
-  if (bad & 1u) return fail(SWX_EINVAL, "offsets must be non-decreasing and within the code arrays");
-  if (bad & 2u) return fail(SWX_EINVAL, "pair index out of range");
-  if (bad & 12u) return fail(SWX_EINVAL, "symbol code outside [0, n)");
-
   // per-pair arrays
   int64_t *qstart = A.get<int64_t>(np), *rstart = A.get<int64_t>(np), *rlen = A.get<int64_t>(np);
   int32_t *qlen = A.get<int32_t>(np);
@@ -1631,22 +1613,45 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
   uint8_t *ovf = A.get<uint8_t>(np), *lanebits = A.get<uint8_t>(np), *err = A.get<uint8_t>(np);
   int32_t *qbeg = A.get<int32_t>(np), *score2 = A.get<int32_t>(np);
   int64_t *rbeg = A.get<int64_t>(np), *rend2 = A.get<int64_t>(np);
-  int64_t *stats = A.get<int64_t>(5);
+  // [0 .. 4] the views' statistics, [5] long pairs, [6] validation flags,
+  // [7] pairs that failed a consistency check
+  int64_t *stats = A.get<int64_t>(8);
+  LongPath lp;
+  lp.is_long = A.get<uint8_t>(np);
+  lp.is_short = A.get<uint8_t>(np);
   if (!qstart || !rstart || !rlen || !qlen || !score || !qend || !rend || !ovf || !lanebits ||
-      !err || !qbeg || !score2 || !rbeg || !rend2 || !stats)
+      !err || !qbeg || !score2 || !rbeg || !rend2 || !stats || !lp.is_long || !lp.is_short)
     return fail(SWX_ENOMEM, "device pool exhausted (pair arrays)");
-  HIP_TRY(hipMemsetAsync(err, 0, np, st));
-  HIP_TRY(hipMemsetAsync(lanebits, 16, np, st));
+  // Validation, views (clamped into the arrays whatever the input holds),
+  // statistics and the split into long and short pairs with one read at the
+  // end: nothing else runs before the input is known to be valid.  (Three
+  // reads and eight small launches more took 0.1 ms of a batch of 500.)
   {
-    const ViewCaps vc{b.nq, b.nr, b.qcat_len, b.rcat_len, INT32_MAX, 0, INT64_MAX};
-    HIP_TRY(launch_views(np, b.qoff, b.roff, b.pair_q, b.pair_r, vc, qstart, qlen, rstart, rlen,
-                         st));
+    FillSet fs{};
+    fs.add(stats, 8, 8, 0);
+    fs.add(err, np, 1, 0);
+    fs.add(lanebits, np, 1, 16);
+    HIP_TRY(fill_set(fs, st));
+    ValidateArgs va{b.qcat, b.qcat_len, b.qoff, b.nq, b.rcat, b.rcat_len, b.roff, b.nr,
+                    b.pair_q, b.pair_r, np, sc.n, (uint32_t *)(stats + 6)};
+    HIP_TRY(launch_validate(va, st));
+    if (b.nq >= 1 && b.nr >= 1) {   // (else every pair's index is out of range)
+      const ViewCaps vc{b.nq, b.nr, b.qcat_len, b.rcat_len, INT32_MAX, 0, INT64_MAX};
+      HIP_TRY(launch_views(np, b.qoff, b.roff, b.pair_q, b.pair_r, vc, qstart, qlen, rstart, rlen,
+                           stats, st));
+      HIP_TRY(split_long(np, qlen, rlen, ctx->long_cells, long_factor(ctx, np), ctx->long_rlen, stats,
+                         lp.is_long, lp.is_short, stats + 5, st));
+    }
   }
+  int64_t hstats[8];
+  if ((rc = read_i64(ctx, stats, hstats, 8))) return rc;
+  const uint32_t bad = (uint32_t)hstats[6];
+  if (bad & 1u) return fail(SWX_EINVAL, "offsets must be non-decreasing and within the code arrays");
+  if (bad & 2u) return fail(SWX_EINVAL, "pair index out of range");
+  if (bad & 12u) return fail(SWX_EINVAL, "symbol code outside [0, n)");
+  lp.nlong = hstats[5];
+  lp.nshort = np - lp.nlong;
   // a score can reach smax * min(qlen, rlen); the 32-bit lanes hold < 2^26
-  HIP_TRY(hipMemsetAsync(stats, 0, 8 * 5, st));
-  HIP_TRY(launch_pair_stats(np, qlen, rlen, stats, st));
-  int64_t hstats[5];
-  if ((rc = read_i64(ctx, stats, hstats, 5))) return rc;
   const int64_t score_bound = (int64_t)std::max(sc.smax, 0) * hstats[0];
   if (score_bound >= (1 << 26) - 1)
     return fail(SWX_EOVERFLOW, "a score could exceed the 32-bit lane range");
@@ -1690,10 +1695,9 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
   }
 
   // long pairs take the intra-sequence path, the rest the batched one
-  LongPath lp;
-  if ((rc = split_pairs(ctx, np, qlen, rlen, hstats[1], lp))) return rc;
   AlonePath al;
   if ((rc = plan_alone(ctx, sc, np, flags, hstats, qlen, rlen, lp, al))) return rc;
+  if (!al.on && (rc = list_pairs(ctx, np, lp))) return rc;
   auto long_forward = [&]() -> int {
     return al.on ? run_alone_forward(ctx, sc, al, score_bound, fview, fout, lanebits)
                  : run_intra_forward(ctx, sc, lp, fview, fout, err, lanebits);
@@ -1753,12 +1757,9 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
     if (!rqs || !rrs || !rrl || !rql || !tgt || !band || !band_q || !rsc || !rqe || !rre || !rov ||
         !f16 || !f32)
       return fail(SWX_ENOMEM, "device pool exhausted (reverse)");
-    HIP_TRY(launch_rev_views(np, qstart, rstart, qlen, rlen, score, qend, rend, rqs, rql, rrs,
-                             rrl, tgt, err, st));
-    HIP_TRY(rev_prepare(np, score, qend, rend, lanebits, sc.smax, sc.o, sc.e, band, band_q, f16,
-                        f32, st));
+    HIP_TRY(rev_setup(np, fview, score, qend, rend, lanebits, sc.smax, sc.o, sc.e,
+                      RevSetup{rqs, rrs, rrl, rql, tgt, band, band_q, rsc, f16, f32}, err, st));
     if (lp.nlong > 0 && lp.nshort > 0) HIP_TRY(clear_flags(lp.nlong, lp.d_long, f16, f32, st));
-    HIP_TRY(hipMemsetAsync(rsc, 0, sizeof(int32_t) * np, st));
     PairView rview{rqs, rrs, rql, rrl, b.qcat, b.rcat, 1};
     FillOut rout{rsc, rqe, rre, rov, err};
     // both lane widths' pair lists first, their counts in one read, so that
@@ -1823,8 +1824,6 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
   int64_t *cig_off_final = A.get<int64_t>(np + 1);
   int32_t *cig_len = A.get<int32_t>(np);
   if (!cig_off_final || !cig_len) return fail(SWX_ENOMEM, "device pool exhausted");
-  HIP_TRY(hipMemsetAsync(cig_len, 0, sizeof(int32_t) * np, st));
-  HIP_TRY(hipMemsetAsync(cig_off_final, 0, sizeof(int64_t) * (np + 1), st));
   int rc_range = SWX_OK;
   if (flags & SWX_CIGAR) {
     if ((rc = run_traceback(ctx, sc, b, np, hstats[0], score, qbeg, qend, rbeg, rend, qstart, rstart, qlen,
@@ -1937,8 +1936,6 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
     HIP_TRY(launch_sub_begins(np, score2, rend2, wqe, sfl, tgt, rsc, rqe, rre, s_score, s_qbeg,
                               s_qend, s_rbeg, s_rend, err, st));
     // CIGARs after the primaries (cigar_used holds their total even when they did not fit)
-    HIP_TRY(hipMemsetAsync(s_cig_len, 0, sizeof(int32_t) * np, st));
-    HIP_TRY(hipMemsetAsync(s_cig_off, 0, sizeof(int64_t) * (np + 1), st));
     const int64_t base = out->cigar_used;
     swx_batch_out so = *out;
     so.cigar = (out->cigar && base <= out->cigar_cap) ? out->cigar + base : nullptr;
@@ -1956,7 +1953,7 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
                                                          : A.get<swx_rec_dev>(np);
     if (!srec) return fail(SWX_ENOMEM, "device pool exhausted");
     HIP_TRY(launch_records(np, s_score, s_score, s_qbeg, s_qend, s_rbeg, s_rend, s_rend, s_cig_off,
-                           s_cig_len, slb, sflags, srec, st));
+                           s_cig_len, slb, sflags, srec, nullptr, nullptr, st));
     if (sflags & SWX_CIGAR) HIP_TRY(shift_cigar_offsets(np, base, srec, st));
     if (out->out_mem != SWX_MEM_DEVICE)
       HIP_TRY(hipMemcpyAsync(out->sub_recs, srec, sizeof(swx_rec) * np, hipMemcpyDeviceToHost, st));
@@ -1967,15 +1964,13 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
                                                        : A.get<swx_rec_dev>(np);
   if (!drec) return fail(SWX_ENOMEM, "device pool exhausted");
   HIP_TRY(launch_records(np, score, score2, qbeg, qend, rbeg, rend, rend2, cig_off_final, cig_len,
-                         lanebits, flags, drec, st));
+                         lanebits, flags, drec, err, stats + 7, st));
   if (out->out_mem != SWX_MEM_DEVICE && np)
     HIP_TRY(hipMemcpyAsync(out->recs, drec, sizeof(swx_rec) * np, hipMemcpyDeviceToHost, st));
   HIP_TRY(hipEventRecord(ctx->ev[7], st));
   // consistency: any per-pair error flag
-  HIP_TRY(hipMemsetAsync(stats, 0, 8, st));
-  HIP_TRY(launch_any_flag(np, err, stats, st));
   int64_t nerr = 0;
-  if ((rc = read_i64(ctx, stats, &nerr))) return rc;
+  if ((rc = read_i64(ctx, stats + 7, &nerr))) return rc;
   ctx->nstages = 7;
   for (int k = 0; k < 7; ++k) {
     float ms = 0.f;
@@ -2052,7 +2047,7 @@ struct GraphState {
   FixedPlan p16, p32, r16, r32;
   // traceback
   uint64_t *tk0, *tk1;
-  int64_t *tv0, *tv1, *ccap, *coff, *counts, *ranges, *len64, *cig_off_final;
+  int64_t *tv0, *tv1, *coff, *counts, *ranges, *len64, *cig_off_final;
   int64_t *tb_sorted = nullptr;
   void *tb_sort_tmp = nullptr;
   size_t tb_sort_bytes = 0;
@@ -2186,10 +2181,7 @@ static int fixed_issue(GraphState &g, hipStream_t st) {
     fs.add(g.err, B, 1, 0);
     fs.add(g.lanebits, B, 1, 32);
     if (!g.alone.on) fs.add(g.maxcol, B * g.RM, 4, 0);
-    fs.add(g.rsc, B, 4, 0);
-    fs.add(g.cig_len, B, 4, 0);
-    fs.add(g.cig_off_final, B + 1, 8, 0);
-    fs.add(g.len64 + B, 1, 8, 0);
+    fs.add(g.counts, 9, 8, 0);
     HIP_TRY(fill_set(fs, st));
   } else {
     HIP_TRY(fill_u8(4, (uint8_t *)g.bad, 0, st));
@@ -2204,7 +2196,7 @@ static int fixed_issue(GraphState &g, hipStream_t st) {
     const ViewCaps vc{g.cfg.nq_cap, g.cfg.nr_cap, g.cfg.qcat_cap, g.cfg.rcat_cap,
                       (int32_t)g.QM, 0, g.RM};
     HIP_TRY(launch_views(B, g.qoff, g.roff, g.pair_q, g.pair_r, vc, g.qstart, g.qlen, g.rstart,
-                         g.rlen, st));
+                         g.rlen, nullptr, st));
   }
   PairView fview{g.qstart, g.rstart, g.qlen, g.rlen, g.qcat, g.rcat, 0};
   FillOut fout{g.score, g.qend, g.rend, g.ovf, g.err};
@@ -2239,11 +2231,9 @@ static int fixed_issue(GraphState &g, hipStream_t st) {
     HIP_TRY(mark_lanes_dev(B, nw, g.ids, g.lanebits, 32, st));
   }
   if (flags & SWX_BEGIN) {
-    HIP_TRY(launch_rev_views(B, g.qstart, g.rstart, g.qlen, g.rlen, g.score, g.qend, g.rend, g.rqs,
-                             g.rql, g.rrs, g.rrl, g.tgt, g.err, st));
-    HIP_TRY(rev_prepare(B, g.score, g.qend, g.rend, g.lanebits, g.sc.smax, g.sc.o, g.sc.e, g.band,
-                        g.band_q, g.f16, g.f32, st));
-    if (!g.intra) HIP_TRY(fill_u8(4 * B, (uint8_t *)g.rsc, 0, st));
+    HIP_TRY(rev_setup(B, fview, g.score, g.qend, g.rend, g.lanebits, g.sc.smax, g.sc.o, g.sc.e,
+                      RevSetup{g.rqs, g.rrs, g.rrl, g.rql, g.tgt, g.band, g.band_q, g.rsc, g.f16, g.f32},
+                      g.err, st));
     PairView rview{g.rqs, g.rrs, g.rql, g.rrl, g.qcat, g.rcat, 1};
     FillOut rout{g.rsc, g.rqe, g.rre, g.rov, g.err};
     if (g.alone.on) {
@@ -2276,10 +2266,6 @@ static int fixed_issue(GraphState &g, hipStream_t st) {
     }
     HIP_TRY(launch_begins(B, g.score, g.qend, g.rend, g.rsc, g.rqe, g.rre, g.qbeg, g.rbeg, g.err, st));
   }
-  if (!g.intra) {
-    HIP_TRY(fill_u8(4 * B, (uint8_t *)g.cig_len, 0, st));
-    HIP_TRY(fill_i64(B + 1, g.cig_off_final, 0, st));
-  }
   if (flags & SWX_CIGAR) {
     TbArgs ta{};
     ta.score = g.score; ta.qbeg = g.qbeg; ta.qend = g.qend; ta.rbeg = g.rbeg; ta.rend = g.rend;
@@ -2290,10 +2276,8 @@ static int fixed_issue(GraphState &g, hipStream_t st) {
     ta.wave_cells = INT64_MAX;   // no host-planned wave traceback in a graph
     ta.cig = g.cscr;
     ta.cig_off = g.coff;
-    HIP_TRY(fill_i64(1, g.ccap + B, 0, st));
-    HIP_TRY(fill_i64(8, g.counts, 0, st));
-    HIP_TRY(tb_classify(ta, B, g.cls, g.tk0, g.tv0, g.ccap, g.counts, nullptr, st));
-    if ((rc = fixed_scan(g, g.ccap, g.coff, B + 1, st))) return rc;
+    if (!g.intra) HIP_TRY(fill_i64(9, g.counts, 0, st));
+    HIP_TRY(tb_classify(ta, B, g.cls, g.tk0, g.tv0, g.coff, g.counts, g.counts + 8, nullptr, st));
     if (g.tb_by_pairs) {
       TbPairs tp{};
       tp.cls = g.cls;
@@ -2331,11 +2315,15 @@ static int fixed_issue(GraphState &g, hipStream_t st) {
       HIP_TRY(tb_strip(tc, tasks, t.cap_tasks, g.tb_sorted, t.bnd, st));
     }
     }
-      if (!g.intra) HIP_TRY(fill_i64(1, g.len64 + B, 0, st));
+    if (B <= kScanLensMax) {
+      HIP_TRY(scan_lens(B, g.cig_len, g.cig_off_final, st));
+    } else {
+      HIP_TRY(fill_i64(1, g.len64 + B, 0, st));
       HIP_TRY(lens_to_i64(B, g.cig_len, g.len64, st));
       if ((rc = fixed_scan(g, g.len64, g.cig_off_final, B + 1, st))) return rc;
-      HIP_TRY(launch_cigar_compact(B, g.cscr, g.coff, g.cig_len, g.cig_off_final, g.cls, g.qbeg,
-                                   g.qend, g.cigar, st));
+    }
+    HIP_TRY(launch_cigar_compact(B, g.cscr, g.coff, g.cig_len, g.cig_off_final, g.cls, g.qbeg,
+                                 g.qend, g.cigar, st));
   }
   if ((flags & SWX_SCORE2) && g.intra) {
     IntraPairArgs e = alone_pairs(g.alone, g.qlen, g.rlen);
@@ -2360,8 +2348,7 @@ static int fixed_issue(GraphState &g, hipStream_t st) {
     }
   }
   HIP_TRY(launch_records(B, g.score, g.score2, g.qbeg, g.qend, g.rbeg, g.rend, g.rend2,
-                         g.cig_off_final, g.cig_len, g.lanebits, flags, g.recs, st));
-  HIP_TRY(launch_any_flag(B, g.err, g.status, st));
+                         g.cig_off_final, g.cig_len, g.lanebits, flags, g.recs, g.err, g.status, st));
   return SWX_OK;
 }
 
@@ -2396,9 +2383,8 @@ static int graph_alloc(GraphState &g) {
   g.ids = A.get<int64_t>(B);
   g.tk0 = A.get<uint64_t>(B);
   g.tk1 = A.get<uint64_t>(B);
-  g.ccap = A.get<int64_t>(B + 1);
-  g.coff = A.get<int64_t>(B + 1);
-  g.counts = A.get<int64_t>(8);
+  g.coff = A.get<int64_t>(B);
+  g.counts = A.get<int64_t>(9);
   g.ranges = A.get<int64_t>(16);
   g.len64 = A.get<int64_t>(B + 1);
   g.cig_off_final = A.get<int64_t>(B + 1);
@@ -2510,7 +2496,7 @@ static int graph_alloc(GraphState &g) {
   g.scan_tmp = A.alloc(g.scan_bytes);
   if (!g.qcat || !g.rcat || !g.qoff || !g.roff || !g.pair_q || !g.pair_r || !g.recs || !g.cigar ||
       !g.cscr || !g.bad || !g.status || !g.f64 || !g.pos || !g.ids || !g.tk0 || !g.tk1 ||
-      !g.ccap || !g.coff || !g.counts || !g.ranges || !g.len64 || !g.cig_off_final ||
+      !g.coff || !g.counts || !g.ranges || !g.len64 || !g.cig_off_final ||
       !g.tb_sort_tmp || !g.scan_tmp)
     return fail(SWX_ENOMEM, "device pool exhausted (graph)");
   return SWX_OK;

@@ -180,9 +180,11 @@ struct TbArgs {
 };
 
 // counts[c] (cleared by the caller) += pairs of class c, and with bytes (may be
-// null) bytes[c] += their scratch on the wave kernel (k_tb_pairs)
+// null) bytes[c] += their scratch on the wave kernel (k_tb_pairs).  coff[p]:
+// pair p's place among the *words CIGAR scratch words (cleared by the caller);
+// cig_len is preset (1 for flat pairs, else 0).
 hipError_t tb_classify(const TbArgs &a, int64_t npairs, uint8_t *cls, uint64_t *key, int64_t *vals,
-                       int64_t *ccap, int64_t *counts, int64_t *bytes, hipStream_t st);
+                       int64_t *coff, int64_t *counts, int64_t *words, int64_t *bytes, hipStream_t st);
 // Wave traceback planned on the device, a workgroup per pair: pairs
 // sorted[lo[x] .. lo[x] + cnt[x]) of each range, or (sorted null) every pair
 // by its class.  Scratch: stride bytes per block, or taken from cap bytes
@@ -237,10 +239,15 @@ hipError_t class_ranges(const int64_t *counts, int64_t *ranges, hipStream_t st);
 hipError_t sort_keys(int64_t n, uint64_t *keys, uint64_t *keys_alt, int64_t *vals,
                      int64_t *vals_alt, void *tmp, size_t *tmp_bytes, int64_t **sorted_out,
                      hipStream_t st, int end_bit = 64, bool graph = false);
-hipError_t rev_prepare(int64_t npairs, const int32_t *score, const int32_t *qend,
-                       const int64_t *rend, const uint8_t *lanebits, int32_t smax, int32_t o,
-                       int32_t e, int32_t *band, int32_t *band_q, uint8_t *f16, uint8_t *f32,
-                       hipStream_t st);
+// what the reversed pass takes of each pair, and its score's preset (k_rev_setup)
+struct RevSetup {
+  int64_t *qstart, *rstart, *rlen;
+  int32_t *qlen, *target, *band, *band_q, *score;
+  uint8_t *f16, *f32;
+};
+hipError_t rev_setup(int64_t npairs, const PairView &v, const int32_t *score, const int32_t *qend,
+                     const int64_t *rend, const uint8_t *lanebits, int32_t smax, int32_t o, int32_t e,
+                     const RevSetup &s, uint8_t *err, hipStream_t st);
 
 hipError_t inter_fill(const InterArgs &a, int lane_bits, int R, hipStream_t st);
 // keys[t] = padded rows x swept columns of task t (a banded task's window of R +
@@ -369,7 +376,8 @@ size_t intra_static_lds();
 hipError_t intra_end(const IntraPairArgs &a, int64_t npairs, hipStream_t st);
 hipError_t intra_score2(const IntraPairArgs &a, int64_t npairs, hipStream_t st);
 hipError_t split_long(int64_t n, const int32_t *qlen, const int64_t *rlen, int64_t cells_thr,
-                      int64_t rlen_thr, uint8_t *is_long, uint8_t *is_short, hipStream_t st);
+                      int64_t mult, int64_t rlen_thr, const int64_t *stats, uint8_t *is_long,
+                      uint8_t *is_short, int64_t *count, hipStream_t st);
 hipError_t gather_pairs(int64_t n, const int64_t *ids, const int32_t *qlen, const int64_t *rlen,
                         const int32_t *score, const int32_t *qend, const int64_t *rend,
                         const int32_t *band, int64_t *out, hipStream_t st);
@@ -383,13 +391,14 @@ hipError_t build_qprof(const int8_t *q, int32_t qlen, const int8_t *matrix, int3
                        int32_t qp, uint8_t *fwd, int64_t rev_row, uint8_t *rev, hipStream_t st);
 // bytes of a reversed row of the shared profile for strips of R rows
 inline int64_t qprof_rev_row(int64_t qlen, int R) { return (2 * qlen + 2 * R + 16 + 15) / 16 * 16; }
-hipError_t launch_pair_stats(int64_t n, const int32_t *qlen, const int64_t *rlen, int64_t *stats,
-                             hipStream_t st);
 hipError_t lens_to_i64(int64_t n, const int32_t *len, int64_t *out, hipStream_t st);
+// off[0 .. n] = exclusive prefix sums of len and their total, in one launch of
+// one block (n up to kScanLensMax)
+constexpr int64_t kScanLensMax = 65536;
+hipError_t scan_lens(int64_t n, const int32_t *len, int64_t *off, hipStream_t st);
 hipError_t mark_lanes(int64_t n, const int64_t *ids, uint8_t *lanebits, int v, hipStream_t st);
 hipError_t mark_lanes_dev(int64_t cap, const int64_t *n_dev, const int64_t *ids, uint8_t *lanebits,
                           int v, hipStream_t st);
-hipError_t launch_any_flag(int64_t n, const uint8_t *flag, int64_t *count, hipStream_t st);
 // bounds the views are clamped into (see k_views)
 struct ViewCaps {
   int64_t nq, nr, qcat_len, rcat_len;
@@ -399,12 +408,7 @@ struct ViewCaps {
 hipError_t launch_views(int64_t npairs, const int64_t *qoff, const int64_t *roff,
                         const int64_t *pair_q, const int64_t *pair_r, const ViewCaps &caps,
                         int64_t *qstart, int32_t *qlen, int64_t *rstart, int64_t *rlen,
-                        hipStream_t st);
-hipError_t launch_rev_views(int64_t npairs, const int64_t *qstart, const int64_t *rstart,
-                            const int32_t *qlen, const int64_t *rlen,
-                            const int32_t *score, const int32_t *qend, const int64_t *rend,
-                            int64_t *rqstart, int32_t *rqlen, int64_t *rrstart, int64_t *rrlen,
-                            int32_t *target, uint8_t *err, hipStream_t st);
+                        int64_t *stats, hipStream_t st);
 hipError_t launch_band_sizes(int64_t npairs, const int32_t *score, const int32_t *qbeg,
                              const int32_t *qend, const int64_t *rbeg, const int64_t *rend,
                              const int32_t *qlen, const int64_t *rlen, const uint8_t *only,
@@ -437,11 +441,12 @@ hipError_t launch_score2_plain(int64_t p, const int32_t *maxcol, int64_t lr, con
                                const int64_t *rbeg, const int64_t *rend, int32_t mask_len,
                                const int32_t *qlen, int32_t *score2, int64_t *rend2,
                                hipStream_t st);
+// err (may be null): *nerr += the pairs whose flag is set
 hipError_t launch_records(int64_t npairs, const int32_t *score1, const int32_t *score2,
                           const int32_t *qbeg, const int32_t *qend, const int64_t *rbeg,
                           const int64_t *rend, const int64_t *rend2, const int64_t *cig_off,
                           const int32_t *cig_len, const uint8_t *lane_bits, uint32_t flags,
-                          swx_rec_dev *recs, hipStream_t st);
+                          swx_rec_dev *recs, const uint8_t *err, int64_t *nerr, hipStream_t st);
 // the suboptimal alignment: window views, anchored reversed views, begins,
 // and CIGAR offsets of records counted from the arena's start
 hipError_t launch_sub_window(int64_t npairs, const int64_t *rstart, const int32_t *qlen,

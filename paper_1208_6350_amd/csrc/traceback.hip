@@ -122,10 +122,11 @@ __device__ __forceinline__ int32_t diagonal_sum(const int8_t *q, const int8_t *r
 }
 
 __global__ __launch_bounds__(256) void k_tb_classify(TbArgs a, int64_t npairs, uint8_t *cls,
-                                                     uint64_t *key, int64_t *vals, int64_t *ccap,
-                                                     int64_t *counts, int64_t *bytes) {
+                                                     uint64_t *key, int64_t *vals, int64_t *coff,
+                                                     int64_t *counts, int64_t *words, int64_t *bytes) {
   __shared__ int8_t s_mat[32 * 32];
   __shared__ unsigned long long s_cnt[8], s_bytes[8];
+  __shared__ int64_t s_words[5];   // CIGAR scratch words of the waves, and where the block's begin
   for (int k = threadIdx.x; k < 32 * 32; k += blockDim.x) {
     const int qc = k / 32, rc = k % 32;
     s_mat[k] = qc < a.n && rc < a.n ? a.matrix[qc * a.n + rc] : (int8_t)0;
@@ -133,10 +134,11 @@ __global__ __launch_bounds__(256) void k_tb_classify(TbArgs a, int64_t npairs, u
   if (threadIdx.x < 8) s_cnt[threadIdx.x] = s_bytes[threadIdx.x] = 0;
   __syncthreads();
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < npairs; p += stride) {
+  for (int64_t p0 = (int64_t)blockIdx.x * blockDim.x; p0 < npairs; p0 += stride) {
+    const int64_t p = p0 + threadIdx.x;
     uint8_t c = 0;
     int64_t m = 0, w = 0, bw = 0, dlo = 0;
-    const int32_t s1 = a.score[p];
+    const int32_t s1 = p < npairs ? a.score[p] : 0;
     if (s1 > 0) {
       if (tb_coords_ok(a, p)) {
         m = a.qend[p] - a.qbeg[p] + 1;
@@ -160,7 +162,28 @@ __global__ __launch_bounds__(256) void k_tb_classify(TbArgs a, int64_t npairs, u
         a.err[p] = 1;
       }
     }
+    // the scratch words of the block's pairs: one place in the buffer for all
+    // of them (no prefix sum over the batch, which took three launches)
+    const int64_t need = (c != 0 && c != kTbFlat) ? (m + w + 2) : 0;
+    int64_t before = need;   // inclusive sum over the wave's lanes
+    for (int off = 1; off < 64; off <<= 1) {
+      const int64_t u = __shfl_up(before, off, 64);
+      if ((int)(threadIdx.x & 63) >= off) before += u;
+    }
+    const int wv = (int)(threadIdx.x >> 6);
+    if ((threadIdx.x & 63) == 63) s_words[wv] = before;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      const int64_t all = s_words[0] + s_words[1] + s_words[2] + s_words[3];
+      s_words[4] = all ? (int64_t)atomicAdd((unsigned long long *)words, (unsigned long long)all) : 0;
+    }
+    __syncthreads();
+    int64_t at = s_words[4] + before - need;
+    for (int k = 0; k < wv; ++k) at += s_words[k];
+    __syncthreads();   // (before the next round's sums)
+    if (p >= npairs) continue;
     cls[p] = c;
+    coff[p] = at;
     // class, then rows (clamped: only the grouping of similar heights matters);
     // wide bands (16 pairs share a task's column window, the union of their
     // bands) by rows in steps of 16, then lowest and highest diagonal, so that
@@ -174,8 +197,7 @@ __global__ __launch_bounds__(256) void k_tb_classify(TbArgs a, int64_t npairs, u
     }
     key[p] = ((uint64_t)c << (kTbKeyBits - 3)) | sub;
     vals[p] = p;
-    ccap[p] = (c != 0 && c != kTbFlat) ? (m + w + 2) : 0;
-    if (c == kTbFlat) a.cig_len[p] = 1;
+    a.cig_len[p] = c == kTbFlat ? 1 : 0;
     if (bytes && c >= 1 && c <= 5) {   // too tall for the wave kernel's strips: more than any scratch
       const bool fits = (m + 64 * kTbPairRows - 1) / (64 * kTbPairRows) <= kTbMaxStripsDecl;
       atomicAdd(&s_bytes[c], (unsigned long long)(fits ? tb_pair_bytes(m, w, dlo, bw) : int64_t(1) << 40));
@@ -560,11 +582,11 @@ __global__ __launch_bounds__(256) void k_tb_band(TbArgs a, const TbTask *tasks, 
 static inline unsigned nblk(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 
 hipError_t tb_classify(const TbArgs &a, int64_t npairs, uint8_t *cls, uint64_t *key, int64_t *vals,
-                       int64_t *ccap, int64_t *counts, int64_t *bytes, hipStream_t st) {
+                       int64_t *coff, int64_t *counts, int64_t *words, int64_t *bytes, hipStream_t st) {
   if (!npairs) return hipSuccess;
   // at most 8 blocks per compute unit: each adds its class counts once
   hipLaunchKernelGGL(k_tb_classify, dim3(std::min(nblk(npairs, 256), 2048u)), dim3(256), 0, st, a, npairs, cls, key,
-                     vals, ccap, counts, bytes);
+                     vals, coff, counts, words, bytes);
   return hipGetLastError();
 }
 
