@@ -1635,15 +1635,17 @@ __global__ __launch_bounds__(64) void k_tb_walk(TbArgs a, const TbWaveJob *jobs,
 template <int RL, int TILE>
 __device__ void tb_wave_walk(const TbArgs &a, const TbWaveJob &jb, const uint8_t *dir,
                              uint4 *s_tile, int lane) {
-  constexpr int64_t SH = 64 * RL;
+  constexpr int32_t SH = 64 * RL;
   constexpr int WB = RL / 2;
   constexpr int TS = TILE / (64 * WB);
-  const int64_t p = jb.pair, m = jb.m, w = jb.w;
+  const int64_t p = jb.pair;
+  // (a column's codes take 128 bytes and more: rows and columns fit 32 bits)
+  const int32_t m = (int32_t)jb.m, w = (int32_t)jb.w;
   const int32_t o = a.o, e = a.e;
-  const int64_t nstrips = (m + SH - 1) / SH;
-  auto strip_base = [&](int64_t s) {
+  const int32_t nstrips = (m + SH - 1) / SH;
+  auto strip_base = [&](int32_t s) {
     int64_t off = 0;
-    for (int64_t k = 0; k < s; ++k) {
+    for (int32_t k = 0; k < s; ++k) {
       int64_t lo, hi;
       tbw_window(k, SH, jb.dlo, jb.bw, w, &lo, &hi);
       off += ((hi - lo) + 63) * 64 * WB;
@@ -1653,16 +1655,20 @@ __device__ void tb_wave_walk(const TbArgs &a, const TbWaveJob &jb, const uint8_t
 
   // ---- walk back from (m, w) in state H (rule T3), uniform on the wave ------
   // Each iteration places the walk in a strip and a tile of its codes and
-  // follows one run of the path (below).
+  // follows one run of the path and the gap step after it (below).  Bound by
+  // the latency of an iteration's instructions and its one LDS read; with the
+  // gap step in an iteration of its own and 64-bit coordinates the walk of
+  // 10,000 rows at 10% errors took 1.24 ms, now TBD.
   uint32_t *out = a.cig + a.cig_off[p];
   int32_t nruns = 0;
-  int64_t i = m, j = w;
+  int32_t i = m, j = w;
   int state = 0;
   uint32_t cur_op = 0xFF, cur_len = 0;
-  int64_t guard = 2 * (m + w) + 4;
-  int64_t ws = nstrips;          // strip whose codes start at wbase
-  int64_t wbase = strip_base(nstrips), wclo = 0, wchi = 0;
-  int64_t tile_s = -1, tile_lo = 0, tile_hi = -1;
+  int64_t guard = 2 * ((int64_t)m + w) + 4;
+  int32_t ws = nstrips;          // strip whose codes start at wbase
+  int64_t wbase = strip_base(nstrips);
+  int32_t wclo = 0, wchi = 0;
+  int32_t tile_s = -1, tile_lo = 0, tile_hi = -1;
   const uint8_t *tile = reinterpret_cast<const uint8_t *>(s_tile);
   bool bad = false;
   auto emit_run = [&](uint32_t op, uint32_t len) {
@@ -1691,23 +1697,26 @@ __device__ void tb_wave_walk(const TbArgs &a, const TbWaveJob &jb, const uint8_t
       }
       continue;
     }
-    const int64_t s = (i - 1) / SH;
+    const int32_t s = (i - 1) / SH;
     while (ws > s) {   // step the strip cursor up (the walk only moves up)
       --ws;
-      tbw_window(ws, SH, jb.dlo, jb.bw, w, &wclo, &wchi);
-      wbase -= ((wchi - wclo) + 63) * 64 * WB;
+      int64_t lo, hi;
+      tbw_window(ws, SH, jb.dlo, jb.bw, w, &lo, &hi);
+      wclo = (int32_t)lo;
+      wchi = (int32_t)hi;
+      wbase -= ((hi - lo) + 63) * 64 * WB;
     }
     if (j < wclo || j >= wchi) { bad = true; break; }
-    const int64_t x = (i - 1) - s * SH;
-    int L = (int)(x / RL), rr = (int)(x % RL);
-    const int64_t t = (j - wclo) + L;
+    const int xi = (i - 1) - s * SH;   // the current row in the strip
+    const int jw = j - wclo;           // the current column in the window
+    const int32_t t = jw + xi / RL;
     if (s != tile_s || t < tile_lo || t > tile_hi) {
       tile_s = s;
       tile_hi = t;
       tile_lo = t >= TS - 1 ? t - (TS - 1) : 0;
       // steps [tile_lo, tile_hi] are contiguous: 16 bytes per lane and load
-      const uint4 *src = reinterpret_cast<const uint4 *>(dir + wbase + tile_lo * 64 * WB);
-      const int nv = (int)((tile_hi - tile_lo + 1) * 64 * WB / 16);
+      const uint4 *src = reinterpret_cast<const uint4 *>(dir + wbase + (int64_t)tile_lo * 64 * WB);
+      const int nv = (tile_hi - tile_lo + 1) * 64 * WB / 16;
       __builtin_amdgcn_wave_barrier();
       for (int v = lane; v < nv; v += 64) s_tile[v] = src[v];
       __asm__ volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
@@ -1717,14 +1726,12 @@ __device__ void tb_wave_walk(const TbArgs &a, const TbWaveJob &jb, const uint8_t
     // k-th cell along the run's direction (diagonal for M, left for D, up for
     // I; invalid past the strip's top, the window's left edge or the tile),
     // and a ballot finds where the run ends.  In state H the diagonal run
-    // continues while a cell's code names the diagonal; a cell that names E
+    // continues while a cell's code names the diagonal; the cell that names E
     // or F takes that gap step at once (same code); a gap run continues while
     // a cell's code extends the gap, the cell that does not still taking its
     // step.  A run cut short by an unreadable cell resumes in the next
     // iteration, after the strip cursor and the tile have moved.
-    const int jw = (int)(j - wclo);    // the current column in the window
-    const int xi = (int)x;             // the current row in the strip
-    const int tlo = (int)tile_lo;
+    const int tlo = tile_lo;
     auto lane_code = [&](int drow, int dcol, bool &valid) -> uint32_t {
       const int xr = xi - lane * drow, jc = jw - lane * dcol;
       const int xq = xr < 0 ? 0 : xr;
@@ -1747,18 +1754,30 @@ __device__ void tb_wave_walk(const TbArgs &a, const TbWaveJob &jb, const uint8_t
       bool v;
       const uint32_t ck = lane_code(1, 1, v);
       const int K = first_false(v && (ck & kCodeNotM) == 0 && j - lane > 0);
+      const unsigned long long readable = __ballot(v);
       if (K > 0) {
         emit_run(0u, (uint32_t)K);
         i -= K;
         j -= K;
         guard -= K;
+        if (K == 64 || !((readable >> K) & 1ull) || i == 0) continue;
+      }
+      // this cell leaves the diagonal: its code names E or F (at column 0 the
+      // path can only go up)
+      const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)ck, K);
+      const uint32_t src = code_src(c);
+      state = src == 0 ? 2 : (int)src;
+      const bool left = state == 1;
+      if (left && j <= 0) { bad = true; break; }
+      const bool longer = (c & (left ? kCodeEExt : kCodeFExt)) != 0;
+      if (!longer || K > 0) {   // (a longer gap from the first cell read: below)
+        if (!longer) state = 0;
+        emit_run(left ? 2u : 1u, 1u);
+        if (left) --j;
+        else --i;
+        --guard;
         continue;
       }
-      // the current cell (lane 0, always readable here) leaves the diagonal:
-      // its code names E or F (at column 0 the path can only go up)
-      const uint32_t c0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)ck);
-      const uint32_t src = code_src(c0);
-      state = src == 0 ? 2 : (int)src;
     }
     const bool left = state == 1;
     bool v;
