@@ -1086,17 +1086,20 @@ constexpr int kTbMaxWaves = 8;
 constexpr int64_t kTbSpinLimit = int64_t(1) << 26;
 constexpr int kTbTileBytes = 32768;
 
-// RL score bytes of the LDS profile as RL/4 words
+// RL score bytes of the LDS profile in words
+constexpr int tb_prof_words(int RL) { return RL >= 4 ? RL / 4 : 1; }
 template <int RL>
-__device__ __forceinline__ void tb_prof_load(const int8_t *src, uint32_t (&w)[RL / 4]) {
+__device__ __forceinline__ void tb_prof_load(const int8_t *src, uint32_t (&w)[tb_prof_words(RL)]) {
   if constexpr (RL == 16) {
     const uint4 v = *reinterpret_cast<const uint4 *>(src);
     w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
   } else if constexpr (RL == 8) {
     const uint2 v = *reinterpret_cast<const uint2 *>(src);
     w[0] = v.x; w[1] = v.y;
-  } else {
+  } else if constexpr (RL == 4) {
     w[0] = *reinterpret_cast<const uint32_t *>(src);
+  } else {
+    w[0] = *reinterpret_cast<const uint16_t *>(src);
   }
 }
 
@@ -1351,7 +1354,9 @@ __global__ __launch_bounds__(64 * kTbMaxWaves) void k_tb_wave(TbArgs a, const Tb
 // is the intra-sequence fill's (k_intra_spread): one 64-bit word per column,
 // valid << 63 | (F + 2^30) << 32 | (H + 2^30), its own flag, 16 columns at a
 // time, read a block ahead; cleared before the launch.  Bound by the chain of
-// strips: a 10,000-row alignment inside its band 3.7 -> 2.5 ms.
+// strips: a 10,000-row alignment inside its band 3.7 -> 2.5 ms on four rows a
+// lane, 2.27 on two (a strip starts its height and 110 steps after the one
+// above: 79 of them take 23,000 shorter steps instead of 40 taking 18,600).
 constexpr int kTbSpreadBlock = 16;
 constexpr int kTbSpreadMaxWaves = 4;
 constexpr uint64_t kTbWordValid = 1ull << 63;
@@ -1373,6 +1378,7 @@ __global__ __launch_bounds__(64 * kTbSpreadMaxWaves) void k_tb_spread(TbArgs a, 
                                                                       int32_t *bndbuf) {
   constexpr int64_t SH = 64 * RL;
   constexpr int WB = RL / 2;                      // code bytes per lane and step
+  constexpr int XW = tb_prof_words(RL);
   constexpr int kUnroll = RL <= 4 ? kTbSpreadBlock : 4;
   constexpr int AGENT = __HIP_MEMORY_SCOPE_AGENT;
   extern __shared__ uint4 s_dyn[];                // per wave: profile [(n+1)][64][RL] score bytes
@@ -1447,17 +1453,21 @@ __global__ __launch_bounds__(64 * kTbSpreadMaxWaves) void k_tb_spread(TbArgs a, 
         qv[k] = (i <= m) ? (int32_t)q[i - 1] : -1;
       }
       for (int sy = 0; sy <= n; ++sy) {
-        uint32_t wv[RL / 4];
+        uint32_t wv[XW];
 #pragma unroll
-        for (int k = 0; k < RL / 4; ++k) wv[k] = 0u;
+        for (int k = 0; k < XW; ++k) wv[k] = 0u;
 #pragma unroll
         for (int k = 0; k < RL; ++k) {
           const uint32_t b = (qv[k] >= 0 && sy < n) ? (uint32_t)(uint8_t)s_mat[qv[k] * n + sy] : 0u;
           wv[k >> 2] |= b << (8 * (k & 3));
         }
-        uint32_t *dst = reinterpret_cast<uint32_t *>(s_prof + ((int64_t)sy * 64 + lane) * RL);
+        int8_t *dst = s_prof + ((int64_t)sy * 64 + lane) * RL;
+        if constexpr (RL == 2) {
+          *reinterpret_cast<uint16_t *>(dst) = (uint16_t)wv[0];
+        } else {
 #pragma unroll
-        for (int k = 0; k < RL / 4; ++k) dst[k] = wv[k];
+          for (int k = 0; k < XW; ++k) reinterpret_cast<uint32_t *>(dst)[k] = wv[k];
+        }
       }
     }
     __asm__ volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -1485,7 +1495,7 @@ __global__ __launch_bounds__(64 * kTbSpreadMaxWaves) void k_tb_spread(TbArgs a, 
       return (lane < kTbSpreadBlock && c < chi && c >= 1) ? (int32_t)(uint8_t)r[c - 1] : n;
     };
     uint32_t sym = (uint32_t)tb_from_above(n, __builtin_amdgcn_readlane(symbols(clo), 0));
-    uint32_t X[RL / 4];
+    uint32_t X[XW];
     tb_prof_load<RL>(s_prof + ((int64_t)sym * 64 + lane) * RL, X);
     int32_t symnext = symbols(clo + 1);
     uint64_t wnext = fetch(clo, kTbSpreadBlock);
@@ -1506,7 +1516,7 @@ __global__ __launch_bounds__(64 * kTbSpreadMaxWaves) void k_tb_spread(TbArgs a, 
         const int32_t hup = tb_from_above(hout, __builtin_amdgcn_readlane(hbuf, tm));
         int32_t fup = tb_from_above(fout, __builtin_amdgcn_readlane(fbuf, tm));
         const uint32_t symn = (uint32_t)tb_from_above((int32_t)sym, __builtin_amdgcn_readlane(symbuf, tm));
-        uint32_t Xn[RL / 4];
+        uint32_t Xn[XW];
         tb_prof_load<RL>(s_prof + ((int64_t)symn * 64 + lane) * RL, Xn);
         int32_t hdiag = hup_prev;
         int32_t hcur = hup;
@@ -1536,12 +1546,13 @@ __global__ __launch_bounds__(64 * kTbSpreadMaxWaves) void k_tb_spread(TbArgs a, 
         fout = fup;
         sym = symn;
 #pragma unroll
-        for (int k = 0; k < RL / 4; ++k) X[k] = Xn[k];
+        for (int k = 0; k < XW; ++k) X[k] = Xn[k];
         if (tm < left) {
           const int64_t t = t0 + tm;
           if constexpr (RL == 16) reinterpret_cast<uint2 *>(dstrip)[t * 64 + lane] = make_uint2(dw[0], dw[1]);
           else if constexpr (RL == 8) reinterpret_cast<uint32_t *>(dstrip)[t * 64 + lane] = dw[0];
-          else reinterpret_cast<uint16_t *>(dstrip)[t * 64 + lane] = (uint16_t)dw[0];
+          else if constexpr (RL == 4) reinterpret_cast<uint16_t *>(dstrip)[t * 64 + lane] = (uint16_t)dw[0];
+          else dstrip[t * 64 + lane] = (uint8_t)dw[0];
         }
         obH = tb_shift_in(obH, hout);
         obF = tb_shift_in(obF, fout);
@@ -1638,6 +1649,7 @@ __device__ void tb_wave_walk(const TbArgs &a, const TbWaveJob &jb, const uint8_t
   constexpr int32_t SH = 64 * RL;
   constexpr int WB = RL / 2;
   constexpr int TS = TILE / (64 * WB);
+  static_assert(TILE % (8 * 64 * 16) == 0, "whole rounds of loads");
   const int64_t p = jb.pair;
   // (a column's codes take 128 bytes and more: rows and columns fit 32 bits)
   const int32_t m = (int32_t)jb.m, w = (int32_t)jb.w;
@@ -1658,7 +1670,8 @@ __device__ void tb_wave_walk(const TbArgs &a, const TbWaveJob &jb, const uint8_t
   // follows one run of the path and the gap step after it (below).  Bound by
   // the latency of an iteration's instructions and its one LDS read; with the
   // gap step in an iteration of its own and 64-bit coordinates the walk of
-  // 10,000 rows at 10% errors took 1.24 ms, now TBD.
+  // 10,000 rows at 10% errors took 1.24 ms; with its tiles loaded eight words a
+  // lane at a time and the runs turned round by all lanes besides, 0.43.
   uint32_t *out = a.cig + a.cig_off[p];
   int32_t nruns = 0;
   int32_t i = m, j = w;
@@ -1718,7 +1731,15 @@ __device__ void tb_wave_walk(const TbArgs &a, const TbWaveJob &jb, const uint8_t
       const uint4 *src = reinterpret_cast<const uint4 *>(dir + wbase + (int64_t)tile_lo * 64 * WB);
       const int nv = (tile_hi - tile_lo + 1) * 64 * WB / 16;
       __builtin_amdgcn_wave_barrier();
-      for (int v = lane; v < nv; v += 64) s_tile[v] = src[v];
+      // (eight loads in flight, past the end the last one again: one at a time
+      // they took half of the walk)
+      for (int v0 = lane; v0 < nv; v0 += 8 * 64) {
+        uint4 x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = src[v0 + 64 * u < nv ? v0 + 64 * u : nv - 1];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s_tile[v0 + 64 * u] = x[u];
+      }
       __asm__ volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
       __builtin_amdgcn_wave_barrier();
     }
@@ -1739,7 +1760,9 @@ __device__ void tb_wave_walk(const TbArgs &a, const TbWaveJob &jb, const uint8_t
       const int tk = jc + Lk - tlo;
       valid = xr >= 0 && jc >= 0 && tk >= 0;
       const uint8_t *wp = tile + (((valid ? tk : 0) * 64 + Lk) * WB);
-      if constexpr (RL == 4) {
+      if constexpr (RL == 2) {
+        return ((uint32_t)*wp >> (4 * (1 - rk))) & 0xFu;
+      } else if constexpr (RL == 4) {
         return ((uint32_t)*reinterpret_cast<const uint16_t *>(wp) >> (4 * (3 - rk))) & 0xFu;
       } else {
         const uint32_t dv = reinterpret_cast<const uint32_t *>(wp)[rk >> 3];
@@ -1794,13 +1817,22 @@ __device__ void tb_wave_walk(const TbArgs &a, const TbWaveJob &jb, const uint8_t
     else i -= moves;
     guard -= moves;
   }
-  if (lane != 0) return;
-  if (bad || i != 0 || j != 0) a.err[p] = 1;
-  if (cur_len) out[nruns++] = (cur_len << 4) | cur_op;
-  for (int32_t x = 0, y = nruns - 1; x < y; ++x, --y) {
-    const uint32_t t = out[x]; out[x] = out[y]; out[y] = t;
+  if (lane == 0) {
+    if (bad || i != 0 || j != 0) a.err[p] = 1;
+    if (cur_len) out[nruns] = (cur_len << 4) | cur_op;
   }
-  a.cig_len[p] = nruns;
+  if (cur_len) ++nruns;
+  if (lane == 0) a.cig_len[p] = nruns;
+  // the runs, last first so far, turned round by the whole wave (one lane alone
+  // waited for a load per run)
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  for (int32_t x = lane; x < nruns / 2; x += 64) {
+    const int32_t y = nruns - 1 - x;
+    const uint32_t t = out[x];
+    out[x] = out[y];
+    out[y] = t;
+  }
 }
 
 int tb_wave_waves(int64_t m, int n, int RL) {
@@ -1818,12 +1850,12 @@ template <int RL>
 static void launch_tb_wave(const TbArgs &a, const TbWaveJob *jobs, int64_t njobs, int waves,
                            int segs, IntraSync *sync, uint8_t *dirw, int32_t *bnd, hipStream_t st) {
   const size_t lds = (size_t)(a.n + 1) * 64 * RL * waves;
-  if (segs > 1) {
+  if (RL == 2 || segs > 1) {   // (two rows per lane: spread pairs only)
     const dim3 g((unsigned)(8 * segs * ((njobs + 7) / 8)));
     hipLaunchKernelGGL(k_tb_spread<RL>, g, dim3(64 * waves), lds, st, a, jobs, njobs, segs, sync,
                        dirw, bnd);
     hipLaunchKernelGGL(k_tb_walk<RL>, dim3((unsigned)njobs), dim3(64), 0, st, a, jobs, dirw);
-  } else {
+  } else if constexpr (RL != 2) {
     hipLaunchKernelGGL(k_tb_wave<RL>, dim3((unsigned)njobs), dim3(64 * waves), lds, st, a, jobs,
                        dirw, bnd);
   }
@@ -1839,6 +1871,10 @@ hipError_t tb_wave(const TbArgs &a, const TbWaveJob *jobs, int64_t njobs, int RL
     if (e != hipSuccess) return e;
   }
   switch (RL) {
+    case 2:
+      if (segs < 2) return hipErrorInvalidValue;
+      launch_tb_wave<2>(a, jobs, njobs, waves, segs, sync, dirw, bnd, st);
+      break;
     case 4: launch_tb_wave<4>(a, jobs, njobs, waves, segs, sync, dirw, bnd, st); break;
     case 8: launch_tb_wave<8>(a, jobs, njobs, waves, segs, sync, dirw, bnd, st); break;
     case 16: launch_tb_wave<16>(a, jobs, njobs, waves, segs, sync, dirw, bnd, st); break;

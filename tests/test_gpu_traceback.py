@@ -81,3 +81,24 @@ def test_pair_per_workgroup(ctx, m, alphabet):
 def test_traceback_routes_by_batch_size(ctx, npairs):
     b = W.config4(npairs=npairs)
     assert_parity(ctx, b)
+
+
+# the walk reads 64 cells of a run at a time: runs of matches and gaps around
+# that length, gaps behind a run and behind another gap, at both tile sizes
+# (long pairs alone spread over workgroups, short strips and tall ones)
+@pytest.mark.parametrize("total", [300, 1500, 5000])
+@pytest.mark.parametrize("gaps", [(3, 1), (6, 0)])
+def test_walk_runs(ctx, total, gaps):
+    g = np.random.Generator(np.random.PCG64(6000 + total))
+    qs, rs = [], []
+    for k in range(12 if total < 5000 else 3):
+        q, r = [], []
+        while sum(map(len, q)) < total:
+            core = g.integers(0, 4, int(g.choice([1, 2, 31, 63, 64, 65, 127, 128, 129])))
+            q.append(core)
+            r.append(core)
+            for side in (q, r) if g.random() < 0.2 else ((q,), (r,))[int(g.integers(0, 2))]:
+                side.append(g.integers(0, 4, int(g.choice([1, 1, 1, 2, 3, 63, 64, 65]))))
+        qs.append(np.concatenate(q).astype(np.int8))
+        rs.append(np.concatenate(r).astype(np.int8))
+    assert_parity(ctx, W.from_lists(f"walk-{total}", W.dna_matrix(), *gaps, qs, rs))
