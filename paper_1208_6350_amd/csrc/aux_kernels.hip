@@ -662,6 +662,68 @@ hipError_t fill_set(const FillSet &f, hipStream_t st) {
   return hipGetLastError();
 }
 
+// Bound by the host link; 16 bytes a thread.  (A pageable hipMemcpyAsync per
+// array took 8-20 us each, whatever its size.)
+__global__ __launch_bounds__(256) void k_copy_set(CopySet c) {
+  const int64_t gs = (int64_t)gridDim.x * blockDim.x;
+  for (int k = 0; k < c.count; ++k) {
+    const uint4 *s = static_cast<const uint4 *>(c.src[k]);
+    uint4 *d = static_cast<uint4 *>(c.dst[k]);
+    const int64_t n = c.bytes[k] / 16, t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (int64_t i = t; i < n; i += gs) d[i] = s[i];
+    if (16 * n + t < c.bytes[k])   // (fewer bytes than a block has threads)
+      static_cast<uint8_t *>(c.dst[k])[16 * n + t] = static_cast<const uint8_t *>(c.src[k])[16 * n + t];
+  }
+}
+
+hipError_t copy_set(const CopySet &c, hipStream_t st) {
+  if (c.count < 0 || c.count > kCopySetMax) return hipErrorInvalidValue;
+  int64_t most = 0;
+  for (int k = 0; k < c.count; ++k) {
+    if (((uintptr_t)c.src[k] | (uintptr_t)c.dst[k]) & 15) return hipErrorInvalidValue;
+    most = std::max(most, c.bytes[k]);
+  }
+  if (most == 0) return hipSuccess;
+  const unsigned blocks = (unsigned)std::min<int64_t>(512, (most + 4095) / 4096);
+  hipLaunchKernelGGL(k_copy_set, dim3(blocks), dim3(256), 0, st, c);
+  return hipGetLastError();
+}
+
+__global__ __launch_bounds__(256) void k_publish(const int64_t *a, int64_t na, const int64_t *b,
+                                                 int64_t nb, int64_t *dst, uint64_t *flag,
+                                                 uint64_t seq) {
+  for (int64_t k = threadIdx.x; k < na + nb; k += blockDim.x) dst[k] = k < na ? a[k] : b[k - na];
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x == 0) __hip_atomic_store(flag, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+hipError_t publish(const int64_t *a, int64_t na, const int64_t *b, int64_t nb, int64_t *dst,
+                   uint64_t *flag, uint64_t seq, hipStream_t st) {
+  hipLaunchKernelGGL(k_publish, dim3(1), dim3(na + nb <= 64 ? 64 : 256), 0, st, a, na, b, nb, dst, flag, seq);
+  return hipGetLastError();
+}
+
+__global__ __launch_bounds__(256) void k_graph_out(int64_t npairs, const swx_rec_dev *recs,
+                                                   const uint32_t *cigar, const int64_t *off,
+                                                   int64_t cap, swx_rec_dev *hrecs, uint32_t *hcigar,
+                                                   int64_t *total) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t gs = (int64_t)gridDim.x * blockDim.x;
+  const int64_t words = off ? off[npairs] : 0;
+  for (int64_t k = t; k < npairs; k += gs) hrecs[k] = recs[k];
+  for (int64_t k = t; k < words && k < cap; k += gs) hcigar[k] = cigar[k];
+  if (t == 0) *total = words;
+}
+
+hipError_t graph_out(int64_t npairs, const swx_rec_dev *recs, const uint32_t *cigar, const int64_t *off,
+                     int64_t cap, swx_rec_dev *hrecs, uint32_t *hcigar, int64_t *total, hipStream_t st) {
+  if (npairs <= 0) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_graph_out, dim3(std::min(blocks_for(npairs, 64), 256u)), dim3(256), 0, st, npairs,
+                     recs, cigar, off, cap, hrecs, hcigar, total);
+  return hipGetLastError();
+}
+
 hipError_t launch_cigar_compact(int64_t npairs, const uint32_t *src, const int64_t *src_off,
                                 const int32_t *len, const int64_t *dst_off, const uint8_t *cls,
                                 const int32_t *qbeg, const int32_t *qend, uint32_t *dst,

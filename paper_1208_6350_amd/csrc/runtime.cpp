@@ -175,6 +175,17 @@ struct swx_ctx {
   // pinned landing area of the small device-to-host reads between stages
   static constexpr int64_t kPinned = 512;   // int64 values
   int64_t *pinned = nullptr;
+  uint64_t *pinned_flag = nullptr;          // behind it: the number of the last read (k_publish)
+  uint64_t reads = 0, pairs = 0;            // numbers given out (k_publish, k_pair_rest)
+  // small host-memory inputs and outputs go through pinned memory that kernels
+  // read and write, made on first use
+  static constexpr int64_t kStage = int64_t(4) << 20;
+  int8_t *stage_in = nullptr, *stage_out = nullptr;
+  bool stage_busy = false;                  // stage_in may still be read, on ...
+  hipStream_t stage_stream = nullptr;
+  int64_t out_used = 0;                     // bytes of stage_out taken by the running call ...
+  struct OutCopy { void *dst; const void *src; size_t bytes; };
+  std::vector<OutCopy> out_copies;          // ... and what to copy from it when it has finished
   void *scratch = nullptr;   // this device's static scratch (swx_align_batch_noalloc)
 };
 
@@ -292,11 +303,30 @@ static hipError_t wait_stream(hipStream_t st) {
   }
 }
 
+// Waits until a kernel of the stream has written `want` to a word of pinned
+// memory: that shows on the host a few microseconds before the end of the
+// kernel does.  The stream is asked now and then, so that an error ends the wait.
+static hipError_t wait_word(hipStream_t st, const uint64_t *word, uint64_t want) {
+  for (uint32_t spins = 1;; ++spins) {
+    if (__atomic_load_n(word, __ATOMIC_ACQUIRE) == want) return hipSuccess;
+    if (spins % 256 == 0) {
+      const hipError_t e = hipStreamQuery(st);
+      if (e == hipSuccess)
+        return __atomic_load_n(word, __ATOMIC_ACQUIRE) == want ? hipSuccess : hipErrorUnknown;
+      if (e != hipErrorNotReady) return e;
+      std::this_thread::yield();
+    } else {
+      __builtin_ia32_pause();
+    }
+  }
+}
+
 template <class T>
 static T *alloc_or_null(DevArena &A, int64_t n) { return A.get<T>(n); }
 
 // Sort the pass's pairs by (band, padded query height, reference length) on
 // the device, cut them into tasks, derive buffer offsets and allocate.
+static int read_two(swx_ctx *ctx, const int64_t *a, int64_t na, const int64_t *b, int64_t nb, int64_t *h);
 static int plan_pass(swx_ctx *ctx, const Scoring &sc, const int64_t *ids, int64_t n,
                      const int32_t *qlen, const int64_t *rlen, const int32_t *band,
                      const int32_t *band_q, int lane_bits, int R, Plan &pl,
@@ -338,10 +368,9 @@ static int plan_pass(swx_ctx *ctx, const Scoring &sc, const int64_t *ids, int64_
   if (!s2) return fail(SWX_ENOMEM, "device pool exhausted (scan)");
   HIP_TRY(launch_exclusive_scan(qsz, qoff, pl.ntasks + 1, s2, &t2, st));
   HIP_TRY(plan_offsets_dev(pl.ntasks, pl.d_tasks, boff, qoff, st));
-  HIP_TRY(hipMemcpyAsync(ctx->pinned, boff + pl.ntasks, 8, hipMemcpyDeviceToHost, st));
-  HIP_TRY(hipMemcpyAsync(ctx->pinned + 1, qoff + pl.ntasks, 8, hipMemcpyDeviceToHost, st));
-  HIP_TRY(wait_stream(st));
-  const int64_t tot[2] = {ctx->pinned[0], ctx->pinned[1]};
+  int64_t tot[2];
+  int rc;
+  if ((rc = read_two(ctx, boff + pl.ntasks, 1, qoff + pl.ntasks, 1, tot))) return rc;
   pl.d_bnd = A.get<uint32_t>(tot[0]);
   pl.d_rsym = A.get<uint2>(rsym_offset(tot[0]));
   if (!pl.d_bnd || !pl.d_rsym) return fail(SWX_ENOMEM, "device pool exhausted (boundary planes)");
@@ -545,12 +574,73 @@ static int scan(swx_ctx *ctx, const int64_t *in, int64_t *out, int64_t n) {
 
 // n values from the device; small reads land in pinned memory (a direct copy,
 // no staging through the runtime's own buffers).  Callers hold ctx->mu.
-static int read_i64(swx_ctx *ctx, const int64_t *d, int64_t *h, int64_t n = 1) {
-  const bool pin = n <= swx_ctx::kPinned;
-  HIP_TRY(hipMemcpyAsync(pin ? ctx->pinned : h, d, 8 * n, hipMemcpyDeviceToHost, ctx->stream));
-  HIP_TRY(wait_stream(ctx->stream));
-  if (pin) memcpy(h, ctx->pinned, 8 * (size_t)n);
+static int read_two(swx_ctx *ctx, const int64_t *a, int64_t na, const int64_t *b, int64_t nb, int64_t *h) {
+  const uint64_t seq = ++ctx->reads;
+  HIP_TRY(publish(a, na, b, nb, ctx->pinned, ctx->pinned_flag, seq, ctx->stream));
+  HIP_TRY(wait_word(ctx->stream, ctx->pinned_flag, seq));
+  memcpy(h, ctx->pinned, 8 * (size_t)(na + nb));
+  if (ctx->stream == ctx->stage_stream) ctx->stage_busy = false;
   return SWX_OK;
+}
+
+static int read_i64(swx_ctx *ctx, const int64_t *d, int64_t *h, int64_t n = 1) {
+  if (n <= swx_ctx::kPinned) return read_two(ctx, d, n, nullptr, 0, h);
+  HIP_TRY(hipMemcpyAsync(h, d, 8 * n, hipMemcpyDeviceToHost, ctx->stream));
+  HIP_TRY(wait_stream(ctx->stream));
+  return SWX_OK;
+}
+
+// Host arrays to device buffers (16-byte aligned).  Small ones in one kernel,
+// through pinned memory.
+struct HostIn { void *dst; const void *src; int64_t bytes; };
+static int upload(swx_ctx *ctx, const HostIn *in, int count) {
+  int64_t total = 0;
+  for (int k = 0; k < count; ++k) total += round_up(in[k].bytes, 16);
+  bool pin = !ctx->arena.fixed() && total <= swx_ctx::kStage && count <= kCopySetMax;
+  if (pin && !ctx->stage_in &&
+      hipHostMalloc(&ctx->stage_in, swx_ctx::kStage, hipHostMallocDefault) != hipSuccess) {
+    ctx->stage_in = nullptr;
+    pin = false;
+  }
+  if (!pin) {
+    for (int k = 0; k < count; ++k)
+      if (in[k].bytes)
+        HIP_TRY(hipMemcpyAsync(in[k].dst, in[k].src, in[k].bytes, hipMemcpyHostToDevice, ctx->stream));
+    return SWX_OK;
+  }
+  if (ctx->stage_busy) HIP_TRY(hipStreamSynchronize(ctx->stage_stream));
+  CopySet c{};
+  int64_t at = 0;
+  for (int k = 0; k < count; ++k) {
+    if (in[k].bytes == 0) continue;
+    memcpy(ctx->stage_in + at, in[k].src, (size_t)in[k].bytes);
+    c.add(ctx->stage_in + at, in[k].dst, in[k].bytes);
+    at += round_up(in[k].bytes, 16);
+  }
+  ctx->stage_busy = true;
+  ctx->stage_stream = ctx->stream;
+  HIP_TRY(copy_set(c, ctx->stream));
+  return SWX_OK;
+}
+
+// Where kernels write an output of `bytes` bytes for the caller's host memory:
+// pinned memory, copied when the call's work has finished (finish_outputs).
+// Null: no room there, the caller copies from a device buffer.
+static void *host_out(swx_ctx *ctx, void *dst, int64_t bytes) {
+  if (ctx->arena.fixed() || ctx->out_used + round_up(bytes, 256) > swx_ctx::kStage) return nullptr;
+  if (!ctx->stage_out &&
+      hipHostMalloc(&ctx->stage_out, swx_ctx::kStage, hipHostMallocDefault) != hipSuccess) {
+    ctx->stage_out = nullptr;
+    return nullptr;
+  }
+  void *at = ctx->stage_out + ctx->out_used;
+  ctx->out_used += round_up(bytes, 256);
+  ctx->out_copies.push_back({dst, at, (size_t)bytes});
+  return at;
+}
+static void finish_outputs(swx_ctx *ctx) {
+  for (const auto &o : ctx->out_copies) memcpy(o.dst, o.src, o.bytes);
+  ctx->out_copies.clear();
 }
 
 // ids of the pairs whose flag is set (device list) and their count (device)
@@ -903,10 +993,13 @@ static int run_traceback(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, 
     return SWX_OK;
   }
   uint32_t *dst = out->cigar, *dtmp = nullptr;
-  if (out->out_mem != SWX_MEM_DEVICE) {
-    dtmp = A.get<uint32_t>(total);
-    if (!dtmp) return fail(SWX_ENOMEM, "device pool exhausted");
-    dst = dtmp;
+  if (out->out_mem != SWX_MEM_DEVICE && total) {
+    dst = (uint32_t *)host_out(ctx, out->cigar, sizeof(uint32_t) * total);
+    if (!dst) {
+      dtmp = A.get<uint32_t>(total);
+      if (!dtmp) return fail(SWX_ENOMEM, "device pool exhausted");
+      dst = dtmp;
+    }
   }
   HIP_TRY(launch_cigar_compact(np, cscr, coff, cig_len, cig_off_final, cls, qbeg, qend, dst, st));
   if (dtmp && total)
@@ -1606,6 +1699,15 @@ static int run_intra_reverse(swx_ctx *ctx, const Scoring &sc, LongPath &lp, cons
   return launch_intra_jobs(ctx, groups, a, bnd_words, true);
 }
 
+// the records' place: the caller's device memory, pinned memory, or (*copy) a
+// device buffer that is copied at the end
+static swx_rec_dev *out_records(swx_ctx *ctx, swx_rec *dst, uint32_t out_mem, int64_t np, bool *copy) {
+  if (out_mem == SWX_MEM_DEVICE) return (swx_rec_dev *)dst;
+  if (void *p = host_out(ctx, dst, (int64_t)sizeof(swx_rec) * np)) return (swx_rec_dev *)p;
+  *copy = true;
+  return ctx->arena.get<swx_rec_dev>(np);
+}
+
 static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, uint32_t flags,
                         int32_t mask_len, swx_batch_out *out, const swx_profile *prof) {
   DevArena &A = ctx->arena;
@@ -1685,9 +1787,7 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
       shp.qlen = (int32_t)prof->query.size();
     } else {
       int64_t qo[2];
-      HIP_TRY(hipMemcpyAsync(ctx->pinned, b.qoff, 16, hipMemcpyDeviceToHost, st));
-      HIP_TRY(wait_stream(st));
-      memcpy(qo, ctx->pinned, 16);
+      if ((rc = read_i64(ctx, b.qoff, qo, 2))) return rc;
       const int64_t ql = qo[1] - qo[0];
       if (ql < 1 || ql > INT32_MAX / 4) return fail(SWX_EINVAL, "bad query length");
       shp.qlen = (int32_t)ql;
@@ -1960,32 +2060,38 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
     if (rc_sub != SWX_OK) rc_range = rc_sub;
     if (!(flags & SWX_CIGAR)) sflags &= ~SWX_CIGAR;   // the primaries did not fit either
     HIP_TRY(hipMemsetAsync(slb, 32, np, st));
-    swx_rec_dev *srec = (out->out_mem == SWX_MEM_DEVICE) ? (swx_rec_dev *)out->sub_recs
-                                                         : A.get<swx_rec_dev>(np);
+    bool scopy = false;
+    swx_rec_dev *srec = out_records(ctx, out->sub_recs, out->out_mem, np, &scopy);
     if (!srec) return fail(SWX_ENOMEM, "device pool exhausted");
     HIP_TRY(launch_records(np, s_score, s_score, s_qbeg, s_qend, s_rbeg, s_rend, s_rend, s_cig_off,
                            s_cig_len, slb, sflags, srec, nullptr, nullptr, st));
     if (sflags & SWX_CIGAR) HIP_TRY(shift_cigar_offsets(np, base, srec, st));
-    if (out->out_mem != SWX_MEM_DEVICE)
+    if (scopy)
       HIP_TRY(hipMemcpyAsync(out->sub_recs, srec, sizeof(swx_rec) * np, hipMemcpyDeviceToHost, st));
   }
 
   // records
-  swx_rec_dev *drec = (out->out_mem == SWX_MEM_DEVICE) ? (swx_rec_dev *)out->recs
-                                                       : A.get<swx_rec_dev>(np);
+  bool rcopy = false;
+  swx_rec_dev *drec = out_records(ctx, out->recs, out->out_mem, np, &rcopy);
   if (!drec) return fail(SWX_ENOMEM, "device pool exhausted");
   HIP_TRY(launch_records(np, score, score2, qbeg, qend, rbeg, rend, rend2, cig_off_final, cig_len,
                          lanebits, flags, drec, err, stats + 7, st));
-  if (out->out_mem != SWX_MEM_DEVICE && np)
+  if (rcopy && np)
     HIP_TRY(hipMemcpyAsync(out->recs, drec, sizeof(swx_rec) * np, hipMemcpyDeviceToHost, st));
   HIP_TRY(hipEventRecord(ctx->ev[7], st));
   // consistency: any per-pair error flag
   int64_t nerr = 0;
   if ((rc = read_i64(ctx, stats + 7, &nerr))) return rc;
+  finish_outputs(ctx);
   ctx->nstages = 7;
   for (int k = 0; k < 7; ++k) {
     float ms = 0.f;
-    HIP_TRY(hipEventElapsedTime(&ms, ctx->ev[k], ctx->ev[k + 1]));
+    hipError_t e = hipEventElapsedTime(&ms, ctx->ev[k], ctx->ev[k + 1]);
+    if (e == hipErrorNotReady) {   // done on the device, not yet seen by the runtime
+      HIP_TRY(hipEventSynchronize(ctx->ev[k + 1]));
+      e = hipEventElapsedTime(&ms, ctx->ev[k], ctx->ev[k + 1]);
+    }
+    HIP_TRY(e);
     ctx->stage_ms[k] = ms;
   }
   if (nerr) return fail(SWX_EINTERNAL, "internal consistency check failed for " +
@@ -2187,7 +2293,7 @@ static int fixed_issue(GraphState &g, hipStream_t st) {
     // the intra route clears all its per-call buffers in one launch (the
     // lanes are 32-bit throughout)
     FillSet fs{};
-    fs.add(g.bad, 1, 4, 0);
+    fs.add(g.bad, 2, 4, 0);
     fs.add(g.status, 1, 8, 0);
     fs.add(g.err, B, 1, 0);
     fs.add(g.lanebits, B, 1, 32);
@@ -2195,7 +2301,7 @@ static int fixed_issue(GraphState &g, hipStream_t st) {
     fs.add(g.counts, 9, 8, 0);
     HIP_TRY(fill_set(fs, st));
   } else {
-    HIP_TRY(fill_u8(4, (uint8_t *)g.bad, 0, st));
+    HIP_TRY(fill_u8(8, (uint8_t *)g.bad, 0, st));
     HIP_TRY(fill_i64(1, g.status, 0, st));
     HIP_TRY(fill_u8(B, g.err, 0, st));
     HIP_TRY(fill_u8(B, g.lanebits, 16, st));
@@ -2387,7 +2493,7 @@ static int graph_alloc(GraphState &g) {
   for (uint8_t **p : {&g.ovf, &g.lanebits, &g.err, &g.rov, &g.f16, &g.f32, &g.cls})
     per_pair = (*p = A.get<uint8_t>(B)) != nullptr && per_pair;
   if (!per_pair) return fail(SWX_ENOMEM, "device pool exhausted (graph)");
-  g.bad = A.get<uint32_t>(1);
+  g.bad = A.get<uint32_t>(2);   // (read as one 64-bit word)
   g.status = A.get<int64_t>(1);
   g.f64 = A.get<int64_t>(B + 1);
   g.pos = A.get<int64_t>(B + 1);
@@ -2585,6 +2691,8 @@ static void release_ctx(swx_ctx *ctx) {
   if (ctx->pinned) (void)hipHostFree(ctx->pinned);
   if (ctx->pair_in) (void)hipHostFree(ctx->pair_in);
   if (ctx->pair_out) (void)hipHostFree(ctx->pair_out);
+  if (ctx->stage_in) (void)hipHostFree(ctx->stage_in);
+  if (ctx->stage_out) (void)hipHostFree(ctx->stage_out);
   for (auto &e : ctx->ev)
     if (e) (void)hipEventDestroy(e);
   for (int k = 0; k < swx_ctx::kAux; ++k) {
@@ -2626,10 +2734,12 @@ int swx_ctx_create(int device, swx_ctx **out) {
   }
   if (hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess ||
       c->cus < 1 || hipMalloc(&c->queue, 256) != hipSuccess ||
-      hipHostMalloc(&c->pinned, 8 * swx_ctx::kPinned, hipHostMallocDefault) != hipSuccess) {
+      hipHostMalloc(&c->pinned, 8 * (swx_ctx::kPinned + 8), hipHostMallocDefault) != hipSuccess) {
     release_ctx(c);
     return fail(SWX_EDEVICE, "could not query the device or allocate the work queue");
   }
+  c->pinned_flag = (uint64_t *)(c->pinned + swx_ctx::kPinned);
+  *c->pinned_flag = 0;
   c->scratch = scratch_address(device);
   if (!c->scratch) {
     release_ctx(c);
@@ -2812,8 +2922,12 @@ static int align_batch_locked(swx_ctx *ctx, const swx_batch *b, swx_batch_out *o
   hipStream_t st = ctx->stream;
   int8_t *dmat = A.get<int8_t>((int64_t)sc.n * sc.n);
   if (!dmat) return fail(SWX_ENOMEM, "device pool exhausted");
-  HIP_TRY(hipMemcpyAsync(dmat, b->matrix, (size_t)sc.n * sc.n, hipMemcpyHostToDevice, st));
   sc.dmat = dmat;
+  HostIn in[7];
+  int nin = 0;
+  in[nin++] = {dmat, b->matrix, (int64_t)sc.n * sc.n};
+  ctx->out_used = 0;
+  ctx->out_copies.clear();
   DeviceBatch db{};
   db.qcat_len = b->qcat_len; db.rcat_len = b->rcat_len; db.nq = b->nq; db.nr = b->nr;
   db.npairs = b->npairs;
@@ -2825,22 +2939,27 @@ static int align_batch_locked(swx_ctx *ctx, const swx_batch *b, swx_batch_out *o
     int64_t *qo = A.get<int64_t>(b->nq + 1), *ro = A.get<int64_t>(b->nr + 1);
     int64_t *pq = A.get<int64_t>(b->npairs), *pr = A.get<int64_t>(b->npairs);
     if (!qc || (!rc8 && !dev_ref) || !qo || !ro || !pq || !pr) return fail(SWX_ENOMEM, "device pool exhausted");
-    if (b->qcat_len) HIP_TRY(hipMemcpyAsync(qc, b->qcat, b->qcat_len, hipMemcpyHostToDevice, st));
-    if (b->rcat_len && !dev_ref)
-      HIP_TRY(hipMemcpyAsync(rc8, b->rcat, b->rcat_len, hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(qo, b->qoff, 8 * (b->nq + 1), hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(ro, b->roff, 8 * (b->nr + 1), hipMemcpyHostToDevice, st));
-    if (b->npairs) {
-      HIP_TRY(hipMemcpyAsync(pq, b->pair_q, 8 * b->npairs, hipMemcpyHostToDevice, st));
-      HIP_TRY(hipMemcpyAsync(pr, b->pair_r, 8 * b->npairs, hipMemcpyHostToDevice, st));
-    }
+    in[nin++] = {qc, b->qcat, b->qcat_len};
+    if (!dev_ref) in[nin++] = {rc8, b->rcat, b->rcat_len};
+    in[nin++] = {qo, b->qoff, 8 * (b->nq + 1)};
+    in[nin++] = {ro, b->roff, 8 * (b->nr + 1)};
+    in[nin++] = {pq, b->pair_q, 8 * b->npairs};
+    in[nin++] = {pr, b->pair_r, 8 * b->npairs};
     db.qcat = qc; db.rcat = dev_ref ? dev_ref : rc8; db.qoff = qo; db.roff = ro; db.pair_q = pq; db.pair_r = pr;
   }
   if (b->npairs == 0) {
     out->cigar_used = 0;
     return SWX_OK;
   }
-  return run_pipeline(ctx, sc, db, b->flags, b->mask_len, out, prof);
+  rc = upload(ctx, in, nin);
+  if (rc == SWX_OK) rc = run_pipeline(ctx, sc, db, b->flags, b->mask_len, out, prof);
+  // a call that failed on its way leaves nothing running on the pinned buffers
+  if (rc != SWX_OK && (ctx->stage_busy || !ctx->out_copies.empty())) {
+    (void)hipStreamSynchronize(st);
+    ctx->stage_busy = false;
+    ctx->out_copies.clear();
+  }
+  return rc;
 }
 
 int swx_align_batch(swx_ctx *ctx, const swx_batch *b, swx_batch_out *out, void *hip_stream) {
@@ -2910,6 +3029,7 @@ static int align_pair_short(const swx_profile *p, const int8_t *ref, bool ref_de
     ctx->pair_out = nullptr;
     return fail(SWX_ENOMEM, "pinned host allocation failed");
   }
+  if (ctx->pairs == 0) ctx->pair_out->done = 0;
   if (flags & (SWX_CIGAR | SWX_SCORE2)) flags |= SWX_BEGIN;
   PairArgs a{};
   a.Lq = (int32_t)Lq;
@@ -2963,10 +3083,12 @@ static int align_pair_short(const swx_profile *p, const int8_t *ref, bool ref_de
   a.src_m = ctx->pair_in + kInM;
   a.out = ctx->pair_out;
   a.out->bad = a.out->err = 0;
+  a.seq = ++ctx->pairs;   // (the word before the first call is 0)
   hipError_t he = pair_stage(a, ctx->stream);
   if (he == hipSuccess) he = pair_forward(a, ctx->stream);
   if (he == hipSuccess) he = pair_rest(a, ctx->stream);
-  const hipError_t hw = wait_stream(ctx->stream);   // the pinned buffers are the next call's too
+  // (the pinned buffers are the next call's too)
+  const hipError_t hw = he == hipSuccess ? wait_word(ctx->stream, &a.out->done, a.seq) : wait_stream(ctx->stream);
   if (he == hipSuccess) he = hw;
   if (he != hipSuccess) return fail(SWX_EDEVICE, std::string("one-pair call: ") + hipGetErrorString(he));
   if (a.out->bad) return fail(SWX_EINVAL, "symbol code outside [0, n)");
@@ -3180,13 +3302,11 @@ int swx_graph_create(swx_ctx *ctx, const swx_graph_cfg *cfg, swx_graph **out, sw
 static int graph_check(swx_graph *gr) {
   GraphState &g = gr->g;
   swx_ctx *ctx = gr->ctx;
-  if (hipMemcpyAsync(ctx->pinned, g.bad, 4, hipMemcpyDeviceToHost, ctx->stream) != hipSuccess ||
-      hipMemcpyAsync(ctx->pinned + 1, g.status, 8, hipMemcpyDeviceToHost, ctx->stream) != hipSuccess ||
-      wait_stream(ctx->stream) != hipSuccess)
+  int64_t h[2];
+  if (read_two(ctx, (const int64_t *)g.bad, 1, g.status, 1, h) != SWX_OK)
     return fail(SWX_EDEVICE, "could not read the graph status");
-  uint32_t bad = 0;
-  memcpy(&bad, ctx->pinned, 4);
-  const int64_t nerr = ctx->pinned[1];
+  const uint32_t bad = (uint32_t)h[0];
+  const int64_t nerr = h[1];
   if (bad & 1u) return fail(SWX_EINVAL, "offsets must be non-decreasing and within the code arrays");
   if (bad & 2u) return fail(SWX_EINVAL, "pair index out of range");
   if (bad & 12u) return fail(SWX_EINVAL, "symbol code outside [0, n)");
@@ -3245,10 +3365,16 @@ int swx_graph_load(swx_graph *gr, const swx_batch *b) {
   // symbols too: a rejected code must never reach the device buffers, where
   // it would outlive this load past the next, shorter one (every run checks
   // the whole code arrays)
-  for (int64_t k = 0; k < b->qcat_len; ++k)
-    if (b->qcat[k] < 0 || b->qcat[k] >= g.sc.n) return fail(SWX_EINVAL, "symbol code outside [0, n)");
-  for (int64_t k = 0; k < b->rcat_len; ++k)
-    if (b->rcat[k] < 0 || b->rcat[k] >= g.sc.n) return fail(SWX_EINVAL, "symbol code outside [0, n)");
+  // (whole arrays without a branch per symbol: 275 KB of a 500-read batch
+  // took 0.1 ms with one)
+  auto symbols_ok = [&](const int8_t *s, int64_t len) {
+    const unsigned n = (unsigned)g.sc.n;
+    unsigned bad = 0;
+    for (int64_t k = 0; k < len; ++k) bad |= (unsigned)((uint8_t)s[k] >= n);
+    return bad == 0;
+  };
+  if (!symbols_ok(b->qcat, b->qcat_len) || !symbols_ok(b->rcat, b->rcat_len))
+    return fail(SWX_EINVAL, "symbol code outside [0, n)");
   // offsets padded with their last value; pair slots past npairs take the
   // empty reference nr (roff[nr] == roff[nr + 1])
   std::vector<int64_t> qo(g.cfg.nq_cap + 1), ro(g.cfg.nr_cap + 1), pq(g.B, 0), pr(g.B, b->nr);
@@ -3256,14 +3382,17 @@ int swx_graph_load(swx_graph *gr, const swx_batch *b) {
   for (int64_t k = 0; k <= g.cfg.nr_cap; ++k) ro[k] = b->roff[std::min(k, b->nr)];
   for (int64_t k = 0; k < b->npairs; ++k) { pq[k] = b->pair_q[k]; pr[k] = b->pair_r[k]; }
   std::lock_guard<std::mutex> lk(gr->ctx->mu);
-  hipStream_t st = gr->ctx->stream;
-  if (b->qcat_len) HIP_TRY(hipMemcpyAsync(g.qcat, b->qcat, b->qcat_len, hipMemcpyHostToDevice, st));
-  if (b->rcat_len) HIP_TRY(hipMemcpyAsync(g.rcat, b->rcat, b->rcat_len, hipMemcpyHostToDevice, st));
-  HIP_TRY(hipMemcpyAsync(g.qoff, qo.data(), 8 * qo.size(), hipMemcpyHostToDevice, st));
-  HIP_TRY(hipMemcpyAsync(g.roff, ro.data(), 8 * ro.size(), hipMemcpyHostToDevice, st));
-  HIP_TRY(hipMemcpyAsync(g.pair_q, pq.data(), 8 * pq.size(), hipMemcpyHostToDevice, st));
-  HIP_TRY(hipMemcpyAsync(g.pair_r, pr.data(), 8 * pr.size(), hipMemcpyHostToDevice, st));
-  HIP_TRY(wait_stream(st));   // the host vectors must outlive the copies
+  const HostIn in[6] = {{g.qcat, b->qcat, b->qcat_len},
+                        {g.rcat, b->rcat, b->rcat_len},
+                        {g.qoff, qo.data(), 8 * (int64_t)qo.size()},
+                        {g.roff, ro.data(), 8 * (int64_t)ro.size()},
+                        {g.pair_q, pq.data(), 8 * (int64_t)pq.size()},
+                        {g.pair_r, pr.data(), 8 * (int64_t)pr.size()}};
+  int rc;
+  if ((rc = upload(gr->ctx, in, 6))) return rc;
+  // the host vectors must outlive the copies, and a run may be on another stream
+  HIP_TRY(wait_stream(gr->ctx->stream));
+  gr->ctx->stage_busy = false;
   return SWX_OK;
 }
 
@@ -3273,6 +3402,30 @@ int swx_graph_read(swx_graph *gr, int64_t npairs, swx_batch_out *out) {
   GraphState &g = gr->g;
   std::lock_guard<std::mutex> lk(gr->ctx->mu);
   if (npairs == 0) { out->cigar_used = 0; return SWX_OK; }
+  swx_ctx *ctx = gr->ctx;
+  // small results in one kernel, through pinned memory: the records, then the
+  // CIGAR words as far as there is room
+  const int64_t head = round_up((int64_t)sizeof(swx_rec) * npairs, 256) + 256;
+  const bool cigars = (g.cfg.flags & SWX_CIGAR) != 0;
+  if (head < swx_ctx::kStage / 2 &&
+      (ctx->stage_out || hipHostMalloc(&ctx->stage_out, swx_ctx::kStage, hipHostMallocDefault) == hipSuccess)) {
+    int64_t *total = (int64_t *)ctx->stage_out;
+    swx_rec_dev *hrecs = (swx_rec_dev *)(ctx->stage_out + 256);
+    uint32_t *hcig = (uint32_t *)(ctx->stage_out + head);
+    const int64_t room = (swx_ctx::kStage - head) / 4;
+    HIP_TRY(hipSetDevice(ctx->device));
+    HIP_TRY(graph_out(npairs, g.recs, g.cigar, cigars ? g.cig_off_final : nullptr, room, hrecs, hcig,
+                      total, ctx->stream));
+    HIP_TRY(wait_stream(ctx->stream));
+    memcpy(out->recs, hrecs, sizeof(swx_rec) * (size_t)npairs);
+    const int64_t used = *total;
+    out->cigar_used = used;
+    if (used > out->cigar_cap || (used && !out->cigar)) return fail(SWX_ERANGE, "CIGAR arena too small");
+    if (used > room) HIP_TRY(hipMemcpy(out->cigar, g.cigar, sizeof(uint32_t) * used, hipMemcpyDeviceToHost));
+    else if (used) memcpy(out->cigar, hcig, sizeof(uint32_t) * (size_t)used);
+    return SWX_OK;
+  }
+  if (head < swx_ctx::kStage / 2) ctx->stage_out = nullptr;   // (no pinned memory to be had)
   HIP_TRY(hipMemcpy(out->recs, g.recs, sizeof(swx_rec) * npairs, hipMemcpyDeviceToHost));
   int64_t used = 0;
   for (int64_t k = 0; k < npairs; ++k)

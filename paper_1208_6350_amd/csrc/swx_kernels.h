@@ -322,6 +322,7 @@ struct PairOut {         // in pinned host memory, the CIGAR's words after it
   swx_rec_dev rec;
   int32_t bad;           // a symbol code outside [0, n)
   int32_t err;           // an internal check failed
+  uint64_t done;         // the call's number, written last
 };
 struct PairState {       // the pair's arrays of one element each (TbArgs)
   int64_t qstart, rstart, rbeg, rend, rlen, cig_off;
@@ -346,6 +347,7 @@ struct PairArgs {
   uint8_t *dir;
   int32_t *bnd;
   PairOut *out;
+  uint64_t seq;            // this call's number
 };
 int pair_waves(int strips, int n);
 hipError_t pair_stage(const PairArgs &a, hipStream_t st);
@@ -429,6 +431,26 @@ struct FillSet {
   }
 };
 hipError_t fill_set(const FillSet &f, hipStream_t st);
+// Copies by a kernel between device memory and pinned host memory.
+constexpr int kCopySetMax = 8;
+struct CopySet {         // every pointer 16-byte aligned
+  const void *src[kCopySetMax];
+  void *dst[kCopySetMax];
+  int64_t bytes[kCopySetMax];
+  int32_t count;
+  void add(const void *s, void *d, int64_t n) {
+    src[count] = s; dst[count] = d; bytes[count] = n; ++count;
+  }
+};
+hipError_t copy_set(const CopySet &c, hipStream_t st);
+// values of up to two device arrays to pinned host memory, one after the other,
+// then *flag = seq
+hipError_t publish(const int64_t *a, int64_t na, const int64_t *b, int64_t nb, int64_t *dst,
+                   uint64_t *flag, uint64_t seq, hipStream_t st);
+// npairs records and, with CIGARs, their words [0, off[npairs]) up to cap, to
+// pinned host memory; *total = off[npairs]
+hipError_t graph_out(int64_t npairs, const swx_rec_dev *recs, const uint32_t *cigar, const int64_t *off,
+                     int64_t cap, swx_rec_dev *hrecs, uint32_t *hcigar, int64_t *total, hipStream_t st);
 // pair 0's CIGAR words and final offsets {0, length} (one-pair calls)
 // cls: the traceback classes (pairs of class kTbFlat hold no scratch words:
 // their one word is made from qbeg and qend)

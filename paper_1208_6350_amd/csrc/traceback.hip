@@ -2063,6 +2063,10 @@ __global__ __launch_bounds__(64 * kPairWaves) void k_pair_rest(PairArgs a) {
     a.out->rec = rec;
     if (err) a.out->err = 1;
   }
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x == 0)
+    __hip_atomic_store(&a.out->done, a.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 hipError_t pair_rest(const PairArgs &a, hipStream_t st) {
