@@ -262,12 +262,13 @@ __global__ void k_band_tb(BandArgs a) {
 // 16 lanes per pair (most CIGARs have few runs), 16 pairs per block
 __global__ void k_cigar_compact(int64_t npairs, const uint32_t *src, const int64_t *src_off,
                                 const int32_t *len, const int64_t *dst_off, const uint8_t *cls,
-                                const int32_t *qbeg, const int32_t *qend, uint32_t *dst) {
+                                const int32_t *qbeg, const int32_t *qend, uint32_t *dst,
+                                int64_t stride, int64_t cap) {
   const int64_t p = (int64_t)blockIdx.x * (blockDim.x / 16) + threadIdx.x / 16;
-  if (p >= npairs) return;
+  if (p >= npairs || dst_off[npairs] > cap) return;
   const int32_t n = len[p];
-  const int64_t so = src_off[p], d = dst_off[p];
-  if (cls[p] == kTbFlat) {   // one run of M over the rectangle's rows
+  const int64_t so = src_off ? src_off[p] : p * stride, d = dst_off[p];
+  if (cls && cls[p] == kTbFlat) {   // one run of M over the rectangle's rows
     if ((threadIdx.x & 15) == 0) dst[d] = (uint32_t)(qend[p] - qbeg[p] + 1) << 4;
     return;
   }
@@ -381,9 +382,10 @@ __global__ void k_records(int64_t npairs, const int32_t *score1, const int32_t *
                           const int32_t *qbeg, const int32_t *qend, const int64_t *rbeg,
                           const int64_t *rend, const int64_t *rend2, const int64_t *cig_off,
                           const int32_t *cig_len, const uint8_t *lane_bits, uint32_t flags,
-                          swx_rec_dev *recs, const uint8_t *err, int64_t *nerr) {
+                          swx_rec_dev *recs, const uint8_t *err, int64_t *nerr, int64_t cap) {
   const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= npairs) return;
+  if ((flags & 2u) && cig_off[npairs] > cap) flags &= ~2u;   // the CIGARs do not fit: none is named
   if (err && err[p]) atomicAdd((unsigned long long *)nerr, 1ull);
   swx_rec_dev r;
   const bool ok = score1[p] > 0;
@@ -727,10 +729,10 @@ hipError_t graph_out(int64_t npairs, const swx_rec_dev *recs, const uint32_t *ci
 hipError_t launch_cigar_compact(int64_t npairs, const uint32_t *src, const int64_t *src_off,
                                 const int32_t *len, const int64_t *dst_off, const uint8_t *cls,
                                 const int32_t *qbeg, const int32_t *qend, uint32_t *dst,
-                                hipStream_t st) {
+                                int64_t stride, int64_t cap, hipStream_t st) {
   if (!npairs) return hipSuccess;
   hipLaunchKernelGGL(k_cigar_compact, dim3(blocks_for(npairs, 16)), dim3(256), 0, st, npairs, src,
-                     src_off, len, dst_off, cls, qbeg, qend, dst);
+                     src_off, len, dst_off, cls, qbeg, qend, dst, stride, cap);
   return hipGetLastError();
 }
 
@@ -753,11 +755,12 @@ hipError_t launch_records(int64_t npairs, const int32_t *score1, const int32_t *
                           const int32_t *qbeg, const int32_t *qend, const int64_t *rbeg,
                           const int64_t *rend, const int64_t *rend2, const int64_t *cig_off,
                           const int32_t *cig_len, const uint8_t *lane_bits, uint32_t flags,
-                          swx_rec_dev *recs, const uint8_t *err, int64_t *nerr, hipStream_t st) {
+                          swx_rec_dev *recs, const uint8_t *err, int64_t *nerr, int64_t cap,
+                          hipStream_t st) {
   if (!npairs) return hipSuccess;
   hipLaunchKernelGGL(k_records, dim3(blocks_for(npairs, 256)), dim3(256), 0, st, npairs, score1,
                      score2, qbeg, qend, rbeg, rend, rend2, cig_off, cig_len, lane_bits, flags,
-                     recs, err, nerr);
+                     recs, err, nerr, cap);
   return hipGetLastError();
 }
 

@@ -873,7 +873,10 @@ hipError_t intra_rev_jobs_fixed(int64_t B, const int32_t *score, const int64_t *
 // an upload and a wait per pass), a second launch for the few pairs above 256
 // rows (one pair: 157 us behind a launch of 294) and 73-88 instructions per
 // step where these take 48-62.  Measured on reads, forward + reversed stage:
-// 500 0.30 + 0.17 -> 0.08 + 0.05 ms, 5,000 0.78 + 0.60 -> 0.25 + 0.13.
+// 500 0.30 + 0.17 -> 0.08 + 0.05 ms, 5,000 0.78 + 0.60 -> 0.25 + 0.13; with the
+// ends found in the sweep and the reversed pass, begins and score2 behind it
+// in the same kernel (32-bit lanes) or in one more (16-bit), instead of five
+// launches of 4-5 us each, 0.11 and 0.38 in all.
 __device__ __forceinline__ StripJob alone_job(const AloneArgs &a, int64_t k, bool rev) {
   StripJob x{};
   const int64_t p = a.ids ? a.ids[k] : k;
@@ -891,9 +894,73 @@ __device__ __forceinline__ StripJob alone_job(const AloneArgs &a, int64_t k, boo
   return x;
 }
 
-// LAST: the suboptimal alignment's end, over a window that ends at its column
-template <bool REV, bool HO, bool LAST>
+// the forward pass's end of pair p (T1), by one thread
+__device__ __forceinline__ void alone_end(const AloneArgs &a, int64_t p, int32_t Lq, const StripBest &b) {
+  const uint32_t M = (1u << kAloneBits) - 1u;
+  a.out.score[p] = (int32_t)(b.word >> kAloneBits);
+  a.out.qend[p] = b.col >= 0 ? (int32_t)(M - (b.word & M)) - (kAloneMaxQ - Lq) : -1;
+  a.out.rend[p] = b.col;
+  a.out.overflow[p] = 0;
+}
+
+// Begin and score2 of pair p from its forward end (score s1 > 0 at row ie,
+// column je) and its max array words.
+template <bool HO>
+__device__ __forceinline__ void alone_rest(const AloneArgs &a, StripJob x, int64_t p, int32_t s1,
+                                           int32_t ie, int64_t je, const int8_t *s_mat,
+                                           uint8_t *s_prof, int64_t *s_rcol, int32_t *s_rrow) {
+  const StripScoring sc{a.n, (uint32_t)a.bias, (uint32_t)a.o, (uint32_t)a.e};
+  const int32_t Lq = x.Lq;
+  const int64_t Lr = x.Lr;
+  int32_t band_q;
+  rev_band(s1, (int64_t)ie + 1, je + 1, a.smax, a.o, a.e, x.band, band_q);
+  x.Lq = ie + 1;
+  x.Lr = x.c1 = je + 1;
+  x.rv = true;
+  x.tgt = s1;
+  x.row0 = 0;
+  x.rcol = s_rcol;
+  x.rrow = s_rrow;
+  if (x.Lq <= 256) strip_alone<4, true, HO>(x, sc, s_mat, s_prof);
+  else strip_alone<8, true, HO>(x, sc, s_mat, s_prof);
+  lds_wave_sync();
+  const int64_t rb = je - *s_rcol;
+  if (threadIdx.x == 0) {
+    if (*s_rcol < 0 || *s_rrow < 0 || *s_rrow > ie) a.err[p] = 1;   // the score has to come back
+    a.qbeg[p] = ie - *s_rrow;
+    a.rbeg[p] = rb;
+  }
+  if (!a.score2) return;
+  int64_t mask = a.mask_len;
+  if (mask < 0) { mask = Lq / 2; if (mask < 15) mask = 15; }
+  StripBest b{0u, -1};
+#pragma unroll 4
+  for (int64_t j = threadIdx.x; j < Lr; j += 64) {
+    const uint32_t w = x.mc[j];
+    if (j < rb - mask || j > je + mask) b.take(w, j, kAloneBits);
+  }
+  b.whole_wave(kAloneBits);
+  if (threadIdx.x == 0) {
+    a.score2[p] = (int32_t)(b.word >> kAloneBits);
+    a.rend2[p] = b.col;
+  }
+}
+
+// no alignment: nothing follows
+__device__ __forceinline__ void alone_none(const AloneArgs &a, int64_t p) {
+  a.qbeg[p] = -1;
+  a.rbeg[p] = -1;
+  if (a.score2) {
+    a.score2[p] = 0;
+    a.rend2[p] = -1;
+  }
+}
+
+enum AloneMode { kAloneForward, kAlonePass, kAloneBegin, kAloneReverse, kAloneLast };
+// kAloneLast: the suboptimal alignment's end, over a window that ends at its column
+template <int MODE, bool HO>
 __global__ __launch_bounds__(64) void k_alone_fill(AloneArgs a) {
+  constexpr bool REV = MODE == kAloneReverse, LAST = MODE == kAloneLast;
   extern __shared__ uint4 s_dyn[];   // [(n + 1) symbols][64 lanes][rows] bytes
   __shared__ int8_t s_mat[32 * 32];
   __shared__ int64_t s_rcol;
@@ -903,37 +970,62 @@ __global__ __launch_bounds__(64) void k_alone_fill(AloneArgs a) {
   for (int i = threadIdx.x; i < a.n * a.n; i += 64) s_mat[i] = a.matrix[i];
   lds_wave_sync();
   StripJob x = alone_job(a, k, REV);
-  if (!REV && a.lanebits && threadIdx.x == 0) a.lanebits[p] = 32;
-  if (x.Lr < 1 || ((REV || LAST) && x.Lq < 1)) return;   // (nothing to find: preset)
-  x.rcol = &s_rcol;
-  x.rrow = &s_rrow;
   const StripScoring sc{a.n, (uint32_t)a.bias, (uint32_t)a.o, (uint32_t)a.e};
   uint8_t *s_prof = reinterpret_cast<uint8_t *>(s_dyn);
-  if (x.Lq + (REV && a.anchor ? 1 : 0) <= 256) {
-    x.row0 = kAloneMaxQ - 256;
-    strip_alone<4, REV, HO, LAST>(x, sc, s_mat, s_prof);
-  } else {
-    strip_alone<8, REV, HO, LAST>(x, sc, s_mat, s_prof);
-  }
-  if constexpr (REV) {
-    lds_wave_sync();
-    if (threadIdx.x == 0) {
-      const bool hit = s_rcol >= 0;
-      a.out.score[p] = hit ? x.tgt : 0;
-      a.out.qend[p] = hit ? s_rrow : -1;
-      a.out.rend[p] = hit ? s_rcol : -1;
-      a.out.overflow[p] = 0;
+  if constexpr (MODE == kAloneBegin) {
+    const int32_t s1 = a.out.score[p];
+    if (s1 > 0) {
+      alone_rest<HO>(a, x, p, s1, a.out.qend[p], a.out.rend[p], s_mat, s_prof, &s_rcol, &s_rrow);
+    } else if (threadIdx.x == 0) {
+      alone_none(a, p);
     }
-  } else if constexpr (LAST) {
+    return;
+  }
+  if ((REV || LAST) && (x.Lq < 1 || x.Lr < 1)) return;   // (nothing to find: preset)
+  x.rcol = &s_rcol;
+  x.rrow = &s_rrow;
+  StripBest best{0u, -1};
+  if (x.Lr >= 1) {
+    if (x.Lq + (REV && a.anchor ? 1 : 0) <= 256) {
+      x.row0 = kAloneMaxQ - 256;
+      strip_alone<4, REV, HO, LAST>(x, sc, s_mat, s_prof, &best);
+    } else {
+      strip_alone<8, REV, HO, LAST>(x, sc, s_mat, s_prof, &best);
+    }
+  }
+  if constexpr (MODE == kAloneForward || MODE == kAlonePass) {
+    best.whole_wave(kAloneBits);
+    if (threadIdx.x == 0) {
+      alone_end(a, p, x.Lq, best);
+      if (a.lanebits) a.lanebits[p] = 32;
+    }
+    if constexpr (MODE == kAlonePass) {
+      if (best.col >= 0) {
+        // (the wave reads its own max array words back for score2)
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        const uint32_t M = (1u << kAloneBits) - 1u;
+        lds_wave_sync();
+        alone_rest<HO>(a, x, p, (int32_t)(best.word >> kAloneBits),
+                       (int32_t)(M - (best.word & M)) - (kAloneMaxQ - x.Lq), best.col, s_mat, s_prof,
+                       &s_rcol, &s_rrow);
+      } else if (threadIdx.x == 0) {
+        alone_none(a, p);
+      }
+    }
+  } else {
     lds_wave_sync();
     if (threadIdx.x == 0) {
-      const uint32_t w = (uint32_t)s_rrow;
-      const int32_t v = (int32_t)(w >> kAloneBits);
-      const uint32_t M = (1u << kAloneBits) - 1u;
-      a.out.score[p] = v;
-      a.out.qend[p] = v > 0 ? (int32_t)(M - (w & M)) - (kAloneMaxQ - x.Lq) : -1;
-      a.out.rend[p] = v > 0 ? x.Lr - 1 : -1;
-      a.out.overflow[p] = 0;
+      if constexpr (REV) {
+        const bool hit = s_rcol >= 0;
+        a.out.score[p] = hit ? x.tgt : 0;
+        a.out.qend[p] = hit ? s_rrow : -1;
+        a.out.rend[p] = hit ? s_rcol : -1;
+        a.out.overflow[p] = 0;
+      } else {
+        const uint32_t w = (uint32_t)s_rrow;
+        alone_end(a, p, x.Lq, StripBest{w, (w >> kAloneBits) ? x.Lr - 1 : -1});
+      }
     }
   }
 }
@@ -951,29 +1043,38 @@ __global__ __launch_bounds__(64) void k_alone_fill16(AloneArgs a) {
   else y.c1 = 0;   // no second pair: no columns
   const StripScoring sc{a.n, (uint32_t)a.bias, (uint32_t)a.o, (uint32_t)a.e};
   uint8_t *s_prof = reinterpret_cast<uint8_t *>(s_dyn);
+  StripBest bx{0u, -1}, by{0u, -1};
   if (x.Lq <= 256 && y.Lq <= 256) {
     x.row0 = kAloneMaxQ - 256;
-    strip_alone16<4, M3, HO>(x, y, sc, s_mat, s_prof, s_prof + (a.n + 1) * 64 * 4);
+    strip_alone16<4, M3, HO>(x, y, sc, s_mat, s_prof, s_prof + (a.n + 1) * 64 * 4, bx, by);
   } else {
-    strip_alone16<8, M3, HO>(x, y, sc, s_mat, s_prof, s_prof + (a.n + 1) * 64 * 8);
+    strip_alone16<8, M3, HO>(x, y, sc, s_mat, s_prof, s_prof + (a.n + 1) * 64 * 8, bx, by);
+  }
+  bx.whole_wave(kAloneBits);
+  by.whole_wave(kAloneBits);
+  if (threadIdx.x == 0) {
+    alone_end(a, a.ids ? a.ids[k] : k, x.Lq, bx);
+    if (k + 1 < a.count) alone_end(a, a.ids ? a.ids[k + 1] : k + 1, y.Lq, by);
   }
 }
 
 static size_t alone_lds(const AloneArgs &a) { return (size_t)(a.n + 1) * 64 * (a.max_q <= 256 ? 4 : 8); }
 
-template <bool REV, bool LAST>
+template <int MODE>
 static hipError_t alone_fill(const AloneArgs &a, hipStream_t st) {
   if (a.count == 0) return hipSuccess;
   if (a.max_q > kAloneMaxQ) return hipErrorInvalidValue;
   const dim3 g((unsigned)a.count), b(64);
-  if (a.bias == a.o) hipLaunchKernelGGL((k_alone_fill<REV, true, LAST>), g, b, alone_lds(a), st, a);
-  else hipLaunchKernelGGL((k_alone_fill<REV, false, LAST>), g, b, alone_lds(a), st, a);
+  if (a.bias == a.o) hipLaunchKernelGGL((k_alone_fill<MODE, true>), g, b, alone_lds(a), st, a);
+  else hipLaunchKernelGGL((k_alone_fill<MODE, false>), g, b, alone_lds(a), st, a);
   return hipGetLastError();
 }
 
-hipError_t alone_forward(const AloneArgs &a, hipStream_t st) { return alone_fill<false, false>(a, st); }
-hipError_t alone_last(const AloneArgs &a, hipStream_t st) { return alone_fill<false, true>(a, st); }
-hipError_t alone_reverse(const AloneArgs &a, hipStream_t st) { return alone_fill<true, false>(a, st); }
+hipError_t alone_forward(const AloneArgs &a, hipStream_t st) { return alone_fill<kAloneForward>(a, st); }
+hipError_t alone_pass(const AloneArgs &a, hipStream_t st) { return alone_fill<kAlonePass>(a, st); }
+hipError_t alone_begin(const AloneArgs &a, hipStream_t st) { return alone_fill<kAloneBegin>(a, st); }
+hipError_t alone_last(const AloneArgs &a, hipStream_t st) { return alone_fill<kAloneLast>(a, st); }
+hipError_t alone_reverse(const AloneArgs &a, hipStream_t st) { return alone_fill<kAloneReverse>(a, st); }
 
 hipError_t alone_forward16(const AloneArgs &a, bool m3, hipStream_t st) {
   if (a.count == 0) return hipSuccess;

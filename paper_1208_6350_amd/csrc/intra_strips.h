@@ -364,9 +364,33 @@ __device__ __forceinline__ bool strips_of_wave(const StripJob &x, const StripSco
 // the first one starts from the anchor and holds the gap run that leaves it
 // (a forward alignment may end in a deletion run), so that only paths from
 // that corner can reach a target above the anchor.  LAST: only the last column's word is wanted, in *rrow.
+// best (forward, may be null): the largest value's word and its first column.
+struct StripBest {
+  uint32_t word;   // max array word, this lane's until whole_wave
+  int64_t col;     // -1: no value above 0
+  __device__ __forceinline__ void take(uint32_t w, int64_t c, int kb) {
+    if ((w >> kb) > (word >> kb)) {   // (a lane's columns come in order)
+      word = w;
+      col = c;
+    }
+  }
+  __device__ __forceinline__ void whole_wave(int kb) {
+    uint32_t v = word >> kb;
+    int64_t c = v ? col : INT64_MAX;
+    for (int off = 32; off >= 1; off >>= 1) {
+      const uint32_t v2 = __shfl_xor(v, off, 64);
+      const int64_t c2 = __shfl_xor(c, off, 64);
+      if (v2 > v || (v2 == v && c2 < c)) { v = v2; c = c2; }
+    }
+    const unsigned long long own = __ballot((word >> kb) == v && col == c);
+    word = v ? (uint32_t)__builtin_amdgcn_readlane((int)word, __builtin_ctzll(own | (1ull << 63))) : 0u;
+    col = v ? c : -1;
+  }
+};
 template <int RL, bool REV, bool HO, bool LAST = false>
 __device__ __forceinline__ void strip_alone(const StripJob &x, const StripScoring &sc,
-                                            const int8_t *s_mat, uint8_t *s_prof) {
+                                            const int8_t *s_mat, uint8_t *s_prof,
+                                            StripBest *best = nullptr) {
   constexpr int SH = 64 * RL;
   constexpr int XW = RL >= 4 ? RL / 4 : 1;
   constexpr int kUnroll = RL <= 4 ? kSpreadBlock : (RL == 8 ? 4 : 1);
@@ -469,7 +493,10 @@ __device__ __forceinline__ void strip_alone(const StripJob &x, const StripScorin
     } else if constexpr (LAST) {
       if (mine && c == chi - 1) *x.rrow = (int32_t)obC;
     } else {
-      if (mine && c >= x.c0) x.mc[c] = obC;
+      if (mine && c >= x.c0) {
+        x.mc[c] = obC;
+        if (best) best->take(obC, c, x.kb);
+      }
     }
   }
 }
@@ -483,7 +510,8 @@ __device__ __forceinline__ void strip_alone(const StripJob &x, const StripScorin
 template <int RL, bool M3, bool HO>
 __device__ __forceinline__ void strip_alone16(const StripJob &x, const StripJob &y,
                                               const StripScoring &sc, const int8_t *s_mat,
-                                              uint8_t *s_profA, uint8_t *s_profB) {
+                                              uint8_t *s_profA, uint8_t *s_profB,
+                                              StripBest &bestA, StripBest &bestB) {
   constexpr int SH = 64 * RL;
   constexpr int kUnroll = RL <= 4 ? kSpreadBlock : 4;
   using T = VT<u16x2>;
@@ -573,8 +601,14 @@ __device__ __forceinline__ void strip_alone16(const StripJob &x, const StripJob 
     }
     const int64_t off = t0 + kSpreadBlock - 1 - (63 - f) - 63 + lane;
     if (lane >= 64 - kSpreadBlock && off >= 0) {
-      if (off < wA && x.cw + off >= x.c0) x.mc[x.cw + off] = obA;
-      if (off < wB && y.cw + off >= y.c0) y.mc[y.cw + off] = obB;
+      if (off < wA && x.cw + off >= x.c0) {
+        x.mc[x.cw + off] = obA;
+        bestA.take(obA, x.cw + off, 16);
+      }
+      if (off < wB && y.cw + off >= y.c0) {
+        y.mc[y.cw + off] = obB;
+        bestB.take(obB, y.cw + off, 16);
+      }
     }
   }
 }

@@ -126,26 +126,9 @@ __global__ void k_compact(int64_t n, const uint8_t *flag, const int64_t *pos, in
   if (p < n && flag[p]) out[pos[p]] = p;
 }
 
-// reversed pass setup: drift band per pair and the lane width it runs at.
-// Every alignment of score score1 in the reversed region starts at the
-// reversed corner (T1 leaves no other cell of that value there).  A path
-// that drifts d diagonals off the corner's diagonal holds at least d gap
-// symbols, so score1 <= smax*min(qend+1, rend+1) - o - (d-1)e: d <= G'.
-// When the drift is towards the query (i - j = d) those d symbols are
-// insertions, which also leave at most qend+1-d rows for matches:
-// score1 <= smax*(qend+1-d) - o - (d-1)e, so d <= Gq =
-// (smax*(qend+1) - o + e - score1) / (smax + e); towards the reference
-// likewise with rend+1 (Gr).  band = max(min(G', Gq), min(G', Gr)) bounds
-// both sides, band_q = min(G', Gq) the query side (e > 0; with e == 0 no band
-// is used).
-__device__ __forceinline__ int64_t rev_drift(int64_t num, int64_t den) {
-  const int64_t g = num / den;
-  return g < 0 ? 0 : (g > (1 << 30) ? (1 << 30) : g);
-}
-
-// The same launch makes the pass's views (prefixes q[0..qend] and r[0..rend],
-// read backwards by the fill), its target, presets its score to none and flags
-// the pairs by lane width (f16, f32: may be null).
+// The reversed pass's setup: the band per pair (rev_band), its views (prefixes q[0..qend] and r[0..rend],
+// read backwards by the fill), its target, its score preset to none and flags
+// by lane width (f16, f32: may be null).
 __global__ void k_rev_setup(int64_t n, PairView v, const int32_t *score, const int32_t *qend,
                             const int64_t *rend, const uint8_t *lanebits, int32_t smax, int32_t o,
                             int32_t e, RevSetup s, uint8_t *err) {
@@ -154,20 +137,7 @@ __global__ void k_rev_setup(int64_t n, PairView v, const int32_t *score, const i
   bool ok = score[p] > 0;
   const int64_t rows = (int64_t)qend[p] + 1, cols = rend[p] + 1;
   int32_t b = 0, bq = 0;
-  if (ok) {
-    if (e > 0) {
-      const int64_t base = -(int64_t)o + e - score[p];
-      const int64_t g = rev_drift((int64_t)smax * (rows < cols ? rows : cols) + base, e);
-      int64_t gq = rev_drift((int64_t)smax * rows + base, (int64_t)smax + e);
-      int64_t gr = rev_drift((int64_t)smax * cols + base, (int64_t)smax + e);
-      gq = gq < g ? gq : g;
-      gr = gr < g ? gr : g;
-      b = (int32_t)(gq > gr ? gq : gr);
-      bq = (int32_t)gq;
-    } else {
-      b = bq = -1;
-    }
-  }
+  if (ok) rev_band(score[p], rows, cols, smax, o, e, b, bq);
   s.band[p] = b;
   s.band_q[p] = bq;
   if (s.f16) {

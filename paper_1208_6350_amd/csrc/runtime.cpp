@@ -626,7 +626,7 @@ static int upload(swx_ctx *ctx, const HostIn *in, int count) {
 // Where kernels write an output of `bytes` bytes for the caller's host memory:
 // pinned memory, copied when the call's work has finished (finish_outputs).
 // Null: no room there, the caller copies from a device buffer.
-static void *host_out(swx_ctx *ctx, void *dst, int64_t bytes) {
+static void *host_place(swx_ctx *ctx, int64_t bytes) {
   if (ctx->arena.fixed() || ctx->out_used + round_up(bytes, 256) > swx_ctx::kStage) return nullptr;
   if (!ctx->stage_out &&
       hipHostMalloc(&ctx->stage_out, swx_ctx::kStage, hipHostMallocDefault) != hipSuccess) {
@@ -635,7 +635,11 @@ static void *host_out(swx_ctx *ctx, void *dst, int64_t bytes) {
   }
   void *at = ctx->stage_out + ctx->out_used;
   ctx->out_used += round_up(bytes, 256);
-  ctx->out_copies.push_back({dst, at, (size_t)bytes});
+  return at;
+}
+static void *host_out(swx_ctx *ctx, void *dst, int64_t bytes) {
+  void *at = host_place(ctx, bytes);
+  if (at) ctx->out_copies.push_back({dst, at, (size_t)bytes});
   return at;
 }
 static void finish_outputs(swx_ctx *ctx) {
@@ -740,9 +744,31 @@ static constexpr int64_t kTbPairsAll = 32768, kTbPairsMax = int64_t(1) << 18;
 static constexpr int64_t kTbPairsBytes = int64_t(600) << 20, kTbWideBytes = int64_t(384) << 20;
 static constexpr int64_t kTbGraphPairs = 4096, kTbGraphBytes = int64_t(1) << 30;   // of a graph (fixed, worst case)
 
+// A batch traced a workgroup per pair without a class pass: scratch and CIGAR
+// words at fixed strides for the longest query and reference, up to
+// kTbGraphBytes, so that nothing has to be read back before the kernel.  With
+// `defer` the CIGARs' total is not read either: the compaction and the records
+// compare it with the capacity on the device, and finish_cigars reads it with
+// the call's last read.  101 host reads: 0.39 -> 0.33 ms for the whole call with
+// what AloneRest saves (nine launches and two waits less in all).
+struct TbDirect {
+  int64_t max_q, max_r, stride;
+  bool defer;
+  // set by run_traceback when it deferred: the total's place, and for host
+  // memory the words' place in pinned memory and its room
+  const int64_t *total;
+  uint32_t *pin;
+  int64_t room;
+  uint32_t *cscr;
+};
+
+static int place_cigars(swx_ctx *ctx, int64_t np, const TbArgs &ta, const int64_t *coff,
+                        const uint8_t *cls, const int64_t *cig_off_final, TbDirect *direct,
+                        swx_batch_out *out, uint32_t *flags, int *rc_range);
+
 // max_rows: most rows of a pair (the shape of the launch, no limit)
 static int run_traceback(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, int64_t np,
-                         int64_t max_rows,
+                         int64_t max_rows, TbDirect *by_stride,
                          const int32_t *score, const int32_t *qbeg, const int32_t *qend,
                          const int64_t *rbeg, const int64_t *rend, const int64_t *qstart,
                          const int64_t *rstart, const int32_t *qlen, const int64_t *rlen,
@@ -758,6 +784,17 @@ static int run_traceback(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, 
   ta.n = sc.n; ta.o = sc.o; ta.e = sc.e; ta.smax = sc.smax;
   ta.cig_len = cig_len; ta.err = err;
   ta.wave_cells = np <= kTbFewPairs ? kWaveTbCellsFew : kWaveTbCells;
+  if (by_stride) {
+    ta.cig_stride = by_stride->max_q + by_stride->max_r + 2;
+    ta.cig = A.get<uint32_t>(np * ta.cig_stride);
+    TbPairs tp{};
+    tp.stride = by_stride->stride;
+    tp.scratch = A.get<uint8_t>(np * tp.stride);
+    if (!ta.cig || !tp.scratch) return fail(SWX_ENOMEM, "device pool exhausted (pair traceback)");
+    HIP_TRY(tb_pairs(ta, tp, np, max_rows, st));
+    HIP_TRY(scan_lens(np, cig_len, cig_off_final, st));
+    return place_cigars(ctx, np, ta, nullptr, nullptr, cig_off_final, by_stride, out, flags, rc_range);
+  }
   uint8_t *cls = A.get<uint8_t>(np);
   uint64_t *k0 = A.get<uint64_t>(np), *k1 = A.get<uint64_t>(np);
   int64_t *v0 = A.get<int64_t>(np), *v1 = A.get<int64_t>(np);
@@ -983,6 +1020,39 @@ static int run_traceback(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, 
     HIP_TRY(lens_to_i64(np, cig_len, len64, st));
     if ((rc = scan(ctx, len64, cig_off_final, np + 1))) return rc;
   }
+  return place_cigars(ctx, np, ta, coff, cls, cig_off_final, nullptr, out, flags, rc_range);
+}
+
+static int place_cigars(swx_ctx *ctx, int64_t np, const TbArgs &ta, const int64_t *coff,
+                        const uint8_t *cls, const int64_t *cig_off_final, TbDirect *direct,
+                        swx_batch_out *out, uint32_t *flags, int *rc_range) {
+  DevArena &A = ctx->arena;
+  hipStream_t st = ctx->stream;
+  const int32_t *cig_len = ta.cig_len;
+  if (direct && direct->defer) {
+    uint32_t *dst = out->cigar;
+    direct->room = out->cigar_cap;
+    if (out->out_mem != SWX_MEM_DEVICE && dst) {
+      // (room kept for the records behind it)
+      const int64_t bytes = swx_ctx::kStage - ctx->out_used - round_up((int64_t)sizeof(swx_rec) * np, 256) - 256;
+      dst = bytes >= 4096 ? (uint32_t *)host_place(ctx, bytes / 256 * 256) : nullptr;
+      if (dst) {
+        direct->pin = dst;
+        direct->room = std::min<int64_t>(out->cigar_cap, bytes / 256 * 64);
+      } else {
+        direct->defer = false;
+      }
+    }
+    if (direct->defer) {
+      direct->total = cig_off_final + np;
+      direct->cscr = ta.cig;
+      if (dst)
+        HIP_TRY(launch_cigar_compact(np, ta.cig, nullptr, cig_len, cig_off_final, nullptr, ta.qbeg,
+                                     ta.qend, dst, ta.cig_stride, direct->room, st));
+      return SWX_OK;
+    }
+  }
+  int rc;
   int64_t total = 0;
   if ((rc = read_i64(ctx, cig_off_final + np, &total))) return rc;
   out->cigar_used = total;
@@ -1001,7 +1071,8 @@ static int run_traceback(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, 
       dst = dtmp;
     }
   }
-  HIP_TRY(launch_cigar_compact(np, cscr, coff, cig_len, cig_off_final, cls, qbeg, qend, dst, st));
+  HIP_TRY(launch_cigar_compact(np, ta.cig, coff, cig_len, cig_off_final, cls, ta.qbeg, ta.qend, dst,
+                               ta.cig_stride, INT64_MAX, st));
   if (dtmp && total)
     HIP_TRY(hipMemcpyAsync(out->cigar, dtmp, sizeof(uint32_t) * total, hipMemcpyDeviceToHost, st));
   return SWX_OK;
@@ -1483,24 +1554,41 @@ static IntraPairArgs alone_pairs(const AlonePath &al, const int32_t *qlen, const
   return e;
 }
 
+// What follows the forward pass of a batch that takes this path as a whole:
+// begins, and with SWX_SCORE2 score2, by the same wave (32-bit lanes) or one
+// kernel (null arrays: the forward pass alone).
+struct AloneRest {
+  int32_t *qbeg = nullptr, *score2 = nullptr;
+  int64_t *rbeg = nullptr, *rend2 = nullptr;
+  uint8_t *err = nullptr;
+  int32_t mask_len = 0;
+};
+static void add_rest(AloneArgs &a, const Scoring &sc, const AloneRest &r) {
+  a.smax = sc.smax;
+  a.mask_len = r.mask_len;
+  a.qbeg = r.qbeg; a.score2 = r.score2; a.rbeg = r.rbeg; a.rend2 = r.rend2;
+  a.err = r.err;
+}
+
 static int run_alone_forward(swx_ctx *ctx, const Scoring &sc, const AlonePath &al, int64_t bound,
-                             const PairView &view, const FillOut &out, uint8_t *lanebits) {
+                             const PairView &view, const FillOut &out, uint8_t *lanebits,
+                             const AloneRest &rest) {
   AloneArgs a = alone_args(sc, al, view, out);
+  add_rest(a, sc, rest);
   if (al.n32 > 0) {
     AloneArgs w = a;
     w.count = al.n32;
     w.lanebits = lanebits;
-    HIP_TRY(alone_forward(w, ctx->stream));
+    if (rest.qbeg) HIP_TRY(alone_pass(w, ctx->stream));
+    else HIP_TRY(alone_forward(w, ctx->stream));
   }
   if (al.count > al.n32) {
     if (al.n32 > 0) a.ids += al.n32;   // (a list, then)
     a.maxcol += al.n32 * al.stride;
     a.count -= al.n32;
     HIP_TRY(alone_forward16(a, bound + sc.bias <= kMax3Lane, ctx->stream));
+    if (rest.qbeg) HIP_TRY(alone_begin(a, ctx->stream));
   }
-  IntraPairArgs e = alone_pairs(al, view.qlen, view.rlen);
-  e.score = out.score; e.qend = out.qend; e.rend = out.rend; e.overflow = out.overflow;
-  HIP_TRY(intra_end(e, al.count, ctx->stream));
   return SWX_OK;
 }
 
@@ -1699,6 +1787,30 @@ static int run_intra_reverse(swx_ctx *ctx, const Scoring &sc, LongPath &lp, cons
   return launch_intra_jobs(ctx, groups, a, bnd_words, true);
 }
 
+// The CIGARs of a deferred traceback (TbDirect), whose total is known now.
+static int finish_cigars(swx_ctx *ctx, int64_t np, const TbDirect &d, int64_t total,
+                         const int32_t *cig_len, const int64_t *cig_off_final, const int32_t *qbeg,
+                         const int32_t *qend, swx_batch_out *out, int *rc_range) {
+  out->cigar_used = total;
+  if (total > out->cigar_cap || (total > 0 && !out->cigar)) {
+    *rc_range = SWX_ERANGE;
+    g_last_error = "CIGAR arena too small";
+    return SWX_OK;
+  }
+  if (out->out_mem == SWX_MEM_DEVICE || total == 0) return SWX_OK;
+  if (total <= d.room) {
+    memcpy(out->cigar, d.pin, sizeof(uint32_t) * (size_t)total);
+    return SWX_OK;
+  }
+  uint32_t *tmp = ctx->arena.get<uint32_t>(total);   // more than the pinned memory holds
+  if (!tmp) return fail(SWX_ENOMEM, "device pool exhausted");
+  HIP_TRY(launch_cigar_compact(np, d.cscr, nullptr, cig_len, cig_off_final, nullptr, qbeg, qend, tmp,
+                               d.max_q + d.max_r + 2, INT64_MAX, ctx->stream));
+  HIP_TRY(hipMemcpyAsync(out->cigar, tmp, sizeof(uint32_t) * total, hipMemcpyDeviceToHost, ctx->stream));
+  HIP_TRY(wait_stream(ctx->stream));
+  return SWX_OK;
+}
+
 // the records' place: the caller's device memory, pinned memory, or (*copy) a
 // device buffer that is copied at the end
 static swx_rec_dev *out_records(swx_ctx *ctx, swx_rec *dst, uint32_t out_mem, int64_t np, bool *copy) {
@@ -1809,8 +1921,19 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
   AlonePath al;
   if ((rc = plan_alone(ctx, sc, np, flags, hstats, qlen, rlen, lp, al))) return rc;
   if (!al.on && (rc = list_pairs(ctx, np, lp))) return rc;
+  AloneRest rest;
+  if (al.all && (flags & SWX_BEGIN)) {
+    rest.qbeg = qbeg;
+    rest.rbeg = rbeg;
+    rest.err = err;
+    rest.mask_len = mask_len;
+    if (flags & SWX_SCORE2) {
+      rest.score2 = score2;
+      rest.rend2 = rend2;
+    }
+  }
   auto long_forward = [&]() -> int {
-    return al.on ? run_alone_forward(ctx, sc, al, score_bound, fview, fout, lanebits)
+    return al.on ? run_alone_forward(ctx, sc, al, score_bound, fview, fout, lanebits, rest)
                  : run_intra_forward(ctx, sc, lp, fview, fout, err, lanebits);
   };
 
@@ -1859,7 +1982,7 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
   HIP_TRY(hipEventRecord(ctx->ev[3], st));
 
   // reversed pass: begin
-  if (flags & SWX_BEGIN) {
+  if ((flags & SWX_BEGIN) && !rest.qbeg) {
     int64_t *rqs = A.get<int64_t>(np), *rrs = A.get<int64_t>(np), *rrl = A.get<int64_t>(np);
     int32_t *rql = A.get<int32_t>(np), *tgt = A.get<int32_t>(np), *band = A.get<int32_t>(np);
     int32_t *band_q = A.get<int32_t>(np), *rsc = A.get<int32_t>(np), *rqe = A.get<int32_t>(np);
@@ -1936,8 +2059,13 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
   int32_t *cig_len = A.get<int32_t>(np);
   if (!cig_off_final || !cig_len) return fail(SWX_ENOMEM, "device pool exhausted");
   int rc_range = SWX_OK;
+  TbDirect direct{hstats[2], hstats[3],
+                  round_up(tb_wave_dir_bytes(hstats[2], hstats[3], kTbPairRows), 256) +
+                      tb_pair_bnd_bytes(hstats[2], hstats[3]),
+                  (flags & SWX_SUBOPT) == 0, nullptr, nullptr, 0, nullptr};
+  TbDirect *const tbd = al.all && np * direct.stride <= kTbGraphBytes ? &direct : nullptr;
   if (flags & SWX_CIGAR) {
-    if ((rc = run_traceback(ctx, sc, b, np, hstats[0], score, qbeg, qend, rbeg, rend, qstart, rstart, qlen,
+    if ((rc = run_traceback(ctx, sc, b, np, hstats[0], tbd, score, qbeg, qend, rbeg, rend, qstart, rstart, qlen,
                             rlen, cig_len, cig_off_final, err, out, &flags, &rc_range)))
       return rc;
   } else {
@@ -1946,7 +2074,7 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
   HIP_TRY(hipEventRecord(ctx->ev[5], st));
 
   // score2 from the max array (final CM plane of the forward tasks)
-  if (flags & SWX_SCORE2) {
+  if ((flags & SWX_SCORE2) && !rest.score2) {
     Score2InterArgs s2{};
     s2.rlen = rlen; s2.qlen = qlen; s2.score1 = score; s2.rbeg = rbeg; s2.rend = rend;
     s2.mask_len = mask_len; s2.score2 = score2; s2.rend2 = rend2;
@@ -2053,7 +2181,7 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
     so.cigar_cap = out->cigar_cap > base ? out->cigar_cap - base : 0;
     uint32_t sflags = SWX_BEGIN | SWX_CIGAR;
     int rc_sub = SWX_OK;
-    if ((rc = run_traceback(ctx, sc, b, np, hstats[0], s_score, s_qbeg, s_qend, s_rbeg, s_rend, qstart,
+    if ((rc = run_traceback(ctx, sc, b, np, hstats[0], tbd, s_score, s_qbeg, s_qend, s_rbeg, s_rend, qstart,
                             rstart, qlen, rlen, s_cig_len, s_cig_off, err, &so, &sflags, &rc_sub)))
       return rc;
     out->cigar_used = base + so.cigar_used;
@@ -2064,7 +2192,7 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
     swx_rec_dev *srec = out_records(ctx, out->sub_recs, out->out_mem, np, &scopy);
     if (!srec) return fail(SWX_ENOMEM, "device pool exhausted");
     HIP_TRY(launch_records(np, s_score, s_score, s_qbeg, s_qend, s_rbeg, s_rend, s_rend, s_cig_off,
-                           s_cig_len, slb, sflags, srec, nullptr, nullptr, st));
+                           s_cig_len, slb, sflags, srec, nullptr, nullptr, INT64_MAX, st));
     if (sflags & SWX_CIGAR) HIP_TRY(shift_cigar_offsets(np, base, srec, st));
     if (scopy)
       HIP_TRY(hipMemcpyAsync(out->sub_recs, srec, sizeof(swx_rec) * np, hipMemcpyDeviceToHost, st));
@@ -2075,13 +2203,22 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
   swx_rec_dev *drec = out_records(ctx, out->recs, out->out_mem, np, &rcopy);
   if (!drec) return fail(SWX_ENOMEM, "device pool exhausted");
   HIP_TRY(launch_records(np, score, score2, qbeg, qend, rbeg, rend, rend2, cig_off_final, cig_len,
-                         lanebits, flags, drec, err, stats + 7, st));
+                         lanebits, flags, drec, err, stats + 7,
+                         direct.total ? (out->cigar ? out->cigar_cap : 0) : INT64_MAX, st));
   if (rcopy && np)
     HIP_TRY(hipMemcpyAsync(out->recs, drec, sizeof(swx_rec) * np, hipMemcpyDeviceToHost, st));
   HIP_TRY(hipEventRecord(ctx->ev[7], st));
   // consistency: any per-pair error flag
   int64_t nerr = 0;
-  if ((rc = read_i64(ctx, stats + 7, &nerr))) return rc;
+  if (direct.total) {
+    int64_t h[2];
+    if ((rc = read_two(ctx, stats + 7, 1, direct.total, 1, h))) return rc;
+    nerr = h[0];
+    if ((rc = finish_cigars(ctx, np, direct, h[1], cig_len, cig_off_final, qbeg, qend, out, &rc_range)))
+      return rc;
+  } else if ((rc = read_i64(ctx, stats + 7, &nerr))) {
+    return rc;
+  }
   finish_outputs(ctx);
   ctx->nstages = 7;
   for (int k = 0; k < 7; ++k) {
@@ -2319,10 +2456,19 @@ static int fixed_issue(GraphState &g, hipStream_t st) {
   FillOut fout{g.score, g.qend, g.rend, g.ovf, g.err};
   IntraArgs ia{};
   if (g.alone.on) {
-    HIP_TRY(alone_forward(alone_args(g.sc, g.alone, fview, fout), st));
-    IntraPairArgs e = alone_pairs(g.alone, g.qlen, g.rlen);
-    e.score = g.score; e.qend = g.qend; e.rend = g.rend; e.overflow = g.ovf;
-    HIP_TRY(intra_end(e, B, st));
+    AloneArgs a = alone_args(g.sc, g.alone, fview, fout);
+    AloneRest rest;
+    rest.qbeg = g.qbeg;
+    rest.rbeg = g.rbeg;
+    rest.err = g.err;
+    rest.mask_len = g.cfg.mask_len;
+    if (flags & SWX_SCORE2) {
+      rest.score2 = g.score2;
+      rest.rend2 = g.rend2;
+    }
+    add_rest(a, g.sc, rest);
+    if (flags & SWX_BEGIN) HIP_TRY(alone_pass(a, st));
+    else HIP_TRY(alone_forward(a, st));
   } else if (g.intra) {
     HIP_TRY(intra_jobs_chunked(B, g.nc, g.chunk, g.qlen, g.rlen, g.sc.smax, g.sc.o, g.sc.e,
                                g.kbits, g.sh, g.RM, g.fbnd_stride, g.jobs, g.ipairs, st));
@@ -2347,18 +2493,13 @@ static int fixed_issue(GraphState &g, hipStream_t st) {
       return rc;
     HIP_TRY(mark_lanes_dev(B, nw, g.ids, g.lanebits, 32, st));
   }
-  if (flags & SWX_BEGIN) {
+  if ((flags & SWX_BEGIN) && !g.alone.on) {
     HIP_TRY(rev_setup(B, fview, g.score, g.qend, g.rend, g.lanebits, g.sc.smax, g.sc.o, g.sc.e,
                       RevSetup{g.rqs, g.rrs, g.rrl, g.rql, g.tgt, g.band, g.band_q, g.rsc, g.f16, g.f32},
                       g.err, st));
     PairView rview{g.rqs, g.rrs, g.rql, g.rrl, g.qcat, g.rcat, 1};
     FillOut rout{g.rsc, g.rqe, g.rre, g.rov, g.err};
-    if (g.alone.on) {
-      AloneArgs a = alone_args(g.sc, g.alone, rview, rout);
-      a.target = g.tgt;
-      a.band = g.band;
-      HIP_TRY(alone_reverse(a, st));
-    } else if (g.intra) {
+    if (g.intra) {
       HIP_TRY(intra_rev_jobs_fixed(B, g.score, g.rend, g.band, g.kbits, g.bnd_stride, g.rjobs, st));
       IntraArgs ra = ia;
       ra.jobs = g.rjobs;
@@ -2392,12 +2533,14 @@ static int fixed_issue(GraphState &g, hipStream_t st) {
     ta.cig_len = g.cig_len; ta.err = g.err;
     ta.wave_cells = INT64_MAX;   // no host-planned wave traceback in a graph
     ta.cig = g.cscr;
-    ta.cig_off = g.coff;
-    if (!g.intra) HIP_TRY(fill_i64(9, g.counts, 0, st));
-    HIP_TRY(tb_classify(ta, B, g.cls, g.tk0, g.tv0, g.coff, g.counts, g.counts + 8, nullptr, st));
+    ta.cig_stride = g.QM + g.RM + 2;
+    if (!g.tb_by_pairs) {
+      ta.cig_off = g.coff;
+      if (!g.intra) HIP_TRY(fill_i64(9, g.counts, 0, st));
+      HIP_TRY(tb_classify(ta, B, g.cls, g.tk0, g.tv0, g.coff, g.counts, g.counts + 8, nullptr, st));
+    }
     if (g.tb_by_pairs) {
       TbPairs tp{};
-      tp.cls = g.cls;
       tp.stride = g.tbp_stride;
       tp.scratch = g.tbp_scratch;
       HIP_TRY(tb_pairs(ta, tp, B, std::min<int64_t>(g.QM, g.RM), st));
@@ -2439,15 +2582,16 @@ static int fixed_issue(GraphState &g, hipStream_t st) {
       HIP_TRY(lens_to_i64(B, g.cig_len, g.len64, st));
       if ((rc = fixed_scan(g, g.len64, g.cig_off_final, B + 1, st))) return rc;
     }
-    HIP_TRY(launch_cigar_compact(B, g.cscr, g.coff, g.cig_len, g.cig_off_final, g.cls, g.qbeg,
-                                 g.qend, g.cigar, st));
+    HIP_TRY(launch_cigar_compact(B, g.cscr, ta.cig_off, g.cig_len, g.cig_off_final,
+                                 g.tb_by_pairs ? nullptr : g.cls, g.qbeg, g.qend, g.cigar,
+                                 ta.cig_stride, INT64_MAX, st));
   }
-  if ((flags & SWX_SCORE2) && g.intra) {
-    IntraPairArgs e = alone_pairs(g.alone, g.qlen, g.rlen);
-    if (!g.alone.on) {
-      e.pairs = g.ipairs; e.maxcol = g.maxcol;
-      e.part_v = g.part_v; e.part_j = g.part_j; e.max_rlen = g.RM;
-    }
+  if ((flags & SWX_SCORE2) && g.alone.on) {
+    // (with the forward pass)
+  } else if ((flags & SWX_SCORE2) && g.intra) {
+    IntraPairArgs e{};
+    e.pairs = g.ipairs; e.maxcol = g.maxcol; e.qlen = g.qlen; e.rlen = g.rlen;
+    e.part_v = g.part_v; e.part_j = g.part_j; e.max_rlen = g.RM;
     e.score = g.score; e.qend = g.qend; e.rend = g.rend; e.rbeg = g.rbeg;
     e.mask_len = g.cfg.mask_len; e.score2 = g.score2; e.rend2 = g.rend2;
     HIP_TRY(intra_score2(e, B, st));
@@ -2465,7 +2609,8 @@ static int fixed_issue(GraphState &g, hipStream_t st) {
     }
   }
   HIP_TRY(launch_records(B, g.score, g.score2, g.qbeg, g.qend, g.rbeg, g.rend, g.rend2,
-                         g.cig_off_final, g.cig_len, g.lanebits, flags, g.recs, g.err, g.status, st));
+                         g.cig_off_final, g.cig_len, g.lanebits, flags, g.recs, g.err, g.status,
+                         INT64_MAX, st));
   return SWX_OK;
 }
 

@@ -173,7 +173,8 @@ struct TbArgs {
   int32_t n, o, e, smax;
   uint32_t *dir;
   uint32_t *cig;
-  const int64_t *cig_off;
+  const int64_t *cig_off;   // null: pair p's run at p * cig_stride
+  int64_t cig_stride;
   int32_t *cig_len;
   uint8_t *err;
   int64_t wave_cells;    // wide bands with more cells go to the wave-parallel kernel
@@ -187,8 +188,9 @@ hipError_t tb_classify(const TbArgs &a, int64_t npairs, uint8_t *cls, uint64_t *
                        int64_t *coff, int64_t *counts, int64_t *words, int64_t *bytes, hipStream_t st);
 // Wave traceback planned on the device, a workgroup per pair: pairs
 // sorted[lo[x] .. lo[x] + cnt[x]) of each range, or (sorted null) every pair
-// by its class.  Scratch: stride bytes per block, or taken from cap bytes
-// through *used.
+// by its class, or (cls null too) every pair by its own look at it: no class
+// pass ran, flat pairs are traced here and every cig_len is set.  Scratch:
+// stride bytes per block, or taken from cap bytes through *used.
 struct TbPairs {
   const int64_t *sorted;
   const uint8_t *cls;
@@ -239,6 +241,37 @@ hipError_t class_ranges(const int64_t *counts, int64_t *ranges, hipStream_t st);
 hipError_t sort_keys(int64_t n, uint64_t *keys, uint64_t *keys_alt, int64_t *vals,
                      int64_t *vals_alt, void *tmp, size_t *tmp_bytes, int64_t **sorted_out,
                      hipStream_t st, int end_bit = 64, bool graph = false);
+// Drift band of the reversed pass over `rows` rows and `cols` columns.
+// Every alignment of score score1 in the reversed region starts at the
+// reversed corner (T1 leaves no other cell of that value there).  A path
+// that drifts d diagonals off the corner's diagonal holds at least d gap
+// symbols, so score1 <= smax*min(qend+1, rend+1) - o - (d-1)e: d <= G'.
+// When the drift is towards the query (i - j = d) those d symbols are
+// insertions, which also leave at most qend+1-d rows for matches:
+// score1 <= smax*(qend+1-d) - o - (d-1)e, so d <= Gq =
+// (smax*(qend+1) - o + e - score1) / (smax + e); towards the reference
+// likewise with rend+1 (Gr).  band = max(min(G', Gq), min(G', Gr)) bounds
+// both sides, band_q = min(G', Gq) the query side (e > 0; with e == 0 no band
+// is used).
+__device__ __forceinline__ int64_t rev_drift(int64_t num, int64_t den) {
+  const int64_t g = num / den;
+  return g < 0 ? 0 : (g > (1 << 30) ? (1 << 30) : g);
+}
+
+__device__ __forceinline__ void rev_band(int32_t score, int64_t rows, int64_t cols, int32_t smax,
+                                         int32_t o, int32_t e, int32_t &band, int32_t &band_q) {
+  band = band_q = -1;
+  if (e <= 0) return;
+  const int64_t base = -(int64_t)o + e - score;
+  const int64_t g = rev_drift((int64_t)smax * (rows < cols ? rows : cols) + base, e);
+  int64_t gq = rev_drift((int64_t)smax * rows + base, (int64_t)smax + e);
+  int64_t gr = rev_drift((int64_t)smax * cols + base, (int64_t)smax + e);
+  gq = gq < g ? gq : g;
+  gr = gr < g ? gr : g;
+  band = (int32_t)(gq > gr ? gq : gr);
+  band_q = (int32_t)gq;
+}
+
 // what the reversed pass takes of each pair, and its score's preset (k_rev_setup)
 struct RevSetup {
   int64_t *qstart, *rstart, *rlen;
@@ -301,12 +334,20 @@ struct AloneArgs {
   int64_t stride;
   uint8_t *lanebits;         // forward: 32 is written (32-bit lanes; may be null)
   const int32_t *target, *band;   // reversed pass (band may be null)
+  // what follows the forward pass in one go (alone_pass, alone_begin): begins
+  // and, with score2, the best outside the mask
+  int32_t smax, mask_len;
+  int32_t *qbeg, *score2;    // (score2 may be null)
+  int64_t *rbeg, *rend2;
+  uint8_t *err;
   uint32_t anchor;           // ... of paths from the corner alone (queries shorter than max_q then), else 0
   FillOut out;
 };
 // above every score of a pair whose words have room for the anchor and a score
 constexpr uint32_t kAloneAnchor = 1u << 15;
 hipError_t alone_forward(const AloneArgs &a, hipStream_t st);
+hipError_t alone_pass(const AloneArgs &a, hipStream_t st);    // forward, 32-bit lanes, and all that follows it
+hipError_t alone_begin(const AloneArgs &a, hipStream_t st);   // what follows it alone
 hipError_t alone_last(const AloneArgs &a, hipStream_t st);   // best of the last column only; empty references skipped
 hipError_t alone_forward16(const AloneArgs &a, bool m3, hipStream_t st);
 hipError_t alone_reverse(const AloneArgs &a, hipStream_t st);
@@ -454,21 +495,25 @@ hipError_t graph_out(int64_t npairs, const swx_rec_dev *recs, const uint32_t *ci
 // pair 0's CIGAR words and final offsets {0, length} (one-pair calls)
 // cls: the traceback classes (pairs of class kTbFlat hold no scratch words:
 // their one word is made from qbeg and qend)
+// (src_off null: runs at p * stride; cls may be null; nothing is copied when
+// the words, dst_off[npairs], are more than cap)
 hipError_t launch_cigar_compact(int64_t npairs, const uint32_t *src, const int64_t *src_off,
                                 const int32_t *len, const int64_t *dst_off, const uint8_t *cls,
                                 const int32_t *qbeg, const int32_t *qend, uint32_t *dst,
-                                hipStream_t st);
+                                int64_t stride, int64_t cap, hipStream_t st);
 hipError_t launch_score2_inter(const Score2InterArgs &a, hipStream_t st);
 hipError_t launch_score2_plain(int64_t p, const int32_t *maxcol, int64_t lr, const int32_t *score1,
                                const int64_t *rbeg, const int64_t *rend, int32_t mask_len,
                                const int32_t *qlen, int32_t *score2, int64_t *rend2,
                                hipStream_t st);
-// err (may be null): *nerr += the pairs whose flag is set
+// err (may be null): *nerr += the pairs whose flag is set; CIGARs of more than
+// cap words in all (cig_off[npairs]) are left out of the records
 hipError_t launch_records(int64_t npairs, const int32_t *score1, const int32_t *score2,
                           const int32_t *qbeg, const int32_t *qend, const int64_t *rbeg,
                           const int64_t *rend, const int64_t *rend2, const int64_t *cig_off,
                           const int32_t *cig_len, const uint8_t *lane_bits, uint32_t flags,
-                          swx_rec_dev *recs, const uint8_t *err, int64_t *nerr, hipStream_t st);
+                          swx_rec_dev *recs, const uint8_t *err, int64_t *nerr, int64_t cap,
+                          hipStream_t st);
 // the suboptimal alignment: window views, anchored reversed views, begins,
 // and CIGAR offsets of records counted from the arena's start
 hipError_t launch_sub_window(int64_t npairs, const int64_t *rstart, const int32_t *qlen,

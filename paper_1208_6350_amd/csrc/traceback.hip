@@ -76,6 +76,11 @@ __device__ __forceinline__ uint32_t row0_code(int64_t j, int32_t o, int32_t e) {
   return (j == 0) ? 0u : (kCodeNotM | ((j == 1 || o <= e) ? 0u : kCodeEExt));
 }
 
+// where pair p's runs go
+__device__ __forceinline__ uint32_t *tb_cig(const TbArgs &a, int64_t p) {
+  return a.cig + (a.cig_off ? a.cig_off[p] : p * a.cig_stride);
+}
+
 __device__ __forceinline__ bool tb_coords_ok(const TbArgs &a, int64_t p) {
   return a.qbeg[p] >= 0 && a.qbeg[p] <= a.qend[p] && a.qend[p] < a.qlen[p] && a.rbeg[p] >= 0 &&
          a.rbeg[p] <= a.rend[p] && a.rend[p] < a.rlen[p];
@@ -1593,7 +1598,7 @@ __global__ __launch_bounds__(64 * kTbPairMaxWaves) void k_tb_pairs(TbArgs a, TbP
     int x = 0;
     while (x + 1 < t.ranges && k >= t.cnt[x]) k -= t.cnt[x++];
     p = t.sorted[t.lo[x] + k];
-  } else {
+  } else if (t.cls) {
     const uint8_t c = t.cls[p];
     if (c == 0 || c == 6 || c == kTbFlat) return;   // nothing to trace, or another kernel's pair
   }
@@ -1601,6 +1606,28 @@ __global__ __launch_bounds__(64 * kTbPairMaxWaves) void k_tb_pairs(TbArgs a, TbP
   jb.pair = p;
   jb.m = a.qend[p] - a.qbeg[p] + 1;
   jb.w = a.rend[p] - a.rbeg[p] + 1;
+  if (!t.sorted && !t.cls) {
+    const int32_t s1 = a.score[p];
+    const bool ok = s1 > 0 && tb_coords_ok(a, p);
+    int32_t sum = 0;   // the main diagonal's, by every wave alike
+    if (ok && jb.m == jb.w && jb.m < (1 << 24)) {
+      const int8_t *q = a.qcat + a.qstart[p] + a.qbeg[p], *r = a.rcat + a.rstart[p] + a.rbeg[p];
+      for (int64_t x = threadIdx.x & 63; x < jb.m; x += 64) {
+        const uint32_t qc = (uint8_t)q[x], rc = (uint8_t)r[x];
+        sum += qc < (uint32_t)a.n && rc < (uint32_t)a.n ? a.matrix[qc * a.n + rc] : 0;   // (a graph's codes may be bad)
+      }
+      for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, 64);
+    }
+    const bool flat = ok && jb.m == jb.w && jb.m < (1 << 24) && sum == s1;
+    if (!ok || flat) {
+      if (threadIdx.x == 0) {
+        if (s1 > 0 && !ok) a.err[p] = 1;
+        a.cig_len[p] = flat ? 1 : 0;
+        if (flat) *tb_cig(a, p) = (uint32_t)jb.m << 4;
+      }
+      return;
+    }
+  }
   safe_band(jb.m, jb.w, a.score[p], a.smax, a.o, a.e, &jb.dlo, &jb.bw);
   const int64_t bytes = tb_pair_bytes(jb.m, jb.w, jb.dlo, jb.bw);
   int64_t off = t.stride * (int64_t)blockIdx.x, room = t.stride;
@@ -1624,7 +1651,7 @@ __global__ __launch_bounds__(64 * kTbPairMaxWaves) void k_tb_pairs(TbArgs a, TbP
 hipError_t tb_pairs(const TbArgs &a, const TbPairs &t, int64_t blocks, int64_t max_rows,
                     hipStream_t st) {
   if (blocks == 0) return hipSuccess;
-  if (!t.sorted && !t.cls) return hipErrorInvalidValue;
+  if (!t.sorted && !t.cls && t.used) return hipErrorInvalidValue;
   const int64_t per = (int64_t)(a.n + 1) * 64 * kTbPairRows;
   int64_t waves = (max_rows + 64 * kTbPairRows - 1) / (64 * kTbPairRows);
   waves = std::min<int64_t>({waves, (int64_t)kTbPairMaxWaves, (65536 - 16384) / per});
@@ -1672,7 +1699,7 @@ __device__ void tb_wave_walk(const TbArgs &a, const TbWaveJob &jb, const uint8_t
   // gap step in an iteration of its own and 64-bit coordinates the walk of
   // 10,000 rows at 10% errors took 1.24 ms; with its tiles loaded eight words a
   // lane at a time and the runs turned round by all lanes besides, 0.43.
-  uint32_t *out = a.cig + a.cig_off[p];
+  uint32_t *out = tb_cig(a, p);
   int32_t nruns = 0;
   int32_t i = m, j = w;
   int state = 0;

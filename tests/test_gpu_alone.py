@@ -127,3 +127,17 @@ def test_suboptimal(mask_len, match, top):
     for p in range(b.npairs):
         g = cig[sub["cigar_off"][p]:sub["cigar_off"][p] + sub["cigar_len"][p]]
         np.testing.assert_array_equal(g, scig[scoff[p]:scoff[p] + sref[p, 3]])
+
+
+# more CIGAR words than the pinned memory beside 45,000 records holds
+def test_many_cigar_words():
+    g = np.random.Generator(np.random.PCG64(8900))
+    n = 45_000
+    core = g.integers(0, 4, size=n * 48).astype(np.int8)
+    q, qoff = W.mutate_many(g, core, np.arange(n + 1) * 48, 0.1, 0.1, 0.1, 4, 4)
+    b = W.from_lists("alone-words", W.dna_matrix(), 2, 1, [q[qoff[k]:qoff[k + 1]] for k in range(n)],
+                     [core[48 * k:48 * k + 48] for k in range(n)])
+    c = swx.Context(0)
+    recs = assert_parity(c, b)
+    c.close()
+    assert recs["cigar_len"].sum() > (4 << 18) - 12 * n
