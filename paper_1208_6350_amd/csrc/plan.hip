@@ -6,6 +6,8 @@
 // dimensions and little padding.  Task sizes and buffer offsets are derived on
 // the device; the host only reads back the totals it must allocate.
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 #include <rocprim/device/device_radix_sort.hpp>
 
 #include "swx_internal.h"
@@ -13,11 +15,33 @@
 
 namespace swx {
 
+// The key's fields from the lowest: reference length, half-strip count of the
+// query, band class.  Their widths cover the batch's longest sequences and no
+// more: a pass of the sort per 8 bits is 40 us for 2,000,000 pairs, and two
+// clears with their launches (44 and 64 bits as fixed fields: 14 passes for
+// both fills of 70 x 70 overlaps, now 5).
+struct PlanBits { int r, q, b; };
+static int bits_of(int64_t v) {
+  int k = 1;
+  while (k < 62 && (int64_t(1) << k) <= v) ++k;
+  return k;
+}
+// max_q, max_r: no pair of the pass is longer (0: not known)
+static PlanBits plan_bits(int64_t max_q, int64_t max_r, int32_t R, bool band) {
+  PlanBits w{28, 16, band ? 20 : 0};
+  if (max_q > 0 || max_r > 0) {
+    w.r = std::min(w.r, bits_of(max_r));
+    w.q = std::min(w.q, bits_of((std::max<int64_t>(max_q, 1) + R / 2 - 1) / (R / 2)));
+    if (band) w.b = std::min(w.b, bits_of(max_r / 2 + 3));   // (a banded class is below rlen / 2)
+  }
+  return w;
+}
+
 // n_dev (may be null): the number of valid ids, read on the device; entries
 // beyond it get the largest key (they sort last and form empty tasks)
 __global__ void k_plan_keys(int64_t n, const int64_t *n_dev, const int64_t *ids, const int32_t *qlen,
-                            const int64_t *rlen, const int32_t *band, int32_t R, uint64_t *keys,
-                            int64_t *vals) {
+                            const int64_t *rlen, const int32_t *band, int32_t R, PlanBits w,
+                            uint64_t *keys, int64_t *vals) {
   const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= n) return;
   if (n_dev && k >= *n_dev) {
@@ -29,19 +53,20 @@ __global__ void k_plan_keys(int64_t n, const int64_t *n_dev, const int64_t *ids,
   int64_t q = qlen[p];
   if (q < 1) q = 1;
   const uint64_t qc = (uint64_t)((q + R / 2 - 1) / (R / 2));   // half-strip buckets
+  auto top = [](int k) { return (uint64_t(1) << k) - 1; };
   uint64_t r = (uint64_t)rlen[p];
-  if (r > 0xFFFFFFFull) r = 0xFFFFFFFull;
+  if (r > top(w.r)) r = top(w.r);
   // band class: the band half-width, except that pairs whose band spans
   // nearly the whole reference (2 * band + R >= rlen: a strip's window then
   // leaves out few columns) are grouped by size alone, after the banded ones,
   // and unbanded pairs come last
   uint64_t b = 0;
   if (band) {
-    if (band[p] < 0) b = 0xFFFFFull;
-    else if (2 * (int64_t)band[p] + R >= (int64_t)rlen[p]) b = 0xFFFFEull;
-    else b = (uint64_t)(band[p] > 0xFFFFD ? 0xFFFFD : band[p]);
+    if (band[p] < 0) b = top(w.b);
+    else if (2 * (int64_t)band[p] + R >= (int64_t)rlen[p]) b = top(w.b) - 1;
+    else b = (uint64_t)band[p] > top(w.b) - 2 ? top(w.b) - 2 : (uint64_t)band[p];
   }
-  keys[k] = (b << 44) | ((qc > 0xFFFF ? 0xFFFF : qc) << 28) | r;
+  keys[k] = (b << (w.q + w.r)) | ((qc > top(w.q) ? top(w.q) : qc) << w.r) | r;
   vals[k] = p;
 }
 
@@ -197,12 +222,12 @@ hipError_t rev_setup(int64_t npairs, const PairView &v, const int32_t *score, co
 }
 
 hipError_t plan_sort(int64_t n, const int64_t *n_dev, const int64_t *ids, const int32_t *qlen,
-                     const int64_t *rlen, const int32_t *band, int32_t R, uint64_t *keys,
-                     uint64_t *keys_alt, int64_t *vals, int64_t *vals_alt, void *tmp,
+                     const int64_t *rlen, const int32_t *band, int32_t R, int64_t max_q, int64_t max_r,
+                     uint64_t *keys, uint64_t *keys_alt, int64_t *vals, int64_t *vals_alt, void *tmp,
                      size_t *tmp_bytes, int64_t **sorted_out, hipStream_t st, bool graph) {
-  // without a band the top field is zero: sort the low 44 bits only.  The
-  // size query covers both bit ranges, so one buffer serves either pass.
-  const int end_bit = band ? 64 : 44;
+  const PlanBits w = n_dev ? plan_bits(0, 0, R, band != nullptr) : plan_bits(max_q, max_r, R, band != nullptr);
+  const int end_bit = w.r + w.q + w.b;
+  // The size query covers both bit ranges, so one buffer serves either pass.
   if (tmp == nullptr) {
     rocprim::double_buffer<uint64_t> kb(keys, keys_alt);
     rocprim::double_buffer<int64_t> vb(vals, vals_alt);
@@ -214,7 +239,7 @@ hipError_t plan_sort(int64_t n, const int64_t *n_dev, const int64_t *ids, const 
   }
   if (n == 0) { *sorted_out = vals; return hipSuccess; }
   hipLaunchKernelGGL(k_plan_keys, dim3(nb(n, 256)), dim3(256), 0, st, n, n_dev, ids, qlen, rlen,
-                     band, R, keys, vals);
+                     band, R, w, keys, vals);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   rocprim::double_buffer<uint64_t> kb(keys, keys_alt);

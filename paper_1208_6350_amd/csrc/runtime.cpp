@@ -152,6 +152,7 @@ struct swx_ctx {
   double stage_ms[8] = {};
   int nstages = 0;
   int64_t fill_cells = 0;   // cells of the last forward fill launch
+  int64_t max_q = 0, max_r = 0;   // longest query and reference of the running batch
   // routing of long pairs to the intra-sequence path and its launch shape
   int64_t long_cells = -1;                 // qlen * rlen above this (-1: from the batch) ...
   int64_t long_rlen = int64_t(1) << 16;    // ... or a reference longer than this
@@ -349,10 +350,10 @@ static int plan_pass(swx_ctx *ctx, const Scoring &sc, const int64_t *ids, int64_
   if (!k0 || !k1 || !v0 || !v1 || !pl.d_tasks || !bsz || !qsz || !boff || !qoff)
     return fail(SWX_ENOMEM, "device pool exhausted (plan)");
   size_t tmp_bytes = 0;
-  HIP_TRY(plan_sort(n, nullptr, ids, qlen, rlen, band, R, k0, k1, v0, v1, nullptr, &tmp_bytes, nullptr, st));
+  HIP_TRY(plan_sort(n, nullptr, ids, qlen, rlen, band, R, ctx->max_q, ctx->max_r, k0, k1, v0, v1, nullptr, &tmp_bytes, nullptr, st));
   void *tmp = A.alloc(tmp_bytes);
   if (!tmp) return fail(SWX_ENOMEM, "device pool exhausted (sort)");
-  HIP_TRY(plan_sort(n, nullptr, ids, qlen, rlen, band, R, k0, k1, v0, v1, tmp, &tmp_bytes, &pl.d_sorted, st));
+  HIP_TRY(plan_sort(n, nullptr, ids, qlen, rlen, band, R, ctx->max_q, ctx->max_r, k0, k1, v0, v1, tmp, &tmp_bytes, &pl.d_sorted, st));
   // profile bytes per padded row and task; -1: a profile shared by every task
   const int64_t per_row = sc.qsel ? 0 : (sp ? -1 : (int64_t)(sc.n + 1) * halves * 64);
   HIP_TRY(plan_tasks_dev(   // also clears bsz[ntasks], qsz[ntasks]
@@ -1874,6 +1875,8 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
   if (bad & 1u) return fail(SWX_EINVAL, "offsets must be non-decreasing and within the code arrays");
   if (bad & 2u) return fail(SWX_EINVAL, "pair index out of range");
   if (bad & 12u) return fail(SWX_EINVAL, "symbol code outside [0, n)");
+  ctx->max_q = hstats[2];
+  ctx->max_r = hstats[3];
   lp.nlong = hstats[5];
   lp.nshort = np - lp.nlong;
   // a score can reach smax * min(qlen, rlen); the 32-bit lanes hold < 2^26
@@ -2359,7 +2362,7 @@ static int fixed_plan_alloc(GraphState &g, FixedPlan &pl, int lane_bits, int R) 
   pl.rsym = A.get<uint2>(rsym_offset(bnd_words) + 16);
   if (!g.sc.qsel) pl.prof = A.get<uint8_t>(pl.ntasks * qp_cap * (g.sc.n + 1) * halves * 64 + 16);
   size_t sb = 0;
-  HIP_TRY(plan_sort(g.B, nullptr, nullptr, nullptr, nullptr, nullptr, R, pl.k0, pl.k1, pl.v0, pl.v1,
+  HIP_TRY(plan_sort(g.B, nullptr, nullptr, nullptr, nullptr, nullptr, R, 0, 0, pl.k0, pl.k1, pl.v0, pl.v1,
                     nullptr, &sb, nullptr, nullptr, true));
   pl.sort_bytes = sb;
   pl.sort_tmp = A.alloc(sb);
@@ -2375,7 +2378,7 @@ static int fixed_fill(GraphState &g, FixedPlan &pl, const int64_t *ids, const in
                       const int32_t *band_q, const PairView &view, bool rev,
                       const int32_t *target, FillOut out, hipStream_t st) {
   size_t sb = pl.sort_bytes;
-  HIP_TRY(plan_sort(pl.cap_n, n_dev, ids, qlen, rlen, band, pl.R, pl.k0, pl.k1, pl.v0, pl.v1,
+  HIP_TRY(plan_sort(pl.cap_n, n_dev, ids, qlen, rlen, band, pl.R, 0, 0, pl.k0, pl.k1, pl.v0, pl.v1,
                     pl.sort_tmp, &sb, &pl.sorted, st, true));
   const int halves = pl.lane_bits == 16 ? 2 : 1;
   const int64_t per_row = g.sc.qsel ? 0 : (int64_t)(g.sc.n + 1) * halves * 64;

@@ -535,8 +535,9 @@ hipError_t launch_begins(int64_t npairs, const int32_t *score1, const int32_t *q
                          const int64_t *rend, const int32_t *rscore, const int32_t *rqend,
                          const int64_t *rrend, int32_t *qbeg, int64_t *rbeg, uint8_t *err,
                          hipStream_t st);
+// max_q, max_r: no pair is longer (0: not known; not used with n_dev)
 hipError_t plan_sort(int64_t n, const int64_t *n_dev, const int64_t *ids, const int32_t *qlen, const int64_t *rlen,
-                     const int32_t *band, int32_t R, uint64_t *keys, uint64_t *keys_alt,
+                     const int32_t *band, int32_t R, int64_t max_q, int64_t max_r, uint64_t *keys, uint64_t *keys_alt,
                      int64_t *vals, int64_t *vals_alt, void *tmp, size_t *tmp_bytes,
                      int64_t **sorted_out, hipStream_t st, bool graph = false);
 hipError_t plan_tasks_dev(int64_t n, const int64_t *n_dev, int64_t ntasks, int32_t slots, int32_t R,
