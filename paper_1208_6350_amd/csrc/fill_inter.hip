@@ -84,16 +84,16 @@ __device__ __forceinline__ uint32_t word_of(const uint4 &v, int k) {
 // 168 (three waves) for shorter strips.
 template <int R> constexpr int fill_waves() { return R >= 32 ? 2 : 3; }
 
-// Shared state of a cooperative task: the four waves of a workgroup take the
+// Shared state of a cooperative task: the waves of a workgroup take the
 // strips of one task round robin, strip s starting on a column group once
 // strip s - 1 has stored that group of the boundary planes (in place: every
 // strip reads a group before it writes it, in strip order).
 struct CoopShared {
   int32_t prog[kCoopMaxStrips];            // strip s stored groups [0, prog & ~bit31); bit 31: done
   int64_t reach[kSlots16];                 // reversed pass: earliest column reaching the target
-  int32_t mval[kCoopWaves][kSlots16];      // per-wave partial results, merged at the end
-  int32_t mrow[kCoopWaves][kSlots16];
-  int64_t mcol[kCoopWaves][kSlots16];
+  int32_t mval[kCoopMaxWaves][kSlots16];      // per-wave partial results, merged at the end
+  int32_t mrow[kCoopMaxWaves][kSlots16];
+  int64_t mcol[kCoopMaxWaves][kSlots16];
   int64_t task;                            // queued scheduling: the workgroup's task
 };
 constexpr int32_t kStripDone = (int32_t)0x80000000u;
@@ -130,7 +130,7 @@ __device__ __forceinline__ void inter_task(const InterArgs &a, const int64_t tid
   int s_first = 0, s_step = 1, s_end = nstrips;
   if (sync) {
     s_first = wave;
-    s_step = kCoopWaves;
+    s_step = a.coop;
   } else if (coop && wave != 0) {
     s_end = 0;   // too many strips to pipeline: wave 0 takes the whole task
   }
@@ -572,7 +572,7 @@ __device__ __forceinline__ void inter_task(const InterArgs &a, const int64_t tid
     if (wave == 0) {
 #pragma unroll
       for (int h = 0; h < NH; ++h) {
-        for (int w = 1; w < kCoopWaves; ++w) {
+        for (int w = 1; w < a.coop; ++w) {
           const int32_t v = cs->mval[w][lane + 64 * h];
           const int32_t r = cs->mrow[w][lane + 64 * h];
           const int64_t c = cs->mcol[w][lane + 64 * h];
@@ -608,7 +608,8 @@ __device__ __forceinline__ void inter_task(const InterArgs &a, const int64_t tid
 // take tasks largest first from a device counter (a work queue: one 64-bit
 // atomic per task) until it runs past the last task.
 template <class V, int R, uint32_t MODE, int FORM, bool REV, bool COOP>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(fill_waves<R>()))) void k_inter_fill(
+__global__ __launch_bounds__(COOP ? 64 * kCoopMaxWaves : 256)
+__attribute__((amdgpu_waves_per_eu(fill_waves<R>()))) void k_inter_fill(
     InterArgs a) {
   struct NoShared {};
   __shared__ uint32_t s_lut[8];
@@ -789,14 +790,14 @@ static hipError_t launch_fill(const InterArgs &a, hipStream_t st) {
   // wait for its longest task: measured 11.35 -> 10.95 ms on the benchmark
   // workload); reversed passes (short tasks, early exits) measured faster in
   // workgroups of four
-  const int waves_per_block = (a.coop > 1 || a.rev) ? 4 : 1;
-  if (a.coop != 1 && a.coop != kCoopWaves) return hipErrorInvalidValue;
+  const int waves_per_block = a.coop > 1 ? a.coop : a.rev ? 4 : 1;
+  if (a.coop < 1 || a.coop > kCoopMaxWaves) return hipErrorInvalidValue;
   int64_t blocks = a.coop > 1 ? a.ntasks : (a.ntasks + waves_per_block - 1) / waves_per_block;
   if (blocks == 0) return hipSuccess;
   if (a.sched == 2) {
     if (!a.queue || a.cus < 1) return hipErrorInvalidValue;
     // resident blocks: waves per SIMD x 4 SIMDs per CU / waves per block
-    const int64_t resident = (int64_t)a.cus * fill_waves<R>() * (4 / waves_per_block);
+    const int64_t resident = (int64_t)a.cus * fill_waves<R>() * 4 / waves_per_block;
     if (blocks > resident) blocks = resident;
     hipLaunchKernelGGL(k_zero_queue, dim3(1), dim3(64), 0, st, a.queue);
   }

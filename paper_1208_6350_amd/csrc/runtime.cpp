@@ -152,7 +152,9 @@ struct swx_ctx {
   double stage_ms[8] = {};
   int nstages = 0;
   int64_t fill_cells = 0;   // cells of the last forward fill launch
-  int64_t max_q = 0, max_r = 0;   // longest query and reference of the running batch
+  // of the running batch: longest query and reference, and the mean query
+  // weighted by reference length
+  int64_t max_q = 0, max_r = 0, mean_q = 0;
   // routing of long pairs to the intra-sequence path and its launch shape
   int64_t long_cells = -1;                 // qlen * rlen above this (-1: from the batch) ...
   int64_t long_rlen = int64_t(1) << 16;    // ... or a reference longer than this
@@ -514,6 +516,14 @@ static int run_fill(swx_ctx *ctx, Plan &pl, const Scoring &sc, const PairView &v
   a.anchor = anchor;
   a.lastcol = lastcol;
   a.coop = coop_waves(ctx->fill_coop, pl.ntasks, ctx->cus);
+  // Cooperative tasks of a reversed pass whose queries fill eight strips run on
+  // eight waves: tasks end early or late with their pairs' begins, and the late
+  // ones are the end of the launch.  (A forward pass keeps its compute units
+  // busy with four.)  A protein of 300 against 50,000 / 100,000 / 200,000
+  // targets, reversed stage on 4 / 8 waves: 2.21 / 1.81, 3.56 / 2.91, 6.72 /
+  // 5.33 ms; reads of 150 (five strips) 1.09 / 1.03 for 70,000 but 1.28 / 1.87
+  // for 200,000; forward 3.36 / 3.52 for 100,000 targets.
+  if (a.coop > 1 && rev && ctx->mean_q >= kCoopMaxWaves * pl.R) a.coop = kCoopMaxWaves;
   // A pass runs its tasks by area (padded rows x swept columns, its cost),
   // largest first: the plan's order (by band, height, then width) leaves
   // mid-sized tasks of short, wide pairs for the end of the launch.  Passes
@@ -1877,6 +1887,7 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
   if (bad & 12u) return fail(SWX_EINVAL, "symbol code outside [0, n)");
   ctx->max_q = hstats[2];
   ctx->max_r = hstats[3];
+  ctx->mean_q = hstats[1] / std::max<int64_t>(hstats[4], 1);
   lp.nlong = hstats[5];
   lp.nshort = np - lp.nlong;
   // a score can reach smax * min(qlen, rlen); the 32-bit lanes hold < 2^26

@@ -111,15 +111,16 @@ struct InterArgs {
   const int64_t *order;       // the tasks by ascending area (padded rows x columns), run from
                               // the end (largest first); null: the plan's order (by height,
                               // then width)
-  int32_t coop;               // 1: one wave per task; 4: the four waves of a workgroup share
-                              // a task, wave w taking strips w, w + 4, ... (a strip starts on
-                              // a column group once the strip above has stored it)
+  int32_t coop;               // 1: one wave per task; C > 1 (up to kCoopMaxWaves): the C waves
+                              // of a workgroup share a task, wave w taking strips w, w + C, ...
+                              // (a strip starts on a column group once the strip above has
+                              // stored it)
 };
 
 // Strips per task that the cooperative mode pipelines (a task with more runs
 // on one wave of its workgroup).
 constexpr int kCoopMaxStrips = 512;
-constexpr int kCoopWaves = 4;
+constexpr int kCoopWaves = 4, kCoopMaxWaves = 8;
 
 // Largest score the 16-bit inter path represents exactly together with its
 // 5-bit row code (value * 32 + code <= 65535).

@@ -1,0 +1,34 @@
+"""GPU: batched tasks shared by the waves of a workgroup, four or (reversed
+passes of tall queries) eight, with fewer and more strips than waves."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import paper_1208_6350_amd as swx
+import workloads as W
+from tests.test_gpu_parity import assert_parity
+
+pytestmark = pytest.mark.gpu
+
+
+# mean query below, at and above eight strips of 32 rows; 130 pairs: two tasks
+@pytest.mark.parametrize("qlens", [(200, 255), (256, 257), (250, 520), (600, 700)])
+@pytest.mark.parametrize("alphabet", [4, 20])
+def test_tall_queries(qlens, alphabet):
+    g = np.random.Generator(np.random.PCG64(9000 + qlens[0]))
+    qs, rs = [], []
+    for k in range(130):
+        q = g.integers(0, alphabet, size=int(g.integers(qlens[0], qlens[1] + 1))).astype(np.int8)
+        r = g.integers(0, alphabet, size=int(g.integers(100, 500))).astype(np.int8)
+        if k % 3:   # a part of the query in the reference, early or late
+            n = min(len(q), len(r)) // 2
+            at, src = int(g.integers(0, len(r) - n + 1)), int(g.integers(0, len(q) - n + 1))
+            r[at:at + n] = q[src:src + n]
+        qs.append(q)
+        rs.append(r)
+    m, gaps = (W.dna_matrix(), (3, 1)) if alphabet == 4 else (W.protein_matrix_standin(), (11, 1))
+    c = swx.Context(0)
+    c.set_tuning(long_cells=1 << 62, long_rlen=1 << 62, fill_coop=2)
+    assert_parity(c, W.from_lists(f"coop-{qlens}-{alphabet}", m, *gaps, qs, rs))
+    c.close()
