@@ -516,6 +516,19 @@ static int run_fill(swx_ctx *ctx, Plan &pl, const Scoring &sc, const PairView &v
   a.anchor = anchor;
   a.lastcol = lastcol;
   a.coop = coop_waves(ctx->fill_coop, pl.ntasks, ctx->cus);
+  // A forward pass with somewhat more tasks than the device holds waves runs a
+  // second round of them, nearly empty at first: cooperative tasks still end
+  // sooner, up to a number that depends on how well the strips fill four waves
+  // (fill on one wave / four waves per task; eight tasks per compute unit: 2048).
+  // 150-nt reads (five strips): 2344 tasks 5.04 / 3.69 ms, 3125 5.18 / 4.86,
+  // 3438 5.15 / 5.33; a protein of 100 (four): 2734 4.25 / 3.44, 3281 4.59 /
+  // 4.12; of 300 (ten): 2188 9.84 / 9.18, 2734 9.99 / 11.2; 70-nt reads
+  // (three): 2254 0.37 / 0.50.
+  if (!rev && a.coop == 1 && ctx->fill_coop == 0 && pl.lane_bits == 16 && ctx->mean_q > 0) {
+    const int64_t strips = (ctx->mean_q + pl.R - 1) / pl.R;
+    const int64_t per_cu = strips < 4 ? 8 : strips <= 5 ? 13 : 10;
+    if (pl.ntasks < per_cu * ctx->cus) a.coop = kCoopWaves;
+  }
   // Cooperative tasks of a reversed pass whose queries fill eight strips run on
   // eight waves: tasks end early or late with their pairs' begins, and the late
   // ones are the end of the launch.  (A forward pass keeps its compute units
