@@ -81,6 +81,7 @@ class DevArena {
       fixed_off_ += bytes;
       return p;
     }
+    const size_t cur0 = cur_, off0 = off_;
     while (cur_ < blocks_.size()) {
       Block &b = blocks_[cur_];
       if (off_ + bytes <= b.size) {
@@ -93,7 +94,12 @@ class DevArena {
     }
     size_t sz = std::max(bytes, size_t(64) << 20);
     void *p = nullptr;
-    if (hipMalloc(&p, sz) != hipSuccess) return nullptr;
+    if (hipMalloc(&p, sz) != hipSuccess) {
+      (void)hipGetLastError();   // (a caller with a smaller way to go on launches kernels next)
+      cur_ = cur0;
+      off_ = off0;
+      return nullptr;
+    }
     blocks_.push_back({p, sz});
     cur_ = blocks_.size() - 1;
     off_ = bytes;
@@ -814,10 +820,12 @@ static int run_traceback(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, 
     TbPairs tp{};
     tp.stride = by_stride->stride;
     tp.scratch = A.get<uint8_t>(np * tp.stride);
-    if (!ta.cig || !tp.scratch) return fail(SWX_ENOMEM, "device pool exhausted (pair traceback)");
-    HIP_TRY(tb_pairs(ta, tp, np, max_rows, st));
-    HIP_TRY(scan_lens(np, cig_len, cig_off_final, st));
-    return place_cigars(ctx, np, ta, nullptr, nullptr, cig_off_final, by_stride, out, flags, rc_range);
+    if (ta.cig && tp.scratch) {
+      HIP_TRY(tb_pairs(ta, tp, np, max_rows, st));
+      HIP_TRY(scan_lens(np, cig_len, cig_off_final, st));
+      return place_cigars(ctx, np, ta, nullptr, nullptr, cig_off_final, by_stride, out, flags, rc_range);
+    }
+    // (device memory is short: the classes below take what the pairs need)
   }
   uint8_t *cls = A.get<uint8_t>(np);
   uint64_t *k0 = A.get<uint64_t>(np), *k1 = A.get<uint64_t>(np);
@@ -867,9 +875,13 @@ static int run_traceback(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, 
   TbPairs tp{};
   int64_t pblocks = 0;
   std::vector<SideLaunch> launches;
-  const bool all = pairs_ok && hc[10] + hc[11] + hc[12] + hc[14] <= kTbPairsBytes;
+  const int64_t pair_bytes = hc[10] + hc[11] + hc[12] + hc[14];
+  bool all = pairs_ok && pair_bytes <= kTbPairsBytes;
+  bool wide = !all && pairs_ok && hc[5] > 0 && hc[14] <= kTbWideBytes;
+  uint8_t *pscratch = all || wide ? A.get<uint8_t>(all ? pair_bytes : hc[14]) : nullptr;
+  if (!pscratch) all = wide = false;   // (the per-lane kernels' scratch is a few times smaller)
   const bool direct = few && all;
-  auto by_pairs = [&](int c) { return all || (pairs_ok && c == 5 && hc[9 + c] <= kTbWideBytes); };
+  auto by_pairs = [&](int c) { return all || (wide && c == 5); };
   if (few && (!direct || hc[6] > 0) && (rc = sort())) return rc;
   int64_t pos = hc[0];
   for (int c : {1, 2, 3, 5}) {
@@ -886,8 +898,7 @@ static int run_traceback(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, 
     tp.sorted = direct ? nullptr : sorted;
     tp.cls = cls;
     tp.used = (unsigned long long *)(counts + 17);
-    tp.scratch = A.get<uint8_t>(tp.cap);
-    if (!tp.scratch) return fail(SWX_ENOMEM, "device pool exhausted (pair traceback)");
+    tp.scratch = pscratch;
     const int64_t blocks = direct ? np : pblocks;
     launches.push_back({(double)tp.cap * 2, [=](hipStream_t s_) { return tb_pairs(ta, tp, blocks, max_rows, s_); }});
   }
@@ -1534,7 +1545,10 @@ static int plan_alone(swx_ctx *ctx, const Scoring &sc, int64_t np, uint32_t flag
   al.stride = max_r;
   al.max_q = (int32_t)max_q;
   al.maxcol = A.get<uint32_t>(al.count * max_r);
-  if (!al.maxcol) return fail(SWX_ENOMEM, "device pool exhausted (max array)");
+  if (!al.maxcol) {   // device memory is short: the general path takes less
+    al = AlonePath{};
+    return SWX_OK;
+  }
   if ((!al.all || (lp.nlong > 0 && lp.nshort > 0 && !w16)) && (rc = list_pairs(ctx, np, lp))) return rc;
   if (!al.all) {
     al.ids = lp.d_long;
@@ -3561,6 +3575,7 @@ int swx_graph_load(swx_graph *gr, const swx_batch *b) {
                         {g.pair_q, pq.data(), 8 * (int64_t)pq.size()},
                         {g.pair_r, pr.data(), 8 * (int64_t)pr.size()}};
   int rc;
+  if (hipSetDevice(gr->ctx->device) != hipSuccess) return fail(SWX_EDEVICE, "hipSetDevice failed");
   if ((rc = upload(gr->ctx, in, 6))) return rc;
   // the host vectors must outlive the copies, and a run may be on another stream
   HIP_TRY(wait_stream(gr->ctx->stream));
