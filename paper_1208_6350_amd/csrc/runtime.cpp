@@ -772,6 +772,12 @@ static TbShape tb_wave_shape(int64_t m, int64_t w, int64_t bw, int n, int64_t jo
 // the per-lane kernels, whose scratch is a few times smaller.
 static constexpr int64_t kTbPairsAll = 32768, kTbPairsMax = int64_t(1) << 18;
 static constexpr int64_t kTbPairsBytes = int64_t(600) << 20, kTbWideBytes = int64_t(384) << 20;
+// Queries of more than 256 rows keep a lane busy for longer: batches of them (on
+// average) go by pairs up to twice the size (per-lane kernels / by pairs, a
+// protein of 300 against 20,000 targets, 0.8 GB, 3.21 / 1.65 ms, 30,000, 1.2 GB,
+// 3.28 / 2.35; of 550 against 20,000, 0.9 GB, 5.00 / 3.57; of 100 against
+// 50,000, 0.8 GB, 0.84 / 1.18; 45,000 reads of 100 to 250, 0.9 GB, 1.27 / 1.41).
+static constexpr int64_t kTbTallRows = 256, kTbTallBytes = int64_t(1300) << 20;
 static constexpr int64_t kTbGraphPairs = 4096, kTbGraphBytes = int64_t(1) << 30;   // of a graph (fixed, worst case)
 
 // A batch traced a workgroup per pair without a class pass: scratch and CIGAR
@@ -876,7 +882,7 @@ static int run_traceback(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, 
   int64_t pblocks = 0;
   std::vector<SideLaunch> launches;
   const int64_t pair_bytes = hc[10] + hc[11] + hc[12] + hc[14];
-  bool all = pairs_ok && pair_bytes <= kTbPairsBytes;
+  bool all = pairs_ok && pair_bytes <= (ctx->mean_q > kTbTallRows ? kTbTallBytes : kTbPairsBytes);
   bool wide = !all && pairs_ok && hc[5] > 0 && hc[14] <= kTbWideBytes;
   uint8_t *pscratch = all || wide ? A.get<uint8_t>(all ? pair_bytes : hc[14]) : nullptr;
   if (!pscratch) all = wide = false;   // (the per-lane kernels' scratch is a few times smaller)
