@@ -1498,6 +1498,7 @@ static bool choose16(const swx_ctx *ctx, const Scoring &sc, const LongPath &lp) 
 // wave's 16-bit lanes) over its whole reference.
 struct AlonePath {
   bool on = false, all = false;   // all: the batched passes are empty
+  bool flag = false;              // ... and short pairs may pass their limit: flagged, run again
   int64_t *ids = nullptr;         // (null: every pair in turn)
   int64_t count = 0, n32 = 0;     // the first n32 on 32-bit lanes
   uint32_t *maxcol = nullptr;
@@ -1507,15 +1508,19 @@ struct AlonePath {
 // References above kAloneSweep columns keep the chunks of the general path
 // until there is a job per pair anyway.
 static constexpr int64_t kAloneMaxR = 8192, kAloneSweep = 1024;
-// Where no score of a batch can saturate the batched pass's 16-bit lanes, its
-// short pairs go the same way, on 16-bit lanes too, up to this many pairs in
-// all (score only, with the reversed pass): nothing is batched then, so there
-// is no plan to build and read back, no pack, and no fill with a few tasks.
+// The short pairs of a batch go the same way, on 16-bit lanes too (those that
+// reach the batched pass's limit of them run again on 32-bit lanes, as there),
+// up to this many pairs in all (score only or queries above 256 rows on
+// average; others with the reversed pass): nothing is batched then, so there is
+// no plan to build and read back, no pack, and no fill with a few tasks.
 // Measured, whole call, long ones alone / all alone / all batched: 20,000
 // reads 3.04 / 2.06 / 3.57 ms, 30,000 3.74 / 2.79 / 3.87, 50,000 4.31 / 4.07 /
 // 4.29, 60,000 4.52 / 4.54 / 4.53 (forward pass alone 1.41 / 1.81 / 1.42,
 // even at 33,000; reversed 1.15 / 1.07 / 1.16); the 4,950 overlaps of 100
 // reads of 70 (none long) 0.98 / 0.50 / 0.98, 19,900 of 200 1.17 / 0.81 / 1.17.
+// A protein of 300, forward and reversed stage, long ones alone or none / all
+// alone: 5,000 targets 1.98 / 1.08 ms, 12,000 3.20 / 1.68, 25,000 4.56 / 3.19,
+// 32,000 4.47 / 3.88, 48,000 4.41 / 5.45; of 80, 40,000 2.35 / 1.84.
 static constexpr int64_t kAlonePairs = 32768, kAlonePairsRev = 49152;
 
 static int plan_alone(swx_ctx *ctx, const Scoring &sc, int64_t np, uint32_t flags, const int64_t *stats,
@@ -1524,13 +1529,16 @@ static int plan_alone(swx_ctx *ctx, const Scoring &sc, int64_t np, uint32_t flag
   const int64_t max_q = stats[2], max_r = stats[3], sum_r = stats[4];
   const int64_t bound = (int64_t)std::max(sc.smax, 0) * stats[0];
   if (A.fixed() || max_q > kAloneMaxQ || max_r > kAloneMaxR) return SWX_OK;
-  if (max_r > kAloneSweep && lp.nlong < 2 * ctx->intra_jobs) return SWX_OK;
   // (a threshold set by the caller says itself which pairs are batched)
-  const bool all = lp.nshort == 0 || (ctx->long_cells < 0 && bound < kInter16Limit &&
-                                      np <= ((flags & SWX_BEGIN) ? kAlonePairsRev : kAlonePairs));
+  const bool all = lp.nshort == 0 ||
+                   (ctx->long_cells < 0 &&
+                    np <= ((flags & SWX_BEGIN) && ctx->mean_q <= kTbTallRows ? kAlonePairsRev : kAlonePairs));
   if (lp.nlong == 0 && !all) return SWX_OK;
+  const int64_t count = all ? np : lp.nlong;
+  if (max_r > kAloneSweep && count < 2 * ctx->intra_jobs) return SWX_OK;
   if (bound + sc.bias > 32766) return SWX_OK;          // (16-bit lanes, 16 code bits)
-  if (np * max_r > 4 * sum_r + (int64_t(1) << 20)) return SWX_OK;   // fixed strides: few skewed pairs
+  // max array words at a fixed stride: within 1 GiB, or few skewed pairs
+  if (count * max_r > std::max(int64_t(1) << 28, 4 * sum_r + (int64_t(1) << 20))) return SWX_OK;
   // the lanes that the general path takes: by the number of its chunks, of
   // which a pair has at least one and at most one per 256 columns
   int rc;
@@ -1546,7 +1554,8 @@ static int plan_alone(swx_ctx *ctx, const Scoring &sc, int64_t np, uint32_t flag
   }
   al.on = true;
   al.all = all;
-  al.count = al.all ? np : lp.nlong;
+  al.count = count;
+  al.flag = all && lp.nshort > 0 && bound >= kInter16Limit;
   al.n32 = w16 ? 0 : lp.nlong;
   al.stride = max_r;
   al.max_q = (int32_t)max_q;
@@ -1616,7 +1625,7 @@ static void add_rest(AloneArgs &a, const Scoring &sc, const AloneRest &r) {
 
 static int run_alone_forward(swx_ctx *ctx, const Scoring &sc, const AlonePath &al, int64_t bound,
                              const PairView &view, const FillOut &out, uint8_t *lanebits,
-                             const AloneRest &rest) {
+                             const uint8_t *is_long, const AloneRest &rest) {
   AloneArgs a = alone_args(sc, al, view, out);
   add_rest(a, sc, rest);
   if (al.n32 > 0) {
@@ -1627,6 +1636,7 @@ static int run_alone_forward(swx_ctx *ctx, const Scoring &sc, const AlonePath &a
     else HIP_TRY(alone_forward(w, ctx->stream));
   }
   if (al.count > al.n32) {
+    a.is_long = is_long;
     if (al.n32 > 0) a.ids += al.n32;   // (a list, then)
     a.maxcol += al.n32 * al.stride;
     a.count -= al.n32;
@@ -1980,7 +1990,8 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
     }
   }
   auto long_forward = [&]() -> int {
-    return al.on ? run_alone_forward(ctx, sc, al, score_bound, fview, fout, lanebits, rest)
+    return al.on ? run_alone_forward(ctx, sc, al, score_bound, fview, fout, lanebits,
+                                     al.flag ? lp.is_long : nullptr, rest)
                  : run_intra_forward(ctx, sc, lp, fview, fout, err, lanebits);
   };
 
@@ -2018,10 +2029,18 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
   // saturated pairs: exact re-run on 32-bit lanes (none where no score of the
   // batch can reach the 16-bit limit, and none of the long pairs)
   int64_t *wide = nullptr, nwide = 0;
-  if (lp.nshort > 0 && score_bound >= kInter16Limit &&
+  if ((lp.nshort > 0 || al.flag) && score_bound >= kInter16Limit &&
       (rc = select_flagged(ctx, ovf, np, &wide, &nwide)))
     return rc;
-  if (nwide > 0) {
+  if (nwide > 0 && al.all) {
+    AloneArgs w = alone_args(sc, al, fview, fout);
+    w.ids = wide;
+    w.count = nwide;
+    w.lanebits = lanebits;
+    w.maxcol = A.get<uint32_t>(nwide * al.stride);
+    if (!w.maxcol) return fail(SWX_ENOMEM, "device pool exhausted (max array)");
+    HIP_TRY(alone_forward(w, st));
+  } else if (nwide > 0) {
     if ((rc = plan_pass(ctx, sc, wide, nwide, qlen, rlen, nullptr, nullptr, 32, R, p32, sp))) return rc;
     if ((rc = run_fill(ctx, p32, sc, fview, false, nullptr, fout, score_bound, -1, 0, 0, sp))) return rc;
     HIP_TRY(mark_lanes(nwide, wide, lanebits, 32, st));

@@ -141,3 +141,26 @@ def test_many_cigar_words():
     recs = assert_parity(c, b)
     c.close()
     assert recs["cigar_len"].sum() > (4 << 18) - 12 * n
+
+
+# short pairs whose scores pass the batched 16-bit limit run again on 32-bit
+# lanes; long ones of the same batch keep their width
+@pytest.mark.parametrize("nlong", [0, 40, 2300])
+def test_short_pairs_past_the_limit(nlong):
+    g = np.random.Generator(np.random.PCG64(9100 + nlong))
+    n = nlong + 60
+    ql, rl = g.integers(30, 80, size=n), g.integers(40, 95, size=n)
+    ql[:nlong], rl[:nlong] = g.integers(150, 200, size=nlong), g.integers(200, 300, size=nlong)
+    qs, rs = pairs(ql, rl, 9200)
+    for k in range(nlong, n, 2):   # every other short pair: its reference's copy
+        rs[k][:len(qs[k])] = qs[k][:len(rs[k])]
+    m = W.dna_matrix() * 0 - 50
+    np.fill_diagonal(m, 60)
+    b = W.from_lists("alone-limit", m.astype(np.int8), 70, 10, qs, rs)
+    c = swx.Context(0)
+    recs = assert_parity(c, b)
+    c.close()
+    want = np.where(recs["score1"] >= 2047, 32, 16)
+    want[:nlong] = 32 if nlong < 1024 else 16
+    np.testing.assert_array_equal(recs["lane_bits"], want)
+    assert (recs["score1"][nlong:] >= 2047).any() and (recs["score1"][nlong:] < 2047).any()
