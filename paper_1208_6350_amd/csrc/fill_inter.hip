@@ -87,16 +87,23 @@ template <int R> constexpr int fill_waves() { return R >= 32 ? 2 : 3; }
 // Shared state of a cooperative task: the waves of a workgroup take the
 // strips of one task round robin, strip s starting on a column group once
 // strip s - 1 has stored that group of the boundary planes (in place: every
-// strip reads a group before it writes it, in strip order).
+// strip reads a group before it writes it, in strip order).  A reversed strip
+// that ends before its band does, because every pair has reached its target
+// by then, ends all strips below it there too (kStripCut): past its end they
+// would run on without waiting, and so write groups that a strip above it may
+// still be writing.  (They have nothing to find there: a column no earlier, a
+// larger row.)
 struct CoopShared {
-  int32_t prog[kCoopMaxStrips];            // strip s stored groups [0, prog & ~bit31); bit 31: done
+  int32_t prog[kCoopMaxStrips];            // strip s stored groups [0, prog & kStripGroups)
   int64_t reach[kSlots16];                 // reversed pass: earliest column reaching the target
   int32_t mval[kCoopMaxWaves][kSlots16];      // per-wave partial results, merged at the end
   int32_t mrow[kCoopMaxWaves][kSlots16];
   int64_t mcol[kCoopMaxWaves][kSlots16];
   int64_t task;                            // queued scheduling: the workgroup's task
 };
-constexpr int32_t kStripDone = (int32_t)0x80000000u;
+constexpr int32_t kStripDone = (int32_t)0x80000000u;   // strip s has ended ...
+constexpr int32_t kStripCut = 0x40000000;              // ... before its band's end
+constexpr int32_t kStripGroups = kStripCut - 1;
 constexpr int64_t kCoopSpinLimit = int64_t(1) << 26;
 
 // How a 16-bit fill keeps a column's maximum (value * 32 + row code): one
@@ -191,15 +198,17 @@ __device__ __forceinline__ void inter_task(const InterArgs &a, const int64_t tid
     const int sR = s * R;
     // cooperative: progress of strip s - 1 (groups known stored; done)
     int32_t avail = 0;
-    bool pdone = (s == 0);
+    bool pdone = (s == 0), pcut = false;
     auto wait_prev = [&](int64_t g) {
       if (!sync || pdone || g < avail) return;
       int64_t spins = 0;
       for (;;) {
-        const int32_t v = __hip_atomic_load(&cs->prog[s - 1], __ATOMIC_RELAXED,
-                                            __HIP_MEMORY_SCOPE_WORKGROUP);
-        avail = v & ~kStripDone;
+        int32_t v = __hip_atomic_load(&cs->prog[s - 1], __ATOMIC_RELAXED,
+                                      __HIP_MEMORY_SCOPE_WORKGROUP);
+        if constexpr (REV) v = __builtin_amdgcn_readfirstlane(v);   // (bounds the strip's loop)
+        avail = v & kStripGroups;
         pdone = (v & kStripDone) != 0;
+        pcut = REV && (v & kStripCut) != 0;
         if (pdone || g < avail) break;
         if (++spins > kCoopSpinLimit) {   // never expected: fail the task's pairs, go on
           spin_fail = true;
@@ -211,14 +220,15 @@ __device__ __forceinline__ void inter_task(const InterArgs &a, const int64_t tid
       }
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
     };
-    auto publish = [&](int64_t groups, bool fin) {
+    auto publish = [&](int64_t groups, bool fin, bool cut = false) {
       if (!sync) return;
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
       if (lane == 0)
-        __hip_atomic_store(&cs->prog[s], (int32_t)groups | (fin ? kStripDone : 0),
+        __hip_atomic_store(&cs->prog[s], (int32_t)groups | (fin ? kStripDone : 0) | (cut ? kStripCut : 0),
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     };
     int64_t clo = 0, chi = rp;
+    int64_t cband = rp;   // end of the strip's band
     if (rev) {
       if (sync) {   // earliest columns reached by strips above, as far as known now
 #pragma unroll
@@ -239,6 +249,8 @@ __device__ __forceinline__ void inter_task(const InterArgs &a, const int64_t tid
         clo = sR - tk.band_q; if (clo < 0) clo = 0;
         const int64_t c2 = (int64_t)sR + R + tk.band;
         if (c2 < chi) chi = c2;
+        cband = (chi + 3) & ~(int64_t)3;
+        if (cband > rp) cband = rp;
       }
       int64_t bound = -1;
 #pragma unroll
@@ -252,7 +264,7 @@ __device__ __forceinline__ void inter_task(const InterArgs &a, const int64_t tid
       if (chi > rp) chi = rp;
       if (clo >= chi) {   // later strips have even later windows
         if (!sync) break;
-        publish(0, true);   // nothing stored: the strip below reads zeros
+        publish(0, true, true);
         continue;
       }
     }
@@ -302,7 +314,8 @@ __device__ __forceinline__ void inter_task(const InterArgs &a, const int64_t tid
     // g+1 are requested before group g is computed, so the loads overlap four
     // columns of arithmetic.
     int64_t cdone = chi;   // one past the last column this strip computes
-    const int64_t g0 = clo >> 2, g1 = chi >> 2;
+    const int64_t g0 = clo >> 2;
+    int64_t g1 = chi >> 2;
     uint4 nh, nf, nc;
     uint2 nsy;
     auto fetch_group = [&](int64_t g) {
@@ -312,6 +325,10 @@ __device__ __forceinline__ void inter_task(const InterArgs &a, const int64_t tid
       bool inprev;
       if (sync) {
         wait_prev(g);
+        if (REV && pcut && avail < g1) {   // the strip ends with the one above, here at the latest
+          g1 = avail > g ? avail : g;
+          cdone = 4 * g1;
+        }
         inprev = (s > 0) && (!rev || 4 * g >= plo) && (g < avail);
       } else {
         inprev = rev ? ((s > 0) && (4 * g >= plo) && (4 * g < phi)) : (s > 0);
@@ -366,6 +383,10 @@ __device__ __forceinline__ void inter_task(const InterArgs &a, const int64_t tid
       }
     };
     fetch_group(g0);
+    if (REV && sync && g1 <= g0) {
+      publish(0, true, true);
+      continue;
+    }
     if constexpr (MODE == kQGen) fetch_prof(nsy.x & 0xFFu, nsy.y & 0xFFu);
 
     // Forward pass: a group's boundary words are stored one group late,
@@ -531,7 +552,7 @@ __device__ __forceinline__ void inter_task(const InterArgs &a, const int64_t tid
       run_groups(std::integral_constant<int, R>{});
     }
     if constexpr (kDelay) flush();   // the strip's last group, before the next strip reads it
-    publish(cdone >> 2, true);
+    publish(cdone >> 2, true, REV && cdone < cband);
     // merge the strip best into the pair best (earlier strips win ties)
 #pragma unroll
     for (int h = 0; h < NH; ++h) {

@@ -32,3 +32,29 @@ def test_tall_queries(qlens, alphabet):
     c.set_tuning(long_cells=1 << 62, long_rlen=1 << 62, fill_coop=2)
     assert_parity(c, W.from_lists(f"coop-{qlens}-{alphabet}", m, *gaps, qs, rs))
     c.close()
+
+
+# Tasks whose 128 pairs are copies of one weak pair: a reversed strip near the
+# top reaches every target at once and ends, while the strip above it still has
+# most of its window to go and the strips below are to end with it.
+@pytest.mark.parametrize("qlens", [(120, 250), (260, 400)])   # four and eight waves
+@pytest.mark.parametrize("alphabet", [4, 20])
+def test_reversed_strips_end_together(qlens, alphabet):
+    import oracle
+    from tests.fullsize import mismatches
+
+    g = np.random.Generator(np.random.PCG64(9100 + qlens[0] + alphabet))
+    copies, kinds = 128, 40
+    qs = [g.integers(0, alphabet, size=int(g.integers(qlens[0], qlens[1] + 1))).astype(np.int8)
+          for _ in range(kinds)]
+    rs = [g.integers(0, alphabet, size=int(g.integers(250, 400))).astype(np.int8) for _ in range(kinds)]
+    m, gaps = (W.dna_matrix(), (3, 1)) if alphabet == 4 else (W.protein_matrix_standin(), (11, 1))
+    b = W.from_lists("copies", m, *gaps, qs, rs)
+    pair = np.repeat(np.arange(kinds), copies)
+    ref, rcig, rcoff = oracle.align_many(b.qcat, b.qoff, b.rcat, b.roff, pair, pair, m, *gaps)
+    c = swx.Context(0)
+    c.set_tuning(long_cells=1 << 62, long_rlen=1 << 62, fill_coop=2)
+    for _ in range(3):
+        recs, cig = c.align_batch(m, *gaps, b.qcat, b.qoff, b.rcat, b.roff, pair, pair)
+        assert mismatches(recs, cig, ref, rcig, rcoff)["pairs_bad"] == 0
+    c.close()
