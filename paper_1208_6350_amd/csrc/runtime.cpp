@@ -158,9 +158,9 @@ struct swx_ctx {
   double stage_ms[8] = {};
   int nstages = 0;
   int64_t fill_cells = 0;   // cells of the last forward fill launch
-  // of the running batch: longest query and reference, and the mean query
-  // weighted by reference length
-  int64_t max_q = 0, max_r = 0, mean_q = 0;
+  // of the running batch: longest query and reference, the mean query
+  // weighted by reference length, and the mean reference
+  int64_t max_q = 0, max_r = 0, mean_q = 0, mean_r = 0;
   // routing of long pairs to the intra-sequence path and its launch shape
   int64_t long_cells = -1;                 // qlen * rlen above this (-1: from the batch) ...
   int64_t long_rlen = int64_t(1) << 16;    // ... or a reference longer than this
@@ -536,13 +536,18 @@ static int run_fill(swx_ctx *ctx, Plan &pl, const Scoring &sc, const PairView &v
     if (pl.ntasks < per_cu * ctx->cus) a.coop = kCoopWaves;
   }
   // Cooperative tasks of a reversed pass whose queries fill eight strips run on
-  // eight waves: tasks end early or late with their pairs' begins, and the late
-  // ones are the end of the launch.  (A forward pass keeps its compute units
-  // busy with four.)  A protein of 300 against 50,000 / 100,000 / 200,000
-  // targets, reversed stage on 4 / 8 waves: 2.21 / 1.81, 3.56 / 2.91, 6.72 /
-  // 5.33 ms; reads of 150 (five strips) 1.09 / 1.03 for 70,000 but 1.28 / 1.87
-  // for 200,000; forward 3.36 / 3.52 for 100,000 targets.
-  if (a.coop > 1 && rev && ctx->mean_q >= kCoopMaxWaves * pl.R) a.coop = kCoopMaxWaves;
+  // eight waves in a search of one query among references of very unequal
+  // length: its launch ends on a few large tasks.  Only while the tasks are few
+  // (3.5 per compute unit): eight waves each, they hold the device with their
+  // strips' waits where four leave room for other tasks.  Reversed stage on
+  // four / eight waves, lengths log-normal around 300 (sigma 0.6): a query of 300
+  // against 60,000 targets 1.87 / 1.72 ms, 100,000 2.49 / 2.21, of 420 1.93 /
+  // 1.82 and 2.46 / 2.57, of 600 2.04 / 2.04 and 2.88 / 2.83; but 200,000 of
+  // 420 3.73 / 3.92 (sigma 0.3: 2.27 / 2.96), 100,000 of equal length 1.45 /
+  // 1.71, and 200,000 reads of 260 against windows of their own 1.86 / 2.65.
+  if (a.coop > 1 && rev && sp && ctx->mean_q >= kCoopMaxWaves * pl.R && ctx->max_r >= 3 * ctx->mean_r &&
+      2 * pl.ntasks <= 7 * (int64_t)ctx->cus)
+    a.coop = kCoopMaxWaves;
   // A pass runs its tasks by area (padded rows x swept columns, its cost),
   // largest first: the plan's order (by band, height, then width) leaves
   // mid-sized tasks of short, wide pairs for the end of the launch.  Passes
@@ -1931,6 +1936,7 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
   ctx->max_q = hstats[2];
   ctx->max_r = hstats[3];
   ctx->mean_q = hstats[1] / std::max<int64_t>(hstats[4], 1);
+  ctx->mean_r = hstats[4] / np;
   lp.nlong = hstats[5];
   lp.nshort = np - lp.nlong;
   // a score can reach smax * min(qlen, rlen); the 32-bit lanes hold < 2^26

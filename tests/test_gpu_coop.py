@@ -58,3 +58,25 @@ def test_reversed_strips_end_together(qlens, alphabet):
         recs, cig = c.align_batch(m, *gaps, b.qcat, b.qoff, b.rcat, b.roff, pair, pair)
         assert mismatches(recs, cig, ref, rcig, rcoff)["pairs_bad"] == 0
     c.close()
+
+
+# One query against references of very unequal length: the reversed pass on
+# eight waves from eight strips of 32 rows on.
+@pytest.mark.parametrize("qlen", [255, 256, 257, 520])
+def test_search_of_unequal_references(qlen):
+    g = np.random.Generator(np.random.PCG64(9200 + qlen))
+    q = g.integers(0, 20, size=qlen).astype(np.int8)
+    rs = []
+    for k in range(130):
+        r = g.integers(0, 20, size=1500 if k % 40 == 0 else int(g.integers(60, 300))).astype(np.int8)
+        if k % 3:
+            n = min(qlen, len(r)) // 2
+            at, src = int(g.integers(0, len(r) - n + 1)), int(g.integers(0, qlen - n + 1))
+            r[at:at + n] = q[src:src + n]
+        rs.append(r)
+    b = W.from_lists(f"search-{qlen}", W.protein_matrix_standin(), 11, 1, [q], rs)
+    b.pair_q, b.pair_r = np.zeros(len(rs), dtype=np.int64), np.arange(len(rs), dtype=np.int64)
+    c = swx.Context(0)
+    c.set_tuning(long_cells=1 << 62, long_rlen=1 << 62)
+    assert_parity(c, b)
+    c.close()
