@@ -522,18 +522,26 @@ static int run_fill(swx_ctx *ctx, Plan &pl, const Scoring &sc, const PairView &v
   a.anchor = anchor;
   a.lastcol = lastcol;
   a.coop = coop_waves(ctx->fill_coop, pl.ntasks, ctx->cus);
-  // A forward pass with somewhat more tasks than the device holds waves runs a
-  // second round of them, nearly empty at first: cooperative tasks still end
-  // sooner, up to a number that depends on how well the strips fill four waves
-  // (fill on one wave / four waves per task; eight tasks per compute unit: 2048).
-  // 150-nt reads (five strips): 2344 tasks 5.04 / 3.69 ms, 3125 5.18 / 4.86,
-  // 3438 5.15 / 5.33; a protein of 100 (four): 2734 4.25 / 3.44, 3281 4.59 /
-  // 4.12; of 300 (ten): 2188 9.84 / 9.18, 2734 9.99 / 11.2; 70-nt reads
-  // (three): 2254 0.37 / 0.50.
+  // A forward pass with somewhat more tasks than the device holds waves (eight
+  // per compute unit: 2048) runs a second round of them, nearly empty at first:
+  // cooperative tasks still end sooner, up to a number of tasks per compute
+  // unit that was measured for each number of strips (how well they fill four
+  // waves is not all of it: five do better than six).  Profiles read per task
+  // keep a lone wave waiting, so that four gain more.  Fill on one wave / four
+  // waves per task, queries of equal height, references of 300 to 500: four
+  // strips 2200 tasks 3.14 / 2.63 ms, 2500 3.22 / 2.92, 2700 3.28 / 3.22; five
+  // 2200 3.89 / 3.41, 2500 4.04 / 3.75, 3000 4.14 / 4.49; six 2200 4.70 / 4.88;
+  // seven 2200 5.45 / 5.00, 2500 (references of 150 to 500) 3.81 / 3.99; eight
+  // 2500 6.39 / 5.58; ten 2200 7.93 / 7.22, 2500 (150 to 500) 5.43 / 5.78; three
+  // 2100 3.16 / 3.31.  Profiles per task: four strips 3300 2.59 / 2.55, six 2500
+  // 3.31 / 2.70, ten 2500 4.69 / 3.82.
   if (!rev && a.coop == 1 && ctx->fill_coop == 0 && pl.lane_bits == 16 && ctx->mean_q > 0) {
     const int64_t strips = (ctx->mean_q + pl.R - 1) / pl.R;
-    const int64_t per_cu = strips < 4 ? 8 : strips <= 5 ? 13 : 10;
-    if (pl.ntasks < per_cu * ctx->cus) a.coop = kCoopWaves;
+    int most = 20;   // tasks per two compute units
+    if (strips < 4 || (strips == 6 && !a.prof)) most = 16;
+    else if (a.prof) most = strips <= 5 ? 26 : 20;
+    else if (strips == 5 || strips == 7 || strips == 10) most = 19;
+    if (2 * pl.ntasks < most * (int64_t)ctx->cus) a.coop = kCoopWaves;
   }
   // Cooperative tasks of a reversed pass whose queries fill eight strips run on
   // eight waves in a search of one query among references of very unequal
