@@ -1523,29 +1523,50 @@ struct AlonePath {
 static constexpr int64_t kAloneMaxR = 8192, kAloneSweep = 1024;
 // The short pairs of a batch go the same way, on 16-bit lanes too (those that
 // reach the batched pass's limit of them run again on 32-bit lanes, as there),
-// up to this many pairs in all (score only or queries above 256 rows on
-// average; others with the reversed pass): nothing is batched then, so there is
-// no plan to build and read back, no pack, and no fill with a few tasks.
+// up to kAlonePairs pairs in all: nothing is batched then, so there is no plan to
+// build and read back, no pack, and no fill with a few tasks.
 // Measured, whole call, long ones alone / all alone / all batched: 20,000
-// reads 3.04 / 2.06 / 3.57 ms, 30,000 3.74 / 2.79 / 3.87, 50,000 4.31 / 4.07 /
-// 4.29, 60,000 4.52 / 4.54 / 4.53 (forward pass alone 1.41 / 1.81 / 1.42,
-// even at 33,000; reversed 1.15 / 1.07 / 1.16); the 4,950 overlaps of 100
+// reads 3.04 / 2.06 / 3.57 ms, 30,000 3.74 / 2.79 / 3.87; the 4,950 overlaps of 100
 // reads of 70 (none long) 0.98 / 0.50 / 0.98, 19,900 of 200 1.17 / 0.81 / 1.17.
 // A protein of 300, forward and reversed stage, long ones alone or none / all
 // alone: 5,000 targets 1.98 / 1.08 ms, 12,000 3.20 / 1.68, 25,000 4.56 / 3.19,
 // 32,000 4.47 / 3.88, 48,000 4.41 / 5.45; of 80, 40,000 2.35 / 1.84.
-static constexpr int64_t kAlonePairs = 32768, kAlonePairsRev = 49152;
+static constexpr int64_t kAlonePairs = 32768;
+// With begins wanted, as the reversed passes gain most, batches of shorter
+// queries go further.  Here every pair costs the forward sweep of 256 rows (64
+// lanes of four), however short its query; batched, the cost does not depend on
+// the number of pairs while their tasks all start at once, but on the strips of
+// the query (beyond four, the four waves of a task take a second turn), on the
+// profile, and on how many pairs are left once the long ones are taken out.
+// Batched / all alone, references of 500, 1,000 and 5,000, 36,000 and 42,000
+// pairs.  Scores from the selector table: queries of 40 0.84 0.72 0.59 and 0.69
+// 0.61 0.52, of 150 1.05 1.02 0.90 and 0.96 0.92 0.87, of 250 1.01 1.09 0.96 and
+// 1.04 1.13 1.15 (49,000: 0.90 0.97); 33,000, of which 0.45 are long, 40 1.11 1.01
+// 0.91, 150 1.41 1.30 1.19.  One query's profile for all (300, 1,000, 3,000): of 60
+// 0.98 1.02 0.62 (49,000 0.87 0.76 0.65), of 150 1.33 1.69 1.36 (49,000 1.18 1.42
+// 1.18).  Profiles read per task (500, 1,000, 5,000): of 100 1.59 1.36 0.81 (49,000
+// 1.43 1.27 0.72), of 250 2.21 2.12 1.67 (49,000 2.23 2.32).
+static int64_t alone_limit(const swx_ctx *ctx, const Scoring &sc, int64_t np, uint32_t flags,
+                           int64_t nlong, bool one_query) {
+  constexpr int64_t kMost = 49152;
+  if (!(flags & SWX_BEGIN) || ctx->mean_q > kTbTallRows) return kAlonePairs;
+  const int64_t strips = (ctx->mean_q + 31) / 32;
+  const bool brief = ctx->mean_r <= 1024;
+  if (!sc.qsel) return strips >= 5 || (brief && !one_query) ? kMost : brief ? 36864 : kAlonePairs;
+  if ((strips >= 5 || brief) && 5 * nlong >= 2 * np) return kMost;
+  return strips >= 6 ? 43008 : strips == 5 && brief ? 36864 : kAlonePairs;
+}
 
-static int plan_alone(swx_ctx *ctx, const Scoring &sc, int64_t np, uint32_t flags, const int64_t *stats,
-                      const int32_t *qlen, const int64_t *rlen, LongPath &lp, AlonePath &al) {
+static int plan_alone(swx_ctx *ctx, const Scoring &sc, int64_t np, uint32_t flags, bool one_query,
+                      const int64_t *stats, const int32_t *qlen, const int64_t *rlen, LongPath &lp,
+                      AlonePath &al) {
   DevArena &A = ctx->arena;
   const int64_t max_q = stats[2], max_r = stats[3], sum_r = stats[4];
   const int64_t bound = (int64_t)std::max(sc.smax, 0) * stats[0];
   if (A.fixed() || max_q > kAloneMaxQ || max_r > kAloneMaxR) return SWX_OK;
   // (a threshold set by the caller says itself which pairs are batched)
-  const bool all = lp.nshort == 0 ||
-                   (ctx->long_cells < 0 &&
-                    np <= ((flags & SWX_BEGIN) && ctx->mean_q <= kTbTallRows ? kAlonePairsRev : kAlonePairs));
+  const bool all = lp.nshort == 0 || (ctx->long_cells < 0 &&
+                                      np <= alone_limit(ctx, sc, np, flags, lp.nlong, one_query));
   if (lp.nlong == 0 && !all) return SWX_OK;
   const int64_t count = all ? np : lp.nlong;
   if (max_r > kAloneSweep && count < 2 * ctx->intra_jobs) return SWX_OK;
@@ -1990,7 +2011,7 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
 
   // long pairs take the intra-sequence path, the rest the batched one
   AlonePath al;
-  if ((rc = plan_alone(ctx, sc, np, flags, hstats, qlen, rlen, lp, al))) return rc;
+  if ((rc = plan_alone(ctx, sc, np, flags, b.nq == 1, hstats, qlen, rlen, lp, al))) return rc;
   if (!al.on && (rc = list_pairs(ctx, np, lp))) return rc;
   AloneRest rest;
   if (al.all && (flags & SWX_BEGIN)) {

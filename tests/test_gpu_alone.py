@@ -164,3 +164,28 @@ def test_short_pairs_past_the_limit(nlong):
     want[:nlong] = 32 if nlong < 1024 else 16
     np.testing.assert_array_equal(recs["lane_bits"], want)
     assert (recs["score1"][nlong:] >= 2047).any() and (recs["score1"][nlong:] < 2047).any()
+
+
+# Above 32,768 pairs a batch only goes pair by pair where its batched passes are
+# the slower way: reads against references this long are not such a batch.
+@pytest.mark.parametrize("count,rlen,batched", [(32768, 2000, False), (32769, 2000, True), (49152, 600, True)])
+def test_where_large_batches_go(count, rlen, batched):
+    from tests.fullsize import mismatches
+
+    g = np.random.Generator(np.random.PCG64(8800 + count))
+    kinds = 64
+    qs, rs = pairs(g.integers(35, 41, size=kinds), g.integers(rlen - 9, rlen + 1, size=kinds), 8801)
+    b = W.from_lists("alone-large", W.dna_matrix(), 3, 1, qs, rs)
+    pair = np.arange(count) % kinds
+    ref, rcig, rcoff = oracle.align_many(b.qcat, b.qoff, b.rcat, b.roff, pair[:kinds], pair[:kinds],
+                                         b.matrix, 3, 1)
+    c = swx.Context(0)
+    for _ in range(2):
+        recs, cig = c.align_batch(b.matrix, 3, 1, b.qcat, b.qoff, b.rcat, b.roff, pair, pair)
+    # (where every pair goes alone its begin comes with the forward pass)
+    assert (c.stage_ms()[3] > 0.05) == batched
+    assert mismatches(recs[:kinds], cig, ref, rcig, rcoff)["pairs_bad"] == 0
+    for f in ("score1", "score2", "read_begin1", "read_end1", "ref_begin1", "ref_end1", "ref_end2",
+              "cigar_len"):
+        assert np.array_equal(recs[f], recs[f][pair]), f
+    c.close()
