@@ -109,6 +109,17 @@ class DevArena {
   T *get(int64_t count) {
     return (T *)alloc(sizeof(T) * (size_t)std::max<int64_t>(count, 1));
   }
+  // Everything taken since a mark is given back (no kernel may use it any more).
+  struct Mark {
+    size_t cur, off, fixed_off;
+  };
+  Mark mark() const { return {cur_, off_, fixed_off_}; }
+  void rewind(const Mark &m) {
+    cur_ = m.cur;
+    off_ = m.off;
+    fixed_off_ = m.fixed_off;
+    fixed_short_ = false;
+  }
 
  private:
   struct Block {
@@ -726,6 +737,13 @@ static int gather_info(swx_ctx *ctx, int64_t n, const int64_t *d_ids, const int3
                        const int64_t *rlen, const int32_t *score, const int32_t *qend,
                        const int64_t *rend, const int32_t *band, std::vector<int64_t> &info);
 
+// Long pairs take the fastest shapes whose scratch can be had: 0 any, 1 none of
+// two rows per lane and no planned chunks (more strips, so more hand-over rows),
+// kLean the least scratch.  The call that allocates nothing has 64 MiB for
+// everything: 1,000 x 5,000,000 takes 150 MiB of hand-over rows in the planned
+// four strips and none in one.
+constexpr int kLean = 2;
+
 // Shape of a wave traceback over m rows, w columns and a band of bw diagonals
 // when `jobs` such pairs share the device (rl 0: too tall for every choice).
 // Strip s starts SH + 110 (spread) or SH + 128 steps after strip s - 1 and sweeps a window of
@@ -735,6 +753,7 @@ static int gather_info(swx_ctx *ctx, int64_t n, const int64_t *d_ids, const int3
 // units a pair's strips spread over up to four waves in each of `segs`
 // workgroups (at most one per compute unit, 32 per XCD), as in the
 // intra-sequence fill.
+// rl_lo, rl_hi: rows per lane to choose from.
 struct TbShape {
   int rl, waves, segs;
   bool operator<(const TbShape &x) const {
@@ -743,7 +762,8 @@ struct TbShape {
   bool operator==(const TbShape &x) const { return rl == x.rl && waves == x.waves && segs == x.segs; }
 };
 
-static TbShape tb_wave_shape(int64_t m, int64_t w, int64_t bw, int n, int64_t jobs, int32_t cus) {
+static TbShape tb_wave_shape(int64_t m, int64_t w, int64_t bw, int n, int64_t jobs, int32_t cus,
+                             int rl_lo, int rl_hi) {
   jobs = std::max<int64_t>(jobs, 1);
   const int64_t segs_max =
       (cus <= 0 || jobs >= cus)
@@ -753,7 +773,7 @@ static TbShape tb_wave_shape(int64_t m, int64_t w, int64_t bw, int n, int64_t jo
   double best_cost = 0;
   for (int RL : {2, 4, 8, 16}) {
     const int64_t SH = 64 * RL, nstrips = (m + SH - 1) / SH;
-    if (nstrips > tb_wave_max_strips()) continue;
+    if (RL < rl_lo || RL > rl_hi || nstrips > tb_wave_max_strips()) continue;
     int64_t waves = tb_wave_waves(m, n, RL), g = 1;
     if (segs_max > 1) {
       const int64_t w4 = std::min<int64_t>(4, waves);
@@ -768,6 +788,37 @@ static TbShape tb_wave_shape(int64_t m, int64_t w, int64_t bw, int n, int64_t jo
     if (best.rl == 0 || cost < best_cost) {
       best = TbShape{RL, (int)waves, (int)g};
       best_cost = cost;
+    }
+  }
+  return best;
+}
+
+// Code bytes and hand-over words of a pair on the wave traceback.
+static void tb_wave_scratch(const TbWaveJob &jb, int RL, int64_t *dir_bytes, int64_t *bnd_words) {
+  const int64_t SH = 64 * RL, nstrips = (jb.m + SH - 1) / SH;
+  *dir_bytes = 0;
+  for (int64_t s = 0; s < nstrips; ++s) {
+    int64_t clo, chi;
+    tbw_window(s, SH, jb.dlo, jb.bw, jb.w, &clo, &chi);
+    *dir_bytes += ((chi - clo) + 63) * 64 * tb_code_bytes(RL);
+  }
+  *dir_bytes = round_up(*dir_bytes, 256);
+  *bnd_words = 2 * (jb.w + 1) * (nstrips + 1);
+}
+
+// The shape with the least scratch (the hand-over words grow with the strips,
+// the codes with their height).
+static TbShape tb_wave_least(const TbWaveJob &jb, int n, int64_t jobs, int32_t cus) {
+  TbShape best{0, 0, 0};
+  int64_t least = 0;
+  for (int RL : {4, 8, 16}) {
+    const TbShape sh = tb_wave_shape(jb.m, jb.w, jb.bw, n, jobs, cus, RL, RL);
+    if (sh.rl == 0) continue;
+    int64_t d, b;
+    tb_wave_scratch(jb, RL, &d, &b);
+    if (best.rl == 0 || d + 4 * b < least) {
+      best = sh;
+      least = d + 4 * b;
     }
   }
   return best;
@@ -1008,39 +1059,46 @@ static int run_traceback(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, 
       wmax = std::max(wmax, jb.w);
       bwmax = std::max(bwmax, jb.bw);
     }
-    // few pairs share one shape, the largest one's, and so one launch (by their
-    // own shapes 100 pairs made two, 4.6 ms instead of 4.2)
-    const TbShape common = tb_wave_shape(mmax, wmax, bwmax, sc.n, nc, ctx->cus);
-    for (int64_t k = 0; k < nc; ++k) {
-      TbWaveJob &jb = jobs[k];
-      shape[k] = nc < ctx->cus && common.rl != 0 ? common : tb_wave_shape(jb.m, jb.w, jb.bw, sc.n, nc, ctx->cus);
-      const int RL = shape[k].rl;
-      if (RL == 0) return fail(SWX_EINVAL, "alignment too long for the wave traceback");
-      const int64_t SH = 64 * RL, nstrips = (jb.m + SH - 1) / SH;
-      jb.dir_off = dbytes;
-      jb.bnd_off = bwords;
-      for (int64_t st_ = 0; st_ < nstrips; ++st_) {
-        int64_t clo, chi;
-        tbw_window(st_, SH, jb.dlo, jb.bw, jb.w, &clo, &chi);
-        dbytes += ((chi - clo) + 63) * 64 * tb_code_bytes(RL);
+    std::vector<int64_t> order(nc);
+    std::vector<TbWaveJob> sorted_jobs(nc);
+    TbWaveJob *dj = nullptr;
+    uint8_t *dirw = nullptr;
+    int32_t *bnd = nullptr;
+    IntraSync *sync = nullptr;
+    int64_t nspread = 0;
+    const DevArena::Mark mark = A.mark();
+    for (int lean = 0;; ++lean) {   // (kLean: the fastest shapes first)
+      // few pairs share one shape, the largest one's, and so one launch (by their
+      // own shapes 100 pairs made two, 4.6 ms instead of 4.2)
+      const int rl_lo = lean == 0 ? 2 : 4;
+      const TbShape common = tb_wave_shape(mmax, wmax, bwmax, sc.n, nc, ctx->cus, rl_lo, 16);
+      dbytes = bwords = nspread = 0;
+      for (int64_t k = 0; k < nc; ++k) {
+        TbWaveJob &jb = jobs[k];
+        shape[k] = lean == kLean                         ? tb_wave_least(jb, sc.n, nc, ctx->cus)
+                   : nc < ctx->cus && common.rl != 0 ? common
+                                                         : tb_wave_shape(jb.m, jb.w, jb.bw, sc.n, nc, ctx->cus, rl_lo, 16);
+        if (shape[k].rl == 0) return fail(SWX_EINVAL, "alignment too long for the wave traceback");
+        int64_t d, w;
+        tb_wave_scratch(jb, shape[k].rl, &d, &w);
+        jb.dir_off = dbytes;
+        jb.bnd_off = bwords;
+        dbytes += d;
+        bwords += w;
+        nspread += shape[k].segs > 1 ? 1 : 0;
       }
-      dbytes = round_up(dbytes, 256);
-      bwords += 2 * (jb.w + 1) * (nstrips + 1);
+      dj = A.get<TbWaveJob>(nc);
+      dirw = A.get<uint8_t>(std::max<int64_t>(dbytes, 256));
+      bnd = A.get<int32_t>(std::max<int64_t>(bwords, 1));
+      sync = nspread ? A.get<IntraSync>(nspread) : nullptr;
+      if (dj && dirw && bnd && (!nspread || sync)) break;
+      if (lean == kLean) return fail(SWX_ENOMEM, "device pool exhausted (wave traceback)");
+      A.rewind(mark);
     }
     // launch groups of equal shape
-    std::vector<int64_t> order(nc);
     std::iota(order.begin(), order.end(), 0);
     std::stable_sort(order.begin(), order.end(), [&](int64_t x, int64_t y) { return shape[x] < shape[y]; });
-    std::vector<TbWaveJob> sorted_jobs(nc);
     for (int64_t k = 0; k < nc; ++k) sorted_jobs[k] = jobs[order[k]];
-    TbWaveJob *dj = A.get<TbWaveJob>(nc);
-    uint8_t *dirw = A.get<uint8_t>(std::max<int64_t>(dbytes, 256));
-    int32_t *bnd = A.get<int32_t>(std::max<int64_t>(bwords, 1));
-    int64_t nspread = 0;
-    for (int64_t k = 0; k < nc; ++k) nspread += shape[k].segs > 1 ? 1 : 0;
-    IntraSync *sync = nspread ? A.get<IntraSync>(nspread) : nullptr;
-    if (!dj || !dirw || !bnd || (nspread && !sync))
-      return fail(SWX_ENOMEM, "device pool exhausted (wave traceback)");
     HIP_TRY(hipMemcpyAsync(dj, sorted_jobs.data(), sizeof(TbWaveJob) * nc, hipMemcpyHostToDevice, st));
     if (nspread)   // the hand-over words of spread pairs start out invalid
       HIP_TRY(hipMemsetAsync(bnd, 0, sizeof(int32_t) * std::max<int64_t>(bwords, 1), st));
@@ -1161,6 +1219,21 @@ static int pick_rl(int64_t rows, int n) {
     const int64_t cost = strips * (12 * RL + 20);
     if (cost < best_cost) { best_cost = cost; best = RL; }
   }
+  return best;
+}
+
+// Most rows per lane, and so fewest strips, that the profiles leave room for
+// (kLean); with two profiles per wave, as in the 16-bit pass, no fewer than pick_rl.
+static int most_rl(int n) {
+  int best = 4;
+  for (int RL : {8, 16, 32})
+    if (intra_lds_bytes(n, RL) + intra_static_lds() <= 65536) best = RL;
+  return best;
+}
+static int most_rl16(int64_t rows, int n) {
+  int best = pick_rl(rows, n);
+  for (int RL : {8, 16, 32})
+    if (RL > best && intra_lds_bytes16(n, RL) + 4096 <= 65536) best = RL;
   return best;
 }
 
@@ -1288,18 +1361,19 @@ typedef std::map<IntraShape, std::vector<IntraJob>> IntraGroups;
 // workgroup (one per SIMD) and as many workgroups as fit at once: at most one
 // per compute unit, and 32 (the compute units of one XCD) per XCD.
 static IntraShape intra_shape(int64_t rows, int64_t width, int32_t band, int n, int64_t jobs,
-                              int32_t cus) {
+                              int32_t cus, int lean) {
   jobs = std::max<int64_t>(jobs, 1);
+  const int rl_lo = lean == 0 ? 2 : lean < kLean ? 4 : most_rl(n);
   if (jobs >= cus || cus <= 0) {
-    const int RL = pick_rl(rows, n);
+    const int RL = std::max(pick_rl(rows, n), rl_lo);
     return {RL, intra_waves((rows + 64 * RL - 1) / (64 * RL), n, RL), 1};
   }
   const int64_t segs_max =
       std::max<int64_t>(1, std::min<int64_t>(cus / jobs, 32 / ((jobs + 7) / 8)));
-  IntraShape best{pick_rl(rows, n), 1, 1};
+  IntraShape best{std::max(pick_rl(rows, n), rl_lo), 1, 1};
   double best_cost = -1;
   for (int RL : {2, 4, 8, 16, 32}) {
-    if (intra_lds_bytes(n, RL) + intra_static_lds() > 65536) continue;
+    if (RL < rl_lo || intra_lds_bytes(n, RL) + intra_static_lds() > 65536) continue;
     const int64_t SH = 64 * RL;
     const int64_t nstrips = std::max<int64_t>(1, (rows + SH - 1) / SH);
     if (nstrips > intra_max_strips()) continue;
@@ -1400,12 +1474,37 @@ static FwdPlan plan_forward(const Scoring &sc, const std::vector<int64_t> &info,
 // their padded height, so any two of them can share a wave.
 typedef std::map<std::pair<int, int64_t>, std::vector<IntraJob>> Jobs16;
 
+// Device memory of a launch of long-pair jobs.
+struct IntraMem {
+  IntraJob *jobs = nullptr, *jobs16 = nullptr;
+  IntraSync *sync = nullptr;
+  uint32_t *bnd = nullptr;   // hand-over rows, bnd_words of them
+  int64_t bnd_words = 0;
+};
+static bool intra_mem(DevArena &A, const IntraGroups &groups, const Jobs16 &jobs16, int64_t bnd_words,
+                      IntraMem &m) {
+  int64_t n32 = 0, nspread = 0, n16 = 0;
+  for (const auto &kv : groups) {
+    n32 += (int64_t)kv.second.size();
+    if (kv.first.segs > 1) nspread += (int64_t)kv.second.size();
+  }
+  for (const auto &kv : jobs16) n16 += round_up((int64_t)kv.second.size(), 2);
+  m = IntraMem{};
+  m.bnd_words = std::max<int64_t>(bnd_words, 1);
+  m.bnd = A.get<uint32_t>(m.bnd_words);
+  bool ok = m.bnd != nullptr;
+  if (n32) ok = (m.jobs = A.get<IntraJob>(n32)) != nullptr && ok;
+  if (nspread) ok = (m.sync = A.get<IntraSync>(nspread)) != nullptr && ok;
+  if (n16) ok = (m.jobs16 = A.get<IntraJob>(n16)) != nullptr && ok;
+  return ok;
+}
+
 // Upload the 16-bit jobs (each key's list padded to an even count with an
-// empty job) and launch them, a pair of jobs per workgroup.
+// empty job) and launch them, a pair of jobs per workgroup; the stream is waited for.
 // packed: jobs of one strip go four waves to a workgroup, a pair of jobs each
 // (planned chunks of equal width: a workgroup ends with its longest wave).
-static int launch_intra16_jobs(swx_ctx *ctx, const Jobs16 &jobs, IntraArgs a, const Scoring &sc,
-                               bool m3, bool packed) {
+static int launch_intra16_jobs(swx_ctx *ctx, const Jobs16 &jobs, IntraArgs a, const IntraMem &mem,
+                               const Scoring &sc, bool m3, bool packed) {
   if (jobs.empty()) return SWX_OK;
   std::vector<IntraJob> all;
   std::vector<std::pair<int64_t, int64_t>> span;   // per key: first job, count
@@ -1419,14 +1518,13 @@ static int launch_intra16_jobs(swx_ctx *ctx, const Jobs16 &jobs, IntraArgs a, co
     }
     span.push_back({first, (int64_t)all.size() - first});
   }
-  IntraJob *dj = ctx->arena.get<IntraJob>((int64_t)all.size());
-  if (!dj) return fail(SWX_ENOMEM, "device pool exhausted (intra jobs)");
-  HIP_TRY(hipMemcpyAsync(dj, all.data(), sizeof(IntraJob) * all.size(), hipMemcpyHostToDevice,
+  HIP_TRY(hipMemcpyAsync(mem.jobs16, all.data(), sizeof(IntraJob) * all.size(), hipMemcpyHostToDevice,
                          ctx->stream));
+  a.bnd = mem.bnd;
   size_t k = 0;
   for (const auto &kv : jobs) {
     const int RL = kv.first.first;
-    a.jobs = dj + span[k].first;
+    a.jobs = mem.jobs16 + span[k].first;
     a.njobs = span[k].second;
     int waves = intra_waves16(kv.first.second, sc.n, RL);
     a.segs = 1;
@@ -1438,11 +1536,9 @@ static int launch_intra16_jobs(swx_ctx *ctx, const Jobs16 &jobs, IntraArgs a, co
   return SWX_OK;
 }
 
-// Upload jobs (grouped by launch shape) and launch them; bnd: the hand-over
-// rows (null: allocated here, bnd_words of them).
-static int launch_intra_jobs(swx_ctx *ctx, const IntraGroups &groups, IntraArgs a,
-                             int64_t bnd_words, bool rev) {
-  DevArena &A = ctx->arena;
+// Upload jobs (grouped by launch shape) and launch them; the stream is waited for.
+static int launch_intra_jobs(swx_ctx *ctx, const IntraGroups &groups, IntraArgs a, const IntraMem &mem,
+                             bool rev) {
   std::vector<IntraJob> all;
   int64_t nspread = 0;
   for (const auto &kv : groups) {
@@ -1450,23 +1546,19 @@ static int launch_intra_jobs(swx_ctx *ctx, const IntraGroups &groups, IntraArgs 
     if (kv.first.segs > 1) nspread += (int64_t)kv.second.size();
   }
   if (all.empty()) return SWX_OK;
-  IntraJob *dj = A.get<IntraJob>((int64_t)all.size());
-  IntraSync *sync = nspread ? A.get<IntraSync>(nspread) : nullptr;
-  if (!a.bnd) a.bnd = A.get<uint32_t>(bnd_words > 0 ? bnd_words : 1);
-  if (!dj || !a.bnd || (nspread && !sync))
-    return fail(SWX_ENOMEM, "device pool exhausted (intra jobs)");
-  HIP_TRY(hipMemcpyAsync(dj, all.data(), sizeof(IntraJob) * all.size(), hipMemcpyHostToDevice,
+  HIP_TRY(hipMemcpyAsync(mem.jobs, all.data(), sizeof(IntraJob) * all.size(), hipMemcpyHostToDevice,
                          ctx->stream));
   if (nspread) {   // the words of spread jobs start out invalid
-    HIP_TRY(intra_sync_init(sync, nspread, ctx->stream));
-    HIP_TRY(hipMemsetAsync(a.bnd, 0, sizeof(uint32_t) * std::max<int64_t>(bnd_words, 1), ctx->stream));
+    HIP_TRY(intra_sync_init(mem.sync, nspread, ctx->stream));
+    HIP_TRY(hipMemsetAsync(mem.bnd, 0, sizeof(uint32_t) * mem.bnd_words, ctx->stream));
   }
+  a.bnd = mem.bnd;
   int64_t off = 0, soff = 0;
   for (const auto &kv : groups) {
-    a.jobs = dj + off;
+    a.jobs = mem.jobs + off;
     a.njobs = (int64_t)kv.second.size();
     a.segs = kv.first.segs;
-    a.sync = kv.first.segs > 1 ? sync + soff : nullptr;
+    a.sync = kv.first.segs > 1 ? mem.sync + soff : nullptr;
     HIP_TRY(intra_fill(a, kv.first.rl, kv.first.waves, rev, ctx->stream));
     off += a.njobs;
     if (kv.first.segs > 1) soff += a.njobs;
@@ -1687,105 +1779,115 @@ static int run_intra_forward(swx_ctx *ctx, const Scoring &sc, LongPath &lp, cons
   if ((rc = read_long(ctx, view.qlen, view.rlen, lp))) return rc;
   const int64_t total_r = long_rlen(lp);
   for (int64_t k = 0; k < lp.nlong; ++k) lp.max_rlen = std::max(lp.max_rlen, lp.info[6 * k + 1]);
-  Jobs16 jobs16;
-  std::vector<int64_t> ids16, ids32;
-  lp.pairs.clear();
   const bool auto16 = choose16(ctx, sc, lp);
   // lanes of each pair, and the 32-bit jobs that will share the device
   std::vector<uint8_t> is16(lp.nlong);
-  std::vector<int64_t> k16, k32;
-  int64_t jobs32 = 0, r16 = 0, r32 = 0;
+  std::vector<int64_t> k16, k32, ids16, ids32;
+  int64_t jobs32 = 0, r16 = 0, r32 = 0, mc_words = 0;
   for (int64_t k = 0; k < lp.nlong; ++k) {
     const int64_t Lq = lp.info[6 * k], Lr = lp.info[6 * k + 1];
     is16[k] = auto16 && intra_fits16(sc, Lq, Lr, pick_rl(Lq, sc.n));
     (is16[k] ? k16 : k32).push_back(k);
+    (is16[k] ? ids16 : ids32).push_back(lp.ids[k]);
     (is16[k] ? r16 : r32) += std::max<int64_t>(Lr, 1);
+    mc_words += Lr;
     if (!is16[k] && Lr > 0) {
       const int64_t C = intra_chunk(sc, Lq, Lr, ctx->intra_jobs, total_r);
       jobs32 += (Lr + C - 1) / C;
     }
   }
-  // a few pairs are planned together (many fill the device by their number);
-  // 32-bit jobs that leave compute units idle spread over several workgroups
-  // each (intra_shape) instead
-  FwdPlan f16, f32;
-  if (lp.nlong <= kFwdPlanPairs) {
-    f16 = plan_forward(sc, lp.info, k16, 2, 2 * ctx->intra_jobs, ctx->cus);
-    f32 = plan_forward(sc, lp.info, k32, 1, ctx->intra_jobs, ctx->cus);
-  }
-  const bool plan16 = f16.rl != 0, plan32 = f32.rl != 0 && f32.jobs >= ctx->cus;
-  IntraShape common32{};   // ... all in one launch, by the largest job's shape
-  if (!plan32 && jobs32 > 0 && jobs32 < ctx->cus) {
-    int64_t rows = 0, width = 0;
-    for (int64_t k : k32) {
-      const int64_t Lq = lp.info[6 * k], Lr = lp.info[6 * k + 1];
-      rows = std::max(rows, Lq);
-      width = std::max(width, std::min(Lr, intra_chunk(sc, Lq, Lr, ctx->intra_jobs, total_r) +
-                                               intra_warmup(sc, Lq, Lr)));
-    }
-    common32 = intra_shape(rows, width, -1, sc.n, jobs32, ctx->cus);
-  }
-  const int64_t simds = 4 * (int64_t)std::max(ctx->cus, 1);
-  IntraGroups groups;
-  int64_t mc_words = 0, bnd_words = 0;
-  bool m3 = true;   // every 16-bit pair's lane values below 0x7C00
-  for (int64_t k = 0; k < lp.nlong; ++k) {
-    const int64_t p = lp.ids[k], Lq = lp.info[6 * k], Lr = lp.info[6 * k + 1];
-    const bool w16 = is16[k];
-    const int64_t W = intra_warmup(sc, Lq, Lr);
-    int64_t C = intra_chunk(sc, Lq, Lr, (w16 ? 2 : 1) * ctx->intra_jobs, total_r);
-    IntraShape shape{};
-    if (w16 && plan16) {
-      C = fwd_chunk(sc, Lq, Lr, f16.rl, 2 * simds, 2 * ctx->intra_jobs, r16);
-      shape = IntraShape{f16.rl, 0, 1};
-    } else if (!w16 && plan32) {
-      C = fwd_chunk(sc, Lq, Lr, f32.rl, simds, ctx->intra_jobs, r32);
-      shape = IntraShape{f32.rl, intra_waves((Lq + 64 * f32.rl - 1) / (64 * f32.rl), sc.n, f32.rl), 1};
-    } else {
-      shape = w16               ? IntraShape{pick_rl(Lq, sc.n), 0, 1}
-              : common32.rl != 0 ? common32
-                                 : intra_shape(Lq, std::min(Lr, C + W), -1, sc.n, jobs32, ctx->cus);
-    }
-    const int RL = shape.rl;
-    const int64_t SH = 64 * RL;
-    const int64_t qp = (Lq + SH - 1) / SH * SH;
-    const int64_t bound = (int64_t)std::max(sc.smax, 0) * std::min(Lq, Lr);
-    const int kb = w16 ? 16 : code_bits(qp);
-    if (kb > 30 || bound >= (int64_t(1) << (32 - kb)))
-      return fail(SWX_EOVERFLOW, "long pair: score range and query length exceed the max-array word");
-    (w16 ? ids16 : ids32).push_back(p);
-    if (w16 && bound + sc.bias > kMax3Lane) m3 = false;
-    IntraPair ip{p, mc_words, kb, (int32_t)SH};
-    lp.pairs.push_back(ip);
-    if (Lr > 0) {
-      const int64_t nstrips = qp / SH;
-      if (nstrips > intra_max_strips())
-        return fail(SWX_EINVAL, "query too long for the intra-sequence path");
-      for (int64_t c0 = 0; c0 < Lr; c0 += C) {
-        IntraJob jb{};
-        jb.pair = p;
-        jb.c0 = c0;
-        jb.c1 = std::min(Lr, c0 + C);
-        jb.cw = std::max<int64_t>(0, c0 - W);
-        jb.mc_off = mc_words;
-        jb.bnd_off = bnd_words;
-        jb.kbits = kb;
-        jb.band = -1;
-        bnd_words += 2 * (jb.c1 - jb.cw) * (nstrips - 1);
-        if (w16) jobs16[{RL, nstrips}].push_back(jb);
-        else groups[shape].push_back(jb);
-      }
-    }
-    mc_words += Lr;
-  }
   lp.d_maxcol = A.get<uint32_t>(std::max<int64_t>(mc_words, 1));
-  if (lp.d_maxcol && mc_words > 0)
-    HIP_TRY(hipMemsetAsync(lp.d_maxcol, 0, sizeof(uint32_t) * mc_words, ctx->stream));
   lp.d_pairs = A.get<IntraPair>(lp.nlong);
   lp.d_part_v = A.get<int32_t>(lp.nlong * intra_slices());
   lp.d_part_j = A.get<int64_t>(lp.nlong * intra_slices());
   if (!lp.d_maxcol || !lp.d_pairs || !lp.d_part_v || !lp.d_part_j)
     return fail(SWX_ENOMEM, "device pool exhausted (max array)");
+  if (mc_words > 0) HIP_TRY(hipMemsetAsync(lp.d_maxcol, 0, sizeof(uint32_t) * mc_words, ctx->stream));
+  const int64_t simds = 4 * (int64_t)std::max(ctx->cus, 1);
+  Jobs16 jobs16;
+  IntraGroups groups;
+  IntraMem mem;
+  bool m3 = true;       // every 16-bit pair's lane values below 0x7C00
+  bool plan16 = false;  // 16-bit chunks planned
+  const DevArena::Mark mark = A.mark();
+  for (int lean = 0;; ++lean) {   // (kLean: the fastest shapes first)
+    jobs16.clear();
+    groups.clear();
+    lp.pairs.clear();
+    // a few pairs are planned together (many fill the device by their number);
+    // 32-bit jobs that leave compute units idle spread over several workgroups
+    // each (intra_shape) instead
+    FwdPlan f16, f32;
+    if (lp.nlong <= kFwdPlanPairs && lean == 0) {
+      f16 = plan_forward(sc, lp.info, k16, 2, 2 * ctx->intra_jobs, ctx->cus);
+      f32 = plan_forward(sc, lp.info, k32, 1, ctx->intra_jobs, ctx->cus);
+    }
+    plan16 = f16.rl != 0;
+    const bool plan32 = f32.rl != 0 && f32.jobs >= ctx->cus;
+    IntraShape common32{};   // ... all in one launch, by the largest job's shape
+    if (!plan32 && jobs32 > 0 && jobs32 < ctx->cus) {
+      int64_t rows = 0, width = 0;
+      for (int64_t k : k32) {
+        const int64_t Lq = lp.info[6 * k], Lr = lp.info[6 * k + 1];
+        rows = std::max(rows, Lq);
+        width = std::max(width, std::min(Lr, intra_chunk(sc, Lq, Lr, ctx->intra_jobs, total_r) +
+                                                 intra_warmup(sc, Lq, Lr)));
+      }
+      common32 = intra_shape(rows, width, -1, sc.n, jobs32, ctx->cus, lean);
+    }
+    int64_t mc_off = 0, bnd_words = 0;
+    for (int64_t k = 0; k < lp.nlong; ++k) {
+      const int64_t p = lp.ids[k], Lq = lp.info[6 * k], Lr = lp.info[6 * k + 1];
+      const bool w16 = is16[k];
+      const int64_t W = intra_warmup(sc, Lq, Lr);
+      int64_t C = intra_chunk(sc, Lq, Lr, (w16 ? 2 : 1) * ctx->intra_jobs, total_r);
+      IntraShape shape{};
+      if (w16 && plan16) {
+        C = fwd_chunk(sc, Lq, Lr, f16.rl, 2 * simds, 2 * ctx->intra_jobs, r16);
+        shape = IntraShape{f16.rl, 0, 1};
+      } else if (!w16 && plan32) {
+        C = fwd_chunk(sc, Lq, Lr, f32.rl, simds, ctx->intra_jobs, r32);
+        shape = IntraShape{f32.rl, intra_waves((Lq + 64 * f32.rl - 1) / (64 * f32.rl), sc.n, f32.rl), 1};
+      } else if (w16) {
+        shape = IntraShape{lean == kLean ? most_rl16(Lq, sc.n) : pick_rl(Lq, sc.n), 0, 1};
+      } else {
+        shape = common32.rl != 0 ? common32
+                                 : intra_shape(Lq, std::min(Lr, C + W), -1, sc.n, jobs32, ctx->cus, lean);
+      }
+      const int RL = shape.rl;
+      const int64_t SH = 64 * RL;
+      const int64_t qp = (Lq + SH - 1) / SH * SH;
+      const int64_t bound = (int64_t)std::max(sc.smax, 0) * std::min(Lq, Lr);
+      const int kb = w16 ? 16 : code_bits(qp);
+      if (kb > 30 || bound >= (int64_t(1) << (32 - kb)))
+        return fail(SWX_EOVERFLOW, "long pair: score range and query length exceed the max-array word");
+      if (w16 && bound + sc.bias > kMax3Lane) m3 = false;
+      lp.pairs.push_back(IntraPair{p, mc_off, kb, (int32_t)SH});
+      if (Lr > 0) {
+        const int64_t nstrips = qp / SH;
+        if (nstrips > intra_max_strips())
+          return fail(SWX_EINVAL, "query too long for the intra-sequence path");
+        for (int64_t c0 = 0; c0 < Lr; c0 += C) {
+          IntraJob jb{};
+          jb.pair = p;
+          jb.c0 = c0;
+          jb.c1 = std::min(Lr, c0 + C);
+          jb.cw = std::max<int64_t>(0, c0 - W);
+          jb.mc_off = mc_off;
+          jb.bnd_off = bnd_words;
+          jb.kbits = kb;
+          jb.band = -1;
+          bnd_words += 2 * (jb.c1 - jb.cw) * (nstrips - 1);
+          if (w16) jobs16[{RL, nstrips}].push_back(jb);
+          else groups[shape].push_back(jb);
+        }
+      }
+      mc_off += Lr;
+    }
+    if (intra_mem(A, groups, jobs16, bnd_words, mem)) break;
+    if (lean == kLean) return fail(SWX_ENOMEM, "device pool exhausted (hand-over rows)");
+    A.rewind(mark);
+  }
   HIP_TRY(hipMemcpyAsync(lp.d_pairs, lp.pairs.data(), sizeof(IntraPair) * lp.nlong,
                          hipMemcpyHostToDevice, ctx->stream));
   IntraArgs a{};
@@ -1794,10 +1896,9 @@ static int run_intra_forward(swx_ctx *ctx, const Scoring &sc, LongPath &lp, cons
   a.n = sc.n; a.o = sc.o; a.e = sc.e; a.bias = sc.bias;
   a.maxcol = lp.d_maxcol;
   a.err = err;
-  a.bnd = A.get<uint32_t>(bnd_words > 0 ? bnd_words : 1);
-  if (!a.bnd) return fail(SWX_ENOMEM, "device pool exhausted (hand-over rows)");
-  if ((rc = launch_intra_jobs(ctx, groups, a, bnd_words, false))) return rc;
-  if ((rc = launch_intra16_jobs(ctx, jobs16, a, sc, m3, plan16))) return rc;
+  if ((rc = launch_intra_jobs(ctx, groups, a, mem, false))) return rc;
+  if ((rc = launch_intra16_jobs(ctx, jobs16, a, mem, sc, m3, plan16))) return rc;
+  A.rewind(mark);   // (both have been waited for)
   // lane widths of the long pairs (diagnostic)
   for (int w = 0; w < 2; ++w) {
     const std::vector<int64_t> &ids = w ? ids32 : ids16;
@@ -1825,8 +1926,7 @@ static int run_intra_reverse(swx_ctx *ctx, const Scoring &sc, LongPath &lp, cons
   int rc;
   if ((rc = gather_info(ctx, lp.nlong, lp.d_long, nullptr, nullptr, score, qend, rend, band, info)))
     return rc;
-  IntraGroups groups;
-  int64_t bnd_words = 0, njobs = 0;
+  int64_t njobs = 0;
   int64_t max_rows = 0, max_cols = 0, max_band = 0;
   for (int64_t k = 0; k < lp.nlong; ++k) {
     if (info[6 * k + 2] <= 0) continue;
@@ -1836,33 +1936,44 @@ static int run_intra_reverse(swx_ctx *ctx, const Scoring &sc, LongPath &lp, cons
     const int64_t band = info[6 * k + 5];   // (none: negative)
     max_band = band < 0 || max_band < 0 ? -1 : std::max(max_band, band);
   }
-  // jobs that leave compute units idle share one shape, the largest job's, and
-  // so one launch: by their own shapes 50 pairs made two, one after the other
-  const IntraShape common = intra_shape(max_rows, max_cols, (int32_t)max_band, sc.n, njobs, ctx->cus);
-  for (int64_t k = 0; k < lp.nlong; ++k) {
-    if (info[6 * k + 2] <= 0) continue;
-    const int64_t rows = info[6 * k + 3] + 1, cols = info[6 * k + 4] + 1;
-    const IntraShape shape =
-        njobs < ctx->cus ? common
-                         : intra_shape(rows, cols, (int32_t)info[6 * k + 5], sc.n, njobs, ctx->cus);
-    const int RL = shape.rl;
-    const int64_t SH = 64 * RL;
-    const int64_t qp = (rows + SH - 1) / SH * SH;
-    const int kb = code_bits(qp);
-    if (kb > 30 || info[6 * k + 2] >= (int64_t(1) << (32 - kb)))
-      return fail(SWX_EOVERFLOW, "long pair: score range and query length exceed the max-array word");
-    const int64_t nstrips = qp / SH;
-    if (nstrips > intra_max_strips())
-      return fail(SWX_EINVAL, "query too long for the intra-sequence path");
-    IntraJob jb{};
-    jb.pair = lp.ids[k];
-    jb.cw = 0; jb.c0 = 0; jb.c1 = cols;
-    jb.mc_off = 0;
-    jb.bnd_off = bnd_words;
-    jb.kbits = kb;
-    jb.band = (int32_t)info[6 * k + 5];
-    bnd_words += 2 * cols * (nstrips - 1);
-    groups[shape].push_back(jb);
+  IntraGroups groups;
+  IntraMem mem;
+  DevArena &A = ctx->arena;
+  const DevArena::Mark mark = A.mark();
+  for (int lean = 0;; ++lean) {   // (kLean: the fastest shapes first)
+    groups.clear();
+    int64_t bnd_words = 0;
+    // jobs that leave compute units idle share one shape, the largest job's, and
+    // so one launch: by their own shapes 50 pairs made two, one after the other
+    const IntraShape common = intra_shape(max_rows, max_cols, (int32_t)max_band, sc.n, njobs, ctx->cus, lean);
+    for (int64_t k = 0; k < lp.nlong; ++k) {
+      if (info[6 * k + 2] <= 0) continue;
+      const int64_t rows = info[6 * k + 3] + 1, cols = info[6 * k + 4] + 1;
+      const IntraShape shape =
+          njobs < ctx->cus ? common
+                           : intra_shape(rows, cols, (int32_t)info[6 * k + 5], sc.n, njobs, ctx->cus, lean);
+      const int RL = shape.rl;
+      const int64_t SH = 64 * RL;
+      const int64_t qp = (rows + SH - 1) / SH * SH;
+      const int kb = code_bits(qp);
+      if (kb > 30 || info[6 * k + 2] >= (int64_t(1) << (32 - kb)))
+        return fail(SWX_EOVERFLOW, "long pair: score range and query length exceed the max-array word");
+      const int64_t nstrips = qp / SH;
+      if (nstrips > intra_max_strips())
+        return fail(SWX_EINVAL, "query too long for the intra-sequence path");
+      IntraJob jb{};
+      jb.pair = lp.ids[k];
+      jb.cw = 0; jb.c0 = 0; jb.c1 = cols;
+      jb.mc_off = 0;
+      jb.bnd_off = bnd_words;
+      jb.kbits = kb;
+      jb.band = (int32_t)info[6 * k + 5];
+      bnd_words += 2 * cols * (nstrips - 1);
+      groups[shape].push_back(jb);
+    }
+    if (intra_mem(A, groups, Jobs16{}, bnd_words, mem)) break;
+    if (lean == kLean) return fail(SWX_ENOMEM, "device pool exhausted (intra jobs)");
+    A.rewind(mark);
   }
   IntraArgs a{};
   a.view = rview;
@@ -1872,7 +1983,9 @@ static int run_intra_reverse(swx_ctx *ctx, const Scoring &sc, LongPath &lp, cons
   a.target = tgt;
   a.out = rout;
   a.err = err;
-  return launch_intra_jobs(ctx, groups, a, bnd_words, true);
+  if ((rc = launch_intra_jobs(ctx, groups, a, mem, true))) return rc;
+  A.rewind(mark);   // (waited for)
+  return SWX_OK;
 }
 
 // The CIGARs of a deferred traceback (TbDirect), whose total is known now.

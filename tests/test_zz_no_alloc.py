@@ -106,3 +106,29 @@ def test_noalloc_limits():
         _same(small, *_host_both(ctx, small))
     finally:
         ctx.close()
+
+
+# What the scratch holds of long pairs: long references (the hit near the end), a
+# long read, several reads of a few kilobases.
+@pytest.mark.parametrize("count,qlen,rlen,flags", [
+    (1, 1000, 1_000_000, swx.SWX_ALL), (1, 1000, 3_000_000, swx.SWX_BEGIN), (1, 1000, 6_000_000, 0),
+    (1, 18_000, 22_000, swx.SWX_ALL), (20, 3000, 8000, swx.SWX_ALL), (60, 3000, 8000, swx.SWX_BEGIN)])
+def test_noalloc_long_pairs(count, qlen, rlen, flags):
+    g = np.random.Generator(np.random.PCG64(7310 + count + rlen))
+    qs, rs = [], []
+    for _ in range(count):
+        r = g.integers(0, 4, rlen).astype(np.int8)
+        at = rlen - qlen - int(g.integers(1, 500))
+        q = r[at:at + qlen].copy()
+        u = g.random(qlen) < 0.05
+        q[u] = g.integers(0, 4, int(u.sum()))
+        q = np.delete(q, np.flatnonzero(g.random(qlen) < 0.01))
+        qs.append(q)
+        rs.append(r)
+    b = W.from_lists(f"noalloc-{qlen}x{rlen}", W.dna_matrix(), 3, 1, qs, rs)
+    ctx = swx.Context(0)
+    try:
+        for _ in range(2):
+            _same(b, *_host_both(ctx, b, flags))
+    finally:
+        ctx.close()
