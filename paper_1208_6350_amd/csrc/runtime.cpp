@@ -3367,7 +3367,7 @@ int swx_align_batch_noalloc(swx_ctx *ctx, const swx_batch *b, swx_batch_out *out
 
 // The one-pair call of short queries (kPairMaxQ x kPairMaxR) in three kernels.
 // ref: host memory, or device memory with ref_dev.  Callers hold ctx->mu and a
-// StreamScope.
+// StreamScope.  1: memory for it could not be had (nothing has run).
 static int align_pair_short(const swx_profile *p, const int8_t *ref, bool ref_dev, int64_t rlen,
                             uint32_t flags, int32_t mask_len, swx_result *out) {
   swx_ctx *ctx = p->ctx;
@@ -3380,13 +3380,13 @@ static int align_pair_short(const swx_profile *p, const int8_t *ref, bool ref_de
   if (!ctx->pair_in &&
       hipHostMalloc(&ctx->pair_in, kInM + 32 * 32, hipHostMallocDefault) != hipSuccess) {
     ctx->pair_in = nullptr;
-    return fail(SWX_ENOMEM, "pinned host allocation failed");
+    return 1;
   }
   if (!ctx->pair_out &&
       hipHostMalloc(&ctx->pair_out, sizeof(PairOut) + 4 * (kPairMaxQ + kPairMaxR + 2),
                     hipHostMallocDefault) != hipSuccess) {
     ctx->pair_out = nullptr;
-    return fail(SWX_ENOMEM, "pinned host allocation failed");
+    return 1;
   }
   if (ctx->pairs == 0) ctx->pair_out->done = 0;
   if (flags & (SWX_CIGAR | SWX_SCORE2)) flags |= SWX_BEGIN;
@@ -3399,34 +3399,46 @@ static int align_pair_short(const swx_profile *p, const int8_t *ref, bool ref_de
   a.flags = flags;
   a.mask_len = mask_len;
   // column chunks, each on a workgroup of its own: as many as shorten the
-  // longest (its warm-up is the widest positive-scoring span), and several
-  // strips' words within a few megabytes
+  // longest sweep (a chunk and its warm-up, the widest positive-scoring span; by
+  // less than 1/32 they are not worth their repeated columns), with at most 64 MiB
+  // of several strips' words (2,048 x 65,536 DNA takes 48; 128 chunks of it took
+  // 180 at scores of 11 with an extension of 1, and 459 at 30, where the warm-up
+  // spans 97% of the reference)
   a.warm = intra_warmup(sc, Lq, rlen);
   a.chunk = std::max<int64_t>(rlen, 1);
-  if (a.warm < rlen)
-    a.chunk = std::max<int64_t>(64, (rlen + (a.strips == 1 ? 255 : 127)) / (a.strips == 1 ? 256 : 128));
-  a.nchunks = (int32_t)((rlen + a.chunk - 1) / a.chunk);
-  a.fstride = (a.strips - 1) * std::min(rlen, a.chunk + a.warm);
-  a.rcount = (a.strips - 1) * rlen;
+  if (a.warm < rlen) {
+    int64_t most = a.strips == 1 ? 256 : 128;
+    if (a.strips > 1)
+      most = std::min(most, std::max<int64_t>(((int64_t(8) << 20) / (a.strips - 1) - rlen) / a.warm, 1));
+    const int64_t c = std::max<int64_t>(64, (rlen + most - 1) / most);
+    if (32 * (c + a.warm) <= 31 * rlen) a.chunk = c;
+  }
   ctx->arena.reset();
   DevArena &A = ctx->arena;
+  a.rcount = (a.strips - 1) * rlen;
   a.q = A.get<int8_t>(Lq);
   a.r = A.get<int8_t>(rlen);
   a.m = A.get<int8_t>((int64_t)sc.n * sc.n);
   a.maxcol = A.get<uint32_t>(rlen);
-  a.fwords = A.get<uint64_t>(a.fstride * a.nchunks);
   a.rwords = A.get<uint64_t>(a.rcount);
   a.state = A.get<PairState>(1);
   uint32_t *cig = A.get<uint32_t>(Lq + rlen + 2);
-  if (!a.q || !a.r || !a.m || !a.maxcol || !a.fwords || !a.rwords || !a.state || !cig)
-    return fail(SWX_ENOMEM, "device pool exhausted (pair)");
+  bool have = a.q && a.r && a.m && a.maxcol && a.rwords && a.state && cig;
   if (flags & SWX_CIGAR) {
     // an alignment of positive score spans at most the warm-up's columns
     const int64_t w = std::min(rlen, a.warm);
     a.dir = A.get<uint8_t>(tb_wave_dir_bytes(Lq, w, kPairRows));
     a.bnd = A.get<int32_t>(2 * (w + 1) * (a.strips + 1));
-    if (!a.dir || !a.bnd) return fail(SWX_ENOMEM, "device pool exhausted (pair traceback)");
+    have = have && a.dir && a.bnd;
   }
+  for (;;) {   // (one chunk where device memory is short)
+    a.nchunks = (int32_t)((rlen + a.chunk - 1) / a.chunk);
+    a.fstride = (a.strips - 1) * std::min(rlen, a.chunk + a.warm);
+    a.fwords = A.get<uint64_t>(a.fstride * a.nchunks);
+    if (a.fwords || a.nchunks == 1) break;
+    a.chunk = rlen;
+  }
+  if (!have || !a.fwords) return 1;
   PairState *y = a.state;
   TbArgs &t = a.tb;
   t.score = &y->score; t.qbeg = &y->qbeg; t.qend = &y->qend; t.rbeg = &y->rbeg; t.rend = &y->rend;
@@ -3515,8 +3527,10 @@ int swx_align(const swx_profile *p, const int8_t *ref, int64_t rlen, uint32_t fl
   }
   StreamScope ss(ctx, hip_stream);
   const bool plain = !subopt && Lq <= kPair32MaxQ && rlen <= kPairMaxR;
-  if (plain && Lq <= kPairMaxQ && rlen > 0)
-    return align_pair_short(p, ref, ref_dev, rlen, flags & SWX_ALL, mask_len, out);
+  if (plain && Lq <= kPairMaxQ && rlen > 0) {
+    const int rc = align_pair_short(p, ref, ref_dev, rlen, flags & SWX_ALL, mask_len, out);
+    if (rc <= 0) return rc;
+  }
   struct Routing {   // plain pairs: the 32-bit long-pair lanes
     swx_ctx *c;
     int64_t cells, len;

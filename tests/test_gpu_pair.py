@@ -133,3 +133,26 @@ def test_bad_symbols_and_empty(ctx):
     rec, cig = swx.swx_align(p, q)   # the context still works
     assert rec["score1"] == 100 and cig == [(50, "M")]
     swx.swx_profile_destroy(p)
+
+
+# Several strips and a warm-up (the widest positive-scoring span) from a small
+# part of the reference to nearly all of it, around the last cut that pays, and
+# the device memory that the call then keeps.
+@pytest.mark.parametrize("qlen,match,ext,rlen", [
+    (300, 2, 1, 948), (300, 2, 1, 1024), (300, 2, 1, 1088), (520, 11, 1, 7000), (520, 30, 1, 17000),
+    (2048, 11, 1, 65536), (2048, 30, 1, 65536), (2048, 30, 1, 65000)])
+def test_warm_ups_and_memory(qlen, match, ext, rlen):
+    import torch
+
+    g = np.random.Generator(np.random.PCG64(8600 + qlen + rlen))
+    q, r = make_pair(g, qlen, rlen, 4)
+    mat = W.dna_matrix(match, -4)
+    c = swx.Context(0)
+    free = torch.cuda.mem_get_info()[0]
+    rec, cig = c.align_pair(q, r, mat, 11, ext, 0)
+    held = free - torch.cuda.mem_get_info()[0]
+    check(rec, cig, q, r, mat, 11, ext, 0)
+    rec, cig = c.align_pair(q, r, mat, 11, ext)
+    check(rec, cig, q, r, mat, 11, ext, swx.SWX_ALL)
+    c.close()
+    assert held <= 160 << 20
