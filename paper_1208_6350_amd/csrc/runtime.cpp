@@ -3634,13 +3634,16 @@ int swx_graph_create(swx_ctx *ctx, const swx_graph_cfg *cfg, swx_graph **out, sw
   }
   g.sc.dmat = dmat;
   if ((rc = graph_alloc(g))) { delete gr; return rc; }
-  // valid empty contents: every code 0, every offset 0, every pair (0, 0)
+  // valid empty contents: every code 0, every offset 0, every pair (0, 0); and no
+  // results, for a read before the first run
   hipStream_t st = ctx->stream;
   bool ok = fill_u8(g.cfg.qcat_cap, (uint8_t *)g.qcat, 0, st) == hipSuccess &&
             fill_u8(g.cfg.rcat_cap, (uint8_t *)g.rcat, 0, st) == hipSuccess &&
             fill_i64(g.cfg.nq_cap + 1, g.qoff, 0, st) == hipSuccess &&
             fill_i64(g.cfg.nr_cap + 1, g.roff, 0, st) == hipSuccess &&
             fill_i64(g.B, g.pair_q, 0, st) == hipSuccess && fill_i64(g.B, g.pair_r, 0, st) == hipSuccess &&
+            fill_u8(sizeof(swx_rec) * g.B, (uint8_t *)g.recs, 0, st) == hipSuccess &&
+            fill_i64(g.B + 1, g.cig_off_final, 0, st) == hipSuccess &&
             hipStreamSynchronize(st) == hipSuccess;
   if (!ok) { delete gr; return fail(SWX_EDEVICE, "could not clear the graph buffers"); }
   // capture the whole chain once
@@ -3786,7 +3789,7 @@ int swx_graph_read(swx_graph *gr, int64_t npairs, swx_batch_out *out) {
     int64_t *total = (int64_t *)ctx->stage_out;
     swx_rec_dev *hrecs = (swx_rec_dev *)(ctx->stage_out + 256);
     uint32_t *hcig = (uint32_t *)(ctx->stage_out + head);
-    const int64_t room = (swx_ctx::kStage - head) / 4;
+    const int64_t room = std::min<int64_t>((swx_ctx::kStage - head) / 4, g.cigar_cap);
     HIP_TRY(hipSetDevice(ctx->device));
     HIP_TRY(graph_out(npairs, g.recs, g.cigar, cigars ? g.cig_off_final : nullptr, room, hrecs, hcig,
                       total, ctx->stream));

@@ -265,3 +265,18 @@ def test_one_pair_graph_multi_strip(ctx, route):
             _say(f"[graph] tall one-pair route {route} pair {p}: score {recs['score1'][0]}")
     finally:
         g.close()
+
+
+@pytest.mark.parametrize("route", ROUTES)
+def test_graph_read_before_the_first_run(ctx, route):
+    a = W.random_pairs(931, 40, (1, 60), (0, 200))
+    g = _graph_for(ctx, a, max_pairs=64, max_qlen=64, max_rlen=256, route=route)
+    try:
+        g.load(a.qcat, a.qoff, a.rcat, a.roff, a.pair_q, a.pair_r)
+        recs, cig = g.read()
+        assert len(cig) == 0 and not recs.view(np.uint8).any()
+        g.run()
+        recs, cig = g.read()
+        _check_oracle(a, recs, cig)
+    finally:
+        g.close()
