@@ -2922,7 +2922,8 @@ static int graph_alloc(GraphState &g) {
     if ((rc = fixed_plan_alloc(g, g.p32, 32, R))) return rc;
     if ((rc = fixed_plan_alloc(g, g.r32, 32, R))) return rc;
   }
-  // traceback: a workgroup per pair where its fixed scratch stays small, else
+  // traceback: a workgroup per pair where its fixed scratch stays small (and can
+  // be had: for queries of less than 256 rows it is more than the classes'), else
   // the band classes, up to every pair in one class
   const int64_t tbp_stride = round_up(tb_wave_dir_bytes(g.QM, g.RM, kTbPairRows), 256) +
                              tb_pair_bnd_bytes(g.QM, g.RM);
@@ -2931,7 +2932,7 @@ static int graph_alloc(GraphState &g) {
   if (g.tb_by_pairs) {
     g.tbp_stride = tbp_stride;
     g.tbp_scratch = A.get<uint8_t>(B * tbp_stride);
-    if (!g.tbp_scratch) return fail(SWX_ENOMEM, "device pool exhausted (graph traceback)");
+    g.tb_by_pairs = g.tbp_scratch != nullptr;
   }
   const int64_t capT = (B + 63) / 64;
   for (int c = 1; c <= 3 && !g.tb_by_pairs; ++c) {
