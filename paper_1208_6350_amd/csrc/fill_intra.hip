@@ -900,7 +900,8 @@ __device__ __forceinline__ void alone_end(const AloneArgs &a, int64_t p, int32_t
   a.out.score[p] = (int32_t)(b.word >> kAloneBits);
   a.out.qend[p] = b.col >= 0 ? (int32_t)(M - (b.word & M)) - (kAloneMaxQ - Lq) : -1;
   a.out.rend[p] = b.col;
-  a.out.overflow[p] = a.is_long && !a.is_long[p] && (int32_t)(b.word >> kAloneBits) >= kInter16Limit;
+  a.out.overflow[p] = 0;
+  if (a.is_long && !a.is_long[p] && (int32_t)(b.word >> kAloneBits) >= kInter16Limit) a.lanebits[p] = 32;
 }
 
 // Begin and score2 of pair p from its forward end (score s1 > 0 at row ie,

@@ -1603,7 +1603,7 @@ static bool choose16(const swx_ctx *ctx, const Scoring &sc, const LongPath &lp) 
 // wave's 16-bit lanes) over its whole reference.
 struct AlonePath {
   bool on = false, all = false;   // all: the batched passes are empty
-  bool flag = false;              // ... and short pairs may pass their limit: flagged, run again
+  bool label = false;             // ... and short pairs may reach the batched pass's limit
   int64_t *ids = nullptr;         // (null: every pair in turn)
   int64_t count = 0, n32 = 0;     // the first n32 on 32-bit lanes
   uint32_t *maxcol = nullptr;
@@ -1613,9 +1613,9 @@ struct AlonePath {
 // References above kAloneSweep columns keep the chunks of the general path
 // until there is a job per pair anyway.
 static constexpr int64_t kAloneMaxR = 8192, kAloneSweep = 1024;
-// The short pairs of a batch go the same way, on 16-bit lanes too (those that
-// reach the batched pass's limit of them run again on 32-bit lanes, as there),
-// up to kAlonePairs pairs in all: nothing is batched then, so there is no plan to
+// The short pairs of a batch go the same way, on 16-bit lanes too (which hold every
+// score here; those that reach the batched pass's limit of them are labelled 32
+// bits, as they run there), up to kAlonePairs pairs in all: nothing is batched then, so there is no plan to
 // build and read back, no pack, and no fill with a few tasks.
 // Measured, whole call, long ones alone / all alone / all batched: 20,000
 // reads 3.04 / 2.06 / 3.57 ms, 30,000 3.74 / 2.79 / 3.87; the 4,950 overlaps of 100
@@ -1681,7 +1681,7 @@ static int plan_alone(swx_ctx *ctx, const Scoring &sc, int64_t np, uint32_t flag
   al.on = true;
   al.all = all;
   al.count = count;
-  al.flag = all && lp.nshort > 0 && bound >= kInter16Limit;
+  al.label = all && lp.nshort > 0 && bound >= kInter16Limit;
   al.n32 = w16 ? 0 : lp.nlong;
   al.stride = max_r;
   al.max_q = (int32_t)max_q;
@@ -1763,6 +1763,7 @@ static int run_alone_forward(swx_ctx *ctx, const Scoring &sc, const AlonePath &a
   }
   if (al.count > al.n32) {
     a.is_long = is_long;
+    a.lanebits = lanebits;
     if (al.n32 > 0) a.ids += al.n32;   // (a list, then)
     a.maxcol += al.n32 * al.stride;
     a.count -= al.n32;
@@ -2139,7 +2140,7 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
   }
   auto long_forward = [&]() -> int {
     return al.on ? run_alone_forward(ctx, sc, al, score_bound, fview, fout, lanebits,
-                                     al.flag ? lp.is_long : nullptr, rest)
+                                     al.label ? lp.is_long : nullptr, rest)
                  : run_intra_forward(ctx, sc, lp, fview, fout, err, lanebits);
   };
 
@@ -2177,18 +2178,10 @@ static int run_pipeline(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, u
   // saturated pairs: exact re-run on 32-bit lanes (none where no score of the
   // batch can reach the 16-bit limit, and none of the long pairs)
   int64_t *wide = nullptr, nwide = 0;
-  if ((lp.nshort > 0 || al.flag) && score_bound >= kInter16Limit &&
+  if (lp.nshort > 0 && score_bound >= kInter16Limit &&
       (rc = select_flagged(ctx, ovf, np, &wide, &nwide)))
     return rc;
-  if (nwide > 0 && al.all) {
-    AloneArgs w = alone_args(sc, al, fview, fout);
-    w.ids = wide;
-    w.count = nwide;
-    w.lanebits = lanebits;
-    w.maxcol = A.get<uint32_t>(nwide * al.stride);
-    if (!w.maxcol) return fail(SWX_ENOMEM, "device pool exhausted (max array)");
-    HIP_TRY(alone_forward(w, st));
-  } else if (nwide > 0) {
+  if (nwide > 0) {
     if ((rc = plan_pass(ctx, sc, wide, nwide, qlen, rlen, nullptr, nullptr, 32, R, p32, sp))) return rc;
     if ((rc = run_fill(ctx, p32, sc, fview, false, nullptr, fout, score_bound, -1, 0, 0, sp))) return rc;
     HIP_TRY(mark_lanes(nwide, wide, lanebits, 32, st));

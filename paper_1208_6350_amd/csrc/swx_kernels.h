@@ -333,8 +333,8 @@ struct AloneArgs {
   uint32_t *maxcol;
   int64_t stride;
   uint8_t *lanebits;         // forward: 32 is written (32-bit lanes; may be null)
-  const uint8_t *is_long;    // 16-bit forward (may be null): other pairs that reach the batched
-                             // pass's limit are flagged as it flags them
+  const uint8_t *is_long;    // 16-bit forward (may be null): ... for other pairs that reach the
+                             // limit of the batched pass's 16-bit lanes, which rerun there
   const int32_t *target, *band;   // reversed pass (band may be null)
   // what follows the forward pass in one go (alone_pass, alone_begin): begins
   // and, with score2, the best outside the mask

@@ -189,3 +189,21 @@ def test_where_large_batches_go(count, rlen, batched):
               "cigar_len"):
         assert np.array_equal(recs[f], recs[f][pair]), f
     c.close()
+
+
+# Short pairs around the batched pass's limit of 16-bit lanes (2,047): scored on
+# 16-bit lanes here, and labelled as there.
+@pytest.mark.parametrize("batched", [False, True])
+def test_label_at_the_batched_limit(batched):
+    m = W.dna_matrix(23, -23)
+    m[3, 3] = 22
+    base = np.tile(np.array([0, 1, 2], dtype=np.int8), 30)[:88]
+    qs = [np.append(base, s) for s in (3, 0)] + [np.append(base, [1, 1]), base[:60]]
+    rs = [q.copy() for q in qs]
+    c = swx.Context(0)
+    if batched:
+        c.set_tuning(long_cells=8192)
+    recs = assert_parity(c, W.from_lists("label", m, 23, 5, qs, rs))
+    assert list(recs["score1"]) == [2046, 2047, 2070, 1380]
+    assert list(recs["lane_bits"]) == [16, 32, 32, 16]
+    c.close()
