@@ -280,7 +280,8 @@ int swx_set_tuning(swx_ctx *ctx, const swx_tuning *t);
  * at least 3% faster), installs the fastest in ctx and returns it in *out.
  * cache_path (may be NULL) names a text file of one JSON object per line,
  * keyed by the device architecture and a coarse workload signature (n, gaps,
- * log2 of the sample size and of its cells); a matching entry is installed
+ * log2 of the sample size, of its cells and, for a sample of a larger batch, of
+ * that batch's pairs, whose routes the sample takes); a matching entry is installed
  * without timing (*from_cache = 1), a new result is appended.  Errors: those
  * of swx_align_batch; SWX_EINVAL for max_pairs < 1 or null pointers. */
 int swx_autotune(swx_ctx *ctx, const swx_batch *b, int64_t max_pairs, const char *cache_path,

@@ -6,7 +6,9 @@
 // height of the batched fill, routing threshold between the batched and the
 // intra-sequence paths, column chunks of the intra path, side streams for the
 // traceback launches, task order of the batched fill), each candidate
-// timed as the best of a few runs after a warm-up.  Results are kept in a
+// timed as the best of a few runs after a warm-up.  A sample takes the routes of
+// the batch it stands for (a sample of 20,000 reads would go pair by pair, where
+// the batched fill's knobs do nothing).  Results are kept in a
 // line-per-entry JSON cache keyed by the device and a coarse signature of the
 // workload (alphabet, gaps, sample size and cell count), so a later call on
 // similar work reuses them without timing.
@@ -48,13 +50,16 @@ int sample_cells(const swx_batch *b, int64_t np, double *cells) {
   return SWX_OK;
 }
 
-std::string make_key(int device, const swx_batch *b, int64_t np, double cells) {
+// all: the pairs of the batch that np of its pairs stand for
+std::string make_key(int device, const swx_batch *b, int64_t np, int64_t all, double cells) {
   hipDeviceProp_t prop{};
   hipGetDeviceProperties(&prop, device);
   char buf[256];
   snprintf(buf, sizeof buf, "%s|n%d|o%d|e%d|np%d|cells%d", prop.gcnArchName, b->n, b->gap_open,
            b->gap_extend, log2_bucket((double)np), log2_bucket(cells));
-  return buf;
+  std::string key = buf;
+  if (all > np) key += "|of" + std::to_string(log2_bucket((double)all));
+  return key;
 }
 
 bool parse_i64(const std::string &line, const char *field, int64_t *v) {
@@ -128,7 +133,7 @@ extern "C" int swx_autotune(swx_ctx *ctx, const swx_batch *b, int64_t max_pairs,
   double cells = 0;
   rc = sample_cells(&s, s.npairs, &cells);
   if (rc) return swx::internal_fail(rc, "could not read the batch's offsets");
-  const std::string key = make_key(swx::internal_device(ctx), &s, s.npairs, cells);
+  const std::string key = make_key(swx::internal_device(ctx), &s, s.npairs, b->npairs, cells);
   swx_tuning cached{};
   if (cache_lookup(cache_path, key, &cached)) {
     rc = swx_set_tuning(ctx, &cached);
@@ -137,6 +142,11 @@ extern "C" int swx_autotune(swx_ctx *ctx, const swx_batch *b, int64_t max_pairs,
     if (from_cache) *from_cache = 1;
     return SWX_OK;
   }
+  struct RouteAs {
+    swx_ctx *c;
+    RouteAs(swx_ctx *c_, int64_t n) : c(c_) { swx::internal_route_as(c, n); }
+    ~RouteAs() { swx::internal_route_as(c, 0); }
+  } route_as(ctx, b->npairs);
   // outputs of the timing runs: host records and CIGAR words
   std::vector<swx_rec> recs((size_t)s.npairs);
   int64_t cap = swx_cigar_bound(&s);

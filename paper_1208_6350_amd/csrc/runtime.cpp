@@ -172,6 +172,9 @@ struct swx_ctx {
   // of the running batch: longest query and reference, the mean query
   // weighted by reference length, and the mean reference
   int64_t max_q = 0, max_r = 0, mean_q = 0, mean_r = 0;
+  // > 0: batches stand for one of this many pairs (the autotuner's samples), and
+  // take the routes that depend on the number of pairs as it would
+  int64_t route_pairs = 0;
   // routing of long pairs to the intra-sequence path and its launch shape
   int64_t long_cells = -1;                 // qlen * rlen above this (-1: from the batch) ...
   int64_t long_rlen = int64_t(1) << 16;    // ... or a reference longer than this
@@ -909,8 +912,9 @@ static int run_traceback(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, 
   HIP_TRY(hipMemsetAsync(counts, 0, 18 * 8, st));
   // a small batch is traced pair by pair, in pair order (k_tb_pairs): it
   // needs no sort unless some of its pairs are long
-  const bool pairs_ok = !A.fixed() && np <= kTbPairsMax;
-  const bool few = pairs_ok && np <= kTbPairsAll;
+  const int64_t rp = std::max(np, ctx->route_pairs);
+  const bool pairs_ok = !A.fixed() && rp <= kTbPairsMax;
+  const bool few = pairs_ok && rp <= kTbPairsAll;
   HIP_TRY(tb_classify(ta, np, cls, k0, v0, coff, counts, counts + 8, pairs_ok ? counts + 9 : nullptr, st));
   int64_t *sorted = nullptr;
   auto sort = [&]() -> int {
@@ -946,8 +950,10 @@ static int run_traceback(swx_ctx *ctx, const Scoring &sc, const DeviceBatch &b, 
   int64_t pblocks = 0;
   std::vector<SideLaunch> launches;
   const int64_t pair_bytes = hc[10] + hc[11] + hc[12] + hc[14];
-  bool all = pairs_ok && pair_bytes <= (ctx->mean_q > kTbTallRows ? kTbTallBytes : kTbPairsBytes);
-  bool wide = !all && pairs_ok && hc[5] > 0 && hc[14] <= kTbWideBytes;
+  const double whole = (double)rp / (double)np;   // (of what the batch stands for)
+  bool all = pairs_ok && whole * (double)pair_bytes <=
+                             (double)(ctx->mean_q > kTbTallRows ? kTbTallBytes : kTbPairsBytes);
+  bool wide = !all && pairs_ok && hc[5] > 0 && whole * (double)hc[14] <= (double)kTbWideBytes;
   uint8_t *pscratch = all || wide ? A.get<uint8_t>(all ? pair_bytes : hc[14]) : nullptr;
   if (!pscratch) all = wide = false;   // (the per-lane kernels' scratch is a few times smaller)
   const bool direct = few && all;
@@ -1623,7 +1629,7 @@ static constexpr int64_t kAloneMaxR = 8192, kAloneSweep = 1024;
 // A protein of 300, forward and reversed stage, long ones alone or none / all
 // alone: 5,000 targets 1.98 / 1.08 ms, 12,000 3.20 / 1.68, 25,000 4.56 / 3.19,
 // 32,000 4.47 / 3.88, 48,000 4.41 / 5.45; of 80, 40,000 2.35 / 1.84.
-static constexpr int64_t kAlonePairs = 32768;
+static constexpr int64_t kAlonePairs = 32768, kAloneMost = 49152;
 // With begins wanted, as the reversed passes gain most, batches of shorter
 // queries go further.  Here every pair costs the forward sweep of 256 rows (64
 // lanes of four), however short its query; batched, the cost does not depend on
@@ -1640,12 +1646,11 @@ static constexpr int64_t kAlonePairs = 32768;
 // 1.43 1.27 0.72), of 250 2.21 2.12 1.67 (49,000 2.23 2.32).
 static int64_t alone_limit(const swx_ctx *ctx, const Scoring &sc, int64_t np, uint32_t flags,
                            int64_t nlong, bool one_query) {
-  constexpr int64_t kMost = 49152;
   if (!(flags & SWX_BEGIN) || ctx->mean_q > kTbTallRows) return kAlonePairs;
   const int64_t strips = (ctx->mean_q + 31) / 32;
   const bool brief = ctx->mean_r <= 1024;
-  if (!sc.qsel) return strips >= 5 || (brief && !one_query) ? kMost : brief ? 36864 : kAlonePairs;
-  if ((strips >= 5 || brief) && 5 * nlong >= 2 * np) return kMost;
+  if (!sc.qsel) return strips >= 5 || (brief && !one_query) ? kAloneMost : brief ? 36864 : kAlonePairs;
+  if ((strips >= 5 || brief) && 5 * nlong >= 2 * np) return kAloneMost;
   return strips >= 6 ? 43008 : strips == 5 && brief ? 36864 : kAlonePairs;
 }
 
@@ -1656,9 +1661,11 @@ static int plan_alone(swx_ctx *ctx, const Scoring &sc, int64_t np, uint32_t flag
   const int64_t max_q = stats[2], max_r = stats[3], sum_r = stats[4];
   const int64_t bound = (int64_t)std::max(sc.smax, 0) * stats[0];
   if (A.fixed() || max_q > kAloneMaxQ || max_r > kAloneMaxR) return SWX_OK;
+  const int64_t rp = std::max(np, ctx->route_pairs);
+  if (rp > np && rp > kAloneMost) return SWX_OK;
   // (a threshold set by the caller says itself which pairs are batched)
   const bool all = lp.nshort == 0 || (ctx->long_cells < 0 &&
-                                      np <= alone_limit(ctx, sc, np, flags, lp.nlong, one_query));
+                                      rp <= alone_limit(ctx, sc, np, flags, lp.nlong, one_query));
   if (lp.nlong == 0 && !all) return SWX_OK;
   const int64_t count = all ? np : lp.nlong;
   if (max_r > kAloneSweep && count < 2 * ctx->intra_jobs) return SWX_OK;
@@ -2975,6 +2982,10 @@ static int graph_alloc(GraphState &g) {
 int internal_fail(int code, const char *msg) { return fail(code, msg); }
 hipStream_t internal_stream(swx_ctx *ctx) { return ctx->stream; }
 int internal_device(const swx_ctx *ctx) { return ctx->device; }
+void internal_route_as(swx_ctx *ctx, int64_t n) {
+  std::lock_guard<std::mutex> g(ctx->mu);
+  ctx->route_pairs = n;
+}
 
 }  // namespace swx
 

@@ -12,4 +12,6 @@ int internal_fail(int code, const char *msg);
 hipStream_t internal_stream(swx_ctx *ctx);
 // the context's HIP device ordinal
 int internal_device(const swx_ctx *ctx);
+// batches on the context take the routes of a batch of n pairs (0: their own)
+void internal_route_as(swx_ctx *ctx, int64_t n);
 }  // namespace swx

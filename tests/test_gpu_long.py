@@ -200,3 +200,23 @@ def test_single_pair_protein_beyond_graph_capacity(ctx):
         for f in FIELDS:
             assert rec[f] == getattr(a, f), (o, e, f)
         assert cig == a.cigar
+
+
+def test_autotune_samples_take_their_batch_s_routes():
+    """A sample of a batch too large to go pair by pair runs batched: its last
+    run has a reversed pass of its own (pair by pair, begins come with the
+    forward pass)."""
+    g = np.random.Generator(np.random.PCG64(4620))
+    b = W.random_pairs(4621, 64, (140, 150), (300, 400), planted=0.8)
+    few = np.arange(20_000) % 64
+    c = swx.Context(0)
+    c.align_batch(b.matrix, b.gap_open, b.gap_extend, b.qcat, b.qoff, b.rcat, b.roff, few, few)
+    assert c.stage_ms()[3] < 0.05
+    pair = g.integers(0, 64, size=60_000)
+    c.autotune(b.matrix, b.gap_open, b.gap_extend, b.qcat, b.qoff, b.rcat, b.roff, pair, pair,
+               max_pairs=20_000)
+    assert c.stage_ms()[3] > 0.05
+    c.align_batch(b.matrix, b.gap_open, b.gap_extend, b.qcat, b.qoff, b.rcat, b.roff, few, few)
+    if c.tuning()["long_cells"] == -1:
+        assert c.stage_ms()[3] < 0.05
+    c.close()
