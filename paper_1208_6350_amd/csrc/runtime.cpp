@@ -558,17 +558,20 @@ static int run_fill(swx_ctx *ctx, Plan &pl, const Scoring &sc, const PairView &v
     if (2 * pl.ntasks < most * (int64_t)ctx->cus) a.coop = kCoopWaves;
   }
   // Cooperative tasks of a reversed pass whose queries fill eight strips run on
-  // eight waves in a search of one query among references of very unequal
-  // length: its launch ends on a few large tasks.  Only while the tasks are few
-  // (3.5 per compute unit): eight waves each, they hold the device with their
-  // strips' waits where four leave room for other tasks.  Reversed stage on
-  // four / eight waves, lengths log-normal around 300 (sigma 0.6): a query of 300
-  // against 60,000 targets 1.87 / 1.72 ms, 100,000 2.49 / 2.21, of 420 1.93 /
-  // 1.82 and 2.46 / 2.57, of 600 2.04 / 2.04 and 2.88 / 2.83; but 200,000 of
-  // 420 3.73 / 3.92 (sigma 0.3: 2.27 / 2.96), 100,000 of equal length 1.45 /
-  // 1.71, and 200,000 reads of 260 against windows of their own 1.86 / 2.65.
-  if (a.coop > 1 && rev && sp && ctx->mean_q >= kCoopMaxWaves * pl.R && ctx->max_r >= 3 * ctx->mean_r &&
-      2 * pl.ntasks <= 7 * (int64_t)ctx->cus)
+  // eight waves while the device holds them all so (one per compute unit): 2,000
+  // reads of 300 against 1,500, reversed stage on four / eight waves 1.81 / 1.62 ms,
+  // proteins 9.59 / 8.01, of 1,000 against 400 7.80 / 7.36.  With more tasks they
+  // hold it with their strips' waits where four leave room for other tasks
+  // (200,000 reads of 260 against windows of their own 1.86 / 2.65), except in a
+  // search of one query among references of very unequal length, whose launch ends
+  // on a few large tasks, up to 3.5 tasks per compute unit: lengths log-normal
+  // around 300 (sigma 0.6), a query of 300 against 60,000 targets 1.87 / 1.72,
+  // 100,000 2.49 / 2.21, of 420 1.93 / 1.82 and 2.46 / 2.57, of 600 2.04 / 2.04 and
+  // 2.88 / 2.83; but 200,000 of 420 3.73 / 3.92 (sigma 0.3: 2.27 / 2.96), and 100,000
+  // of equal length 1.45 / 1.71.
+  if (a.coop > 1 && rev && ctx->mean_q >= kCoopMaxWaves * pl.R &&
+      (pl.ntasks <= ctx->cus ||
+       (sp && ctx->max_r >= 3 * ctx->mean_r && 2 * pl.ntasks <= 7 * (int64_t)ctx->cus)))
     a.coop = kCoopMaxWaves;
   // A pass runs its tasks by area (padded rows x swept columns, its cost),
   // largest first: the plan's order (by band, height, then width) leaves
