@@ -111,8 +111,8 @@ struct InterArgs {
   const int64_t *order;       // the tasks by ascending area (padded rows x columns), run from
                               // the end (largest first); null: the plan's order (by height,
                               // then width)
-  int32_t coop;               // 1: one wave per task; C > 1 (up to kCoopMaxWaves): the C waves
-                              // of a workgroup share a task, wave w taking strips w, w + C, ...
+  int32_t coop;               // 1: one wave per task; C > 1 (kCoopWaves; reversed passes up to
+                              // kCoopMaxWaves): the C waves of a workgroup share a task, wave w taking strips w, w + C, ...
                               // (a strip starts on a column group once the strip above has
                               // stored it)
 };
