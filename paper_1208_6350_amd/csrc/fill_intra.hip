@@ -1214,7 +1214,6 @@ __global__ void k_intra_sync_init(IntraSync *sync, int64_t njobs) {
   if (j >= njobs) return;
   IntraSync &y = sync[j];
   for (int i = threadIdx.x; i < kIntraMaxStrips; i += blockDim.x) {
-    y.prog[i] = 0;
     y.done[i] = 0;
     y.rcol[i] = -1;
     y.rrow[i] = -1;

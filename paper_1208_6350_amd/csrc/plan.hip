@@ -227,14 +227,15 @@ hipError_t plan_sort(int64_t n, const int64_t *n_dev, const int64_t *ids, const 
                      size_t *tmp_bytes, int64_t **sorted_out, hipStream_t st, bool graph) {
   const PlanBits w = n_dev ? plan_bits(0, 0, R, band != nullptr) : plan_bits(max_q, max_r, R, band != nullptr);
   const int end_bit = w.r + w.q + w.b;
-  // The size query covers both bit ranges, so one buffer serves either pass.
   if (tmp == nullptr) {
     rocprim::double_buffer<uint64_t> kb(keys, keys_alt);
     rocprim::double_buffer<int64_t> vb(vals, vals_alt);
-    size_t b44 = 0, b64 = 0;
-    hipError_t e = radix_pairs(graph, nullptr, b44, kb, vb, (size_t)n, 44u, st);
-    if (e == hipSuccess) e = radix_pairs(graph, nullptr, b64, kb, vb, (size_t)n, 64u, st);
-    *tmp_bytes = b44 > b64 ? b44 : b64;
+    // (a graph's one buffer serves its passes with and without bands)
+    size_t own = 0, b44 = 0, b64 = 0;
+    hipError_t e = radix_pairs(graph, nullptr, own, kb, vb, (size_t)n, (unsigned)end_bit, st);
+    if (graph && e == hipSuccess) e = radix_pairs(graph, nullptr, b44, kb, vb, (size_t)n, 44u, st);
+    if (graph && e == hipSuccess) e = radix_pairs(graph, nullptr, b64, kb, vb, (size_t)n, 64u, st);
+    *tmp_bytes = std::max(own, std::max(b44, b64));
     return e;
   }
   if (n == 0) { *sorted_out = vals; return hipSuccess; }

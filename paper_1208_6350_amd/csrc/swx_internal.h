@@ -159,8 +159,7 @@ constexpr int kIntraMaxStrips = 256;
 // Progress of one spread job (its strips on several workgroups), in global
 // memory; intra_sync_init sets it before each launch.
 struct IntraSync {
-  int32_t prog[kIntraMaxStrips];     // columns published by strip s (from its window start)
-  int32_t done[kIntraMaxStrips];     // strip s finished (its progress is final)
+  int32_t done[kIntraMaxStrips];     // strip s has stored every word it will
   int64_t rcol[kIntraMaxStrips];     // reversed pass: first column of strip s reaching the target (-1)
   int32_t rrow[kIntraMaxStrips];     // ... and its row (-1)
   unsigned long long best;           // reversed pass: smallest such column so far (~0: none)

@@ -27,25 +27,6 @@ struct PackArgs {            // QGEN profile construction
   int32_t n, bias, halves, strip_rows, rev;
 };
 
-struct BandArgs {
-  int64_t npairs;
-  const int32_t *score;
-  const int32_t *qbeg, *qend;
-  const int64_t *rbeg, *rend;
-  const int64_t *qstart, *rstart;   // forward view
-  const int32_t *qlen;
-  const int64_t *rlen;
-  const int8_t *qcat, *rcat;
-  const int8_t *matrix;
-  int32_t n, o, e, smax;
-  uint8_t *dir;            const int64_t *dir_off;
-  int32_t *rowbuf;         const int64_t *row_off;   // 2 rows (H, F) of row_cap ints
-  uint32_t *cig;           const int64_t *cig_off;   // scratch runs
-  int32_t *cig_len;
-  uint8_t *err;
-  const uint8_t *only;     // when set, only pairs with only[p] == 5 (wide bands)
-};
-
 struct Score2InterArgs {
   const InterTask *tasks;
   int64_t ntasks;
@@ -454,12 +435,6 @@ hipError_t launch_views(int64_t npairs, const int64_t *qoff, const int64_t *roff
                         const int64_t *pair_q, const int64_t *pair_r, const ViewCaps &caps,
                         int64_t *qstart, int32_t *qlen, int64_t *rstart, int64_t *rlen,
                         int64_t *stats, hipStream_t st);
-hipError_t launch_band_sizes(int64_t npairs, const int32_t *score, const int32_t *qbeg,
-                             const int32_t *qend, const int64_t *rbeg, const int64_t *rend,
-                             const int32_t *qlen, const int64_t *rlen, const uint8_t *only,
-                             int32_t smax, int32_t o, int32_t e, int64_t *dir_size,
-                             int64_t *cig_cap, int64_t *row_cap, hipStream_t st);
-hipError_t launch_band_tb(const BandArgs &a, hipStream_t st);
 // one launch for many clears: entry k sets n[k] elements of size[k] bytes
 // (1, 4 or 8) at p[k] to v[k]
 constexpr int kFillSetMax = 12;
@@ -494,7 +469,7 @@ hipError_t publish(const int64_t *a, int64_t na, const int64_t *b, int64_t nb, i
 // pinned host memory; *total = off[npairs]
 hipError_t graph_out(int64_t npairs, const swx_rec_dev *recs, const uint32_t *cigar, const int64_t *off,
                      int64_t cap, swx_rec_dev *hrecs, uint32_t *hcigar, int64_t *total, hipStream_t st);
-// pair 0's CIGAR words and final offsets {0, length} (one-pair calls)
+// CIGAR words to their final offsets
 // cls: the traceback classes (pairs of class kTbFlat hold no scratch words:
 // their one word is made from qbeg and qend)
 // (src_off null: runs at p * stride; cls may be null; nothing is copied when
@@ -504,10 +479,6 @@ hipError_t launch_cigar_compact(int64_t npairs, const uint32_t *src, const int64
                                 const int32_t *qbeg, const int32_t *qend, uint32_t *dst,
                                 int64_t stride, int64_t cap, hipStream_t st);
 hipError_t launch_score2_inter(const Score2InterArgs &a, hipStream_t st);
-hipError_t launch_score2_plain(int64_t p, const int32_t *maxcol, int64_t lr, const int32_t *score1,
-                               const int64_t *rbeg, const int64_t *rend, int32_t mask_len,
-                               const int32_t *qlen, int32_t *score2, int64_t *rend2,
-                               hipStream_t st);
 // err (may be null): *nerr += the pairs whose flag is set; CIGARs of more than
 // cap words in all (cig_off[npairs]) are left out of the records
 hipError_t launch_records(int64_t npairs, const int32_t *score1, const int32_t *score2,

@@ -1344,7 +1344,6 @@ __global__ __launch_bounds__(64 * kTbMaxWaves) void k_tb_wave(TbArgs a, const Tb
   __shared__ int32_t s_prog[kTbMaxStrips];   // columns of strip s's last row published
   __shared__ int32_t s_done[kTbMaxStrips];
   const TbWaveJob jb = jobs[blockIdx.x];
-  if (jb.m <= 0) return;   // a job without an alignment (one-pair graphs plan it on the device)
   uint8_t *dir = dirw + jb.dir_off;
   tb_wave_fill<RL>(a, jb, s_prog, s_done, s_mat, reinterpret_cast<int8_t *>(s_dyn), dir,
                    bndbuf + jb.bnd_off);
@@ -1398,7 +1397,6 @@ __global__ __launch_bounds__(64 * kTbSpreadMaxWaves) void k_tb_spread(TbArgs a, 
   const int64_t seg = slot % G;
   if (jix >= njobs) return;
   const TbWaveJob jb = jobs[jix];
-  if (jb.m <= 0) return;
   const int32_t *done = sync[jix].done;
   const int64_t p = jb.pair, m = jb.m, w = jb.w;
   const int n = a.n;
@@ -1666,7 +1664,6 @@ template <int RL>
 __global__ __launch_bounds__(64) void k_tb_walk(TbArgs a, const TbWaveJob *jobs, uint8_t *dirw) {
   __shared__ uint4 s_tile[kTbTileBytes / 16];
   const TbWaveJob jb = jobs[blockIdx.x];
-  if (jb.m <= 0) return;
   tb_wave_walk<RL, kTbTileBytes>(a, jb, dirw + jb.dir_off, s_tile, (int)(threadIdx.x & 63));
 }
 
@@ -1982,22 +1979,8 @@ __global__ __launch_bounds__(64 * kPairWaves) void k_pair_rest(PairArgs a) {
     rec.ref_end1 = je;
     err = ie < 0 || ie >= a.Lq;
     if ((a.flags & 1u) && !err) {
-      // the drift band of the reversed pass (see k_rev_prepare)
-      int32_t band = -1;
-      if (a.e > 0) {
-        const int64_t rows = (int64_t)ie + 1, cols = je + 1;
-        const int64_t base = -(int64_t)a.o + a.e - s1;
-        auto drift = [](int64_t num, int64_t den) {
-          const int64_t g = num / den;
-          return g < 0 ? (int64_t)0 : (g > (1 << 30) ? int64_t(1) << 30 : g);
-        };
-        const int64_t g = drift((int64_t)a.smax * (rows < cols ? rows : cols) + base, a.e);
-        int64_t gq = drift((int64_t)a.smax * rows + base, (int64_t)a.smax + a.e);
-        int64_t gr = drift((int64_t)a.smax * cols + base, (int64_t)a.smax + a.e);
-        gq = gq < g ? gq : g;
-        gr = gr < g ? gr : g;
-        band = (int32_t)(gq > gr ? gq : gr);
-      }
+      int32_t band, band_q;
+      rev_band(s1, (int64_t)ie + 1, je + 1, a.smax, a.o, a.e, band, band_q);
       StripJob x{};
       x.qs = a.q;
       x.rs = a.r;
