@@ -95,7 +95,8 @@ typedef struct {
   int64_t ref_begin1, ref_end1, ref_end2;
   int64_t cigar_off;
   int32_t cigar_len;
-  int32_t lane_bits;   /* lane width that produced the result (16 or 32); diagnostic only */
+  int32_t lane_bits;   /* lane width of the result's score (16 or 32; 32 from 2,047 on for
+                          pairs that a larger batch would batch); diagnostic only */
 } swx_rec;
 
 /* Single-pair result: the record plus a CIGAR owned by the result, and with
@@ -111,7 +112,10 @@ typedef struct {
 
 /* ---- context --------------------------------------------------------------
  * device: HIP device ordinal.  The context owns a stream and a device memory
- * pool that grows on demand and is reused across calls. */
+ * pool that grows on demand, is reused across calls and is released with the
+ * context.  Batches that go pair by pair (swx_tuning below) take up to 1 GiB of
+ * it for max arrays and 1.3 GiB per traceback (two with SWX_SUBOPT) where that
+ * can be had; other work takes what its pairs need. */
 int swx_ctx_create(int device, swx_ctx **out);
 int swx_ctx_destroy(swx_ctx *ctx);
 
@@ -239,9 +243,15 @@ int64_t swx_cigar_bound(const swx_batch *b);
  *                          16-bit lane half.  long_cells = -1 (the default)
  *                          derives the threshold from each call: twice the
  *                          call's cells per lane half of a full GPU, at least
- *                          2048.  long_cells >= -1, long_rlen >= 0.
- *   intra_jobs             target number of column chunks over all long pairs
- *                          of one call, >= 1.
+ *                          2048; and calls of up to 32,768 pairs (49,152 where
+ *                          that is faster still) with queries of at most 512
+ *                          and references of at most 8,192 then batch nothing:
+ *                          every pair takes a wave of its own (or half of one),
+ *                          and the knobs of the batched fill change nothing.
+ *                          long_cells >= -1, long_rlen >= 0.
+ *   intra_jobs             number of column chunks over all long pairs of one
+ *                          call, >= 1: what many long pairs are cut into, and
+ *                          the most that up to 64, cut for one wave per SIMD, are.
  *   fill_rows              query rows per strip of the batched fill: 16, 24 or
  *                          32 (24 applies to alphabets of at most 4 symbols;
  *                          others use 32 instead).
@@ -259,9 +269,11 @@ typedef struct {
                             first (default); 2 a grid of resident waves taking tasks
                             largest first from a device work queue */
   int32_t fill_coop;     /* 0 (default): a pass with fewer tasks than the device holds
-                            waves runs each task on the four waves of a workgroup, which
-                            take its strips round robin (a strip follows the one above
-                            column group by column group); 1: never; 2: always */
+                            waves, or a forward pass with somewhat more, runs each task on
+                            the waves of a workgroup, which take its strips round robin (a
+                            strip follows the one above column group by column group): four,
+                            or eight in some reversed passes of eight strips and more; 1:
+                            never; 2: always */
   int32_t intra_bits;    /* lanes of the intra-sequence forward pass. 16: packed 16-bit
                             lanes, two column chunks per wave (on twice intra_jobs chunks),
                             for every long pair whose scores fit (smax * min(qlen, rlen)
