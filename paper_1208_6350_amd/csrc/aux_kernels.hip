@@ -520,8 +520,10 @@ hipError_t launch_records(int64_t npairs, const int32_t *score1, const int32_t *
 // ---- the suboptimal alignment (the one behind score2) -------------------------
 // Step 1: a window of the reference ending at ref_end2 that holds every
 // positive-scoring path into that column (no such path spans more than
-// W = Lq + (smax*Lq - o)/e + 1 columns; with e = 0 the whole prefix), so the
-// forward recurrence started there is exact at the window's last column.
+// W = Lq + max(smax*Lq - o, 0)/e + 1 columns, as a query whose best score
+// cannot pay for a gap still spans its own length; with e = 0 the whole
+// prefix), so the forward recurrence started there is exact at the window's
+// last column.
 __global__ void k_sub_window(int64_t npairs, const int64_t *rstart, const int32_t *qlen,
                              const int32_t *score2, const int64_t *rend2, int32_t smax, int32_t o,
                              int32_t e, int64_t *wrstart, int64_t *wrlen, uint8_t *flag) {
@@ -531,7 +533,8 @@ __global__ void k_sub_window(int64_t npairs, const int64_t *rstart, const int32_
   int64_t lo = 0;
   if (ok && e > 0) {
     const int64_t lq = qlen[p];
-    const int64_t span = lq + ((int64_t)smax * lq - o) / e + 1;
+    const int64_t gain = (int64_t)smax * lq - o;
+    const int64_t span = lq + (gain > 0 ? gain : 0) / e + 1;
     lo = rend2[p] - span + 1;
     if (lo < 0) lo = 0;
   }

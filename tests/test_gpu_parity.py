@@ -426,6 +426,34 @@ def test_suboptimal_alignment(ctx, mask_len):
         assert (s2 > 0).sum() > b.npairs // 3
 
 
+@pytest.mark.parametrize("long_cells", [-1, 0, 1 << 40])
+@pytest.mark.parametrize("o,e", [(11, 1), (40, 2)])
+def test_suboptimal_below_the_cost_of_a_gap(ctx, o, e, long_cells):
+    """Queries whose best score cannot pay for one gap: their second alignment
+    still spans as many columns as it has rows."""
+    b = _two_copy_pairs(74, 300, o=o, e=e)
+    qs = [b.qcat[b.qoff[p]:b.qoff[p + 1]][:1 + p % 20] for p in range(b.npairs)]
+    rs = [np.concatenate([q, b.rcat[b.roff[p]:b.roff[p + 1]][:30], q]) for p, q in enumerate(qs)]
+    b = W.from_lists("below-a-gap", W.dna_matrix(), o, e, qs, rs)
+    ctx.set_tuning(long_cells=long_cells)
+    try:
+        recs, cig, sub = ctx.align_batch(b.matrix, o, e, b.qcat, b.qoff, b.rcat, b.roff, b.pair_q,
+                                         b.pair_r, swx.SWX_ALL | swx.SWX_SUBOPT, 2)
+    finally:
+        ctx.set_tuning(long_cells=-1)
+    ref, _, _ = oracle.align_many(b.qcat, b.qoff, b.rcat, b.roff, b.pair_q, b.pair_r, b.matrix, o,
+                                  e, swx.SWX_ALL, 2)
+    sref, scig, scoff = oracle.suboptimal_many(b.qcat, b.qoff, b.rcat, b.roff, b.pair_q, b.pair_r,
+                                               b.matrix, o, e, ref[:, 1], ref[:, 6])
+    assert (ref[:, 1] > 0).sum() > b.npairs // 3
+    np.testing.assert_array_equal(sub["score1"], ref[:, 1])
+    for f, col in (("read_begin1", 0), ("read_end1", 1), ("ref_begin1", 2), ("cigar_len", 3)):
+        np.testing.assert_array_equal(sub[f], sref[:, col], err_msg=f)
+    for p in range(b.npairs):
+        g = cig[sub["cigar_off"][p]:sub["cigar_off"][p] + sub["cigar_len"][p]]
+        np.testing.assert_array_equal(g, scig[scoff[p]:scoff[p] + sref[p, 3]])
+
+
 def test_single_pair_suboptimal(ctx):
     """SWX_SUBOPT through the one-pair call (swx_align): the primary record and
     CIGAR, and the suboptimal alignment's begins, end and CIGAR, equal the
