@@ -102,9 +102,13 @@ struct CoopShared {
   int64_t mcol[WAVES][kSlots16];
   int64_t task;                            // queued scheduling: the workgroup's task
 };
-// Forward passes always have four waves, known to the compiler: with their number
-// read from the arguments (and room for eight) the forward fill of 4,096 reads of
-// 256 against 2,000, 32 tasks, took 3.00 ms instead of 2.78.
+// Forward passes always have four waves.  Four-symbol kernels know that when they
+// are compiled: with the number read from the arguments the forward fill of 4,096
+// reads of 256 against 2,000, 32 tasks, took 3.00 ms instead of 2.78.  Kernels with
+// a query profile measured the other way round, so they do read it: 4,000 to
+// 200,000 targets for one query or several, 4 to 16 strips, 2 to 3% faster on
+// average where scores are clamped (one query of 300, 100,000 targets, all of them
+// batched: 10.83 -> 10.44 ms), and the same where they are not.
 template <bool REV> constexpr int coop_most() { return REV ? kCoopMaxWaves : kCoopWaves; }
 constexpr int32_t kStripDone = (int32_t)0x80000000u;   // strip s has ended ...
 constexpr int32_t kStripCut = 0x40000000;              // ... before its band's end
@@ -140,7 +144,7 @@ __device__ __forceinline__ void inter_task(const InterArgs &a, const int64_t tid
   // cooperative task: this wave's strips are s_first, s_first + s_step, ...
   constexpr bool coop = COOP;
   const bool sync = coop && nstrips <= kCoopMaxStrips;
-  const int waves = REV ? a.coop : kCoopWaves;   // of a cooperative task
+  const int waves = REV || MODE == kQGen ? a.coop : kCoopWaves;   // of a cooperative task
   int s_first = 0, s_step = 1, s_end = nstrips;
   if (sync) {
     s_first = wave;
